@@ -30,10 +30,7 @@ struct DeviceScope {
 // Largest page id a kernel may use: ids are device data and are clamped to [0, page_hi].
 int page_hi_of(const rapid_attn_shape* s) { return s->n_pages > 0 ? s->n_pages - 1 : 0x7fffffff; }
 
-#ifndef RAPID_WIDE_FROM
-#define RAPID_WIDE_FROM 5
-#endif
-constexpr int kWideFromBlocks = RAPID_WIDE_FROM;    // row blocks from which the two-team attention kernel is used
+constexpr int kWideFromBlocks = 5;    // row blocks from which the two-team attention kernel is used
 
 // Row blocks of 16 packed query rows that the partials of a shape are laid out in.  Five and six
 // blocks run on the two-team kernel (teams of 3 + 2 and 3 + 3 blocks).
@@ -41,7 +38,7 @@ int attn_row_blocks(const rapid_attn_shape* s, int* wide)
 {
     const int G = s->n_q_heads / s->n_kv_heads;
     const int rb = (s->q_max * G + 15) / 16;
-    if (wide) *wide = (rb >= kWideFromBlocks && rb >= 4) ? 1 : 0;
+    if (wide) *wide = rb >= kWideFromBlocks ? 1 : 0;
     return rb;
 }
 
@@ -81,6 +78,12 @@ int check_attn_shape(const rapid_attn_shape* s)
     return RAPID_OK;
 }
 
+// A batch whose lengths are known to differ: the caller passed their sum and it is below nine tenths of B * max_ctx.
+bool ragged_batch(const rapid_attn_shape* s)
+{
+    return s->batch > 1 && s->ctx_sum_hint > 0 && s->ctx_sum_hint * 10 < (int64_t)s->batch * s->max_ctx * 9;
+}
+
 // Tokens per KV split, a multiple of 128, never below 256 (two tiles per wave).
 // Measured on uniform and ragged batches of 2..64 sequences: a workgroup costs about 8 us
 // besides its streaming time, so for sequences of equal length one workgroup per compute
@@ -96,7 +99,7 @@ int plan_chunk(const rapid_ctx* ctx, const rapid_attn_shape* s)
     const int64_t n_cu = ctx ? ctx->n_cu : 256;
     const int64_t units = (int64_t)s->batch * s->n_kv_heads;
     const int64_t full = (int64_t)s->batch * s->max_ctx;
-    const bool ragged = s->batch > 1 && s->ctx_sum_hint > 0 && s->ctx_sum_hint * 10 < full * 9;
+    const bool ragged = ragged_batch(s);
     const int64_t tokens = (s->ctx_sum_hint > 0 && s->ctx_sum_hint < full) ? s->ctx_sum_hint : full;
     // workgroups that may hold tokens: every (sequence, head) wastes less than one split, so
     // sum_b ceil(L_b / chunk) * Hkv <= tokens * Hkv / chunk + units stays within two full rounds
@@ -127,12 +130,30 @@ void plan_layout(const rapid_ctx* ctx, AttnLaunch& a)
 {
     a.rot = a.hstride > a.tstride && a.Hkv > 1;
     a.skew = 0;
+    if (a.groups) {
+        // balanced shares are always a single wave of workgroups
+        if (a.rot && a.Hkv % 2 == 0) a.skew = a.wide ? 2 : 3;
+        return;
+    }
     const int64_t wgs = (int64_t)a.B * a.Hkv * a.nsplit;
     // measured: 3/32 of the split for the one-team kernel (config 3: 88.2 us with 384 tokens, 89.5 with 256,
     // 91.1 with none), 1/16 for the two-team kernel, which runs all waves through the same number of tiles
     // (70B shape: 93-94 us with 256 tokens, 96.5 with 384)
     if (a.rot && a.Hkv % 2 == 0 && a.nsplit >= 2 && wgs <= ctx->n_cu)
         a.skew = a.wide ? a.chunk / 16 / 128 * 128 : (a.chunk * 3 / 32 + 64) / 128 * 128;
+}
+
+// Groups of the balanced plan (verify_attn.hip), 0 = the fixed grid of splits.  Taken by ragged batches whose split the
+// caller leaves to the library: the partials (one slot per head, group and sequence boundary) have to fit the workspace that
+// the split size answers for, and a head needs a handful of groups for the shares to be worth cutting.
+int plan_groups(const rapid_ctx* ctx, const rapid_attn_shape* s, int nsplit)
+{
+    if (s->chunk_tokens > 0 || !ragged_batch(s)) return 0;
+    const int n_cu = ctx ? ctx->n_cu : 256;
+    const int groups = n_cu / s->n_kv_heads & ~1;
+    if (groups < 8 || groups + s->batch - 1 > (int64_t)s->batch * nsplit) return 0;
+    if ((int64_t)s->batch * (s->max_ctx / 128 + 8) >= (int64_t)1 << 30) return 0;      // positions are 32-bit
+    return groups;
 }
 
 }  // namespace
@@ -265,6 +286,8 @@ int rapid_verify_attn(rapid_ctx* ctx, const rapid_attn_shape* shape,
     a.chunk = plan_chunk(ctx, shape);
     a.nsplit = (shape->max_ctx + a.chunk - 1) / a.chunk;
     a.RB = attn_row_blocks(shape, &a.wide);
+    a.groups = plan_groups(ctx, shape, a.nsplit);
+    a.nslots = a.groups + a.B - 1;
     a.bstride = shape->kv_batch_stride;
     a.tstride = shape->kv_token_stride;
     a.hstride = shape->kv_head_stride;

@@ -29,9 +29,12 @@ struct AttnLaunch {
     int32_t B, Qmax, Hq, Hkv, G, D, gamma;
     int32_t max_ctx;    // host bound of ctx_lens
     int32_t chunk, nsplit, RB;   // RB: 16-row blocks of the partials (wide: two teams of (RB + 1) / 2 and RB / 2 blocks)
-    int32_t wide;       // 1: eight-wave kernel with two row teams
+    int32_t wide;       // 1: eight-wave kernel with two row teams (from five row blocks on)
     int32_t rot;        // 1: dispatch slot x serves head (x + split) mod Hkv, 0: head x
+    int32_t groups;     // > 0: balanced shares of a ragged batch, one workgroup per (kv head, group); even
+    int32_t nslots;     // balanced shares: partial slots per kv head (groups + B - 1)
     int32_t skew;       // tokens moved from the splits on odd dispatch slots to those on even ones
+                        // (balanced shares: 32nds of the mean share)
     int64_t bstride, tstride, hstride, pstride;   // elements
     int32_t page_shift, page_mask, max_pages;     // page_shift < 0: contiguous
     int32_t page_hi;    // largest page id the kernels will use (ids are clamped to [0, page_hi])

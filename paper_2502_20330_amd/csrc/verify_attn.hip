@@ -307,26 +307,106 @@ __device__ __forceinline__ int split_end(const AttnLaunch& a, int s, int h)
     return s + 1 < a.nsplit ? split_begin(a, s + 1, h) : a.nsplit * a.chunk;
 }
 
+// ---- balanced shares of a ragged batch.  The fixed grid of splits above gives every sequence the same split
+// size, so with unequal lengths some workgroups stream a full split and others a rest, and the last round
+// leaves compute units idle: eight 16-token-page sequences of 16K..131K tokens ran at 69 % of the HBM peak where one
+// sequence of 131K runs at 76 %.  Here the grid is one workgroup per compute unit ("group" g of kv head h) and the tokens of the
+// whole batch are laid end to end, in quanta of 128 tokens (whole tiles for all waves), and cut into equal
+// shares: group g works on the piece of every sequence that falls into its share.  Every piece beyond a
+// group's first costs a pipeline start and an epilogue, so each sequence counts kPieceQuanta more than its tokens.
+// The lengths are device data: every workgroup derives the shares from ctx_lens (B values, one wave scan).
+constexpr int kQuantum = 128;
+constexpr int kPieceQuanta = 3;
+
+__device__ __forceinline__ int seq_len(const AttnLaunch& a, int b)
+{
+    return min(a.ctx_lens[b], a.max_ctx);               // device data: never address past the planned range
+}
+// Cost of a sequence in quanta: its own, after kPieceQuanta for the piece.
+__device__ __forceinline__ int seq_cost(int L) { return L > 0 ? (L + kQuantum - 1) / kQuantum + kPieceQuanta : 0; }
+
+// 64 sequences at a time, one per lane: (inclusive prefix of the cost, own cost) of sequence b0 + lane.
+__device__ __forceinline__ int scan_costs(int cost, int lane)
+{
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(cost, o);
+        if (lane >= o) cost += y;
+    }
+    return cost;
+}
+struct Shares {
+    int pairs;                      // pairs of groups in use
+    int pair_quanta, pair_rest;     // quanta of a pair; the first pair_rest pairs take one more
+    int skew32;                     // 32nds of the mean share that move from the odd dispatch slots to the even ones
+    __device__ __forceinline__ int pair_begin(int i) const { return i * pair_quanta + min(i, pair_rest); }
+    // first cost quantum of group g of head h (the parity of the dispatch slot decides who takes more, as for the splits)
+    __device__ __forceinline__ int begin(int g, int h) const
+    {
+        const int p0 = pair_begin(min(g >> 1, pairs));
+        if (!(g & 1) || (g >> 1) >= pairs) return p0;
+        const int len = pair_begin((g >> 1) + 1) - p0;
+        return p0 + (int)(((int64_t)len * (32 + ((h & 1) ? -skew32 : skew32))) >> 6);
+    }
+    // the pair that owns cost quantum x
+    __device__ __forceinline__ int pair_of(int x) const
+    {
+        const int head = pair_rest * (pair_quanta + 1);
+        return x < head ? (int)((unsigned)x / (unsigned)(pair_quanta + 1))
+                        : pair_rest + (int)((unsigned)(x - head) / (unsigned)max(pair_quanta, 1));
+    }
+};
+__device__ __forceinline__ Shares make_shares(const AttnLaunch& a, int total)
+{
+    // at least four quanta a pair, so that either group of a pair in use has one (the merge counts on it)
+    Shares s;
+    s.pairs = max(1, min(a.groups / 2, total / 4));
+    s.pair_quanta = (int)((unsigned)total / (unsigned)s.pairs);
+    s.pair_rest = total - s.pair_quanta * s.pairs;
+    s.skew32 = a.skew;
+    return s;
+}
+// Total cost of the batch (every lane of a wave gets it).
+__device__ __forceinline__ int total_cost(const AttnLaunch& a, int lane)
+{
+    int total = 0;
+    for (int b0 = 0; b0 < a.B; b0 += 64)
+        total += __builtin_amdgcn_readlane(scan_costs(b0 + lane < a.B ? seq_cost(seq_len(a, b0 + lane)) : 0, lane), 63);
+    return total;
+}
+// Calls piece(b, L, c0, c1) for every piece [c0, c1) of a sequence b that group g of head h owns, in order.
+template <class Piece>
+__device__ __forceinline__ void for_each_piece(const AttnLaunch& a, int g, int h, int lane, Piece piece)
+{
+    const Shares sh = make_shares(a, total_cost(a, lane));
+    const int x0 = sh.begin(g, h), x1 = sh.begin(g + 1, h);
+    int before = 0;                                      // cost of the sequences before b0
+    for (int b0 = 0; b0 < a.B; b0 += 64) {
+        const int len = b0 + lane < a.B ? seq_len(a, b0 + lane) : 0;
+        const int cost = seq_cost(len);
+        const int end = before + scan_costs(cost, lane);
+        const int tok = end - cost + kPieceQuanta;       // cost position of the sequence's first token quantum
+        const bool mine = cost > 0 && end > x0 && tok < x1;
+        for (unsigned long long todo = __ballot(mine); todo; todo &= todo - 1) {
+            const int l = __ffsll((long long)todo) - 1;
+            const int t = __builtin_amdgcn_readlane(tok, l), L = __builtin_amdgcn_readlane(len, l);
+            const int c0 = max(x0 - t, 0) * kQuantum;
+            const int c1 = min((min(x1, __builtin_amdgcn_readlane(end, l)) - t) * kQuantum, L);
+            if (c0 < c1) piece(b0 + l, L, c0, c1);
+        }
+        before = __builtin_amdgcn_readlane(end, 63);
+        if (before >= x1) break;
+    }
+}
+
+// One workgroup's work on tokens [c0, c1) of one (sequence, kv head): the partial goes to the packed rows
+// from `pbase` on.
 template <int D, int RB, bool PAGED>
-__global__ void __launch_bounds__(kWaves * 64) verify_attn_split(AttnLaunch a)
+__device__ __forceinline__ void split_piece(const AttnLaunch& a, char* smem, int b, int hkv, int L, int c0, int c1, int64_t pbase)
 {
     using G = Geo<D>;
     constexpr int RP = RB * 16;
     constexpr int kAhead = 3 * G::NLD;     // loads issued after the tile a wait is for
-    extern __shared__ __attribute__((aligned(1024))) char smem[];
-
-    // With rotation, dispatch slot x = blockIdx.x serves kv head (x + split) mod Hkv.
-    // Workgroups go to the chip's eight dies round robin in dispatch order, so the
-    // splits of one head are then spread over all dies (and all L2s) instead of
-    // sitting on one, and the parity of x is the parity of the die.  Without it,
-    // the heads of one token range sit next to each other in dispatch order, which
-    // suits caches whose heads interleave inside a token row.
-    const int split = blockIdx.y, b = blockIdx.z;
-    const int hkv = a.rot ? (int)((blockIdx.x + split) % a.Hkv) : (int)blockIdx.x;
-    const int L = min(a.ctx_lens[b], a.max_ctx);        // device data: never address past the planned range
-    const int c0 = split_begin(a, split, hkv);
-    if (c0 >= L) return;                             // this split holds no token of sequence b
-    const int c1 = min(split_end(a, split, hkv), L);
     const int Q = seq_queries(a, b);
     const int R = Q * a.G;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -493,7 +573,6 @@ __global__ void __launch_bounds__(kWaves * 64) verify_attn_split(AttnLaunch a)
         }
     }
     __syncthreads();
-    const int64_t pbase = (((int64_t)b * a.Hkv + hkv) * a.nsplit + split) * RP;
     floatx4* po = reinterpret_cast<floatx4*>(a.part_o + pbase * D);
     for (int f = tid; f < R * (D / 4); f += kWaves * 64) {
         const int row = f / (D / 4), d4 = f % (D / 4);
@@ -511,6 +590,35 @@ __global__ void __launch_bounds__(kWaves * 64) verify_attn_split(AttnLaunch a)
             }
         }
     }
+}
+
+// Partials of a fixed grid: [b][kv head][split]; of balanced shares: [kv head][g + b], which no two pieces
+// share (from one piece of a head to the next, g or b grows).
+template <int D, int RB, bool PAGED, bool BALANCED>
+__global__ void __launch_bounds__(kWaves * 64) verify_attn_split(AttnLaunch a)
+{
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    // With rotation, dispatch slot x = blockIdx.x serves kv head (x + split) mod Hkv.
+    // Workgroups go to the chip's eight dies round robin in dispatch order, so the
+    // splits of one head are then spread over all dies (and all L2s) instead of
+    // sitting on one, and the parity of x is the parity of the die.  Without it,
+    // the heads of one token range sit next to each other in dispatch order, which
+    // suits caches whose heads interleave inside a token row.
+    const int split = blockIdx.y, b = blockIdx.z;
+    const int hkv = a.rot ? (int)((blockIdx.x + split) % a.Hkv) : (int)blockIdx.x;
+    if (BALANCED) {
+        for_each_piece(a, split, hkv, threadIdx.x & 63, [&](int pb, int L, int c0, int c1) {
+            split_piece<D, RB, PAGED>(a, smem, pb, hkv, L, c0, c1, ((int64_t)hkv * a.nslots + split + pb) * (RB * 16));
+            wait_loads<0>();                             // the partial's stores are out of the load account
+            __syncthreads();                             // the exchange buffers become rings again
+        });
+        return;
+    }
+    const int L = seq_len(a, b);
+    const int c0 = split_begin(a, split, hkv);
+    if (c0 >= L) return;                                 // this split holds no token of sequence b
+    split_piece<D, RB, PAGED>(a, smem, b, hkv, L, c0, min(split_end(a, split, hkv), L),
+                              (((int64_t)b * a.Hkv + hkv) * a.nsplit + split) * (RB * 16));
 }
 
 // ---------------------------------------------------------------- wide row counts: two row teams
@@ -562,7 +670,7 @@ struct WideWave {
     RowAddr addr;
     char *kring, *vring, *qlds;
     uint32_t kring_lds, vring_lds;
-    int b, hkv, split, L, Q, R, c0, c1, ntq, last_tok;
+    int b, hkv, L, Q, R, c0, c1, ntq, last_tok;
     int lane, wave, team, pr;
 };
 
@@ -701,22 +809,20 @@ __device__ __forceinline__ void wide_team(const AttnLaunch& a, const WideWave& w
 // Team 0 takes RB0 row blocks, team 1 the next RB1 (RB0 >= RB1): five row blocks run as 3 + 2, so that
 // no wave spends a third of its matrix and softmax work on rows that do not exist.
 template <int D, int RB0, int RB1, bool PAGED>
-__global__ void __launch_bounds__(2 * kWaves * 64) verify_attn_split_wide(AttnLaunch a)
+__device__ __forceinline__ void split_piece_wide(const AttnLaunch& a, char* smem, int b, int hkv, int L, int c0, int c1,
+                                                 int64_t pbase)
 {
     using G = Geo<D>;
     constexpr int RPT0 = RB0 * 16, RPT1 = RB1 * 16;
     constexpr int RP = RPT0 + RPT1;        // rows of the workgroup (= a.RB * 16)
     constexpr int MLS = RPT0 > RPT1 ? RPT0 : RPT1;
-    extern __shared__ __attribute__((aligned(1024))) char smem[];
 
     WideWave w;
-    w.split = blockIdx.y;
-    w.b = blockIdx.z;
-    w.hkv = a.rot ? (int)((blockIdx.x + w.split) % a.Hkv) : (int)blockIdx.x;
-    w.L = min(a.ctx_lens[w.b], a.max_ctx);
-    w.c0 = split_begin(a, w.split, w.hkv);
-    if (w.c0 >= w.L) return;
-    w.c1 = min(split_end(a, w.split, w.hkv), w.L);
+    w.b = b;
+    w.hkv = hkv;
+    w.L = L;
+    w.c0 = c0;
+    w.c1 = c1;
     w.Q = seq_queries(a, w.b);
     w.R = w.Q * a.G;
     const int tid = threadIdx.x;
@@ -763,7 +869,6 @@ __global__ void __launch_bounds__(2 * kWaves * 64) verify_attn_split_wide(AttnLa
 
     constexpr int OROW = D + 4;
     float* mlbuf = reinterpret_cast<float*>(smem) + 2 * RP * OROW;              // [8 waves][MLS][2]
-    const int64_t pbase = (((int64_t)w.b * a.Hkv + w.hkv) * a.nsplit + w.split) * RP;
     if (RB0 == RB1 || team == 0)
         wide_team<D, RB0, MLS, PAGED>(a, w, smem, team * RPT0, reinterpret_cast<float*>(smem) + team * 2 * RPT0 * OROW,
                                       mlbuf, pbase);
@@ -784,12 +889,35 @@ __global__ void __launch_bounds__(2 * kWaves * 64) verify_attn_split_wide(AttnLa
     }
 }
 
+template <int D, int RB0, int RB1, bool PAGED, bool BALANCED>
+__global__ void __launch_bounds__(2 * kWaves * 64) verify_attn_split_wide(AttnLaunch a)
+{
+    constexpr int RP = (RB0 + RB1) * 16;
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int split = blockIdx.y, b = blockIdx.z;
+    const int hkv = a.rot ? (int)((blockIdx.x + split) % a.Hkv) : (int)blockIdx.x;
+    if (BALANCED) {
+        for_each_piece(a, split, hkv, threadIdx.x & 63, [&](int pb, int L, int c0, int c1) {
+            split_piece_wide<D, RB0, RB1, PAGED>(a, smem, pb, hkv, L, c0, c1, ((int64_t)hkv * a.nslots + split + pb) * RP);
+            wait_loads<0>();
+            __syncthreads();
+        });
+        return;
+    }
+    const int L = seq_len(a, b);
+    const int c0 = split_begin(a, split, hkv);
+    if (c0 >= L) return;
+    split_piece_wide<D, RB0, RB1, PAGED>(a, smem, b, hkv, L, c0, min(split_end(a, split, hkv), L),
+                                         (((int64_t)b * a.Hkv + hkv) * a.nsplit + split) * RP);
+}
+
 // Merge the splits of one query row: out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
 // One workgroup of D threads per (sequence, kv head, packed row), splits taken 32 at a
 // time.  The kernel is latency bound, so every thread issues the loads of its column
 // for a whole block of splits before anything else, next to the (m, l) loads; the
-// weights are formed while they are in flight.
-template <int D>
+// weights are formed while they are in flight.  (With balanced shares the lengths decide which
+// partials belong to the sequence, so there they come first.)
+template <int D, bool BALANCED>
 __global__ void __launch_bounds__(D) verify_attn_merge(AttnLaunch a)
 {
     constexpr int SB = 32;                             // splits per block
@@ -807,15 +935,39 @@ __global__ void __launch_bounds__(D) verify_attn_merge(AttnLaunch a)
         if (a.lse_out && d == 0) a.lse_out[((int64_t)b * a.Hq + h) * a.Qmax + qi] = 0.f;
         return;
     }
-    const int64_t pbase = ((int64_t)b * a.Hkv + hkv) * a.nsplit * RP;
+    int64_t pbase = ((int64_t)b * a.Hkv + hkv) * a.nsplit * RP;
     float M = -INFINITY, den = 0.f, num = 0.f;
     int ns = a.nsplit;                                 // refined below, once the length has arrived
+    if (BALANCED) {
+        // the groups whose shares hold a token of this sequence
+        const int lane = d & 63;
+        int before = 0, total = 0, cost = 0;
+        for (int b0 = 0; b0 < a.B; b0 += 64) {
+            const int own = b0 + lane < a.B ? seq_cost(seq_len(a, b0 + lane)) : 0;
+            const int end = total + scan_costs(own, lane);
+            if (b >= b0 && b < b0 + 64) {
+                cost = __builtin_amdgcn_readlane(own, b - b0);
+                before = __builtin_amdgcn_readlane(end, b - b0) - cost;
+            }
+            total = __builtin_amdgcn_readlane(end, 63);
+        }
+        const Shares sh = make_shares(a, total);
+        const int x0 = before + kPieceQuanta, x1 = before + cost;     // the cost quanta of its tokens
+        ns = 0;
+        if (x0 < x1) {
+            int g0 = 2 * sh.pair_of(x0), g1 = 2 * sh.pair_of(x1 - 1) + 1;
+            if (sh.begin(g0 + 1, hkv) <= x0) ++g0;
+            if (sh.begin(g1, hkv) >= x1) --g1;
+            ns = g1 - g0 + 1;
+            pbase = ((int64_t)hkv * a.nslots + g0 + b) * RP;
+        }
+    }
     for (int s0 = 0; s0 < ns; s0 += SB) {
         // The loads of a block do not wait for the sequence length: every split slot of the
         // workspace is addressable, and the slots of splits that hold no token (stale or
         // never written) are discarded after the fact.  The length is one more dependent
         // memory round trip that this way overlaps with the loads.
-        const int nsb = min(SB, a.nsplit - s0);
+        const int nsb = min(SB, (BALANCED ? ns : a.nsplit) - s0);
         const float* po = a.part_o + (pbase + (int64_t)s0 * RP + row) * D + d;
         float o[SB];
 #pragma unroll
@@ -826,8 +978,8 @@ __global__ void __launch_bounds__(D) verify_attn_merge(AttnLaunch a)
             ms = ml[0];
             ls = ml[1];
         }
-        if (s0 == 0) {
-            const int L = min(a.ctx_lens[b], a.max_ctx);
+        if (!BALANCED && s0 == 0) {
+            const int L = seq_len(a, b);
             ns = min(L / a.chunk + 2, a.nsplit);      // splits that hold a token of this sequence
             while (ns > 0 && split_begin(a, ns - 1, hkv) >= L) --ns;
         }
@@ -868,82 +1020,92 @@ __global__ void __launch_bounds__(D) verify_attn_merge(AttnLaunch a)
         a.lse_out[((int64_t)b * a.Hq + h) * a.Qmax + qi] = (M + log2f(den)) * 0.6931471805599453f;
 }
 
-template <int D, int RB, bool PAGED>
+// Grid: (kv head, split, sequence), or one workgroup per (kv head, group) with balanced shares.
+dim3 split_grid(const AttnLaunch& a) { return a.groups ? dim3(a.Hkv, a.groups, 1) : dim3(a.Hkv, a.nsplit, a.B); }
+
+template <int D, int RB, bool PAGED, bool BALANCED>
 hipError_t launch_split(const AttnLaunch& a, hipStream_t stream)
 {
     constexpr int lds = attn_lds_bytes<D, RB>();
-    auto fn = verify_attn_split<D, RB, PAGED>;
-    dim3 grid(a.Hkv, a.nsplit, a.B), block(kWaves * 64);
-    hipLaunchKernelGGL(fn, grid, block, lds, stream, a);
+    auto fn = verify_attn_split<D, RB, PAGED, BALANCED>;
+    hipLaunchKernelGGL(fn, split_grid(a), dim3(kWaves * 64), lds, stream, a);
     return hipGetLastError();
 }
 
-template <int D, int RB0, int RB1, bool PAGED>
+template <int D, int RB0, int RB1, bool PAGED, bool BALANCED>
 hipError_t launch_split_wide(const AttnLaunch& a, hipStream_t stream)
 {
     constexpr int lds = attn_wide_lds_bytes<D, RB0, RB1>();
-    auto fn = verify_attn_split_wide<D, RB0, RB1, PAGED>;
-    dim3 grid(a.Hkv, a.nsplit, a.B), block(2 * kWaves * 64);
-    hipLaunchKernelGGL(fn, grid, block, lds, stream, a);
+    auto fn = verify_attn_split_wide<D, RB0, RB1, PAGED, BALANCED>;
+    hipLaunchKernelGGL(fn, split_grid(a), dim3(2 * kWaves * 64), lds, stream, a);
     return hipGetLastError();
 }
-template <int D, int RB0, int RB1, bool PAGED>
+template <int D, int RB0, int RB1, bool PAGED, bool BALANCED>
 hipError_t configure_split_wide()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(verify_attn_split_wide<D, RB0, RB1, PAGED>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(verify_attn_split_wide<D, RB0, RB1, PAGED, BALANCED>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, attn_wide_lds_bytes<D, RB0, RB1>());
 }
 
 // The split kernels use more dynamic LDS than the default limit allows; raise it once
 // per device, ahead of any launch (and so outside any stream capture).
-template <int D, int RB, bool PAGED>
+template <int D, int RB, bool PAGED, bool BALANCED>
 hipError_t configure_split()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(verify_attn_split<D, RB, PAGED>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(verify_attn_split<D, RB, PAGED, BALANCED>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, attn_lds_bytes<D, RB>());
 }
-template <int D, bool PAGED>
+template <int D, bool PAGED, bool BALANCED>
 hipError_t configure_rb()
 {
     hipError_t e;
-    if ((e = configure_split<D, 1, PAGED>()) != hipSuccess) return e;
-    if ((e = configure_split<D, 2, PAGED>()) != hipSuccess) return e;
-    if ((e = configure_split<D, 3, PAGED>()) != hipSuccess) return e;
-    if ((e = configure_split<D, 4, PAGED>()) != hipSuccess) return e;
-    if ((e = configure_split<D, 5, PAGED>()) != hipSuccess) return e;
-    if ((e = configure_split_wide<D, 2, 2, PAGED>()) != hipSuccess) return e;
-    if ((e = configure_split_wide<D, 3, 2, PAGED>()) != hipSuccess) return e;
-    return configure_split_wide<D, 3, 3, PAGED>();
+    if ((e = configure_split<D, 1, PAGED, BALANCED>()) != hipSuccess) return e;
+    if ((e = configure_split<D, 2, PAGED, BALANCED>()) != hipSuccess) return e;
+    if ((e = configure_split<D, 3, PAGED, BALANCED>()) != hipSuccess) return e;
+    if ((e = configure_split<D, 4, PAGED, BALANCED>()) != hipSuccess) return e;
+    if ((e = configure_split_wide<D, 3, 2, PAGED, BALANCED>()) != hipSuccess) return e;
+    return configure_split_wide<D, 3, 3, PAGED, BALANCED>();
+}
+template <int D>
+hipError_t configure_d()
+{
+    hipError_t e;
+    if ((e = configure_rb<D, false, false>()) != hipSuccess) return e;
+    if ((e = configure_rb<D, false, true>()) != hipSuccess) return e;
+    if ((e = configure_rb<D, true, false>()) != hipSuccess) return e;
+    return configure_rb<D, true, true>();
 }
 
-template <int D, bool PAGED>
+template <int D, bool PAGED, bool BALANCED>
 hipError_t dispatch_rb(const AttnLaunch& a, hipStream_t stream)
 {
-    if (a.wide) {                                    // a.RB row blocks over two teams
-        if (a.RB == 4) return launch_split_wide<D, 2, 2, PAGED>(a, stream);
-        if (a.RB == 5) return launch_split_wide<D, 3, 2, PAGED>(a, stream);
-        if (a.RB == 6) return launch_split_wide<D, 3, 3, PAGED>(a, stream);
-        return hipErrorInvalidValue;
-    }
+    hipError_t e = hipErrorInvalidValue;
     switch (a.RB) {
-        case 1: return launch_split<D, 1, PAGED>(a, stream);
-        case 2: return launch_split<D, 2, PAGED>(a, stream);
-        case 3: return launch_split<D, 3, PAGED>(a, stream);
-        case 4: return launch_split<D, 4, PAGED>(a, stream);
-        case 5: return launch_split<D, 5, PAGED>(a, stream);
+        case 1: e = launch_split<D, 1, PAGED, BALANCED>(a, stream); break;
+        case 2: e = launch_split<D, 2, PAGED, BALANCED>(a, stream); break;
+        case 3: e = launch_split<D, 3, PAGED, BALANCED>(a, stream); break;
+        case 4: e = launch_split<D, 4, PAGED, BALANCED>(a, stream); break;
+        case 5: e = launch_split_wide<D, 3, 2, PAGED, BALANCED>(a, stream); break;     // two teams from five row blocks on
+        case 6: e = launch_split_wide<D, 3, 3, PAGED, BALANCED>(a, stream); break;
     }
-    return hipErrorInvalidValue;
+    if (e != hipSuccess) return e;
+    auto merge = verify_attn_merge<D, BALANCED>;
+    hipLaunchKernelGGL(merge, dim3(a.Qmax * a.G, a.Hkv, a.B), dim3(D), 0, stream, a);
+    return hipGetLastError();
+}
+template <int D>
+hipError_t dispatch_d(const AttnLaunch& a, hipStream_t stream)
+{
+    if (a.page_shift >= 0) return a.groups ? dispatch_rb<D, true, true>(a, stream) : dispatch_rb<D, true, false>(a, stream);
+    return a.groups ? dispatch_rb<D, false, true>(a, stream) : dispatch_rb<D, false, false>(a, stream);
 }
 
 }  // namespace
 
 hipError_t configure_verify_attn()
 {
-    hipError_t e;
-    if ((e = configure_rb<128, false>()) != hipSuccess) return e;
-    if ((e = configure_rb<128, true>()) != hipSuccess) return e;
-    if ((e = configure_rb<64, false>()) != hipSuccess) return e;
-    return configure_rb<64, true>();
+    const hipError_t e = configure_d<128>();
+    return e != hipSuccess ? e : configure_d<64>();
 }
 
 size_t attn_workspace_bytes(int B, int Hkv, int nsplit, int RB, int D)
@@ -955,14 +1117,7 @@ size_t attn_workspace_bytes(int B, int Hkv, int nsplit, int RB, int D)
 
 hipError_t launch_verify_attn(const AttnLaunch& a, hipStream_t stream)
 {
-    hipError_t e;
-    const bool paged = a.page_shift >= 0;
-    if (a.D == 128) e = paged ? dispatch_rb<128, true>(a, stream) : dispatch_rb<128, false>(a, stream);
-    else if (a.D == 64) e = paged ? dispatch_rb<64, true>(a, stream) : dispatch_rb<64, false>(a, stream);
-    else return hipErrorInvalidValue;
-    if (e != hipSuccess) return e;
-    dim3 grid(a.Qmax * a.G, a.Hkv, a.B);
-    if (a.D == 128) hipLaunchKernelGGL(verify_attn_merge<128>, grid, dim3(128), 0, stream, a);
-    else hipLaunchKernelGGL(verify_attn_merge<64>, grid, dim3(64), 0, stream, a);
-    return hipGetLastError();
+    if (a.D == 128) return dispatch_d<128>(a, stream);
+    if (a.D == 64) return dispatch_d<64>(a, stream);
+    return hipErrorInvalidValue;
 }
