@@ -325,9 +325,10 @@ __device__ __forceinline__ void poll_into(Addr addr, int lo, int hi, u64* dst, i
 // is compiled without implicit multiply-add contraction so that the two instantiations round alike.
 // UNROLL: the register path unrolls (its arrays need constant indices); the memory path keeps its
 // loops rolled, it is code that normally never runs and should stay small.
-template <int NV, bool UNROLL, class GetT, class GetD>
-__device__ __forceinline__ void slice_stats(GetT gt, GetD gd, bool do_t, bool do_d, float c, float* sh, int& bank,
-                                            float& mt, float& st, float& md, float& sd)
+// put_t / put_d receive the exponentials relative to the slice's maximum (the register path keeps them).
+template <int NV, bool UNROLL, class GetT, class GetD, class PutT, class PutD>
+__device__ __forceinline__ void slice_stats(GetT gt, GetD gd, PutT put_t, PutD put_d, bool do_t, bool do_d, float c,
+                                            float* sh, int& bank, float& mt, float& st, float& md, float& sd)
 {
     mt = -INFINITY;
     md = -INFINITY;
@@ -349,16 +350,18 @@ __device__ __forceinline__ void slice_stats(GetT gt, GetD gd, bool do_t, bool do
     if (do_t && mt > -INFINITY)
 #pragma unroll UNROLL ? NV : 1
         for (int v = 0; v < NV; ++v) {
-            const floatx4 x = gt(v);
+            floatx4 x = gt(v);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) st += fexp2((x[j] - mt) * c);
+            for (int j = 0; j < 4; ++j) st += x[j] = fexp2((x[j] - mt) * c);
+            put_t(v, x);
         }
     if (do_d && md > -INFINITY)
 #pragma unroll UNROLL ? NV : 1
         for (int v = 0; v < NV; ++v) {
-            const floatx4 y = gd(v);
+            floatx4 y = gd(v);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) sd += fexp2((y[j] - md) * c);
+            for (int j = 0; j < 4; ++j) sd += y[j] = fexp2((y[j] - md) * c);
+            put_d(v, y);
         }
     block_reduce2(st, sd, sh, bank, OpAddF(), OpAddF());
 }
@@ -366,8 +369,51 @@ __device__ __forceinline__ void slice_stats(GetT gt, GetD gd, bool do_t, bool do
 // Row normalisers in the form the elementwise pass uses (log2 units).
 struct PairNorm { float Mt, l2St, Md, l2Sd; };
 
-// d = z/T + eta (q - p) of one entry, in log2 units relative to zmax_t/T.  Entries past V were
-// loaded as -inf: p = q = 0 and d = -inf.
+// The shifted row p_hat ~ e^{z/T + eta (q - p)}, in two forms.
+//
+// Plain (eta <= kPlainEta): the exponentials e_t, e_d of the slice statistics stay in the registers, p and q are
+// multiples of them, and f = e_t e^{eta (q - p)} takes ONE further exponential per entry pair (three in all; the
+// logarithmic form takes five of these quarter-rate instructions).  f is relative to the slice's maximum; the slice
+// publishes (max f, sum f) scaled to the row's maximum, so the slices' results simply add up.  In fp32 e_t is lost
+// below 2^-126 of the maximum, while the shift moves an entry by at most eta log2(e) either way: what is lost is
+// below V 2^(2 eta log2(e) - 126) of the sum, 2^-46 for eta = 20 and the largest vocabulary.
+//
+// Logarithmic (larger eta, where that bound does not hold): d = z/T + eta (q - p) in log2 units relative to zmax_t/T,
+// (max d, sum 2^(d - max)) per slice.
+constexpr float kPlainEta = 20.f;
+
+struct Mix { float ap, aq, scale; };         // e_t ap = eta p, e_d aq = eta q (times log2 e); slice -> row scale
+// Rt, Rd: what the slice's e_t, e_d are relative to
+__device__ __forceinline__ Mix make_mix(float Rt, float Rd, const PairNorm& r, float c, float eta_l2)
+{
+    return Mix{eta_l2 * fexp2((Rt - r.Mt) * c - r.l2St), eta_l2 * fexp2((Rd - r.Md) * c - r.l2Sd), fexp2((Rt - r.Mt) * c)};
+}
+__device__ __forceinline__ float mixed(float et, float ed, const Mix& m) { return et * fexp2(fmaf(ed, m.aq, -(et * m.ap))); }
+// exponential of a logit relative to R (a slice without finite logits: 0)
+__device__ __forceinline__ floatx4 rel_exp(floatx4 z, float R, float c)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) z[j] = R > -INFINITY ? fexp2((z[j] - R) * c) : 0.f;
+    return z;
+}
+// (max f, sum f) of a slice; f(v) yields f of the thread's v-th float4
+template <int NV, bool UNROLL, class GetF>
+__device__ __forceinline__ void mixed_stats(GetF f, float scale, float* sh, int& bank, float& fmx, float& fsum)
+{
+    fmx = 0.f;
+    fsum = 0.f;
+#pragma unroll UNROLL ? NV : 1
+    for (int v = 0; v < NV; ++v) {
+        const floatx4 x = f(v);
+        fmx = fmaxf(fmx, fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
+        fsum += (x[0] + x[1]) + (x[2] + x[3]);
+    }
+    block_reduce2(fmx, fsum, sh, bank, OpMaxF(), OpAddF());
+    fmx *= scale;
+    fsum *= scale;
+}
+
+// d of one entry.  Entries past V were loaded as -inf: p = q = 0 and d = -inf.
 __device__ __forceinline__ float shifted(float zt, float zd, const PairNorm& r, float c, float eta_l2)
 {
     const float at = (zt - r.Mt) * c;
@@ -446,7 +492,8 @@ struct LdsA {
 // ---------------------------------------------------------------- accept_rows
 // One workgroup per work item (sequence b, row k, slice w), slice index fastest in dispatch order, so
 // the slices of one row pair are worked on by different workgroups at about the same time.
-template <int NV>
+// PLAIN: the form of the shifted row (see above).
+template <int NV, bool PLAIN>
 __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws, int W, int n_items)
 {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
@@ -511,10 +558,13 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
             return [row, vec, s, tid, V](int v) { return load4(row, (int64_t)s * kSlice + (v * kThreads + tid) * 4, V, vec); };
         };
 
-        // ---- statistics of the own slice
+        // ---- statistics of the own slice; the plain form keeps the exponentials in place of the logits
+        float mt = -INFINITY, md = -INFINITY;
         if (own_t || own_d) {
-            float mt, st, md, sd;
-            slice_stats<NV, true>(reg_t, reg_d, own_t, own_d, c, lds.red, bank, mt, st, md, sd);
+            float st, sd;
+            auto put_t = [&](int v, floatx4 e) { if (PLAIN) x[v] = e; };
+            auto put_d = [&](int v, floatx4 e) { if (PLAIN) y[v] = e; };
+            slice_stats<NV, true>(reg_t, reg_d, put_t, put_d, own_t, own_d, c, lds.red, bank, mt, st, md, sd);
             if (tid == 0) {
                 if (own_t) publish2f(slot_t + 2 * w, mt, st, tg);
                 if (own_d) publish2f(slot_d + 2 * w, md, sd, tg);
@@ -541,7 +591,9 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
                     const bool miss_t = need_t && !have(got, s), miss_d = need_d && !have(got + W2w, s);
                     if (!miss_t && !miss_d) continue;
                     float mt, st, md, sd;
-                    slice_stats<NV, false>(mem_slice(zt, vec_t, s), mem_slice(zd, vec_d, s), miss_t, miss_d, c, lds.red, bank, mt, st, md, sd);
+                    auto drop = [](int, floatx4) {};
+                    slice_stats<NV, false>(mem_slice(zt, vec_t, s), mem_slice(zd, vec_d, s), drop, drop, miss_t, miss_d, c,
+                                           lds.red, bank, mt, st, md, sd);
                     if (tid == 0) {
                         if (miss_t) { keep2f(got, s, mt, st); publish2f(slot_t + 2 * s, mt, st, tg); }
                         if (miss_d) { keep2f(got + W2w, s, md, sd); publish2f(slot_d + 2 * s, md, sd, tg); }
@@ -602,14 +654,33 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
             }
             __syncthreads();
             const PairNorm r = lds.norm;
-            // ---- d for the own slice (kept in x), its statistics
+            // ---- the shifted row over the own slice
             float mh, shs;
-            auto d_first = [&](int v) {
+            if (PLAIN) {
+                const float Rt = own_t ? mt : r.Mt, Rd = own_d ? md : r.Md;
+                // a side with supplied statistics still holds logits; so does a slice without finite ones (exponentials: 0)
+                if (!own_t || !(Rt > -INFINITY))
 #pragma unroll
-                for (int j = 0; j < 4; ++j) x[v][j] = shifted(x[v][j], y[v][j], r, c, eta_l2);
-                return x[v];
-            };
-            shifted_stats<NV, true>(d_first, reg_t, lds.red, bank, mh, shs);
+                    for (int v = 0; v < NV; ++v) x[v] = rel_exp(x[v], Rt, c);
+                if (!own_d || !(Rd > -INFINITY))
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) y[v] = rel_exp(y[v], Rd, c);
+                const Mix m = make_mix(Rt, Rd, r, c, eta_l2);
+                auto f = [&](int v) {
+                    floatx4 w4;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) w4[j] = mixed(x[v][j], y[v][j], m);
+                    return w4;
+                };
+                mixed_stats<NV, true>(f, m.scale, lds.red, bank, mh, shs);
+            } else {
+                auto d_first = [&](int v) {                   // d replaces the logits in x
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[v][j] = shifted(x[v][j], y[v][j], r, c, eta_l2);
+                    return x[v];
+                };
+                shifted_stats<NV, true>(d_first, reg_t, lds.red, bank, mh, shs);
+            }
             if (tid == 0) publish2f(slot_h + 2 * w, mh, shs, tg);
             STAMP_AT(id, 4);
         }
@@ -644,15 +715,28 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
                         if (have(got_h, s)) continue;
                         auto gt = mem_slice(zt, vec_t, s);
                         auto gd = mem_slice(zd, vec_d, s);
-                        auto d_mem = [&](int v) {
-                            floatx4 t4 = gt(v);
-                            const floatx4 d4 = gd(v);
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) t4[j] = shifted(t4[j], d4[j], r, c, eta_l2);
-                            return t4;
-                        };
                         float mh, shs;
-                        shifted_stats<NV, false>(d_mem, d_mem, lds.red, bank, mh, shs);
+                        if (PLAIN) {
+                            const float Rt = own_t ? lo_f(got[2 * s]) : r.Mt, Rd = own_d ? lo_f(got[W2w + 2 * s]) : r.Md;
+                            const Mix m = make_mix(Rt, Rd, r, c, eta_l2);
+                            auto f_mem = [&](int v) {
+                                floatx4 t4 = rel_exp(gt(v), Rt, c);
+                                const floatx4 d4 = rel_exp(gd(v), Rd, c);
+#pragma unroll
+                                for (int j = 0; j < 4; ++j) t4[j] = mixed(t4[j], d4[j], m);
+                                return t4;
+                            };
+                            mixed_stats<NV, false>(f_mem, m.scale, lds.red, bank, mh, shs);
+                        } else {
+                            auto d_mem = [&](int v) {
+                                floatx4 t4 = gt(v);
+                                const floatx4 d4 = gd(v);
+#pragma unroll
+                                for (int j = 0; j < 4; ++j) t4[j] = shifted(t4[j], d4[j], r, c, eta_l2);
+                                return t4;
+                            };
+                            shifted_stats<NV, false>(d_mem, d_mem, lds.red, bank, mh, shs);
+                        }
                         if (tid == 0) { keep2f(got_h, s, mh, shs); publish2f(slot_h + 2 * s, mh, shs, tg); count_giveup(ws.status, tg); }
                         __syncthreads();
                     }
@@ -665,7 +749,17 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
                 if (pair) {
                     Mt = lds.dec[0]; St = lds.dec[1]; Md = lds.dec[2]; Sd = lds.dec[3];
                     auto pair_h = [&](int i) { return make_float2(lo_f(got_h[2 * i]), lo_f(got_h[2 * i + 1])); };
-                    wave_combine_f64(pair_h, W, kLn2, Mh, Sh);
+                    if (PLAIN) {                             // (max f, sum f): 1 / Sh of the other form is Mh / Sh here
+                        double m = 0.0, sum = 0.0;
+                        for (int i = lane; i < W; i += 64) {
+                            m = fmax(m, (double)pair_h(i).x);
+                            sum += (double)pair_h(i).y;
+                        }
+                        Mh = wave_max(m);
+                        Sh = wave_sum(sum);
+                    } else {
+                        wave_combine_f64(pair_h, W, kLn2, Mh, Sh);
+                    }
                 } else {
                     wave_combine_f64(pair_t, n_t, a.inv_T_exact, Mt, St);
                 }
@@ -678,12 +772,13 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
                         bool ok = false;
                         const bool in_range = xtok >= 0 && xtok < V;
                         if (in_range) {
-                            // p = e^at / St, q = e^ad / Sd, p_hat = e^(at + eta (q - p) - Mh ln2) / Sh, max p_hat = 1 / Sh
+                            // p = e^at / St, q = e^ad / Sd; plain: p_hat = e^(at + eta (q - p)) / Sh, max p_hat = Mh / Sh;
+                            // logarithmic: p_hat = e^(at + eta (q - p) - Mh ln2) / Sh, max p_hat = 1 / Sh
                             const double invT = a.inv_T_exact;
                             const double at = ((double)zx_t - Mt) * invT;
                             const double p = exp_c(at) / St, q = exp_c(((double)zx_d - Md) * invT) / Sd;
-                            double ph = exp_c(at + (double)a.eta * (q - p) - Mh * kLn2) / Sh;
-                            if (ph < (double)a.tail_alpha / Sh) ph = p;
+                            double ph = exp_c(at + (double)a.eta * (q - p) - (PLAIN ? 0.0 : Mh * kLn2)) / Sh;
+                            if (ph < (double)a.tail_alpha * (PLAIN ? Mh : 1.0) / Sh) ph = p;
                             rho = q > 0.0 ? ph / q : INFINITY;
                             const double u = (double)a.uniforms[(int64_t)b * rows + k];
                             ok = u <= fmin(1.0, rho);
@@ -1021,9 +1116,11 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)
     const int grid = (int)n_items;
     const size_t lds_a = sizeof(LdsA) + (size_t)6 * W * sizeof(u64);
     const dim3 blk(kThreads);
-    if (nv == 8) hipLaunchKernelGGL(accept_rows<8>, dim3(grid), blk, lds_a, stream, a, ws, W, (int)n_items);
-    else if (nv == 4) hipLaunchKernelGGL(accept_rows<4>, dim3(grid), blk, lds_a, stream, a, ws, W, (int)n_items);
-    else hipLaunchKernelGGL(accept_rows<2>, dim3(grid), blk, lds_a, stream, a, ws, W, (int)n_items);
+    const bool plain = a.eta <= kPlainEta;
+    auto rows_kernel = nv == 8 ? (plain ? accept_rows<8, true> : accept_rows<8, false>)
+                     : nv == 4 ? (plain ? accept_rows<4, true> : accept_rows<4, false>)
+                               : (plain ? accept_rows<2, true> : accept_rows<2, false>);
+    hipLaunchKernelGGL(rows_kernel, dim3(grid), blk, lds_a, stream, a, ws, W, (int)n_items);
     const size_t lds_b = sizeof(LdsB) + (size_t)4 * ws.w2 * sizeof(u64);
     if ((int64_t)ws.w2 * a.B <= a.n_cu)
         hipLaunchKernelGGL((accept_draw_row<8, 2>), dim3(ws.w2, a.B), blk, lds_b, stream, a, ws, ws.w2);

@@ -1,0 +1,75 @@
+"""The two forms in which the accept pass keeps the shifted row p_hat ~ exp(z/T + eta (q - p)): multiples of the kept
+exponentials up to eta = 20, logarithms above.  Both around the switch, with every slice size, at low temperature (where
+exponentials underflow), with masked parts of the vocabulary (-inf and the lowest float), with and without supplied row
+statistics, and with every exchange recomputed: against the oracle, and bit for bit between the runs."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as gu
+from paper_2502_20330_amd import binding
+from paper_2502_20330_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _masked(acc, kind):
+    zt, zd = acc.target_logits, acc.draft_logits
+    low = {"none": None, "inf": -np.inf, "lowest": np.finfo(np.float32).min}[kind]
+    if low is None:
+        return acc
+    # a whole slice of either row and scattered entries; never a drafted token
+    for z in (zt, zd):
+        z[:, :, 16384:33000] = low
+        z[:, :, 5::97] = low
+    keep = np.arange(zt.shape[2])
+    keep = keep[(keep % 97 != 5) & ((keep < 16384) | (keep >= 33000))]
+    rng = np.random.default_rng(9)
+    best = keep[np.argsort(-zd[:, :, keep], axis=-1)[..., :6]]
+    acc.draft_tokens[:] = np.take_along_axis(best, rng.integers(0, 6, acc.draft_tokens.shape)[..., None], -1)[..., 0]
+    return acc
+
+
+def _chunk_stats(z, chunk, T):
+    rows = z.reshape(-1, z.shape[-1]).astype(np.float64)
+    n = -(-rows.shape[1] // chunk)
+    rows = np.pad(rows, ((0, 0), (0, n * chunk - rows.shape[1])), constant_values=-np.inf).reshape(len(rows), n, chunk)
+    m = rows.max(-1)
+    with np.errstate(invalid="ignore", over="ignore"):
+        e = np.where(np.isfinite(rows), np.exp((rows - np.where(np.isfinite(m), m, 0.0)[..., None]) / T), 0.0)
+    return torch.from_numpy(np.stack([m, e.sum(-1)], -1).astype(np.float32)).cuda()
+
+
+@pytest.mark.parametrize("slice_entries", [4096, 16384])
+@pytest.mark.parametrize("eta,T,mask", [(20.0, 0.1, "none"), (20.5, 0.1, "none"), (20.0, 1.0, "inf"), (20.5, 1.0, "inf"),
+                                        (1.0, 0.1, "lowest"), (50.0, 0.7, "lowest"), (0.0, 0.05, "inf")])
+def test_both_forms_match_the_oracle_and_each_other(slice_entries, eta, T, mask):
+    cfg = wl.scaled(wl.CONFIGS["llama8b_32k"], batch=4, vocab=50257, gamma_choices=(2, 4), eta=eta, temperature=T, name="forms")
+    acc = _masked(wl.gen_accept_inputs(cfg, salt=31), mask)
+    r = gu.rapid()
+    runs = []
+    try:
+        r.set_option(binding.OPT_ACCEPT_SLICE, slice_entries)
+        for wait in (100, 0, 2):
+            r.set_option(binding.OPT_ACCEPT_WAIT_US, wait)
+            gpu, ref = gu.run_accept_case(acc, eta=eta, temperature=T)
+            runs.append(gpu)
+        r.set_option(binding.OPT_ACCEPT_WAIT_US, 100)
+        dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+        for side in ((True, True), (True, False), (False, True)):
+            out = r.rapid_accept(dev(acc.target_logits), dev(acc.draft_logits), dev(acc.draft_tokens), eta, dev(acc.uniforms),
+                                 gammas=dev(acc.gammas), temperature=T,
+                                 target_stats=_chunk_stats(acc.target_logits, 1000, T) if side[0] else None,
+                                 draft_stats=_chunk_stats(acc.draft_logits, 1000, T) if side[1] else None)
+            torch.cuda.synchronize()
+            runs.append(tuple(t.cpu().numpy() for t in out))
+    finally:
+        r.set_option(binding.OPT_ACCEPT_WAIT_US, 100)
+        r.set_option(binding.OPT_ACCEPT_SLICE, 0)
+    for other in runs[1:3]:
+        assert all(np.array_equal(x.view(np.int32), y.view(np.int32)) for x, y in zip(runs[0], other))
+    for gpu in runs:
+        st = gu.compare_accept(gpu, ref, acc.gammas, cfg.gamma_max)
+        assert st["n_mismatch"] == 0 and st["token_mismatch"] == 0 and st["exempt_sequences"] == 0, st
+        # fp32 arguments of the exponentials: |z - max| / T up to 30 / 0.05 at 2^-24, a few times over
+        assert st["max_ratio_rel_err"] <= 1e-4, st
