@@ -67,7 +67,7 @@ namespace {
 
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
-constexpr int kDrawSlice = kThreads * 8;            // smallest slice of accept_draw_row (8 entries per thread)
+constexpr int kDrawSlice = kThreads * 2;            // smallest slice of accept_draw_row (2 entries per thread)
 constexpr int kMinSlice = kThreads * 4 * 2;         // smallest slice of accept_rows (NV = 2)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr double kLn2 = 0.6931471805599453;
@@ -161,6 +161,28 @@ __device__ __forceinline__ floatx4 load4(const float* row, int64_t i, int V, boo
     return load4_edge(row, i, V);
 }
 
+// NE consecutive logits of a row from index i on (i a multiple of NE).
+template <int NE>
+__device__ __forceinline__ void load_run(float (&r)[NE], const float* row, int64_t i, int V, bool vec)
+{
+    if constexpr (NE == 2) {
+        if (vec && i + 1 < V) {
+            const float2 x = *reinterpret_cast<const float2*>(row + i);
+            r[0] = x.x;
+            r[1] = x.y;
+        } else {
+            for (int j = 0; j < 2; ++j) r[j] = i + j < V ? row[i + j] : -INFINITY;
+        }
+    } else {
+#pragma unroll
+        for (int v = 0; v < NE / 4; ++v) {
+            const floatx4 x = load4(row, i + v * 4, V, vec);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[v * 4 + j] = x[j];
+        }
+    }
+}
+
 // Drafts of sequence b; device data, so clamped to the range the buffers were sized for.
 __device__ __forceinline__ int seq_gamma(const AcceptLaunch& a, int b)
 {
@@ -180,7 +202,7 @@ struct Ws {
     double* rows;     // [B][gmax+1][4]: zmax_t, zmax_d (raw maxima, exact)
     int32_t* flags;   // [B][gmax]: 1 = draft k passed its accept test, 2 = its id was outside [0, V)
     int wmax;         // slots per row (slices of the smallest slice size)
-    int w2;           // workgroups per sequence in accept_draw_row
+    int w2;           // workgroups per sequence in accept_draw_row at most
     size_t bytes;
 };
 constexpr int kCntRows = 8, kCntDraw = 9, kGiveRows = 10;
@@ -284,6 +306,73 @@ __device__ __forceinline__ double exp_c(double x)
     p = fma(p, r, 1.0);
     return ldexp(p, (int)k);
 }
+// The exponentials of accept_draw_row, millions of them at large batches: exp(x) = 2^e 2^(j/64) exp(r) with the
+// powers in a table that the workgroup keeps in LDS, |r| <= ln2/128 and a polynomial of degree 5 (r^6/720 < 4e-17).
+// About two thirds of exp_c's time; same range, ~3e-16.  Rounding to a multiple of ln2/64 by adding 1.5 2^52 leaves
+// the integer in the low word.
+__device__ const double kExp2Table[64] = {
+    0x1.0000000000000p+0, 0x1.02c9a3e778061p+0, 0x1.059b0d3158574p+0, 0x1.0874518759bc8p+0,
+    0x1.0b5586cf9890fp+0, 0x1.0e3ec32d3d1a2p+0, 0x1.11301d0125b51p+0, 0x1.1429aaea92de0p+0,
+    0x1.172b83c7d517bp+0, 0x1.1a35beb6fcb75p+0, 0x1.1d4873168b9aap+0, 0x1.2063b88628cd6p+0,
+    0x1.2387a6e756238p+0, 0x1.26b4565e27cddp+0, 0x1.29e9df51fdee1p+0, 0x1.2d285a6e4030bp+0,
+    0x1.306fe0a31b715p+0, 0x1.33c08b26416ffp+0, 0x1.371a7373aa9cbp+0, 0x1.3a7db34e59ff7p+0,
+    0x1.3dea64c123422p+0, 0x1.4160a21f72e2ap+0, 0x1.44e086061892dp+0, 0x1.486a2b5c13cd0p+0,
+    0x1.4bfdad5362a27p+0, 0x1.4f9b2769d2ca7p+0, 0x1.5342b569d4f82p+0, 0x1.56f4736b527dap+0,
+    0x1.5ab07dd485429p+0, 0x1.5e76f15ad2148p+0, 0x1.6247eb03a5585p+0, 0x1.6623882552225p+0,
+    0x1.6a09e667f3bcdp+0, 0x1.6dfb23c651a2fp+0, 0x1.71f75e8ec5f74p+0, 0x1.75feb564267c9p+0,
+    0x1.7a11473eb0187p+0, 0x1.7e2f336cf4e62p+0, 0x1.82589994cce13p+0, 0x1.868d99b4492edp+0,
+    0x1.8ace5422aa0dbp+0, 0x1.8f1ae99157736p+0, 0x1.93737b0cdc5e5p+0, 0x1.97d829fde4e50p+0,
+    0x1.9c49182a3f090p+0, 0x1.a0c667b5de565p+0, 0x1.a5503b23e255dp+0, 0x1.a9e6b5579fdbfp+0,
+    0x1.ae89f995ad3adp+0, 0x1.b33a2b84f15fbp+0, 0x1.b7f76f2fb5e47p+0, 0x1.bcc1e904bc1d2p+0,
+    0x1.c199bdd85529cp+0, 0x1.c67f12e57d14bp+0, 0x1.cb720dcef9069p+0, 0x1.d072d4a07897cp+0,
+    0x1.d5818dcfba487p+0, 0x1.da9e603db3285p+0, 0x1.dfc97337b9b5fp+0, 0x1.e502ee78b3ff6p+0,
+    0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0, 0x1.fa7c1819e90d8p+0,
+};
+//
+// a * b + k with the constant in scalar registers: left to itself the compiler keeps each coefficient in a vector register
+// pair (or copies it into one before every multiply-add), and the fifty of them spill the entries' own state.
+__device__ __forceinline__ double fma_k(double a, double b, double k)
+{
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(k));
+    return d;
+}
+__device__ __forceinline__ double exp_tab(double x, const double* tab)
+{
+    constexpr double kShift = 6755399441055744.0;
+    x = fmax(x, -746.0);
+    double kf = x * (64 * 1.4426950408889634);
+    kf += kShift;
+    const int k = (int)__double_as_longlong(kf);
+    const double kd = kf - kShift;
+    double r = fma(kd, -6.93147180369123816490e-01 / 64, x);
+    r = fma(kd, -1.90821492927058770002e-10 / 64, r);
+    double p = r * (1.0 / 120.0);
+    p += 1.0 / 24.0;
+    p = fma_k(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    const double t = tab[k & 63];
+    return ldexp(fma(t, p * r, t), k >> 6);
+}
+// exp(x) for the shift eta (q - p), which is tiny for all but the heaviest tokens: a polynomial up to 2^-6
+// (x^7/5040 < 5e-17).  Which form a lane takes depends on its x alone, so the result does not depend on its wave.
+__device__ __forceinline__ double exp_shift(double x, const double* tab)
+{
+    double p = x * (1.0 / 720.0);
+    p += 1.0 / 120.0;
+    p = fma_k(p, x, 1.0 / 24.0);
+    p = fma_k(p, x, 1.0 / 6.0);
+    p = fma(p, x, 0.5);
+    p = fma(p, x, 1.0);
+    p = fma(p, x, 1.0);
+    const bool large = !(fabs(x) <= 0.015625);
+    if (__any(large)) {
+        const double full = exp_tab(x, tab);
+        p = large ? full : p;
+    }
+    return p;
+}
 // Wave 0: poll the words addr(lo) .. addr(hi - 1) into dst[lo .. hi) until every one carries its
 // tag or `wait_ticks` have passed; *nmiss = words still unpublished (dst then holds what was there).
 // lo and hi are even and addr(i) has the parity of i.  Two words per lane and round.
@@ -316,6 +405,32 @@ __device__ __forceinline__ void poll_into(Addr addr, int lo, int hi, u64* dst, i
         miss += __popcll(__ballot(pa)) + __popcll(__ballot(pb));
     }
     if (lane == 0) *nmiss = miss;
+}
+
+// The same by the whole workgroup, one word per thread and round, for exchanges of hundreds of words;
+// miss[wave] = words of that wave still unpublished.  The caller synchronises before it reads dst and miss.
+__device__ __forceinline__ void poll_all(const u64* words, int n, u64* dst, int* miss, int64_t wait_ticks, const Tags& tg)
+{
+    const int64_t t0 = (int64_t)wall_clock64();
+    const uint32_t want = tag_of(threadIdx.x, tg);        // kThreads is even: every word of a thread has its parity
+    int m = 0;
+    for (int i0 = 0; i0 < n; i0 += kThreads) {
+        const int i = i0 + threadIdx.x;
+        u64 v = 0;
+        bool p = i < n;
+        for (;;) {
+            if (p) {
+                v = slot_load(words + i);
+                p = (uint32_t)(v >> 32) != want;
+            }
+            if (!__any(p)) break;
+            if ((int64_t)wall_clock64() - t0 >= wait_ticks) break;
+            __builtin_amdgcn_s_sleep(2);
+        }
+        if (i < n) dst[i] = v;
+        m += __popcll(__ballot(p));
+    }
+    if ((threadIdx.x & 63) == 0) miss[threadIdx.x >> 6] = m;
 }
 
 // ---------------------------------------------------------------- accept_rows: per-slice arithmetic
@@ -814,14 +929,17 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
 // Number of accepted drafts: index of the first failed accept test, or g.  Every wave reads the flags of
 // all gmax positions, one per lane, without waiting for the sequence's own count g (one dependent memory
 // round trip less); positions >= g hold whatever an earlier call left and are cut off by the min.
-__device__ __forceinline__ int first_reject(const Ws& ws, int b, int gmax, int g)
+// bad = positions < g whose id lies outside the vocabulary.
+__device__ __forceinline__ int first_reject(const Ws& ws, int b, int gmax, int g, int& bad)
 {
     const int lane = threadIdx.x & 63;
     int n = 0x7fffffff;
+    bad = 0;
     for (int k0 = 0; k0 < gmax; k0 += 64) {
         const int k = k0 + lane;
         const int f = k < gmax ? ws.flags[(int64_t)b * gmax + k] : 1;
         const unsigned long long rejected = __ballot(f != 1);
+        bad += __popcll(__ballot(f == 2 && k < g));
         if (rejected && n == 0x7fffffff) n = k0 + __ffsll((long long)rejected) - 1;
     }
     return min(n, g);
@@ -840,16 +958,17 @@ struct DrawNorm { double iSt, iSd, iSh, thr, eta; };
 
 struct LdsB {
     double red[4 * kWaves];
-    int nmiss;
+    double tab[64];       // 2^(j/64)
+    int miss[kWaves];
     u64 slots[];          // 4 W2 words: the two fp64 values of every slice for the current phase
 };
 
 // The three quantities of one entry that the phases are made of.
-__device__ __forceinline__ double draw_f(double et, double ed, const DrawNorm& nm)
+__device__ __forceinline__ double draw_f(double et, double ed, const DrawNorm& nm, const double* tab)
 {
-    return et * exp_c(nm.eta * (ed * nm.iSd - et * nm.iSt));
+    return et * exp_shift(nm.eta * (ed * nm.iSd - et * nm.iSt), tab);
 }
-// f = draw_f(et, ed, nm): the register path kept it from phase 2, the memory path forms it again (same bits).
+// f = draw_f(et, ed, nm, tab): the register path kept it from phase 2, the memory path forms it again (same bits).
 __device__ __forceinline__ double draw_weight(double et, double ed, double f, const DrawNorm& nm, double& p)
 {
     p = et * nm.iSt;
@@ -860,18 +979,19 @@ __device__ __forceinline__ double draw_weight(double et, double ed, double f, co
 }
 // Accumulates entry (et, ed) into the two running values of `phase`; the entries of a thread are
 // taken in index order both by the register path and by the memory path.
-__device__ __forceinline__ void draw_accumulate(int phase, double et, double ed, const DrawNorm& nm, double& a0, double& a1)
+__device__ __forceinline__ void draw_accumulate(int phase, double et, double ed, const DrawNorm& nm, const double* tab, double& a0,
+                                                double& a1)
 {
     if (phase == 1) {
         a0 += et;
         a1 += ed;
     } else if (phase == 2) {
-        const double f = draw_f(et, ed, nm);
+        const double f = draw_f(et, ed, nm, tab);
         a0 += f;
         a1 = fmax(a1, f);
     } else {
         double p;
-        a0 += draw_weight(et, ed, draw_f(et, ed, nm), nm, p);
+        a0 += draw_weight(et, ed, draw_f(et, ed, nm, tab), nm, p);
         a1 += p;
     }
 }
@@ -889,25 +1009,9 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     STAMP(8);
     const int g = seq_gamma(a, b);
-    const int n = first_reject(ws, b, a.gmax, g);
+    int bad;
+    const int n = first_reject(ws, b, a.gmax, g, bad);
     const double u = (double)a.uniforms[(int64_t)b * (a.gmax + 1) + a.gmax];
-    if (w == 0) {
-        // accepted drafts, then -1 (the draw fills slot n)
-        for (int k = tid; k <= a.gmax; k += kThreads)
-            if (k != n) a.out_tokens[(int64_t)b * (a.gmax + 1) + k] = k < n ? a.tokens[(int64_t)b * a.gmax + k] : -1;
-        if (tid == 0) {
-            a.n_accepted[b] = n;
-            int bad = 0;                                      // drafted ids outside the vocabulary
-            for (int k = 0; k < g; ++k) bad += ws.flags[(int64_t)b * a.gmax + k] == 2;
-            if (bad) atomicAdd(ws.status + 0, bad);
-            if (b == 0) {
-                // give-ups of accept_rows (counted under that kernel's tag), then its counter moves on
-                const Tags ta = make_tags((uint32_t)ws.status[kCntRows]);
-                if ((uint32_t)ws.status[kGiveRows + 1] == ta.t0) atomicAdd(ws.status + 1, ws.status[kGiveRows]);
-                ws.status[kCntRows] += 1;
-            }
-        }
-    }
     const Tags tg = make_tags(~(uint32_t)ws.status[kCntDraw]);
     const int V = a.V;
     int bank = 0;
@@ -923,18 +1027,26 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
     // f = e_t exp(eta (q - p)) after phase 2 and the draw weight after phase 3
     double et[NE], ed[NE], wgt[NE];
     const int64_t first = (int64_t)w * kSlice + (int64_t)tid * NE;
+    float t_in[NE], d_in[NE];
 #pragma unroll
-    for (int v = 0; v < NE / 4; ++v) {
-        const floatx4 t4 = load4(zt, first + v * 4, V, vec_t);
-        floatx4 d4 = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-        if (!bonus) d4 = load4(zd, first + v * 4, V, vec_d);
+    for (int i = 0; i < NE; ++i) d_in[i] = -INFINITY;
+    load_run<NE>(t_in, zt, first, V, vec_t);
+    if (!bonus) load_run<NE>(d_in, zd, first, V, vec_d);
+    if (tid < 64) lds.tab[tid] = kExp2Table[tid];
+    __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            et[v * 4 + j] = exp_c(((double)t4[j] - Mt) * invT);
-            ed[v * 4 + j] = bonus ? 0.0 : exp_c(((double)d4[j] - Md) * invT);
-            wgt[v * 4 + j] = 0.0;
-        }
+    for (int i = 0; i < NE; ++i) {
+        et[i] = exp_tab(((double)t_in[i] - Mt) * invT, lds.tab);
+        if (OCC > 2) __builtin_amdgcn_sched_barrier(0);       // few registers: one entry's temporaries at a time
     }
+#pragma unroll
+    for (int i = 0; i < NE; ++i) ed[i] = 0.0;
+    if (!bonus)
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            ed[i] = exp_tab(((double)d_in[i] - Md) * invT, lds.tab);
+            if (OCC > 2) __builtin_amdgcn_sched_barrier(0);
+        }
     STAMP(9);
     DrawNorm nm{1.0, 0.0, 0.0, 0.0, (double)a.eta};
     u64* my_slots = ws.slot_b + (int64_t)b * ws.w2 * 12;
@@ -955,28 +1067,39 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
     const int nphase = bonus ? 1 : 3;
     for (int phase = 1; phase <= nphase; ++phase) {
         double a0 = 0.0, a1 = phase == 2 ? -INFINITY : 0.0;
+        if (phase == 1) {
 #pragma unroll
-        for (int i = 0; i < NE; ++i) {
-            if (phase == 2) {                                 // f is kept for phase 3 (no second exponential)
-                wgt[i] = draw_f(et[i], ed[i], nm);
+            for (int i = 0; i < NE; ++i) {
+                a0 += et[i];
+                a1 += ed[i];
+            }
+        } else if (phase == 2) {                              // f is kept for phase 3 (no second exponential)
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                wgt[i] = draw_f(et[i], ed[i], nm, lds.tab);
                 a0 += wgt[i];
                 a1 = fmax(a1, wgt[i]);
-            } else if (phase == 3) {                          // the weights are kept for the token search
+                if (OCC > 2) __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {                                              // the weights are kept for the token search
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
                 double p;
                 wgt[i] = draw_weight(et[i], ed[i], wgt[i], nm, p);
                 a0 += wgt[i];
                 a1 += p;
-            } else {
-                draw_accumulate(phase, et[i], ed[i], nm, a0, a1);
             }
         }
         if (phase == 2) block_reduce2(a0, a1, lds.red, bank, OpAddD(), OpMaxD());
         else block_reduce2(a0, a1, lds.red, bank, OpAddD(), OpAddD());
         u64* base = my_slots + (phase - 1) * 4 * W2;         // slice s: words base[4 s .. 4 s + 3]
         if (tid == 0) { put_d(base + 4 * w, a0, tg, true); put_d(base + 4 * w + 2, a1, tg, true); }
-        if (tid < 64) poll_into([&](int i) { return base + i; }, 0, 4 * W2, lds.slots, &lds.nmiss, a.wait_ticks, tg);
+        poll_all(base, 4 * W2, lds.slots, lds.miss, a.wait_ticks, tg);
         __syncthreads();
-        if (__builtin_expect(lds.nmiss != 0, 0)) {
+        int miss = 0;
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) miss |= lds.miss[i];
+        if (__builtin_expect(miss != 0, 0)) {
             // a slice whose sums did not arrive: the same sums from the logits in memory
             for (int s = 0; s < W2; ++s) {
                 const u64* have = lds.slots + 4 * s;
@@ -985,9 +1108,9 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
 #pragma unroll 1
                 for (int i = 0; i < NE; ++i) {
                     const int64_t e = (int64_t)s * kSlice + (int64_t)tid * NE + i;
-                    const double met = e < V ? exp_c(((double)zt[e] - Mt) * invT) : 0.0;
-                    const double med = (!bonus && e < V) ? exp_c(((double)zd[e] - Md) * invT) : 0.0;
-                    draw_accumulate(phase, met, med, nm, m0, m1);
+                    const double met = e < V ? exp_tab(((double)zt[e] - Mt) * invT, lds.tab) : 0.0;
+                    const double med = (!bonus && e < V) ? exp_tab(((double)zd[e] - Md) * invT, lds.tab) : 0.0;
+                    draw_accumulate(phase, met, med, nm, lds.tab, m0, m1);
                 }
                 if (phase == 2) block_reduce2(m0, m1, lds.red, bank, OpAddD(), OpMaxD());
                 else block_reduce2(m0, m1, lds.red, bank, OpAddD(), OpAddD());
@@ -1046,6 +1169,21 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
     const double t = u * Wtot;
     prefix_pass(t, true, owner, excl);
     STAMP(13);
+    if (w == 0) {
+        // What the draw does not wait for: accepted drafts, then -1 (the draw fills slot n), and the counters.
+        for (int k = tid; k <= a.gmax; k += kThreads)
+            if (k != n) a.out_tokens[(int64_t)b * (a.gmax + 1) + k] = k < n ? a.tokens[(int64_t)b * a.gmax + k] : -1;
+        if (tid == 0) {
+            a.n_accepted[b] = n;
+            if (bad) atomicAdd(ws.status + 0, bad);
+            if (b == 0) {
+                // give-ups of accept_rows (counted under that kernel's tag), then its counter moves on
+                const Tags ta = make_tags((uint32_t)ws.status[kCntRows]);
+                if ((uint32_t)ws.status[kGiveRows + 1] == ta.t0) atomicAdd(ws.status + 1, ws.status[kGiveRows]);
+                ws.status[kCntRows] += 1;
+            }
+        }
+    }
     if (owner < 0) {                                          // no weight anywhere (NaN / infinite logits): any valid id
         if (w == 0 && tid == 0) a.out_tokens[(int64_t)b * (a.gmax + 1) + n] = 0;
         return;
@@ -1099,6 +1237,18 @@ size_t accept_workspace_bytes(int B, int gmax, int V)
     return carve(nullptr, B, gmax, V).bytes;
 }
 
+// Entries per thread of accept_draw_row: the fewest that leave every workgroup a compute unit of its own and keep the
+// exchange among at most 64 workgroups (one sequence: vocabulary 32001 22.1 us with 2, 23.0 with 4, 26.7 with 8;
+// 128256 23.7 with 2 on 126 workgroups, 23.0 with 4, 25.0 with 8).
+static int draw_entries(const AcceptLaunch& a)
+{
+    for (int ne = 2; ne < 8; ne *= 2) {
+        const int64_t wgs = ((int64_t)a.V + kThreads * ne - 1) / (kThreads * ne);
+        if (wgs <= 64 && wgs * a.B <= a.n_cu) return ne;
+    }
+    return 8;
+}
+
 hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)
 {
     Ws ws = carve(a.workspace, a.B, a.gmax, a.V);
@@ -1121,10 +1271,13 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)
                      : nv == 4 ? (plain ? accept_rows<4, true> : accept_rows<4, false>)
                                : (plain ? accept_rows<2, true> : accept_rows<2, false>);
     hipLaunchKernelGGL(rows_kernel, dim3(grid), blk, lds_a, stream, a, ws, W, (int)n_items);
-    const size_t lds_b = sizeof(LdsB) + (size_t)4 * ws.w2 * sizeof(u64);
-    if ((int64_t)ws.w2 * a.B <= a.n_cu)
-        hipLaunchKernelGGL((accept_draw_row<8, 2>), dim3(ws.w2, a.B), blk, lds_b, stream, a, ws, ws.w2);
-    else
-        hipLaunchKernelGGL((accept_draw_row<8, 4>), dim3(ws.w2, a.B), blk, lds_b, stream, a, ws, ws.w2);
+    const auto draw_wgs = [&](int ne) { return (a.V + kThreads * ne - 1) / (kThreads * ne); };
+    const int ne = draw_entries(a);
+    const int W2 = draw_wgs(ne);
+    auto draw_kernel = ne == 2 ? accept_draw_row<2, 2>
+                     : ne == 4 ? accept_draw_row<4, 2>
+                     : (int64_t)W2 * a.B <= a.n_cu ? accept_draw_row<8, 2> : accept_draw_row<8, 4>;
+    const size_t lds_b = sizeof(LdsB) + (size_t)4 * W2 * sizeof(u64);
+    hipLaunchKernelGGL(draw_kernel, dim3(W2, a.B), blk, lds_b, stream, a, ws, W2);
     return hipGetLastError();
 }
