@@ -145,40 +145,79 @@ __device__ __forceinline__ void block_reduce2(T& a, T& b, T* sh, int& bank, OpA 
     for (int w = 1; w < kWaves; ++w) { a = opa(a, s[w]); b = opb(b, s[kWaves + w]); }
 }
 
-// Four consecutive logits of a row starting at index i (i % 4 == 0); entries at or past V
-// come back as -inf.  `vec` says the row base is 16-byte aligned (V a multiple of 4 keeps all
-// rows aligned; otherwise the loads are scalar, which is slower but reads the same values).
-__device__ __attribute__((noinline)) floatx4 load4_edge(const float* row, int64_t i, int V)
+// Rows of logits start at any multiple of 4 bytes (a vocabulary that is not a multiple of four leaves three rows of
+// four unaligned); 128-bit global loads need no more than that.  (Scalar loads for such rows: an odd vocabulary of
+// 50257, eight sequences, took 22 us in accept_rows alone.)
+typedef floatx4 floatx4_any __attribute__((aligned(4)));
+__device__ __forceinline__ floatx4 load4_full(const float* p) { return *reinterpret_cast<const floatx4_any*>(p); }
+
+// Four consecutive logits of a row from index i on, where the row may end: entries at or past V come back as -inf.
+// Threads at the end load the row's last four entries and shift them.  Load and shift are two steps, so that a caller
+// has all its loads in flight before it waits for the first (V >= 4; shorter rows: load4).
+__device__ __forceinline__ floatx4 load4_tail(const float* row, int i, int V) { return load4_full(row + min(i, V - 4)); }
+__device__ __forceinline__ floatx4 shift_tail(floatx4 x, int i, int V)
 {
+    const int s = i - (V - 4);                            // entries of the load that lie before i
+    if (s > 0) {
+        if (s & 1) x = floatx4{x[1], x[2], x[3], -INFINITY};
+        if (s & 2) x = floatx4{x[2], x[3], -INFINITY, -INFINITY};
+        if (s > 3) x = floatx4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    }
+    return x;
+}
+__device__ __forceinline__ floatx4 load4(const float* row, int i, int V)
+{
+    if (V >= 4) return shift_tail(load4_tail(row, i, V), i, V);
     floatx4 r = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 3; ++j)
         if (i + j < V) r[j] = row[i + j];
     return r;
 }
-__device__ __forceinline__ floatx4 load4(const float* row, int64_t i, int V, bool vec)
+// N runs of four, `step` entries apart, the first at index i; `full`: the row holds all of them for every thread.
+template <int N>
+__device__ __forceinline__ void load_runs(floatx4 (&r)[N], const float* row, int i, int step, int V, bool full)
 {
-    if (__builtin_expect(vec && i + 3 < V, 1)) return *reinterpret_cast<const floatx4*>(row + i);
-    return load4_edge(row, i, V);
-}
-
-// NE consecutive logits of a row from index i on (i a multiple of NE).
-template <int NE>
-__device__ __forceinline__ void load_run(float (&r)[NE], const float* row, int64_t i, int V, bool vec)
-{
-    if constexpr (NE == 2) {
-        if (vec && i + 1 < V) {
-            const float2 x = *reinterpret_cast<const float2*>(row + i);
-            r[0] = x.x;
-            r[1] = x.y;
-        } else {
-            for (int j = 0; j < 2; ++j) r[j] = i + j < V ? row[i + j] : -INFINITY;
+    if (full) {
+#pragma unroll
+        for (int v = 0; v < N; ++v) r[v] = load4_full(row + i + v * step);
+    } else if (V >= 4) {
+#pragma unroll
+        for (int v = 0; v < N; ++v) {
+            r[v] = floatx4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+            if (i + v * step < V) r[v] = load4_tail(row, i + v * step, V);
         }
     } else {
 #pragma unroll
-        for (int v = 0; v < NE / 4; ++v) {
-            const floatx4 x = load4(row, i + v * 4, V, vec);
+        for (int v = 0; v < N; ++v) r[v] = load4(row, i + v * step, V);
+    }
+}
+template <int N>
+__device__ __forceinline__ void shift_runs(floatx4 (&r)[N], int i, int step, int V, bool full)
+{
+    if (full || V < 4) return;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) r[v * 4 + j] = x[j];
+    for (int v = 0; v < N; ++v) r[v] = shift_tail(r[v], i + v * step, V);
+}
+// NE consecutive logits from index i on.
+template <int NE>
+__device__ __forceinline__ void load_row(float (&t)[NE], const float* rt, float (&d)[NE], const float* rd, int i, int V, bool full)
+{
+    if constexpr (NE >= 4) {
+        floatx4 x[NE / 4], y[NE / 4];
+        load_runs(x, rt, i, 4, V, full);
+        if (rd) load_runs(y, rd, i, 4, V, full);
+        shift_runs(x, i, 4, V, full);
+        if (rd) shift_runs(y, i, 4, V, full);
+#pragma unroll
+        for (int j = 0; j < NE; ++j) {
+            t[j] = x[j / 4][j % 4];
+            d[j] = rd ? y[j / 4][j % 4] : -INFINITY;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < NE; ++j) {
+            t[j] = i + j < V ? rt[i + j] : -INFINITY;
+            d[j] = rd && i + j < V ? rd[i + j] : -INFINITY;
         }
     }
 }
@@ -630,26 +669,12 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
         const bool pair = k < g;
         const float* zt = row_t(b, k);
         const float* zd = pair ? row_d(b, k) : nullptr;
-        const bool vec_t = (reinterpret_cast<uintptr_t>(zt) & 15) == 0;
-        const bool vec_d = (reinterpret_cast<uintptr_t>(zd) & 15) == 0;
-        if (vec_t && (!pair || vec_d) && (int64_t)(w + 1) * kSlice <= V) {
-            // the whole slice exists and both rows are aligned: plain 128-bit loads (uniform branch)
-            const floatx4* pt = reinterpret_cast<const floatx4*>(zt + (int64_t)w * kSlice) + tid;
-#pragma unroll
-            for (int v = 0; v < NV; ++v) x[v] = pt[v * kThreads];
-            if (pair) {
-                const floatx4* pd = reinterpret_cast<const floatx4*>(zd + (int64_t)w * kSlice) + tid;
-#pragma unroll
-                for (int v = 0; v < NV; ++v) y[v] = pd[v * kThreads];
-            }
-        } else {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) x[v] = load4(zt, (int64_t)w * kSlice + (v * kThreads + tid) * 4, V, vec_t);
-            if (pair) {
-#pragma unroll
-                for (int v = 0; v < NV; ++v) y[v] = load4(zd, (int64_t)w * kSlice + (v * kThreads + tid) * 4, V, vec_d);
-            }
-        }
+        const bool full = (int64_t)(w + 1) * kSlice <= V;
+        const int i = w * kSlice + tid * 4;
+        load_runs(x, zt, i, kThreads * 4, V, full);
+        if (pair) load_runs(y, zd, i, kThreads * 4, V, full);
+        shift_runs(x, i, kThreads * 4, V, full);
+        if (pair) shift_runs(y, i, kThreads * 4, V, full);
     };
 
     // Everything after the loads of one item.
@@ -660,8 +685,6 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
         const bool pair = k < g;                              // row g has a target row only (the bonus position)
         const float* zt = row_t(b, k);
         const float* zd = pair ? row_d(b, k) : nullptr;
-        const bool vec_t = (reinterpret_cast<uintptr_t>(zt) & 15) == 0;
-        const bool vec_d = (reinterpret_cast<uintptr_t>(zd) & 15) == 0;
         const bool own_t = a.ext_t == nullptr, own_d = pair && a.ext_d == nullptr;
         u64* slot_t = ws.slot_t + ((int64_t)b * rows + k) * ws.wmax * 2;
         u64* slot_d = ws.slot_d + ((int64_t)b * a.gmax + (pair ? k : 0)) * ws.wmax * 2;
@@ -669,8 +692,8 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
         auto reg_t = [&](int v) { return x[v]; };
         auto reg_d = [&](int v) { return y[v]; };
         // slice s of either row straight from memory (a slice another workgroup owns)
-        auto mem_slice = [&](const float* row, bool vec, int s) {
-            return [row, vec, s, tid, V](int v) { return load4(row, (int64_t)s * kSlice + (v * kThreads + tid) * 4, V, vec); };
+        auto mem_slice = [&](const float* row, int s) {
+            return [row, s, tid, V](int v) { return load4(row, s * kSlice + (v * kThreads + tid) * 4, V); };
         };
 
         // ---- statistics of the own slice; the plain form keeps the exponentials in place of the logits
@@ -707,7 +730,7 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
                     if (!miss_t && !miss_d) continue;
                     float mt, st, md, sd;
                     auto drop = [](int, floatx4) {};
-                    slice_stats<NV, false>(mem_slice(zt, vec_t, s), mem_slice(zd, vec_d, s), drop, drop, miss_t, miss_d, c,
+                    slice_stats<NV, false>(mem_slice(zt, s), mem_slice(zd, s), drop, drop, miss_t, miss_d, c,
                                            lds.red, bank, mt, st, md, sd);
                     if (tid == 0) {
                         if (miss_t) { keep2f(got, s, mt, st); publish2f(slot_t + 2 * s, mt, st, tg); }
@@ -828,8 +851,8 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
                     const PairNorm r = lds.norm;
                     for (int s = 0; s < W; ++s) {
                         if (have(got_h, s)) continue;
-                        auto gt = mem_slice(zt, vec_t, s);
-                        auto gd = mem_slice(zd, vec_d, s);
+                        auto gt = mem_slice(zt, s);
+                        auto gd = mem_slice(zd, s);
                         float mh, shs;
                         if (PLAIN) {
                             const float Rt = own_t ? lo_f(got[2 * s]) : r.Mt, Rd = own_d ? lo_f(got[W2w + 2 * s]) : r.Md;
@@ -1018,8 +1041,6 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
     const bool bonus = n >= g;
     const float* zt = a.zt + ((int64_t)b * (a.gmax + 1) + n) * V;
     const float* zd = bonus ? nullptr : a.zd + ((int64_t)b * a.gmax + n) * V;
-    const bool vec_t = (reinterpret_cast<uintptr_t>(zt) & 15) == 0;
-    const bool vec_d = (reinterpret_cast<uintptr_t>(zd) & 15) == 0;
     const double* rec = ws.rows + ((int64_t)b * (a.gmax + 1) + n) * 4;
     const double Mt = rec[0], Md = rec[1], invT = a.inv_T_exact;
 
@@ -1028,10 +1049,7 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
     double et[NE], ed[NE], wgt[NE];
     const int64_t first = (int64_t)w * kSlice + (int64_t)tid * NE;
     float t_in[NE], d_in[NE];
-#pragma unroll
-    for (int i = 0; i < NE; ++i) d_in[i] = -INFINITY;
-    load_run<NE>(t_in, zt, first, V, vec_t);
-    if (!bonus) load_run<NE>(d_in, zd, first, V, vec_d);
+    load_row<NE>(t_in, zt, d_in, zd, (int)first, V, (int64_t)(w + 1) * kSlice <= V);
     if (tid < 64) lds.tab[tid] = kExp2Table[tid];
     __syncthreads();
 #pragma unroll
