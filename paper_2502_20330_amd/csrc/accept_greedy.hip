@@ -9,16 +9,17 @@
 // the lowest index.  The accept test stays the literal r <= min(1, limit of the ratio).
 //
 // Two launches, every logit read once:
-//   greedy_slice_argmax  per 4096-entry slice of every row: (max, lowest index of the max)
+//   greedy_slice_argmax  per slice of every row: (max, lowest index of the max); bound by HBM
 //   greedy_decide        one workgroup per sequence: rows combined, gaps compared in fp64 (the
-//                        difference of two fp32 numbers is exact there), prefix length, token
+//                        difference of two fp32 numbers is exact there), prefix length, token; bound by
+//                        the latency of its chain of loads
+#include "logit_rows.h"
 #include "rapid_internal.h"
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kDecide = 1024;                          // threads of greedy_decide: a wave per row, 16 rows at a time
 constexpr int kSlice = kThreads * 16;
 
 struct GreedyWs {
@@ -52,7 +53,9 @@ __device__ __forceinline__ void take_better(float& m, int& i, float m2, int i2)
     if (m2 > m || (m2 == m && i2 < i)) { m = m2; i = i2; }
 }
 
-// Row y of sequence b: y <= gmax the target rows, then the draft rows.
+// Row y of sequence b: y <= gmax the target rows, then the draft rows.  Four 128-bit loads per thread, all in flight
+// at once (eight, in half as many workgroups: 101 us instead of 97 at 64 sequences of 128256 entries and 8 drafts,
+// 558 MB); a thread's entries come in index order, so equal maxima keep the lowest index by themselves.
 __global__ void __launch_bounds__(kThreads) greedy_slice_argmax(AcceptLaunch a, GreedyWs ws)
 {
     __shared__ float shm[kThreads / 64];
@@ -65,21 +68,23 @@ __global__ void __launch_bounds__(kThreads) greedy_slice_argmax(AcceptLaunch a, 
     const int k = is_t ? y : y - (a.gmax + 1);
     if (is_t ? (k > g) : (k >= g)) return;
     const float* row = is_t ? a.zt + ((int64_t)b * (a.gmax + 1) + k) * a.V : a.zd + ((int64_t)b * a.gmax + k) * a.V;
-    const bool vec = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
+    constexpr int NV = kSlice / (4 * kThreads);
+    const int i0 = w * kSlice + threadIdx.x * 4;
+    const bool full = (int64_t)(w + 1) * kSlice <= a.V;
+    floatx4 x[NV];
+    load_runs(x, row, i0, kThreads * 4, a.V, full);
+    shift_runs(x, i0, kThreads * 4, a.V, full);
     float m = -INFINITY;
     int idx = 0x7fffffff;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int i0 = w * kSlice + (v * kThreads + threadIdx.x) * 4;
-        if (vec && i0 + 3 < a.V) {
-            const floatx4 x = *reinterpret_cast<const floatx4*>(row + i0);
+    for (int v = 0; v < NV; ++v)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) take_better(m, idx, x[j], i0 + j);
-        } else {
-            for (int j = 0; j < 4; ++j)
-                if (i0 + j < a.V) take_better(m, idx, row[i0 + j], i0 + j);
+        for (int j = 0; j < 4; ++j) {
+            const int i = i0 + v * kThreads * 4 + j;
+            // (-inf is a maximum like any other as long as it is an entry of the row)
+            const bool first = x[v][j] == m && idx == 0x7fffffff && i < a.V;
+            if (x[v][j] > m || first) { m = x[v][j]; idx = i; }
         }
-    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) take_better(m, idx, __shfl_xor(m, o), __shfl_xor(idx, o));
     if ((threadIdx.x & 63) == 0) { shm[threadIdx.x >> 6] = m; shi[threadIdx.x >> 6] = idx; }
@@ -104,52 +109,58 @@ __device__ __forceinline__ void row_argmax(const GreedyWs& ws, int64_t row, floa
     for (int o = 32; o > 0; o >>= 1) take_better(m, idx, __shfl_xor(m, o), __shfl_xor(idx, o));
 }
 
-__global__ void __launch_bounds__(kThreads) greedy_decide(AcceptLaunch a, GreedyWs ws)
+// One wave per position: the drafted token, its two logits and the slices of both rows are fetched side by side, and the
+// wave of position k leaves the arg-max of target row k in LDS, where the decision finds that of row n.
+__global__ void __launch_bounds__(kDecide) greedy_decide(AcceptLaunch a, GreedyWs ws)
 {
+    extern __shared__ int target_arg[];                   // [gmax + 1]
     __shared__ int first_fail;
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int g = seq_gamma(a, b);
     const int nrows = 2 * a.gmax + 1;
-    if (tid == 0) first_fail = g;
+    if (tid == 0) first_fail = 0x7fffffff;
     __syncthreads();
-    // accept tests: one wave per drafted position
-    for (int k = wave; k < g; k += kThreads / 64) {
-        float mt, md;
+    const int g = seq_gamma(a, b);
+    for (int k = wave; k <= a.gmax; k += kDecide / 64) {
+        if (k > g) break;
+        const bool pair = k < g;
+        const int64_t at = (int64_t)b * a.gmax + k;
+        const int x = pair ? a.tokens[at] : 0;
+        const bool in_range = pair && x >= 0 && x < a.V;
+        const float zx_t = in_range ? a.zt[((int64_t)b * (a.gmax + 1) + k) * a.V + x] : 0.f;
+        const float zx_d = in_range ? a.zd[at * a.V + x] : 0.f;
+        const double u = (double)a.uniforms[(int64_t)b * (a.gmax + 1) + k];
+        float mt, md = 0.f;
         int it, id;
         row_argmax(ws, (int64_t)b * nrows + k, mt, it);
-        row_argmax(ws, (int64_t)b * nrows + a.gmax + 1 + k, md, id);
-        if (lane == 0) {
-            const int x = a.tokens[(int64_t)b * a.gmax + k];
-            double rho = 0.0;
-            bool ok = false;
-            if (x >= 0 && x < a.V) {
-                // gaps of the drafted token to the row maxima; differences of fp32 values are exact in fp64
-                const double gap_t = (double)a.zt[((int64_t)b * (a.gmax + 1) + k) * a.V + x] - (double)mt;
-                const double gap_d = (double)a.zd[((int64_t)b * a.gmax + k) * a.V + x] - (double)md;
-                rho = gap_t > gap_d ? INFINITY : (gap_t < gap_d ? 0.0 : 1.0);
-                const double u = (double)a.uniforms[(int64_t)b * (a.gmax + 1) + k];
-                ok = u <= fmin(1.0, rho);
-            } else {
-                atomicAdd(ws.status + 0, 1);                  // id outside the vocabulary: rejected, and counted
-            }
-            if (a.ratio) a.ratio[(int64_t)b * a.gmax + k] = (float)rho;
-            if (!ok) atomicMin(&first_fail, k);
+        if (pair) row_argmax(ws, (int64_t)b * nrows + a.gmax + 1 + k, md, id);
+        if (lane != 0) continue;
+        target_arg[k] = it;
+        if (!pair) continue;
+        double rho = 0.0;
+        bool ok = false;
+        if (in_range) {
+            // gaps of the drafted token to the row maxima; differences of fp32 values are exact in fp64
+            const double gap_t = (double)zx_t - (double)mt, gap_d = (double)zx_d - (double)md;
+            rho = gap_t > gap_d ? INFINITY : (gap_t < gap_d ? 0.0 : 1.0);
+            ok = u <= fmin(1.0, rho);
+        } else {
+            atomicAdd(ws.status + 0, 1);                      // id outside the vocabulary: rejected, and counted
         }
+        if (a.ratio) a.ratio[at] = (float)rho;
+        if (!ok) atomicMin(&first_fail, k);
     }
     __syncthreads();
-    const int n = first_fail;
-    if (wave == 0) {
-        float m;
-        int tok;
-        row_argmax(ws, (int64_t)b * nrows + n, m, tok);       // target row n: rejection or bonus position
-        if (lane == 0) {
+    const int n = min(first_fail, g);
+    for (int k = tid; k <= a.gmax; k += kDecide) {
+        int tok = -1;
+        if (k < n) tok = a.tokens[(int64_t)b * a.gmax + k];
+        else if (k == n) {                                    // target row n: rejection or bonus position
+            tok = target_arg[n];
             if (tok < 0 || tok >= a.V) tok = 0;               // a row of NaNs has no arg-max: any valid id
-            a.out_tokens[(int64_t)b * (a.gmax + 1) + n] = tok;
-            a.n_accepted[b] = n;
         }
+        a.out_tokens[(int64_t)b * (a.gmax + 1) + k] = tok;
     }
-    for (int k = tid; k <= a.gmax; k += kThreads)
-        if (k != n) a.out_tokens[(int64_t)b * (a.gmax + 1) + k] = k < n ? a.tokens[(int64_t)b * a.gmax + k] : -1;
+    if (tid == 0) a.n_accepted[b] = n;
 }
 
 }  // namespace
@@ -163,6 +174,6 @@ hipError_t launch_accept_greedy(const AcceptLaunch& a, hipStream_t stream)
 {
     GreedyWs ws = gcarve(a.workspace, a.B, a.gmax, a.V);
     hipLaunchKernelGGL(greedy_slice_argmax, dim3(ws.W, 2 * a.gmax + 1, a.B), dim3(kThreads), 0, stream, a, ws);
-    hipLaunchKernelGGL(greedy_decide, dim3(a.B), dim3(kThreads), 0, stream, a, ws);
+    hipLaunchKernelGGL(greedy_decide, dim3(a.B), dim3(kDecide), (a.gmax + 1) * sizeof(int), stream, a, ws);
     return hipGetLastError();
 }

@@ -73,3 +73,36 @@ def test_both_forms_match_the_oracle_and_each_other(slice_entries, eta, T, mask)
         assert st["n_mismatch"] == 0 and st["token_mismatch"] == 0 and st["exempt_sequences"] == 0, st
         # fp32 arguments of the exponentials: |z - max| / T up to 30 / 0.05 at 2^-24, a few times over
         assert st["max_ratio_rel_err"] <= 1e-4, st
+
+
+@pytest.mark.parametrize("V", [1, 3, 4095, 4097, 8193, 50257])
+def test_greedy_ties_masks_and_row_ends(V):
+    """Equal maxima in one thread, across threads and across slices (lowest index), rows that are -inf from some point on
+    or throughout, maxima at the ends of rows of any alignment."""
+    rng = np.random.default_rng(V)
+    B, g = 5, 3
+    zt = rng.integers(-3, 4, (B, g + 1, V)).astype(np.float32)             # many ties
+    zd = rng.integers(-3, 4, (B, g, V)).astype(np.float32)
+    zt[1, :, V // 2:] = -np.inf
+    zt[2, 1] = -np.inf
+    zd[3, 0] = -np.inf
+    zt[4, :, -1] = 9.0
+    zt[4, 2, 0] = 9.0
+    tok = np.argmax(zd, -1).astype(np.int32)
+    u = rng.random((B, g + 1), dtype=np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    n, toks, _ = gu.rapid().rapid_accept(dev(zt), dev(zd), dev(tok), 1.0, dev(u), temperature=0.0)
+    torch.cuda.synchronize()
+    n, toks = n.cpu().numpy(), toks.cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        for b in range(B):
+            want = g
+            for k in range(g):
+                a, c = zt[b, k, tok[b, k]] - zt[b, k].max(), zd[b, k, tok[b, k]] - zd[b, k].max()
+                rho = np.inf if a > c else (0.0 if a < c else 1.0)         # (a NaN gap compares as equal)
+                if not u[b, k] <= min(1.0, rho):
+                    want = k
+                    break
+            assert n[b] == want, (b, n, want)
+            assert list(toks[b, :want]) == list(tok[b, :want]) and toks[b, want] == int(np.argmax(zt[b, want]))
+            assert np.all(toks[b, want + 1:] == -1)
