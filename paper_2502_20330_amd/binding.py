@@ -121,12 +121,19 @@ def _check(lib, status: int, ctx=None):
         raise RapidError(status, msg)
 
 
+# A call of a few microseconds of device time must not wait for its marshalling: plain integers go where the prototypes
+# say c_void_p (ctypes converts them), the raw stream comes from torch without a Stream object.
 def _dptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream_ptr(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream_ptr(device: torch.device) -> int:
+    if _raw_stream is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 class Rapid:
@@ -181,26 +188,17 @@ class Rapid:
                    softmax_scale: Optional[float] = None, chunk_tokens: int = 0,
                    ctx_sum_hint: int = 0) -> AttnShape:
         B, Qmax, Hq, d = q.shape
-        s = AttnShape()
-        s.batch, s.q_max, s.n_q_heads, s.head_dim = B, Qmax, Hq, d
-        s.n_kv_heads = k_cache.shape[2]
-        s.max_ctx = int(ctx_max)
-        s.gamma = Qmax - 1 if gamma is None else int(gamma)
-        s.softmax_scale = float(softmax_scale) if softmax_scale is not None else d ** -0.5
-        st = k_cache.stride()
-        if k_cache.stride(3) != 1:
+        rows, tokens, Hkv, _ = k_cache.shape
+        st0, st1, st2, st3 = k_cache.stride()
+        if st3 != 1:
             raise RapidError(-1, "head_dim must be the contiguous dimension of the KV cache")
+        scale = float(softmax_scale) if softmax_scale is not None else d ** -0.5
+        gamma = Qmax - 1 if gamma is None else int(gamma)
         if page_table is None:
-            s.kv_batch_stride, s.kv_token_stride, s.kv_head_stride = st[0], st[1], st[2]
-            s.kv_page_stride, s.page_size, s.max_pages = 0, 0, 0
-        else:
-            s.kv_page_stride, s.kv_token_stride, s.kv_head_stride = st[0], st[1], st[2]
-            s.kv_batch_stride = 0
-            s.page_size, s.max_pages = k_cache.shape[1], page_table.shape[1]
-        s.chunk_tokens = int(chunk_tokens)
-        s.n_pages = 0 if page_table is None else int(k_cache.shape[0])
-        s.ctx_sum_hint = int(ctx_sum_hint)
-        return s
+            return AttnShape(B, Qmax, Hq, Hkv, d, int(ctx_max), gamma, scale, st0, st1, st2, 0, 0, 0,
+                             int(chunk_tokens), 0, int(ctx_sum_hint))
+        return AttnShape(B, Qmax, Hq, Hkv, d, int(ctx_max), gamma, scale, 0, st1, st2, st0, tokens,
+                         page_table.shape[1], int(chunk_tokens), rows, int(ctx_sum_hint))
 
     def verify_attn_chunk(self, shape: AttnShape) -> int:
         c = self.lib.rapid_verify_attn_chunk(self._ctx, ctypes.byref(shape))
@@ -227,12 +225,15 @@ class Rapid:
                                     ctx_sum_hint=ctx_sum_hint)
         if out is None:
             out = torch.empty_like(q)
-        need = self.lib.rapid_verify_attn_workspace_bytes(self._ctx, ctypes.byref(shape))
-        ws = self._workspace(need)
-        rc = self.lib.rapid_verify_attn(self._ctx, ctypes.byref(shape), _dptr(q), _dptr(k_cache), _dptr(v_cache),
-                                        _dptr(ctx_lens), _dptr(gammas), _dptr(page_table), _dptr(out),
-                                        _dptr(lse_out), _dptr(ws), ws.numel(), _stream_ptr(self.device))
-        _check(self.lib, rc, self._ctx)
+        args = (self._ctx, shape, q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), ctx_lens.data_ptr(), _dptr(gammas),
+                _dptr(page_table), out.data_ptr(), _dptr(lse_out))
+        ws, stream = self._ws, _stream_ptr(self.device)
+        rc = self.lib.rapid_verify_attn(*args, _dptr(ws), 0 if ws is None else ws.numel(), stream)
+        if rc == RAPID_EWORKSPACE:                             # the last check of the call: nothing has been launched
+            ws = self._workspace(self.lib.rapid_verify_attn_workspace_bytes(self._ctx, shape))
+            rc = self.lib.rapid_verify_attn(*args, ws.data_ptr(), ws.numel(), stream)
+        if rc:
+            _check(self.lib, rc, self._ctx)
         return out
 
     def rapid_verify_attn_static(self, q, k_cache, v_cache, ctx_lens, gamma: Optional[int] = None, *, gammas=None,
@@ -268,29 +269,31 @@ class Rapid:
         if outs is None:
             n_acc = torch.empty(B, dtype=torch.int32, device=self.device)
             toks = torch.empty(B, g + 1, dtype=torch.int32, device=self.device)
-            ratio = torch.zeros(B, max(g, 1), dtype=torch.float32, device=self.device)[:, :g] if want_ratio else None
-            if ratio is not None:
-                ratio = ratio.contiguous()
+            ratio = None
+            if want_ratio:
+                # without per-sequence counts every element is written
+                make = torch.empty if gammas is None else torch.zeros
+                ratio = make((B, g), dtype=torch.float32, device=self.device)
         else:
             n_acc, toks, ratio = outs
-        need = self.lib.rapid_accept_workspace_bytes(self._ctx, B, g, V)
-        ws = self._accept_workspace(need)
-        if target_stats is None and draft_stats is None:
-            rc = self.lib.rapid_accept(self._ctx, B, g, V, _dptr(target_logits), _dptr(draft_logits),
-                                       _dptr(draft_tokens), _dptr(gammas), float(eta), float(temperature),
-                                       float(tail_alpha), _dptr(uniforms), _dptr(n_acc), _dptr(toks), _dptr(ratio),
-                                       _dptr(ws), ws.numel(), _stream_ptr(self.device))
-        else:
+        prestats = target_stats is not None or draft_stats is not None
+        args = (self._ctx, B, g, V, target_logits.data_ptr(), draft_logits.data_ptr(), draft_tokens.data_ptr(), _dptr(gammas),
+                float(eta), float(temperature), float(tail_alpha), uniforms.data_ptr())
+        results = (n_acc.data_ptr(), toks.data_ptr(), _dptr(ratio))
+        if prestats:
             for st, rows in ((target_stats, B * (g + 1)), (draft_stats, B * g)):
                 assert st is None or (st.dtype == torch.float32 and st.is_contiguous() and st.dim() == 3
                                       and st.shape[0] == rows and st.shape[2] == 2)
-            rc = self.lib.rapid_accept_prestats(
-                self._ctx, B, g, V, _dptr(target_logits), _dptr(draft_logits), _dptr(draft_tokens), _dptr(gammas),
-                float(eta), float(temperature), float(tail_alpha), _dptr(uniforms),
-                _dptr(target_stats), 0 if target_stats is None else target_stats.shape[1],
-                _dptr(draft_stats), 0 if draft_stats is None else draft_stats.shape[1],
-                _dptr(n_acc), _dptr(toks), _dptr(ratio), _dptr(ws), ws.numel(), _stream_ptr(self.device))
-        _check(self.lib, rc, self._ctx)
+            args += (_dptr(target_stats), 0 if target_stats is None else target_stats.shape[1],
+                     _dptr(draft_stats), 0 if draft_stats is None else draft_stats.shape[1])
+        call = self.lib.rapid_accept_prestats if prestats else self.lib.rapid_accept
+        ws, stream = self._ws_accept, _stream_ptr(self.device)
+        rc = call(*args, *results, _dptr(ws), 0 if ws is None else ws.numel(), stream)
+        if rc == RAPID_EWORKSPACE:                             # the last check of the call: nothing has been launched
+            ws = self._accept_workspace(self.lib.rapid_accept_workspace_bytes(self._ctx, B, g, V))
+            rc = call(*args, *results, ws.data_ptr(), ws.numel(), stream)
+        if rc:
+            _check(self.lib, rc, self._ctx)
         return n_acc, toks, ratio
 
     # ------------------------------------------------------------------ cache bookkeeping
