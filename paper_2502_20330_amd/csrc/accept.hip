@@ -12,7 +12,7 @@
 // Two launches:
 //
 //   accept_rows   reads every logit ONCE.  A row pair (target row k, draft row k) is cut into
-//       slices of 2048*NV entries; one workgroup of 512 threads holds its slice of both rows in
+//       slices; one workgroup of 256 or 512 threads holds its slice of both rows in
 //       registers.  It publishes the slice's (max, sum exp) of either row, picks up the
 //       publications of the other workgroups of the row pair, and with the row normalisers
 //       forms d = z/T + eta (q - p) for its slice (still in registers) and publishes
@@ -124,25 +124,25 @@ __device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, OpAdd
 __device__ __forceinline__ double wave_max(double v) { return wave_reduce(v, OpMaxD()); }
 __device__ __forceinline__ double wave_sum(double v) { return wave_reduce(v, OpAddD()); }
 
-// Block-wide reductions over kThreads threads of two values at once; results go to every thread.
-// `sh` holds two banks of 2*kWaves slots used alternately (`bank` flips on every call), so one
+// Block-wide reductions over NW waves of two values at once; results go to every thread.
+// `sh` holds two banks of 2*NW slots used alternately (`bank` flips on every call), so one
 // barrier per reduction is enough: a wave can only be two reductions ahead of another one after
 // that one has passed the barrier in between, i.e. after it has finished reading the bank.
-// Fixed order: the wave scan above, then waves 0..7.
-template <class T, class OpA, class OpB>
+// Fixed order: the wave scan above, then waves 0..NW-1.
+template <int NW = kWaves, class T, class OpA, class OpB>
 __device__ __forceinline__ void block_reduce2(T& a, T& b, T* sh, int& bank, OpA opa, OpB opb)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     a = wave_scan(a, opa);
     b = wave_scan(b, opb);
-    T* s = sh + bank * 2 * kWaves;
+    T* s = sh + bank * 2 * NW;
     bank ^= 1;
-    if (lane == 63) { s[wave] = a; s[kWaves + wave] = b; }
+    if (lane == 63) { s[wave] = a; s[NW + wave] = b; }
     __syncthreads();
     a = s[0];
-    b = s[kWaves];
+    b = s[NW];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) { a = opa(a, s[w]); b = opb(b, s[kWaves + w]); }
+    for (int w = 1; w < NW; ++w) { a = opa(a, s[w]); b = opb(b, s[NW + w]); }
 }
 
 // NE consecutive logits from index i on.
@@ -427,7 +427,7 @@ __device__ __forceinline__ void poll_all(const u64* words, int n, u64* dst, int*
 // UNROLL: the register path unrolls (its arrays need constant indices); the memory path keeps its
 // loops rolled, it is code that normally never runs and should stay small.
 // put_t / put_d receive the exponentials relative to the slice's maximum (the register path keeps them).
-template <int NV, bool UNROLL, class GetT, class GetD, class PutT, class PutD>
+template <int NW, int NV, bool UNROLL, class GetT, class GetD, class PutT, class PutD>
 __device__ __forceinline__ void slice_stats(GetT gt, GetD gd, PutT put_t, PutD put_d, bool do_t, bool do_d, float c,
                                             float* sh, int& bank, float& mt, float& st, float& md, float& sd)
 {
@@ -445,7 +445,7 @@ __device__ __forceinline__ void slice_stats(GetT gt, GetD gd, PutT put_t, PutD p
             const floatx4 y = gd(v);
             md = fmaxf(md, fmaxf(fmaxf(y[0], y[1]), fmaxf(y[2], y[3])));
         }
-    block_reduce2(mt, md, sh, bank, OpMaxF(), OpMaxF());
+    block_reduce2<NW>(mt, md, sh, bank, OpMaxF(), OpMaxF());
     st = 0.f;
     sd = 0.f;
     if (do_t && mt > -INFINITY)
@@ -464,7 +464,7 @@ __device__ __forceinline__ void slice_stats(GetT gt, GetD gd, PutT put_t, PutD p
             for (int j = 0; j < 4; ++j) sd += y[j] = fexp2((y[j] - md) * c);
             put_d(v, y);
         }
-    block_reduce2(st, sd, sh, bank, OpAddF(), OpAddF());
+    block_reduce2<NW>(st, sd, sh, bank, OpAddF(), OpAddF());
 }
 
 // Row normalisers in the form the elementwise pass uses (log2 units).
@@ -498,7 +498,7 @@ __device__ __forceinline__ floatx4 rel_exp(floatx4 z, float R, float c)
     return z;
 }
 // (max f, sum f) of a slice; f(v) yields f of the thread's v-th float4
-template <int NV, bool UNROLL, class GetF>
+template <int NW, int NV, bool UNROLL, class GetF>
 __device__ __forceinline__ void mixed_stats(GetF f, float scale, float* sh, int& bank, float& fmx, float& fsum)
 {
     fmx = 0.f;
@@ -509,7 +509,7 @@ __device__ __forceinline__ void mixed_stats(GetF f, float scale, float* sh, int&
         fmx = fmaxf(fmx, fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
         fsum += (x[0] + x[1]) + (x[2] + x[3]);
     }
-    block_reduce2(fmx, fsum, sh, bank, OpMaxF(), OpAddF());
+    block_reduce2<NW>(fmx, fsum, sh, bank, OpMaxF(), OpAddF());
     fmx *= scale;
     fsum *= scale;
 }
@@ -525,7 +525,7 @@ __device__ __forceinline__ float shifted(float zt, float zd, const PairNorm& r, 
 
 // (max d, sum exp2(d - max)) of a slice; d_first(v) yields d of the thread's v-th float4 (the register
 // path also stores it), d_again(v) yields it again (from the registers, or recomputed: same value).
-template <int NV, bool UNROLL, class GetFirst, class GetAgain>
+template <int NW, int NV, bool UNROLL, class GetFirst, class GetAgain>
 __device__ __forceinline__ void shifted_stats(GetFirst d_first, GetAgain d_again, float* sh, int& bank, float& mh,
                                               float& shs)
 {
@@ -536,7 +536,7 @@ __device__ __forceinline__ void shifted_stats(GetFirst d_first, GetAgain d_again
         const floatx4 d = d_first(v);
         mh = fmaxf(mh, fmaxf(fmaxf(d[0], d[1]), fmaxf(d[2], d[3])));
     }
-    block_reduce2(mh, unused, sh, bank, OpMaxF(), OpMaxF());
+    block_reduce2<NW>(mh, unused, sh, bank, OpMaxF(), OpMaxF());
     shs = 0.f;
     unused = 0.f;
     if (mh > -INFINITY)
@@ -546,7 +546,7 @@ __device__ __forceinline__ void shifted_stats(GetFirst d_first, GetAgain d_again
 #pragma unroll
             for (int j = 0; j < 4; ++j) shs += fexp2(d[j] - mh);
         }
-    block_reduce2(shs, unused, sh, bank, OpAddF(), OpAddF());
+    block_reduce2<NW>(shs, unused, sh, bank, OpAddF(), OpAddF());
 }
 
 // Wave 0: combine n (max, sum) pairs, maxima raw logits, sums of exp((z - max)/T):
@@ -594,12 +594,12 @@ struct LdsA {
 // One workgroup per work item (sequence b, row k, slice w), slice index fastest in dispatch order, so
 // the slices of one row pair are worked on by different workgroups at about the same time.
 // PLAIN: the form of the shifted row (see above).
-template <int NV, bool PLAIN>
-__global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws, int W, int n_items)
+template <int NT, int NV, int OCC, bool PLAIN>
+__global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, int W, int n_items)
 {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     LdsA& lds = *reinterpret_cast<LdsA*>(smem_raw);
-    constexpr int kSlice = kThreads * 4 * NV;
+    constexpr int NW = NT / 64, kSlice = NT * 4 * NV;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int V = a.V, rows = a.gmax + 1;
     int bank = 0;
@@ -618,10 +618,10 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
         const float* zd = pair ? row_d(b, k) : nullptr;
         const bool full = (int64_t)(w + 1) * kSlice <= V;
         const int i = w * kSlice + tid * 4;
-        load_runs(x, zt, i, kThreads * 4, V, full);
-        if (pair) load_runs(y, zd, i, kThreads * 4, V, full);
-        shift_runs(x, i, kThreads * 4, V, full);
-        if (pair) shift_runs(y, i, kThreads * 4, V, full);
+        load_runs(x, zt, i, NT * 4, V, full);
+        if (pair) load_runs(y, zd, i, NT * 4, V, full);
+        shift_runs(x, i, NT * 4, V, full);
+        if (pair) shift_runs(y, i, NT * 4, V, full);
     };
 
     // Everything after the loads of one item.
@@ -640,7 +640,7 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
         auto reg_d = [&](int v) { return y[v]; };
         // slice s of either row straight from memory (a slice another workgroup owns)
         auto mem_slice = [&](const float* row, int s) {
-            return [row, s, tid, V](int v) { return load4(row, s * kSlice + (v * kThreads + tid) * 4, V); };
+            return [row, s, tid, V](int v) { return load4(row, s * kSlice + (v * NT + tid) * 4, V); };
         };
 
         // ---- statistics of the own slice; the plain form keeps the exponentials in place of the logits
@@ -649,7 +649,7 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
             float st, sd;
             auto put_t = [&](int v, floatx4 e) { if (PLAIN) x[v] = e; };
             auto put_d = [&](int v, floatx4 e) { if (PLAIN) y[v] = e; };
-            slice_stats<NV, true>(reg_t, reg_d, put_t, put_d, own_t, own_d, c, lds.red, bank, mt, st, md, sd);
+            slice_stats<NW, NV, true>(reg_t, reg_d, put_t, put_d, own_t, own_d, c, lds.red, bank, mt, st, md, sd);
             if (tid == 0) {
                 if (own_t) publish2f(slot_t + 2 * w, mt, st, tg);
                 if (own_d) publish2f(slot_d + 2 * w, md, sd, tg);
@@ -677,7 +677,7 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
                     if (!miss_t && !miss_d) continue;
                     float mt, st, md, sd;
                     auto drop = [](int, floatx4) {};
-                    slice_stats<NV, false>(mem_slice(zt, s), mem_slice(zd, s), drop, drop, miss_t, miss_d, c,
+                    slice_stats<NW, NV, false>(mem_slice(zt, s), mem_slice(zd, s), drop, drop, miss_t, miss_d, c,
                                            lds.red, bank, mt, st, md, sd);
                     if (tid == 0) {
                         if (miss_t) { keep2f(got, s, mt, st); publish2f(slot_t + 2 * s, mt, st, tg); }
@@ -702,34 +702,34 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
                 // The caller's statistics are hundreds of pairs per row in memory: all eight waves fetch them at
                 // once (one round trip) and two block reductions combine them (a side without supplied statistics
                 // brings its W gathered pairs the same way); every workgroup of the row pair gets the same bits.
-                float2 vt[2], vd[2];                          // pairs tid and tid + kThreads; beyond: the loops below
+                float2 vt[2], vd[2];                          // pairs tid and tid + NT; beyond: the loops below
                 float mt = -INFINITY, md = -INFINITY;
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
-                    const int i = tid + j * kThreads;
+                    const int i = tid + j * NT;
                     vt[j] = i < n_t ? pair_t(i) : make_float2(-INFINITY, 0.f);
                     vd[j] = i < n_d ? pair_d(i) : make_float2(-INFINITY, 0.f);
                     mt = fmaxf(mt, vt[j].x);
                     md = fmaxf(md, vd[j].x);
                 }
-                for (int i = tid + 2 * kThreads; i < n_t; i += kThreads) mt = fmaxf(mt, pair_t(i).x);
-                for (int i = tid + 2 * kThreads; i < n_d; i += kThreads) md = fmaxf(md, pair_d(i).x);
-                block_reduce2(mt, md, lds.red, bank, OpMaxF(), OpMaxF());
+                for (int i = tid + 2 * NT; i < n_t; i += NT) mt = fmaxf(mt, pair_t(i).x);
+                for (int i = tid + 2 * NT; i < n_d; i += NT) md = fmaxf(md, pair_d(i).x);
+                block_reduce2<NW>(mt, md, lds.red, bank, OpMaxF(), OpMaxF());
                 float st = 0.f, sd = 0.f;
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     if (vt[j].y > 0.f) st += vt[j].y * fexp2((vt[j].x - mt) * c);
                     if (vd[j].y > 0.f) sd += vd[j].y * fexp2((vd[j].x - md) * c);
                 }
-                for (int i = tid + 2 * kThreads; i < n_t; i += kThreads) {
+                for (int i = tid + 2 * NT; i < n_t; i += NT) {
                     const float2 v = pair_t(i);
                     if (v.y > 0.f) st += v.y * fexp2((v.x - mt) * c);
                 }
-                for (int i = tid + 2 * kThreads; i < n_d; i += kThreads) {
+                for (int i = tid + 2 * NT; i < n_d; i += NT) {
                     const float2 v = pair_d(i);
                     if (v.y > 0.f) sd += v.y * fexp2((v.x - md) * c);
                 }
-                block_reduce2(st, sd, lds.red, bank, OpAddF(), OpAddF());
+                block_reduce2<NW>(st, sd, lds.red, bank, OpAddF(), OpAddF());
                 if (tid == 0) lds.norm = PairNorm{mt, __log2f(st), md, __log2f(sd)};
             } else if (tid < 64) {
                 PairNorm r;
@@ -757,14 +757,14 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
                     for (int j = 0; j < 4; ++j) w4[j] = mixed(x[v][j], y[v][j], m);
                     return w4;
                 };
-                mixed_stats<NV, true>(f, m.scale, lds.red, bank, mh, shs);
+                mixed_stats<NW, NV, true>(f, m.scale, lds.red, bank, mh, shs);
             } else {
                 auto d_first = [&](int v) {                   // d replaces the logits in x
 #pragma unroll
                     for (int j = 0; j < 4; ++j) x[v][j] = shifted(x[v][j], y[v][j], r, c, eta_l2);
                     return x[v];
                 };
-                shifted_stats<NV, true>(d_first, reg_t, lds.red, bank, mh, shs);
+                shifted_stats<NW, NV, true>(d_first, reg_t, lds.red, bank, mh, shs);
             }
             if (tid == 0) publish2f(slot_h + 2 * w, mh, shs, tg);
             STAMP_AT(id, 4);
@@ -811,7 +811,7 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
                                 for (int j = 0; j < 4; ++j) t4[j] = mixed(t4[j], d4[j], m);
                                 return t4;
                             };
-                            mixed_stats<NV, false>(f_mem, m.scale, lds.red, bank, mh, shs);
+                            mixed_stats<NW, NV, false>(f_mem, m.scale, lds.red, bank, mh, shs);
                         } else {
                             auto d_mem = [&](int v) {
                                 floatx4 t4 = gt(v);
@@ -820,7 +820,7 @@ __global__ void __launch_bounds__(kThreads, 4) accept_rows(AcceptLaunch a, Ws ws
                                 for (int j = 0; j < 4; ++j) t4[j] = shifted(t4[j], d4[j], r, c, eta_l2);
                                 return t4;
                             };
-                            shifted_stats<NV, false>(d_mem, d_mem, lds.red, bank, mh, shs);
+                            shifted_stats<NW, NV, false>(d_mem, d_mem, lds.red, bank, mh, shs);
                         }
                         if (tid == 0) { keep2f(got_h, s, mh, shs); publish2f(slot_h + 2 * s, mh, shs, tg); count_giveup(ws.status, tg); }
                         __syncthreads();
@@ -1217,25 +1217,26 @@ static int draw_entries(const AcceptLaunch& a)
 hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)
 {
     Ws ws = carve(a.workspace, a.B, a.gmax, a.V);
-    // Slice size of accept_rows: the largest of 16384 / 8192 / 4096 entries that still gives two
-    // workgroups per compute unit; small batches take the smallest so that the chip is used at all.
+    // Slice size of accept_rows: 10240 entries on 256 threads where the grid then gives two workgroups per compute unit,
+    // else 8192 or 4096 on 512 threads; small batches take the smallest so that the chip is used at all.  The pass is bound
+    // by the bytes in flight while workgroups wait for one another: four workgroups of 256 threads hold 320 KB of a
+    // compute unit's 512 KB of registers, two of 512 threads with slices of 16384 hold 256 KB (64 sequences: 92 us of
+    // accept_rows against 78; 8192 on 256 threads: 81; 12288: spills).
     const int64_t rows = (int64_t)a.B * (a.gmax + 1);
-    int nv = 2;
-    for (int cand = 8; cand >= 2; cand >>= 1) {
-        const int64_t Wc = ((int64_t)a.V + 2048 * cand - 1) / (2048 * cand);
-        if (cand == 2 || rows * Wc >= 2 * (int64_t)a.n_cu) { nv = cand; break; }
-    }
-    if (a.force_nv == 2 || a.force_nv == 4 || a.force_nv == 8) nv = a.force_nv;
-    const int W = (a.V + 2048 * nv - 1) / (2048 * nv);
-    const int64_t n_items = rows * W;
-    const int grid = (int)n_items;
-    const size_t lds_a = sizeof(LdsA) + (size_t)6 * W * sizeof(u64);
-    const dim3 blk(kThreads);
+    const auto slices = [&](int slice) { return (a.V + slice - 1) / slice; };
+    int slice = kMinSlice;
     const bool plain = a.eta <= kPlainEta;
-    auto rows_kernel = nv == 8 ? (plain ? accept_rows<8, true> : accept_rows<8, false>)
-                     : nv == 4 ? (plain ? accept_rows<4, true> : accept_rows<4, false>)
-                               : (plain ? accept_rows<2, true> : accept_rows<2, false>);
-    hipLaunchKernelGGL(rows_kernel, dim3(grid), blk, lds_a, stream, a, ws, W, (int)n_items);
+    for (int cand : {plain ? 10240 : 16384, 8192})            // (the logarithmic form needs more registers)
+        if (rows * slices(cand) >= 2 * (int64_t)a.n_cu) { slice = cand; break; }
+    if (a.force_slice) slice = a.force_slice;
+    auto rows_kernel = slice == 16384 ? (plain ? accept_rows<512, 8, 4, true> : accept_rows<512, 8, 4, false>)
+                     : slice == 10240 ? accept_rows<256, 10, 4, true>
+                     : slice == 8192 ? (plain ? accept_rows<512, 4, 4, true> : accept_rows<512, 4, 4, false>)
+                                     : (plain ? accept_rows<512, 2, 4, true> : accept_rows<512, 2, 4, false>);
+    const int W = slices(slice);
+    const int64_t n_items = rows * W;
+    const size_t lds_a = sizeof(LdsA) + (size_t)6 * W * sizeof(u64);
+    hipLaunchKernelGGL(rows_kernel, dim3((unsigned)n_items), dim3(slice == 10240 ? 256 : 512), lds_a, stream, a, ws, W, (int)n_items);
     const auto draw_wgs = [&](int ne) { return (a.V + kThreads * ne - 1) / (kThreads * ne); };
     const int ne = draw_entries(a);
     const int W2 = draw_wgs(ne);
@@ -1243,6 +1244,6 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)
                      : ne == 4 ? accept_draw_row<4, 2>
                      : (int64_t)W2 * a.B <= a.n_cu ? accept_draw_row<8, 2> : accept_draw_row<8, 4>;
     const size_t lds_b = sizeof(LdsB) + (size_t)4 * W2 * sizeof(u64);
-    hipLaunchKernelGGL(draw_kernel, dim3(W2, a.B), blk, lds_b, stream, a, ws, W2);
+    hipLaunchKernelGGL(draw_kernel, dim3(W2, a.B), dim3(kThreads), lds_b, stream, a, ws, W2);
     return hipGetLastError();
 }

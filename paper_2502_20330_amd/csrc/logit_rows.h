@@ -38,7 +38,7 @@ __device__ __forceinline__ void load_runs(floatx4 (&r)[N], const float* row, int
 {
     if (full) {
 #pragma unroll
-        for (int v = 0; v < N; ++v) r[v] = load4_full(row + i + v * step);
+        for (int v = 0; v < N; ++v) r[v] = load4_full(row + v * step + (unsigned)i);      // uniform base + 32-bit offset
     } else if (V >= 4) {
 #pragma unroll
         for (int v = 0; v < N; ++v) {

@@ -387,7 +387,7 @@ int rapid_accept_prestats(rapid_ctx* ctx, int batch, int gamma_max, int vocab,
     a.nch_d = draft_chunks;
     a.wait_ticks = ctx->accept_wait_ticks;
     a.n_cu = ctx->n_cu;
-    a.force_nv = ctx->accept_slice / 2048;
+    a.force_slice = ctx->accept_slice;
     DeviceScope dev(ctx->device);
     if (dev.err != hipSuccess) return hip_fail(ctx, dev.err);
     hipError_t e = greedy ? launch_accept_greedy(a, static_cast<hipStream_t>(stream))

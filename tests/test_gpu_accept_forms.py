@@ -40,11 +40,11 @@ def _chunk_stats(z, chunk, T):
     return torch.from_numpy(np.stack([m, e.sum(-1)], -1).astype(np.float32)).cuda()
 
 
-@pytest.mark.parametrize("slice_entries", [4096, 16384])
+@pytest.mark.parametrize("slice_entries", [4096, 16384, 0])          # 0: the library's choice at 24 sequences, 10240 or 16384
 @pytest.mark.parametrize("eta,T,mask", [(20.0, 0.1, "none"), (20.5, 0.1, "none"), (20.0, 1.0, "inf"), (20.5, 1.0, "inf"),
                                         (1.0, 0.1, "lowest"), (50.0, 0.7, "lowest"), (0.0, 0.05, "inf")])
 def test_both_forms_match_the_oracle_and_each_other(slice_entries, eta, T, mask):
-    cfg = wl.scaled(wl.CONFIGS["llama8b_32k"], batch=4, vocab=50257, gamma_choices=(2, 4), eta=eta, temperature=T, name="forms")
+    cfg = wl.scaled(wl.CONFIGS["llama8b_32k"], batch=4 if slice_entries else 24, vocab=50257, gamma_choices=(2, 4), eta=eta, temperature=T, name="forms")
     acc = _masked(wl.gen_accept_inputs(cfg, salt=31), mask)
     r = gu.rapid()
     runs = []
