@@ -395,12 +395,13 @@ __device__ __forceinline__ void poll_into(Addr addr, int lo, int hi, u64* dst, i
 
 // The same by the whole workgroup, one word per thread and round, for exchanges of hundreds of words;
 // miss[wave] = words of that wave still unpublished.  The caller synchronises before it reads dst and miss.
+template <int NT>
 __device__ __forceinline__ void poll_all(const u64* words, int n, u64* dst, int* miss, int64_t wait_ticks, const Tags& tg)
 {
     const int64_t t0 = (int64_t)wall_clock64();
-    const uint32_t want = tag_of(threadIdx.x, tg);        // kThreads is even: every word of a thread has its parity
+    const uint32_t want = tag_of(threadIdx.x, tg);        // NT is even: every word of a thread has its parity
     int m = 0;
-    for (int i0 = 0; i0 < n; i0 += kThreads) {
+    for (int i0 = 0; i0 < n; i0 += NT) {
         const int i = i0 + threadIdx.x;
         u64 v = 0;
         bool p = i < n;
@@ -916,7 +917,7 @@ __device__ __forceinline__ int first_reject(const Ws& ws, int b, int gmax, int g
 }
 
 // ---------------------------------------------------------------- accept_draw_row (fp64)
-// Thread t of workgroup w owns the NE consecutive entries  w*512*NE + t*NE + i  (i = 0..NE-1), so
+// Thread t of workgroup w owns the NE consecutive entries  w*NT*NE + t*NE + i  (i = 0..NE-1), so
 // vocabulary order inside a workgroup is thread order.
 //
 // Phase 1: e_t = exp((z - zmax)/T), e_d likewise; sums -> p = e_t/S_t, q = e_d/S_d.
@@ -925,6 +926,9 @@ __device__ __forceinline__ int first_reject(const Ws& ws, int b, int gmax, int g
 // Phase 3: the residual weights max(p - p_hat', p - q, 0) and p; their sums per slice.
 // The bonus row (all drafts accepted) draws from p: phase 1 only, weights e_t.
 struct DrawNorm { double iSt, iSd, iSh, thr, eta; };
+template <int N> struct Phase { static constexpr int value = N; };
+// A value that is the same in every lane, into scalar registers.
+__device__ __forceinline__ double uniform(double v) { return lane_value(v, 0); }
 
 struct LdsB {
     double red[4 * kWaves];
@@ -947,8 +951,8 @@ __device__ __forceinline__ double draw_weight(double et, double ed, double f, co
     if (ph < nm.thr) ph = p;
     return fmax(fmax(p - ph, p - q), 0.0);
 }
-// Accumulates entry (et, ed) into the two running values of `phase`; the entries of a thread are
-// taken in index order both by the register path and by the memory path.
+// The memory path's sums: entry (et, ed) into the two running values of `phase`, the entries of a thread in index
+// order as in the register path.
 __device__ __forceinline__ void draw_accumulate(int phase, double et, double ed, const DrawNorm& nm, const double* tab, double& a0,
                                                 double& a1)
 {
@@ -966,37 +970,37 @@ __device__ __forceinline__ void draw_accumulate(int phase, double et, double ed,
     }
 }
 
-// OCC = waves per SIMD the kernel is compiled for: 4 (two workgroups per compute unit, 128 registers,
-// a few spilled) for grids of several rounds, 2 (256 registers, no spills) when every workgroup has a
-// compute unit to itself anyway.
-template <int NE, int OCC>
-__global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a, Ws ws, int W2)
+// NT threads of NE entries.  OCC = waves per SIMD the kernel is compiled for; at 4 (two workgroups of 512 threads per
+// compute unit) the entries are taken one at a time, which keeps the registers below 128.
+template <int NT, int NE, int OCC>
+__global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws, int W2)
 {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+    constexpr int NW = NT / 64;
     LdsB& lds = *reinterpret_cast<LdsB*>(smem_raw);
-    constexpr int kSlice = kThreads * NE;
+    constexpr int kSlice = NT * NE;
     const int w = blockIdx.x, b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     STAMP(8);
     const int g = seq_gamma(a, b);
     int bad;
     const int n = first_reject(ws, b, a.gmax, g, bad);
-    const double u = (double)a.uniforms[(int64_t)b * (a.gmax + 1) + a.gmax];
-    const Tags tg = make_tags(~(uint32_t)ws.status[kCntDraw]);
+    const double u = uniform((double)a.uniforms[(int64_t)b * (a.gmax + 1) + a.gmax]);
+    const Tags tg = make_tags(__builtin_amdgcn_readfirstlane(~(uint32_t)ws.status[kCntDraw]));
     const int V = a.V;
     int bank = 0;
     const bool bonus = n >= g;
     const float* zt = a.zt + ((int64_t)b * (a.gmax + 1) + n) * V;
     const float* zd = bonus ? nullptr : a.zd + ((int64_t)b * a.gmax + n) * V;
     const double* rec = ws.rows + ((int64_t)b * (a.gmax + 1) + n) * 4;
-    const double Mt = rec[0], Md = rec[1], invT = a.inv_T_exact;
+    const double Mt = uniform(rec[0]), Md = uniform(rec[1]), invT = a.inv_T_exact;
 
     // own slice: e_t, e_d of the thread's entries, kept in registers for all phases; wgt holds
     // f = e_t exp(eta (q - p)) after phase 2 and the draw weight after phase 3
     double et[NE], ed[NE], wgt[NE];
-    const int64_t first = (int64_t)w * kSlice + (int64_t)tid * NE;
+    const int first = w * kSlice + tid * NE;
     float t_in[NE], d_in[NE];
-    load_row<NE>(t_in, zt, d_in, zd, (int)first, V, (int64_t)(w + 1) * kSlice <= V);
+    load_row<NE>(t_in, zt, d_in, zd, first, V, (int64_t)(w + 1) * kSlice <= V);
     if (tid < 64) lds.tab[tid] = kExp2Table[tid];
     __syncthreads();
 #pragma unroll
@@ -1013,7 +1017,7 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
             if (OCC > 2) __builtin_amdgcn_sched_barrier(0);
         }
     STAMP(9);
-    DrawNorm nm{1.0, 0.0, 0.0, 0.0, (double)a.eta};
+    DrawNorm nm{1.0, 0.0, 0.0, 0.0, uniform((double)a.eta)};
     u64* my_slots = ws.slot_b + (int64_t)b * ws.w2 * 12;
 
     // Reduction of word `word` (0 / 1) of the current phase over all slices, in a fixed order (the
@@ -1029,41 +1033,18 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
         return wave_max(s);
     };
 
-    const int nphase = bonus ? 1 : 3;
-    for (int phase = 1; phase <= nphase; ++phase) {
-        double a0 = 0.0, a1 = phase == 2 ? -INFINITY : 0.0;
-        if (phase == 1) {
-#pragma unroll
-            for (int i = 0; i < NE; ++i) {
-                a0 += et[i];
-                a1 += ed[i];
-            }
-        } else if (phase == 2) {                              // f is kept for phase 3 (no second exponential)
-#pragma unroll
-            for (int i = 0; i < NE; ++i) {
-                wgt[i] = draw_f(et[i], ed[i], nm, lds.tab);
-                a0 += wgt[i];
-                a1 = fmax(a1, wgt[i]);
-                if (OCC > 2) __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {                                              // the weights are kept for the token search
-#pragma unroll
-            for (int i = 0; i < NE; ++i) {
-                double p;
-                wgt[i] = draw_weight(et[i], ed[i], wgt[i], nm, p);
-                a0 += wgt[i];
-                a1 += p;
-            }
-        }
-        if (phase == 2) block_reduce2(a0, a1, lds.red, bank, OpAddD(), OpMaxD());
-        else block_reduce2(a0, a1, lds.red, bank, OpAddD(), OpAddD());
+    // One phase's exchange: the sums of the own slice in, every slice's in lds.slots when it returns.
+    auto exchange = [&](auto phase_constant, double a0, double a1) {
+        constexpr int phase = decltype(phase_constant)::value;
+        if (phase == 2) block_reduce2<NW>(a0, a1, lds.red, bank, OpAddD(), OpMaxD());
+        else block_reduce2<NW>(a0, a1, lds.red, bank, OpAddD(), OpAddD());
         u64* base = my_slots + (phase - 1) * 4 * W2;         // slice s: words base[4 s .. 4 s + 3]
         if (tid == 0) { put_d(base + 4 * w, a0, tg, true); put_d(base + 4 * w + 2, a1, tg, true); }
-        poll_all(base, 4 * W2, lds.slots, lds.miss, a.wait_ticks, tg);
+        poll_all<NT>(base, 4 * W2, lds.slots, lds.miss, a.wait_ticks, tg);
         __syncthreads();
         int miss = 0;
 #pragma unroll
-        for (int i = 0; i < kWaves; ++i) miss |= lds.miss[i];
+        for (int i = 0; i < NW; ++i) miss |= lds.miss[i];
         if (__builtin_expect(miss != 0, 0)) {
             // a slice whose sums did not arrive: the same sums from the logits in memory
             for (int s = 0; s < W2; ++s) {
@@ -1072,13 +1053,13 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
                 double m0 = 0.0, m1 = phase == 2 ? -INFINITY : 0.0;
 #pragma unroll 1
                 for (int i = 0; i < NE; ++i) {
-                    const int64_t e = (int64_t)s * kSlice + (int64_t)tid * NE + i;
+                    const int e = s * kSlice + tid * NE + i;
                     const double met = e < V ? exp_tab(((double)zt[e] - Mt) * invT, lds.tab) : 0.0;
                     const double med = (!bonus && e < V) ? exp_tab(((double)zd[e] - Md) * invT, lds.tab) : 0.0;
                     draw_accumulate(phase, met, med, nm, lds.tab, m0, m1);
                 }
-                if (phase == 2) block_reduce2(m0, m1, lds.red, bank, OpAddD(), OpMaxD());
-                else block_reduce2(m0, m1, lds.red, bank, OpAddD(), OpAddD());
+                if (phase == 2) block_reduce2<NW>(m0, m1, lds.red, bank, OpAddD(), OpMaxD());
+                else block_reduce2<NW>(m0, m1, lds.red, bank, OpAddD(), OpAddD());
                 if (tid == 0) {
                     put_d(lds.slots + 4 * s, m0, tg, false);
                     put_d(lds.slots + 4 * s + 2, m1, tg, false);
@@ -1090,14 +1071,50 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
             }
         }
         STAMP(9 + phase);
-        if (phase == 1 && !bonus) {
-            nm.iSt = 1.0 / all_sum(0);
-            nm.iSd = 1.0 / all_sum(1);
-        } else if (phase == 2) {
-            nm.iSh = 1.0 / all_sum(0);
-            nm.thr = (double)a.tail_alpha * (all_max(1) * nm.iSh);   // alpha * max p_hat
+    };
+
+    // Phase 1
+    {
+        double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            a0 += et[i];
+            a1 += ed[i];
         }
-        if (phase < nphase) __syncthreads();                  // lds.slots are rewritten by the next phase
+        exchange(Phase<1>(), a0, a1);
+    }
+    if (!bonus) {
+        nm.iSt = uniform(1.0 / all_sum(0));
+        nm.iSd = uniform(1.0 / all_sum(1));
+        __syncthreads();                                      // lds.slots are rewritten by the next phase
+        // Phase 2; f is kept for phase 3 (no second exponential)
+        {
+            double a0 = 0.0, a1 = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                wgt[i] = draw_f(et[i], ed[i], nm, lds.tab);
+                a0 += wgt[i];
+                a1 = fmax(a1, wgt[i]);
+                if (OCC > 2) __builtin_amdgcn_sched_barrier(0);
+            }
+            exchange(Phase<2>(), a0, a1);
+        }
+        nm.iSh = uniform(1.0 / all_sum(0));
+        nm.thr = uniform((double)a.tail_alpha * (all_max(1) * nm.iSh));   // alpha * max p_hat
+        __syncthreads();
+        // Phase 3; the weights are kept for the token search
+        {
+            double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                double p;
+                wgt[i] = draw_weight(et[i], ed[i], wgt[i], nm, p);
+                a0 += wgt[i];
+                a1 += p;
+                if (OCC > 2) __builtin_amdgcn_sched_barrier(0);
+            }
+            exchange(Phase<3>(), a0, a1);
+        }
     }
 
     // ---- which slice holds the crossing.  Inclusive prefix sums over the slices in slice order
@@ -1136,7 +1153,7 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
     STAMP(13);
     if (w == 0) {
         // What the draw does not wait for: accepted drafts, then -1 (the draw fills slot n), and the counters.
-        for (int k = tid; k <= a.gmax; k += kThreads)
+        for (int k = tid; k <= a.gmax; k += NT)
             if (k != n) a.out_tokens[(int64_t)b * (a.gmax + 1) + k] = k < n ? a.tokens[(int64_t)b * a.gmax + k] : -1;
         if (tid == 0) {
             a.n_accepted[b] = n;
@@ -1173,8 +1190,8 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
     for (int i = 0; i < NE; ++i) {
         const double nxt = run + wgt[i];
         if (wgt[i] > 0.0) {
-            my_hi = (int)first + i;
-            if (nxt > t) my_lo = min(my_lo, (int)first + i);
+            my_hi = first + i;
+            if (nxt > t) my_lo = min(my_lo, first + i);
         }
         run = nxt;
     }
@@ -1183,12 +1200,12 @@ __global__ void __launch_bounds__(kThreads, OCC) accept_draw_row(AcceptLaunch a,
     const unsigned long long hit = __ballot(my_lo != 0x7fffffff), any = __ballot(my_hi >= 0);
     const int lo_w = hit ? __shfl(my_lo, __ffsll((long long)hit) - 1) : 0x7fffffff;
     const int hi_w = any ? __shfl(my_hi, 63 - __clzll((long long)any)) : -1;
-    int* picks = reinterpret_cast<int*>(lds.red + 2 * kWaves);    // [kWaves][2], past the wave totals above
+    int* picks = reinterpret_cast<int*>(lds.red + 2 * NW);    // [NW][2], past the wave totals above
     if (lane == 0) { picks[2 * wave] = lo_w; picks[2 * wave + 1] = hi_w; }
     __syncthreads();
     if (tid == 0) {
         int lo = 0x7fffffff, hi = -1;
-        for (int s = 0; s < kWaves; ++s) { lo = min(lo, picks[2 * s]); hi = max(hi, picks[2 * s + 1]); }
+        for (int s = 0; s < NW; ++s) { lo = min(lo, picks[2 * s]); hi = max(hi, picks[2 * s + 1]); }
         const int tok = lo != 0x7fffffff ? lo : hi;           // hi: rounding at the slice's end
         a.out_tokens[(int64_t)b * (a.gmax + 1) + n] = tok;
     }
@@ -1202,16 +1219,25 @@ size_t accept_workspace_bytes(int B, int gmax, int V)
     return carve(nullptr, B, gmax, V).bytes;
 }
 
-// Entries per thread of accept_draw_row: the fewest that leave every workgroup a compute unit of its own and keep the
-// exchange among at most 64 workgroups (one sequence: vocabulary 32001 22.1 us with 2, 23.0 with 4, 26.7 with 8;
-// 128256 23.7 with 2 on 126 workgroups, 23.0 with 4, 25.0 with 8).
-static int draw_entries(const AcceptLaunch& a)
+// The build of accept_draw_row for a call.  Small batches: the fewest entries per thread that leave every workgroup a
+// compute unit of its own and keep the exchange among at most 64 workgroups (one sequence: vocabulary 32001 22.1 us
+// with 2, 23.0 with 4, 26.7 with 8; 128256 23.7 with 2 on 126 workgroups, 23.0 with 4, 25.0 with 8).  Eight entries while
+// the grid is one round of two workgroups per compute unit; beyond that 20 entries on 256 threads, which hold a quarter more
+// entries at a time and so need fewer rounds of the three exchanges (64 sequences of 128256: 135 us against 140; 32 of
+// 152064: 95 against 105; 32 of 128256 the same).
+struct DrawShape {
+    void (*kernel)(AcceptLaunch, Ws, int);
+    int threads, wgs;
+};
+static DrawShape draw_shape(const AcceptLaunch& a)
 {
-    for (int ne = 2; ne < 8; ne *= 2) {
-        const int64_t wgs = ((int64_t)a.V + kThreads * ne - 1) / (kThreads * ne);
-        if (wgs <= 64 && wgs * a.B <= a.n_cu) return ne;
-    }
-    return 8;
+    const auto wgs = [&](int threads, int ne) { return (a.V + threads * ne - 1) / (threads * ne); };
+    const int w2 = wgs(512, 2), w4 = wgs(512, 4), w8 = wgs(512, 8);
+    if (w2 <= 64 && (int64_t)w2 * a.B <= a.n_cu) return {accept_draw_row<512, 2, 2>, 512, w2};
+    if (w4 <= 64 && (int64_t)w4 * a.B <= a.n_cu) return {accept_draw_row<512, 4, 2>, 512, w4};
+    if ((int64_t)w8 * a.B <= a.n_cu) return {accept_draw_row<512, 8, 2>, 512, w8};
+    if ((int64_t)w8 * a.B <= 2 * (int64_t)a.n_cu) return {accept_draw_row<512, 8, 4>, 512, w8};
+    return {accept_draw_row<256, 20, 2>, 256, wgs(256, 20)};
 }
 
 hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)
@@ -1237,13 +1263,8 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)
     const int64_t n_items = rows * W;
     const size_t lds_a = sizeof(LdsA) + (size_t)6 * W * sizeof(u64);
     hipLaunchKernelGGL(rows_kernel, dim3((unsigned)n_items), dim3(slice == 10240 ? 256 : 512), lds_a, stream, a, ws, W, (int)n_items);
-    const auto draw_wgs = [&](int ne) { return (a.V + kThreads * ne - 1) / (kThreads * ne); };
-    const int ne = draw_entries(a);
-    const int W2 = draw_wgs(ne);
-    auto draw_kernel = ne == 2 ? accept_draw_row<2, 2>
-                     : ne == 4 ? accept_draw_row<4, 2>
-                     : (int64_t)W2 * a.B <= a.n_cu ? accept_draw_row<8, 2> : accept_draw_row<8, 4>;
-    const size_t lds_b = sizeof(LdsB) + (size_t)4 * W2 * sizeof(u64);
-    hipLaunchKernelGGL(draw_kernel, dim3(W2, a.B), dim3(kThreads), lds_b, stream, a, ws, W2);
+    const DrawShape draw = draw_shape(a);
+    const size_t lds_b = sizeof(LdsB) + (size_t)4 * draw.wgs * sizeof(u64);
+    hipLaunchKernelGGL(draw.kernel, dim3(draw.wgs, a.B), dim3(draw.threads), lds_b, stream, a, ws, draw.wgs);
     return hipGetLastError();
 }

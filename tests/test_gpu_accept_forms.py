@@ -106,3 +106,24 @@ def test_greedy_ties_masks_and_row_ends(V):
             assert n[b] == want, (b, n, want)
             assert list(toks[b, :want]) == list(tok[b, :want]) and toks[b, want] == int(np.argmax(zt[b, want]))
             assert np.all(toks[b, want + 1:] == -1)
+
+
+@pytest.mark.parametrize("batch,V", [(1, 20000), (1, 100001), (6, 100001), (24, 50257), (44, 50257), (600, 1030)])
+def test_every_build_of_the_draw_and_its_give_up_path(batch, V):
+    """Vocabularies and batches that select 2, 4, 8 and 20 entries per thread (one round of workgroups and several), a row
+    end inside a thread's entries; with every exchange recomputed the results are the same bits."""
+    cfg = wl.scaled(wl.CONFIGS["llama8b_32k"], batch=batch, vocab=V, gamma_choices=(0, 1), draft_noise_std=2.0, name="draws")
+    acc = wl.gen_accept_inputs(cfg, salt=V)
+    r = gu.rapid()
+    runs = []
+    try:
+        for wait in (100, 0, 2):
+            r.set_option(binding.OPT_ACCEPT_WAIT_US, wait)
+            gpu, ref = gu.run_accept_case(acc, eta=cfg.eta)
+            runs.append(gpu)
+    finally:
+        r.set_option(binding.OPT_ACCEPT_WAIT_US, 100)
+    for other in runs[1:]:
+        assert all(np.array_equal(x.view(np.int32), y.view(np.int32)) for x, y in zip(runs[0], other))
+    st = gu.compare_accept(runs[0], ref, acc.gammas, cfg.gamma_max)
+    assert st["n_mismatch"] == 0 and st["token_mismatch"] == 0 and st["exempt_sequences"] == 0, st
