@@ -400,6 +400,14 @@ __device__ __forceinline__ void for_each_piece(const AttnLaunch& a, int g, int h
     }
 }
 
+// Splits of a fixed grid that hold a token of a sequence of length L (head h).
+__device__ __forceinline__ int live_splits(const AttnLaunch& a, int L, int h)
+{
+    int ns = min(L / a.chunk + 2, a.nsplit);
+    while (ns > 0 && split_begin(a, ns - 1, h) >= L) --ns;
+    return ns;
+}
+
 // One workgroup's work on tokens [c0, c1) of one (sequence, kv head): the partial goes to the packed rows
 // from `pbase` on.
 template <int D, int RB, bool PAGED>
@@ -912,18 +920,41 @@ __global__ void __launch_bounds__(2 * kWaves * 64) verify_attn_split_wide(AttnLa
                                          (((int64_t)b * a.Hkv + hkv) * a.nsplit + split) * RP);
 }
 
+// Reductions over 32 values, one per lane of the wave's lower and again of its upper half; result in every lane.
+template <int ROR>
+__device__ __forceinline__ float row_ror(float v)      // rotation inside rows of 16 lanes, without LDS
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ROR, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float lane_of(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+__device__ __forceinline__ float max32(float v)
+{
+    v = fmaxf(v, row_ror<8>(v));
+    v = fmaxf(v, row_ror<4>(v));
+    v = fmaxf(v, row_ror<2>(v));
+    v = fmaxf(v, row_ror<1>(v));
+    return fmaxf(lane_of(v, 0), lane_of(v, 16));
+}
+__device__ __forceinline__ float sum32(float v)
+{
+    v += row_ror<8>(v);
+    v += row_ror<4>(v);
+    v += row_ror<2>(v);
+    v += row_ror<1>(v);
+    return lane_of(v, 0) + lane_of(v, 16);
+}
+
 // Merge the splits of one query row: out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
 // One workgroup of D threads per (sequence, kv head, packed row), splits taken 32 at a
 // time.  The kernel is latency bound, so every thread issues the loads of its column
 // for a whole block of splits before anything else, next to the (m, l) loads; the
-// weights are formed while they are in flight.  (With balanced shares the lengths decide which
+// weights are formed while they are in flight.  Every wave forms all weights for itself, split j's in lane j, and
+// multiplies by them out of scalar registers: no LDS and no barrier.  (With balanced shares the lengths decide which
 // partials belong to the sequence, so there they come first.)
 template <int D, bool BALANCED>
 __global__ void __launch_bounds__(D) verify_attn_merge(AttnLaunch a)
 {
     constexpr int SB = 32;                             // splits per block
-    __shared__ float wgt[SB];
-    __shared__ float red[2][4];
     const int row = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
     const int d = threadIdx.x;
     const int Q = seq_queries(a, b);
@@ -973,46 +1004,33 @@ __global__ void __launch_bounds__(D) verify_attn_merge(AttnLaunch a)
         float o[SB];
 #pragma unroll
         for (int j = 0; j < SB; ++j) o[j] = j < nsb ? po[(int64_t)j * RP * D] : 0.f;
+        const int sl = d & (SB - 1);                   // this lane's split
         float ms = -INFINITY, ls = 0.f;
-        if (d < nsb) {
-            const float* ml = a.part_ml + (pbase + (int64_t)(s0 + d) * RP + row) * 2;
+        if (sl < nsb) {
+            const float* ml = a.part_ml + (pbase + (int64_t)(s0 + sl) * RP + row) * 2;
             ms = ml[0];
             ls = ml[1];
         }
         if (!BALANCED && s0 == 0) {
-            const int L = seq_len(a, b);
-            ns = min(L / a.chunk + 2, a.nsplit);      // splits that hold a token of this sequence
-            while (ns > 0 && split_begin(a, ns - 1, hkv) >= L) --ns;
+            ns = live_splits(a, seq_len(a, b), hkv);
         }
         const int nb = min(SB, ns - s0);
 #pragma unroll
         for (int j = 0; j < SB; ++j) o[j] = j < nb ? o[j] : 0.f;
-        if (d >= nb) { ms = -INFINITY; ls = 0.f; }
-        float mb = ms;                                 // D >= 64 > SB: the first wave holds them all
-#pragma unroll
-        for (int off = 16; off > 0; off >>= 1) mb = fmaxf(mb, __shfl_xor(mb, off));
-        if (d == 0) red[0][0] = mb;
-        __syncthreads();
-        mb = red[0][0];
-        const float Mn = fmaxf(M, mb);
+        if (sl >= nb) { ms = -INFINITY; ls = 0.f; }
+        const float Mn = fmaxf(M, max32(ms));
         const float Mu = (Mn == -INFINITY) ? 0.f : Mn;
         const float resc = fast_exp2(M - Mu);
         M = Mn;
-        float w = fast_exp2(ms - Mu), dl = w * ls;     // threads >= nb: w = 0
-#pragma unroll
-        for (int off = 16; off > 0; off >>= 1) dl += __shfl_xor(dl, off);
-        if (d < SB) wgt[d] = w;
-        if (d == 0) red[1][0] = dl;
-        __syncthreads();
-        den = den * resc + red[1][0];
+        const float w = fast_exp2(ms - Mu);            // lanes >= nb: 0
+        den = den * resc + sum32(w * ls);
         float acc0 = 0.f, acc1 = 0.f;
 #pragma unroll
         for (int j = 0; j < SB; j += 2) {
-            acc0 = fmaf(wgt[j], o[j], acc0);
-            acc1 = fmaf(wgt[j + 1], o[j + 1], acc1);
+            acc0 = fmaf(lane_of(w, j), o[j], acc0);
+            acc1 = fmaf(lane_of(w, j + 1), o[j + 1], acc1);
         }
         num = num * resc + (acc0 + acc1);
-        __syncthreads();                               // wgt/red are rewritten by the next block
     }
     float o = den > 0.f ? num / den : 0.f;
     __bf16 ob = (__bf16)o;
