@@ -1243,8 +1243,9 @@ static DrawShape draw_shape(const AcceptLaunch& a)
 hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)
 {
     Ws ws = carve(a.workspace, a.B, a.gmax, a.V);
-    // Slice size of accept_rows: 10240 entries on 256 threads where the grid then gives two workgroups per compute unit,
-    // else 8192 or 4096 on 512 threads; small batches take the smallest so that the chip is used at all.  The pass is bound
+    // Slice size of accept_rows: 10240 entries on 256 threads where the grid then gives one and a half workgroups per compute
+    // unit (eight sequences of 11 rows and vocabulary 50257: 27.8 us, with 8192 on 512 threads 29.0; four of 9 and 128256: 29.0
+    // against 30.2), else 8192 or 4096 on 512 threads; small batches take the smallest so that the chip is used at all.  The pass is bound
     // by the bytes in flight while workgroups wait for one another: four workgroups of 256 threads hold 320 KB of a
     // compute unit's 512 KB of registers, two of 512 threads with slices of 16384 hold 256 KB (64 sequences: 92 us of
     // accept_rows against 78; 8192 on 256 threads: 81; 12288: spills).
@@ -1253,7 +1254,7 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)
     int slice = kMinSlice;
     const bool plain = a.eta <= kPlainEta;
     for (int cand : {plain ? 10240 : 16384, 8192})            // (the logarithmic form needs more registers)
-        if (rows * slices(cand) >= 2 * (int64_t)a.n_cu) { slice = cand; break; }
+        if (2 * rows * slices(cand) >= (cand == 10240 ? 3 : 4) * (int64_t)a.n_cu) { slice = cand; break; }
     if (a.force_slice) slice = a.force_slice;
     auto rows_kernel = slice == 16384 ? (plain ? accept_rows<512, 8, 4, true> : accept_rows<512, 8, 4, false>)
                      : slice == 10240 ? accept_rows<256, 10, 4, true>
