@@ -116,8 +116,10 @@ typedef struct rapid_attn_shape {
                               /* batches; results never depend on it                           */
 } rapid_attn_shape;
 
-/* Tokens per KV split the library will use for `shape` (multiple of 128), and
- * through it the number of splits per (sequence, kv head): ceil(max_ctx / chunk). */
+/* Tokens per KV split the library plans with for `shape` (multiple of 128), and
+ * through it the number of splits per (sequence, kv head): ceil(max_ctx / chunk); both size the workspace.
+ * (Ragged batches with ctx_sum_hint set and chunk_tokens 0 are divided on the device instead, into equal shares
+ * of their tokens, within the same workspace.) */
 int rapid_verify_attn_chunk(const rapid_ctx* ctx, const rapid_attn_shape* shape);
 
 /* Bytes of device workspace rapid_verify_attn needs for `shape` (0 on a bad shape). */

@@ -454,7 +454,8 @@ __device__ __forceinline__ void slice_stats(GetT gt, GetD gd, PutT put_t, PutD p
         for (int v = 0; v < NV; ++v) {
             floatx4 x = gt(v);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) st += x[j] = fexp2((x[j] - mt) * c);
+            for (int j = 0; j < 4; ++j) x[j] = fexp2((x[j] - mt) * c);
+            st += (x[0] + x[1]) + (x[2] + x[3]);
             put_t(v, x);
         }
     if (do_d && md > -INFINITY)
@@ -462,7 +463,8 @@ __device__ __forceinline__ void slice_stats(GetT gt, GetD gd, PutT put_t, PutD p
         for (int v = 0; v < NV; ++v) {
             floatx4 y = gd(v);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) sd += y[j] = fexp2((y[j] - md) * c);
+            for (int j = 0; j < 4; ++j) y[j] = fexp2((y[j] - md) * c);
+            sd += (y[0] + y[1]) + (y[2] + y[3]);
             put_d(v, y);
         }
     block_reduce2<NW>(st, sd, sh, bank, OpAddF(), OpAddF());

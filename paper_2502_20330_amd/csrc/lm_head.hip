@@ -117,10 +117,8 @@ __global__ void __launch_bounds__(kWaves * 64) lm_head_stream(LmHeadLaunch a)
     // reads the last 16 rows instead (the epilogue drops the rows that belong to the block before)
     auto block_row0 = [&](int jj) { return min(v0 + (jj * kWaves + wave) * 16, a.vocab - 16); };
 
-    // tile j of the s-th slab: j = 0..NR-1 the row blocks of the h slab, j = NR.. the wave's W blocks
-    auto issue = [&](int s, int j, int slot) {
-        const int sp = s + s_first;
-        const int64_t kbyte = (int64_t)(sp >= nslab ? sp - nslab : sp) * SK * 2;
+    // tile j of the slab at byte kbyte of a row: j = 0..NR-1 the row blocks of the h slab, j = NR.. the wave's W blocks
+    auto issue = [&](uint32_t kbyte, int j, int slot) {
         const uint32_t dst = ring_lds + slot * T::BYTES;
         if (j < NR) {
             const char* base = reinterpret_cast<const char*>(a.h) + kbyte;
@@ -142,12 +140,18 @@ __global__ void __launch_bounds__(kWaves * 64) lm_head_stream(LmHeadLaunch a)
 
     if (nbw > 0) {                                       // (a wave without blocks: ranges of fewer than four blocks)
         int ps = 0, pj = 0, pt = 0;                      // next tile to request: slab, index, linear number
+        uint32_t pk = (uint32_t)s_first * SK * 2;        // the slab's place in a row
         auto request_next = [&]() {
             const int sl = pt & (T::SLOTS - 1);
-            if (ps < nslab) issue(ps, pj, sl);
-            else issue(nslab - 1, 0, sl);                // past the end: a cached h tile keeps the count uniform
+            if (ps < nslab) issue(pk, pj, sl);
+            else issue(pk, 0, sl);                       // past the end: a cached h tile keeps the count uniform
             ++pt;
-            if (++pj >= NR + nbw) { pj = 0; ++ps; }
+            if (++pj >= NR + nbw) {
+                pj = 0;
+                ++ps;
+                pk += SK * 2;
+                if (pk == row_bytes) pk = 0;
+            }
         };
 #pragma unroll
         for (int j = 0; j < T::AHEAD; ++j) request_next();

@@ -87,11 +87,11 @@ bool ragged_batch(const rapid_attn_shape* s)
 // Tokens per KV split, a multiple of 128, never below 256 (two tiles per wave).
 // Measured on uniform and ragged batches of 2..64 sequences: a workgroup costs about 8 us
 // besides its streaming time, so for sequences of equal length one workgroup per compute
-// unit (a single round of long splits) beats any finer grid by 5..15 %.  When the lengths
-// differ, a single round leaves compute units idle behind the short sequences; two rounds
-// let the dispatcher back-fill.  The host cannot see the lengths (device data), so it
-// plans for equal lengths unless the caller passes their sum: then the split is sized so
-// that the non-empty workgroups fill at most two rounds.
+// unit (a single round of long splits) beats any finer grid by 5..15 %.  The host cannot see
+// the lengths (device data), so it plans for equal lengths unless the caller passes their sum
+// and they differ: then the split size is the one that would fill two rounds.  Such batches run on balanced
+// shares (plan_groups); the split size still sizes their workspace, and is used where the shares' partials
+// would not fit it.
 int plan_chunk(const rapid_ctx* ctx, const rapid_attn_shape* s)
 {
     const int quantum = 128;
