@@ -15,8 +15,8 @@
 //       slices; one workgroup of 256 or 512 threads holds its slice of both rows in
 //       registers.  It publishes the slice's (max, sum exp) of either row, picks up the
 //       publications of the other workgroups of the row pair, and with the row normalisers
-//       forms d = z/T + eta (q - p) for its slice (still in registers) and publishes
-//       (max d, sum exp(d - max)).  The workgroup of slice 0 then collects all slices of its row,
+//       forms f = exp(z/T + eta (q - p)) for its slice (from the exponentials, still in registers) and
+//       publishes (max f, sum f).  The workgroup of slice 0 then collects all slices of its row,
 //       combines them in fp64 and runs the accept test of the drafted token.
 //
 //   accept_draw_row   n = first rejected position; the draw weights of row n (the residual,
@@ -183,7 +183,7 @@ struct Ws {
                       //       [kGiveRows], [kGiveRows + 1] give-ups of accept_rows: count, tag of the call
     u64* slot_t;      // [B][gmax+1][wmax][2]  (raw max, sum exp((z-max)/T)) per slice of a target row
     u64* slot_d;      // [B][gmax][wmax][2]
-    u64* slot_h;      // [B][gmax][wmax][2]    (max d, sum exp2(d - max)), d in log2 units relative to zmax_t/T
+    u64* slot_h;      // [B][gmax][wmax][2]    shifted row: (max f, sum f) relative to zmax_t/T, or its logarithmic form
     u64* slot_b;      // [B][3][w2][4]         two fp64 values per slice and phase of accept_draw_row
     double* rows;     // [B][gmax+1][4]: zmax_t, zmax_d (raw maxima, exact)
     int32_t* flags;   // [B][gmax]: 1 = draft k passed its accept test, 2 = its id was outside [0, V)

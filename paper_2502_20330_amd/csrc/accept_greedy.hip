@@ -110,10 +110,12 @@ __device__ __forceinline__ void row_argmax(const GreedyWs& ws, int64_t row, floa
 }
 
 // One wave per position: the drafted token, its two logits and the slices of both rows are fetched side by side, and the
-// wave of position k leaves the arg-max of target row k in LDS, where the decision finds that of row n.
+// wave of position k leaves the arg-max of target row k in LDS, where the decision finds that of row n (the first kKept rows:
+// gmax has no small bound; beyond them row n is combined once more).
+constexpr int kKept = 1024;
 __global__ void __launch_bounds__(kDecide) greedy_decide(AcceptLaunch a, GreedyWs ws)
 {
-    extern __shared__ int target_arg[];                   // [gmax + 1]
+    __shared__ int target_arg[kKept];
     __shared__ int first_fail;
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nrows = 2 * a.gmax + 1;
@@ -134,7 +136,7 @@ __global__ void __launch_bounds__(kDecide) greedy_decide(AcceptLaunch a, GreedyW
         row_argmax(ws, (int64_t)b * nrows + k, mt, it);
         if (pair) row_argmax(ws, (int64_t)b * nrows + a.gmax + 1 + k, md, id);
         if (lane != 0) continue;
-        target_arg[k] = it;
+        if (k < kKept) target_arg[k] = it;
         if (!pair) continue;
         double rho = 0.0;
         bool ok = false;
@@ -151,11 +153,18 @@ __global__ void __launch_bounds__(kDecide) greedy_decide(AcceptLaunch a, GreedyW
     }
     __syncthreads();
     const int n = min(first_fail, g);
+    if (n >= kKept) {                                         // uniform
+        float m;
+        int it;
+        if (wave == 0) row_argmax(ws, (int64_t)b * nrows + n, m, it);
+        if (tid == 0) target_arg[0] = it;
+        __syncthreads();
+    }
     for (int k = tid; k <= a.gmax; k += kDecide) {
         int tok = -1;
         if (k < n) tok = a.tokens[(int64_t)b * a.gmax + k];
         else if (k == n) {                                    // target row n: rejection or bonus position
-            tok = target_arg[n];
+            tok = target_arg[n < kKept ? n : 0];
             if (tok < 0 || tok >= a.V) tok = 0;               // a row of NaNs has no arg-max: any valid id
         }
         a.out_tokens[(int64_t)b * (a.gmax + 1) + k] = tok;
@@ -174,6 +183,6 @@ hipError_t launch_accept_greedy(const AcceptLaunch& a, hipStream_t stream)
 {
     GreedyWs ws = gcarve(a.workspace, a.B, a.gmax, a.V);
     hipLaunchKernelGGL(greedy_slice_argmax, dim3(ws.W, 2 * a.gmax + 1, a.B), dim3(kThreads), 0, stream, a, ws);
-    hipLaunchKernelGGL(greedy_decide, dim3(a.B), dim3(kDecide), (a.gmax + 1) * sizeof(int), stream, a, ws);
+    hipLaunchKernelGGL(greedy_decide, dim3(a.B), dim3(kDecide), 0, stream, a, ws);
     return hipGetLastError();
 }

@@ -127,3 +127,23 @@ def test_every_build_of_the_draw_and_its_give_up_path(batch, V):
         assert all(np.array_equal(x.view(np.int32), y.view(np.int32)) for x, y in zip(runs[0], other))
     st = gu.compare_accept(runs[0], ref, acc.gammas, cfg.gamma_max)
     assert st["n_mismatch"] == 0 and st["token_mismatch"] == 0 and st["exempt_sequences"] == 0, st
+
+
+@pytest.mark.parametrize("g", [1023, 1024, 1100, 20000])
+def test_greedy_with_thousands_of_drafted_positions(g):
+    """More positions than the decision keeps arg-maxima for in LDS: all accepted, and rejected at the last one."""
+    rng = np.random.default_rng(g)
+    V = 7
+    zt = rng.standard_normal((2, g + 1, V)).astype(np.float32)
+    zd = zt[:, :g].copy()
+    tok = np.argmax(zd, -1).astype(np.int32)
+    tok[1, g - 1] = -5                                        # outside the vocabulary: rejected
+    u = np.full((2, g + 1), 0.5, dtype=np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    n, toks, _ = gu.rapid().rapid_accept(dev(zt), dev(zd), dev(tok), 1.0, dev(u), temperature=0.0)
+    torch.cuda.synchronize()
+    n, toks = n.cpu().numpy(), toks.cpu().numpy()
+    assert list(n) == [g, g - 1]
+    for b in range(2):
+        np.testing.assert_array_equal(toks[b, :n[b]], tok[b, :n[b]])
+        assert toks[b, n[b]] == int(np.argmax(zt[b, n[b]])) and np.all(toks[b, n[b] + 1:] == -1)
