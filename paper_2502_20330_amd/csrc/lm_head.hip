@@ -94,11 +94,6 @@ __global__ void __launch_bounds__(kWaves * 64) lm_head_stream(LmHeadLaunch a)
     const int v0 = blockIdx.x * nb * 16;
     const uint32_t row_bytes = (uint32_t)a.hidden * 2u;
     const int nslab = a.hidden / SK;
-    // Where the row pitch is a multiple of 4 KiB, all workgroups in the same slab at the same time would read the same
-    // part of every 4 KiB and with it a part of the memory channels only (hidden 2048: 5.7 TB/s, 6144: 5.7, where 3584
-    // reads 6.7).  There the workgroups of a die start at slabs one apart and wrap around: 6.6 and 6.8 TB/s; hidden 8192
-    // 315 -> 311 us, 4096 the same to 10 % faster (vocabulary 50257).  Other pitches spread by themselves.
-    const int s_first = row_bytes % 4096 == 0 ? (int)((blockIdx.x / 8) % (unsigned)nslab) : 0;
     char* ring = smem + wave * kRing;
     const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + wave * kRing;
 
@@ -117,8 +112,9 @@ __global__ void __launch_bounds__(kWaves * 64) lm_head_stream(LmHeadLaunch a)
     // reads the last 16 rows instead (the epilogue drops the rows that belong to the block before)
     auto block_row0 = [&](int jj) { return min(v0 + (jj * kWaves + wave) * 16, a.vocab - 16); };
 
-    // tile j of the slab at byte kbyte of a row: j = 0..NR-1 the row blocks of the h slab, j = NR.. the wave's W blocks
-    auto issue = [&](uint32_t kbyte, int j, int slot) {
+    // tile j of slab s: j = 0..NR-1 the row blocks of the h slab, j = NR.. the wave's W blocks
+    auto issue = [&](int s, int j, int slot) {
+        const int64_t kbyte = (int64_t)s * SK * 2;
         const uint32_t dst = ring_lds + slot * T::BYTES;
         if (j < NR) {
             const char* base = reinterpret_cast<const char*>(a.h) + kbyte;
@@ -140,18 +136,12 @@ __global__ void __launch_bounds__(kWaves * 64) lm_head_stream(LmHeadLaunch a)
 
     if (nbw > 0) {                                       // (a wave without blocks: ranges of fewer than four blocks)
         int ps = 0, pj = 0, pt = 0;                      // next tile to request: slab, index, linear number
-        uint32_t pk = (uint32_t)s_first * SK * 2;        // the slab's place in a row
         auto request_next = [&]() {
             const int sl = pt & (T::SLOTS - 1);
-            if (ps < nslab) issue(pk, pj, sl);
-            else issue(pk, 0, sl);                       // past the end: a cached h tile keeps the count uniform
+            if (ps < nslab) issue(ps, pj, sl);
+            else issue(nslab - 1, 0, sl);                // past the end: a cached h tile keeps the count uniform
             ++pt;
-            if (++pj >= NR + nbw) {
-                pj = 0;
-                ++ps;
-                pk += SK * 2;
-                if (pk == row_bytes) pk = 0;
-            }
+            if (++pj >= NR + nbw) { pj = 0; ++ps; }
         };
 #pragma unroll
         for (int j = 0; j < T::AHEAD; ++j) request_next();
