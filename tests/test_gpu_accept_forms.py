@@ -147,3 +147,23 @@ def test_greedy_with_thousands_of_drafted_positions(g):
     for b in range(2):
         np.testing.assert_array_equal(toks[b, :n[b]], tok[b, :n[b]])
         assert toks[b, n[b]] == int(np.argmax(zt[b, n[b]])) and np.all(toks[b, n[b] + 1:] == -1)
+
+
+@pytest.mark.parametrize("eta", [1e6, 2.2e7, 6e7, 1e8, 2e8, 3e8, 1e12, 1e30])
+def test_shift_of_any_size(eta):
+    """A shift eta (q - p) far past the range of the exponential.  Token 0 (q = 0.9, p = 0.5) takes all of p_hat, so its residual
+    max(p - p_hat, p - q, 0) is 0 and it is never drawn after a reject; the others (q < p) keep p, the draw is theirs.  The
+    last token, p = q = 1e-30, keeps p_hat's normaliser above zero whatever the shift makes of token 0."""
+    V, B = 101, 64
+    p = np.concatenate([[0.5], np.full(99, 0.5 / 99), [1e-30]])
+    q = np.concatenate([[0.9], np.full(99, 0.1 / 99), [1e-30]])
+    zt = np.broadcast_to(np.log(p).astype(np.float32), (B, 2, V))
+    zd = np.broadcast_to(np.log(q).astype(np.float32), (B, 1, V))
+    u = np.stack([np.full(B, 0.5), (np.arange(B) + 0.5) / B], 1).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    n, toks, ratio = gu.rapid().rapid_accept(dev(zt), dev(zd), torch.full((B, 1), 3, dtype=torch.int32, device="cuda"), eta,
+                                             dev(u), tail_alpha=0.0)
+    torch.cuda.synchronize()
+    assert not n.any() and not ratio.any()                     # p_hat of the drafted token is 0
+    want = 1 + np.floor(u[:, 1] * 99)                          # 99 equal weights, and u stays clear of their edges
+    np.testing.assert_array_equal(toks[:, 0].cpu().numpy(), want)
