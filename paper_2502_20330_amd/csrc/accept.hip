@@ -71,7 +71,6 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kDrawSlice = kThreads * 2;            // smallest slice of accept_draw_row (2 entries per thread)
 constexpr int kMinSlice = kThreads * 4 * 2;         // smallest slice of accept_rows (NV = 2)
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr double kLn2 = 0.6931471805599453;
 
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -842,13 +841,13 @@ __device__ __forceinline__ double uniform(double v) { return lane_value(v, 0); }
 
 struct LdsB {
     double red[4 * kWaves];
-    double tab[64];       // 2^(j/64)
+    Exp2 tab;             // 2^(j/64)
     int miss[kWaves];
     u64 slots[];          // 4 W2 words: the two fp64 values of every slice for the current phase
 };
 
 // The three quantities of one entry that the phases are made of.
-__device__ __forceinline__ double draw_f(double et, double ed, const DrawNorm& nm, const double* tab)
+__device__ __forceinline__ double draw_f(double et, double ed, const DrawNorm& nm, const Exp2& tab)
 {
     return et * exp_shift(nm.eta * (ed * nm.iSd - et * nm.iSt), tab);
 }
@@ -863,7 +862,7 @@ __device__ __forceinline__ double draw_weight(double et, double ed, double f, co
 }
 // The memory path's sums: entry (et, ed) into the two running values of `phase`, the entries of a thread in index
 // order as in the register path.
-__device__ __forceinline__ void draw_accumulate(int phase, double et, double ed, const DrawNorm& nm, const double* tab, double& a0,
+__device__ __forceinline__ void draw_accumulate(int phase, double et, double ed, const DrawNorm& nm, const Exp2& tab, double& a0,
                                                 double& a1)
 {
     if (phase == 1) {
@@ -881,12 +880,13 @@ __device__ __forceinline__ void draw_accumulate(int phase, double et, double ed,
 }
 
 // NT threads of NE entries.  OCC = waves per SIMD the kernel is compiled for; at 4 (two workgroups of 512 threads per
-// compute unit) the entries are taken one at a time, which keeps the registers below 128.
+// compute unit, 128 registers) and with 20 entries (256 registers) the entries are taken one at a time: several at once spill.
 template <int NT, int NE, int OCC>
 __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws, int W2)
 {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     constexpr int NW = NT / 64;
+    constexpr bool kOneByOne = OCC > 2 || NE > 8;         // few registers: one entry's temporaries at a time
     LdsB& lds = *reinterpret_cast<LdsB*>(smem_raw);
     constexpr int kSlice = NT * NE;
     const int w = blockIdx.x, b = blockIdx.y;
@@ -911,12 +911,12 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
     const int first = w * kSlice + tid * NE;
     float t_in[NE], d_in[NE];
     load_row<NE>(t_in, zt, d_in, zd, first, V, (int64_t)(w + 1) * kSlice <= V);
-    if (tid < 64) lds.tab[tid] = kExp2Table[tid];
+    if (tid < 64) { lds.tab.v[tid] = kExp2Table.v[tid]; lds.tab.rest[tid] = kExp2Table.rest[tid]; }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < NE; ++i) {
         et[i] = exp_tab(((double)t_in[i] - Mt) * invT, lds.tab);
-        if (OCC > 2) __builtin_amdgcn_sched_barrier(0);       // few registers: one entry's temporaries at a time
+        if (kOneByOne) asm volatile("" ::: "memory");
     }
 #pragma unroll
     for (int i = 0; i < NE; ++i) ed[i] = 0.0;
@@ -924,7 +924,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
             ed[i] = exp_tab(((double)d_in[i] - Md) * invT, lds.tab);
-            if (OCC > 2) __builtin_amdgcn_sched_barrier(0);
+            if (kOneByOne) asm volatile("" ::: "memory");
         }
     STAMP(9);
     DrawNorm nm{1.0, 0.0, 0.0, 0.0, uniform((double)a.eta)};
@@ -1005,7 +1005,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
                 wgt[i] = draw_f(et[i], ed[i], nm, lds.tab);
                 a0 += wgt[i];
                 a1 = fmax(a1, wgt[i]);
-                if (OCC > 2) __builtin_amdgcn_sched_barrier(0);
+                if (kOneByOne) asm volatile("" ::: "memory");
             }
             exchange(Phase<2>(), a0, a1);
         }
@@ -1021,7 +1021,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
                 wgt[i] = draw_weight(et[i], ed[i], wgt[i], nm, p);
                 a0 += wgt[i];
                 a1 += p;
-                if (OCC > 2) __builtin_amdgcn_sched_barrier(0);
+                if (kOneByOne) asm volatile("" ::: "memory");
             }
             exchange(Phase<3>(), a0, a1);
         }

@@ -53,3 +53,15 @@ def test_ends_of_the_range(exp64, which):
     assert np.all(exp64(which, np.array([0.0, -0.0])) == 1.0)
     if which:                                                  # (the exponential of the decisions sees no such arguments)
         assert np.all(np.isposinf(exp64(which, np.array([1e15, 1e30, 3e38, np.inf]))))
+
+
+@pytest.mark.parametrize("which", [0, 1, 2])
+@pytest.mark.parametrize("lo,hi", [(-2.0 ** -6, 2.0 ** -6), (-1.0, 0.0), (-30.0, 0.0), (-700.0, 0.0), (-20.0, 20.0), (0.0, 700.0)])
+def test_relative_error(exp64, which, lo, hi):
+    """All three forms stay within 1.4e-16: half a unit of the last place (1.11e-16) for the final rounding, the rest for the
+    polynomial and the reduction.  What the draw computes with the table is no coarser than what the decisions use."""
+    x = np.random.default_rng(int(which + 10 * (hi - lo))).uniform(lo, hi, 400000)
+    want = np.exp(x.astype(np.longdouble))                     # 64 bits of mantissa: 2^-63 of its own
+    assert np.finfo(np.longdouble).nmant >= 63
+    err = np.abs((exp64(which, x).astype(np.longdouble) - want) / want).max()
+    assert float(err) <= 1.4e-16, float(err)
