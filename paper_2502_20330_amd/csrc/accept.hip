@@ -747,8 +747,9 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
                     if (PLAIN) {                             // (max f, sum f): 1 / Sh of the other form is Mh / Sh here
                         double m = 0.0, sum = 0.0;
                         for (int i = lane; i < W; i += 64) {
-                            m = fmax(m, (double)pair_h(i).x);
-                            sum += (double)pair_h(i).y;
+                            const float2 v = pair_h(i);
+                            m = fmax(m, (double)v.x);
+                            if (v.y > 0.f) sum += (double)v.y;   // a slice with a NaN is left out here as everywhere
                         }
                         Mh = wave_max(m);
                         Sh = wave_sum(sum);

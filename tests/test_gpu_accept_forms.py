@@ -167,3 +167,49 @@ def test_shift_of_any_size(eta):
     assert not n.any() and not ratio.any()                     # p_hat of the drafted token is 0
     want = 1 + np.floor(u[:, 1] * 99)                          # 99 equal weights, and u stays clear of their edges
     np.testing.assert_array_equal(toks[:, 0].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("eta", [0.0, 1.0, 20.0, 25.0])
+@pytest.mark.parametrize("slice_entries", [4096, 8192, 16384])
+def test_a_nan_logit_costs_its_slice_only(slice_entries, eta):
+    """One NaN in a target row, a draft row or both: sums leave out the slice that holds it, so the ratio stays finite and the
+    accept test can still reject (a NaN ratio would accept every draft).  Expected ratios in float64 with that slice taken
+    out; the tail rule is off, so that no maximum enters."""
+    V, g, at = 50257, 3, 20000
+    rng = np.random.default_rng(3)
+    zt = (4 * rng.standard_normal((3, g + 1, V))).astype(np.float32)
+    zd = (zt[:, :g] + rng.standard_normal((3, g, V))).astype(np.float32)
+    tok = np.argsort(-zd, -1)[..., 5].astype(np.int32)
+    u = np.full((3, g + 1), 0.999, dtype=np.float32)
+    zt[[0, 2], 1, at] = np.nan
+    zd[[1, 2], 1, at] = np.nan
+    want = np.empty((3, g))
+    lo = at // slice_entries * slice_entries
+    for b in range(3):
+        for k in range(g):
+            t, d = zt[b, k].astype(np.float64), zd[b, k].astype(np.float64)
+            with np.errstate(invalid="ignore"):
+                et, ed = np.exp(t - np.nanmax(t)), np.exp(d - np.nanmax(d))
+            out = np.zeros(V, dtype=bool)
+            out[lo:lo + slice_entries] = True
+            p = et / (et[~out] if np.isnan(t).any() else et).sum()
+            q = ed / (ed[~out] if np.isnan(d).any() else ed).sum()
+            f = p * np.exp(eta * (q - p))
+            ph = f / (f[~out] if np.isnan(t).any() or np.isnan(d).any() else f).sum()
+            want[b, k] = ph[tok[b, k]] / q[tok[b, k]]
+    assert np.all(np.isfinite(want)) and np.all(np.abs(np.minimum(want, 1) - 0.999) > 1e-3) and (want[:, 1] < 0.9).any()
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    r = gu.rapid()
+    try:
+        r.set_option(binding.OPT_ACCEPT_SLICE, slice_entries)
+        for wait in (100, 0):
+            r.set_option(binding.OPT_ACCEPT_WAIT_US, wait)
+            n, toks, ratio = r.rapid_accept(dev(zt), dev(zd), dev(tok), eta, dev(u), tail_alpha=0.0)
+            torch.cuda.synchronize()
+            np.testing.assert_allclose(ratio.cpu().numpy(), want, rtol=1e-4)
+            for b in range(3):
+                fail = np.flatnonzero(want[b] < 0.999)
+                assert int(n[b]) == (fail[0] if len(fail) else g)
+    finally:
+        r.set_option(binding.OPT_ACCEPT_WAIT_US, 100)
+        r.set_option(binding.OPT_ACCEPT_SLICE, 0)
