@@ -183,7 +183,7 @@ struct Ws {
                       //       [kGiveRows], [kGiveRows + 1] give-ups of accept_rows: count, tag of the call
     u64* slot_t;      // [B][gmax+1][wmax][2]  (raw max, sum exp((z-max)/T)) per slice of a target row
     u64* slot_d;      // [B][gmax][wmax][2]
-    u64* slot_h;      // [B][gmax][wmax][2]    shifted row: (max f, sum f) relative to zmax_t/T, or its logarithmic form
+    u64* slot_h;      // [B][gmax][wmax][2]    shifted row: (max f, sum f) relative to the slice's maximum, or its logarithmic form
     u64* slot_b;      // [B][3][w2][4]         two fp64 values per slice and phase of accept_draw_row
     double* rows;     // [B][gmax+1][4]: zmax_t, zmax_d (raw maxima, exact)
     int32_t* flags;   // [B][gmax]: 1 = draft k passed its accept test, 2 = its id was outside [0, V)
@@ -384,8 +384,8 @@ struct PairNorm { float Mt, l2St, Md, l2Sd; };
 //
 // Plain (eta <= kPlainEta): the exponentials e_t, e_d of the slice statistics stay in the registers, p and q are
 // multiples of them, and f = e_t e^{eta (q - p)} takes ONE further exponential per entry pair (three in all; the
-// logarithmic form takes five of these quarter-rate instructions).  f is relative to the slice's maximum; the slice
-// publishes (max f, sum f) scaled to the row's maximum, so the slices' results simply add up.  In fp32 e_t is lost
+// logarithmic form takes five of these quarter-rate instructions).  f is relative to the slice's maximum, and so is the
+// (max f, sum f) that the slice publishes; the decision brings the slices to the row's maximum in fp64.  In fp32 e_t is lost
 // below 2^-126 of the maximum, while the shift moves an entry by at most eta log2(e) either way: what is lost is
 // below V 2^(2 eta log2(e) - 126) of the sum, 2^-46 for eta = 20 and the largest vocabulary.
 //
@@ -393,11 +393,11 @@ struct PairNorm { float Mt, l2St, Md, l2Sd; };
 // (max d, sum 2^(d - max)) per slice.
 constexpr float kPlainEta = 20.f;
 
-struct Mix { float ap, aq, scale; };         // e_t ap = eta p, e_d aq = eta q (times log2 e); slice -> row scale
+struct Mix { float ap, aq; };                // e_t ap = eta p, e_d aq = eta q (times log2 e)
 // Rt, Rd: what the slice's e_t, e_d are relative to
 __device__ __forceinline__ Mix make_mix(float Rt, float Rd, const PairNorm& r, float c, float eta_l2)
 {
-    return Mix{eta_l2 * fexp2((Rt - r.Mt) * c - r.l2St), eta_l2 * fexp2((Rd - r.Md) * c - r.l2Sd), fexp2((Rt - r.Mt) * c)};
+    return Mix{eta_l2 * fexp2((Rt - r.Mt) * c - r.l2St), eta_l2 * fexp2((Rd - r.Md) * c - r.l2Sd)};
 }
 __device__ __forceinline__ float mixed(float et, float ed, const Mix& m) { return et * fexp2(fmaf(ed, m.aq, -(et * m.ap))); }
 // exponential of a logit relative to R (a slice without finite logits: 0)
@@ -409,7 +409,7 @@ __device__ __forceinline__ floatx4 rel_exp(floatx4 z, float R, float c)
 }
 // (max f, sum f) of a slice; f(v) yields f of the thread's v-th float4
 template <int NW, int NV, bool UNROLL, class GetF>
-__device__ __forceinline__ void mixed_stats(GetF f, float scale, float* sh, int& bank, float& fmx, float& fsum)
+__device__ __forceinline__ void mixed_stats(GetF f, float* sh, int& bank, float& fmx, float& fsum)
 {
     fmx = 0.f;
     fsum = 0.f;
@@ -420,8 +420,6 @@ __device__ __forceinline__ void mixed_stats(GetF f, float scale, float* sh, int&
         fsum += (x[0] + x[1]) + (x[2] + x[3]);
     }
     block_reduce2<NW>(fmx, fsum, sh, bank, OpMaxF(), OpAddF());
-    fmx *= scale;
-    fsum *= scale;
 }
 
 // d of one entry.  Entries past V were loaded as -inf: p = q = 0 and d = -inf.
@@ -667,7 +665,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
                     for (int j = 0; j < 4; ++j) w4[j] = mixed(x[v][j], y[v][j], m);
                     return w4;
                 };
-                mixed_stats<NW, NV, true>(f, m.scale, lds.red, bank, mh, shs);
+                mixed_stats<NW, NV, true>(f, lds.red, bank, mh, shs);
             } else {
                 auto d_first = [&](int v) {                   // d replaces the logits in x
 #pragma unroll
@@ -691,6 +689,11 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
                 if (xtok >= 0 && xtok < V) { zx_t = zt[xtok]; zx_d = zd[xtok]; }
             }
             u64* got_h = lds.slots + 2 * W2w;
+            // plain form: what slice i's f is relative to, on the row's scale; lane i's own before it waits
+            auto scale_of = [&](int i) {
+                return own_t ? exp_c(((double)lo_f(got[2 * i]) - (double)lds.norm.Mt) * a.inv_T_exact) : 1.0;
+            };
+            double scale = 1.0;
             if (!pair) {
                 gather(own_t, false);                         // (a pair's workgroups all gathered above)
             } else {
@@ -702,6 +705,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
                     else wave_combine_f64(pair_d, n_d, a.inv_T_exact, M, S);
                     if (lane == 0) { lds.dec[2 * (wave - 1)] = M; lds.dec[2 * (wave - 1) + 1] = S; }
                 }
+                if (PLAIN && tid < W && tid < 64) scale = scale_of(tid);
                 if (tid < 64) poll_into([&](int i) { return slot_h + i; }, 0, W2w, got_h, &lds.nmiss, a.wait_ticks, tg);
                 __syncthreads();
                 if (__builtin_expect(lds.nmiss != 0, 0)) {
@@ -721,7 +725,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
                                 for (int j = 0; j < 4; ++j) t4[j] = mixed(t4[j], d4[j], m);
                                 return t4;
                             };
-                            mixed_stats<NW, NV, false>(f_mem, m.scale, lds.red, bank, mh, shs);
+                            mixed_stats<NW, NV, false>(f_mem, lds.red, bank, mh, shs);
                         } else {
                             auto d_mem = [&](int v) {
                                 floatx4 t4 = gt(v);
@@ -748,8 +752,9 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
                         double m = 0.0, sum = 0.0;
                         for (int i = lane; i < W; i += 64) {
                             const float2 v = pair_h(i);
-                            m = fmax(m, (double)v.x);
-                            if (v.y > 0.f) sum += (double)v.y;   // a slice with a NaN is left out here as everywhere
+                            if (i >= 64) scale = scale_of(i);
+                            m = fmax(m, (double)v.x * scale);
+                            if (v.y > 0.f) sum += (double)v.y * scale;   // a slice with a NaN is left out here as everywhere
                         }
                         Mh = wave_max(m);
                         Sh = wave_sum(sum);

@@ -213,3 +213,38 @@ def test_a_nan_logit_costs_its_slice_only(slice_entries, eta):
     finally:
         r.set_option(binding.OPT_ACCEPT_WAIT_US, 100)
         r.set_option(binding.OPT_ACCEPT_SLICE, 0)
+
+
+@pytest.mark.parametrize("slice_entries", [4096, 8192, 16384])
+@pytest.mark.parametrize("supplied", [False, True])
+def test_slices_are_combined_in_float64(slice_entries, supplied):
+    """Every slice of a target row holds one value, a different distance below the maximum, and eta = 0: sums inside a slice
+    are whole numbers, so all that rounds is the way from the slices' scale to the row's.  With that in float64 the ratio is
+    the float64 value to the last bit of its own float32 (2^-24), where float32 exponentials of distances up to 12 are off
+    by as much as half a unit of 2^-20 in the argument."""
+    rng = np.random.default_rng(6)
+    B, W = 32, 4
+    V = W * slice_entries
+    a = rng.uniform(0.5, 12.0, (B, 2, W))
+    a[:, :, 0] = 0.0
+    zt = np.repeat(-a.astype(np.float32), slice_entries, -1)
+    zt[:, :, 1:slice_entries] = -np.inf                       # the maximum itself: one entry, so that the others weigh
+    zd = np.zeros((B, 1, V), dtype=np.float32)
+    tok = rng.integers(slice_entries, V, (B, 1)).astype(np.int32)
+    u = rng.random((B, 2), dtype=np.float32)
+    e = np.exp(zt[:, 0].astype(np.float64))
+    want = np.take_along_axis(e, tok, -1) / e.sum(-1, keepdims=True) * V
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    r = gu.rapid()
+    try:
+        r.set_option(binding.OPT_ACCEPT_SLICE, slice_entries)
+        stats = _chunk_stats(zt, slice_entries, 1.0) if supplied else None
+        _, _, ratio = r.rapid_accept(dev(zt), dev(zd), dev(tok), 0.0, dev(u), tail_alpha=0.0, target_stats=stats)
+        torch.cuda.synchronize()
+    finally:
+        r.set_option(binding.OPT_ACCEPT_SLICE, 0)
+    err = np.abs(ratio.cpu().numpy().astype(np.float64) / want - 1)
+    bound = 2.0 ** -24 + 1e-12
+    if supplied:                                              # the entries then carry the distance themselves, in float32
+        bound += 2.0 ** -20
+    assert err.max() <= bound, err.max()
