@@ -275,7 +275,7 @@ int rapid_lm_head(rapid_ctx* ctx, int n_rows, int hidden, int vocab,
  *   target_stats fp32 [B*(gamma_max+1), target_chunks, 2] or NULL; row b*(gamma_max+1)+k
  *   draft_stats  fp32 [B*gamma_max,     draft_chunks,  2] or NULL
  * each pair = (max of the raw logits of the chunk, sum exp((z - max)/temperature)) for ANY
- * partition of the vocabulary into chunks (an empty chunk: sum 0); the temperature must be the
+ * partition of the vocabulary into chunks (an empty chunk: sum 0, any maximum); the temperature must be the
  * one passed here.  A NULL side is computed from the logits as in rapid_accept.  Everything
  * else, including the workspace size, is as for rapid_accept.
  */

@@ -458,6 +458,8 @@ __device__ __forceinline__ void shifted_stats(GetFirst d_first, GetAgain d_again
     block_reduce2<NW>(shs, unused, sh, bank, OpAddF(), OpAddF());
 }
 
+// The maximum of a (max, sum) pair; that of an empty chunk (sum 0) does not count, whatever it is.
+__device__ __forceinline__ float max_of(float2 v) { return v.y == 0.f ? -INFINITY : v.x; }
 // Wave 0: combine n (max, sum) pairs, maxima raw logits, sums of exp((z - max)/T):
 // M = max, S = sum_i s_i 2^((m_i - M) c); fp32, fixed order.  Result valid in every lane of wave 0.
 template <class Pair>
@@ -481,7 +483,7 @@ __device__ __forceinline__ void wave_combine_f64(Pair pair, int n, double scale,
 {
     const int lane = threadIdx.x & 63;
     double m = -INFINITY;
-    for (int i = lane; i < n; i += 64) m = fmax(m, (double)pair(i).x);
+    for (int i = lane; i < n; i += 64) m = fmax(m, (double)max_of(pair(i)));
     M = wave_max(m);
     double s = 0.0;
     for (int i = lane; i < n; i += 64) {
@@ -618,11 +620,11 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
                     const int i = tid + j * NT;
                     vt[j] = i < n_t ? pair_t(i) : make_float2(-INFINITY, 0.f);
                     vd[j] = i < n_d ? pair_d(i) : make_float2(-INFINITY, 0.f);
-                    mt = fmaxf(mt, vt[j].x);
-                    md = fmaxf(md, vd[j].x);
+                    mt = fmaxf(mt, max_of(vt[j]));
+                    md = fmaxf(md, max_of(vd[j]));
                 }
-                for (int i = tid + 2 * NT; i < n_t; i += NT) mt = fmaxf(mt, pair_t(i).x);
-                for (int i = tid + 2 * NT; i < n_d; i += NT) md = fmaxf(md, pair_d(i).x);
+                for (int i = tid + 2 * NT; i < n_t; i += NT) mt = fmaxf(mt, max_of(pair_t(i)));
+                for (int i = tid + 2 * NT; i < n_d; i += NT) md = fmaxf(md, max_of(pair_d(i)));
                 block_reduce2<NW>(mt, md, lds.red, bank, OpMaxF(), OpMaxF());
                 float st = 0.f, sd = 0.f;
 #pragma unroll

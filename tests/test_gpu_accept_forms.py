@@ -248,3 +248,31 @@ def test_slices_are_combined_in_float64(slice_entries, supplied):
     if supplied:                                              # the entries then carry the distance themselves, in float32
         bound += 2.0 ** -20
     assert err.max() <= bound, err.max()
+
+
+@pytest.mark.parametrize("eta", [0.5, 20.0, 30.0])
+@pytest.mark.parametrize("excess", [0.0, 60.0, 100.0, 124.0, 400.0])
+def test_the_maximum_of_an_empty_chunk_does_not_count(eta, excess):
+    """Supplied statistics may hold empty chunks (sum 0), whatever stands in their maximum: here `excess` powers of two above
+    the row's own, far enough for float32 exponentials relative to it to run out of range.  Same results as the oracle's."""
+    cfg = wl.scaled(wl.CONFIGS["llama8b_32k"], batch=6, vocab=20000, gamma_choices=(2, 3), eta=eta, draft_noise_std=1.0, name="empty")
+    acc = wl.gen_accept_inputs(cfg, salt=8)
+    acc.target_logits -= 40                                   # rows whose maxima are below 0, where a zeroed pair lies above them
+    acc.draft_logits -= 40
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+    def stats(z):
+        st = _chunk_stats(z, 700, 1.0)
+        empty = torch.zeros_like(st[:, :2])
+        empty[..., 0] = st[..., 0].amax(1, keepdim=True) + excess * np.log(2)
+        return torch.cat([empty[:, :1], st, empty[:, 1:]], 1).contiguous()
+
+    ref = gu.run_accept_case(acc, eta=eta)[1]
+    for sides in ((True, True), (True, False), (False, True)):
+        got = gu.rapid().rapid_accept(dev(acc.target_logits), dev(acc.draft_logits), dev(acc.draft_tokens), eta, dev(acc.uniforms),
+                                      gammas=dev(acc.gammas), target_stats=stats(acc.target_logits) if sides[0] else None,
+                                      draft_stats=stats(acc.draft_logits) if sides[1] else None)
+        torch.cuda.synchronize()
+        res = gu.compare_accept(tuple(t.cpu().numpy() for t in got), ref, acc.gammas, cfg.gamma_max)
+        assert res["n_mismatch"] == 0 and res["token_mismatch"] == 0 and res["exempt_sequences"] == 0, res
+        assert res["max_ratio_rel_err"] <= 1e-4, res
