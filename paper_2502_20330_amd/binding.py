@@ -279,7 +279,7 @@ class Rapid:
         prestats = target_stats is not None or draft_stats is not None
         args = (self._ctx, B, g, V, target_logits.data_ptr(), draft_logits.data_ptr(), draft_tokens.data_ptr(), _dptr(gammas),
                 float(eta), float(temperature), float(tail_alpha), uniforms.data_ptr())
-        results = (n_acc.data_ptr(), toks.data_ptr(), _dptr(ratio))
+        results = (_dptr(n_acc), _dptr(toks), _dptr(ratio))
         if prestats:
             for st, rows in ((target_stats, B * (g + 1)), (draft_stats, B * g)):
                 assert st is None or (st.dtype == torch.float32 and st.is_contiguous() and st.dim() == 3

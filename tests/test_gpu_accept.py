@@ -276,6 +276,18 @@ def test_bad_arguments_return_error_codes():
         assert e.value.status == -1
 
 
+@pytest.mark.parametrize("missing", [0, 1])
+def test_a_missing_output_is_refused_by_the_library(missing):
+    from paper_2502_20330_amd import binding
+    z, zd = torch.zeros(1, 2, 8, device="cuda"), torch.zeros(1, 1, 8, device="cuda")
+    t = torch.zeros(1, 1, dtype=torch.int32, device="cuda")
+    outs = [torch.empty(1, dtype=torch.int32, device="cuda"), torch.empty(1, 2, dtype=torch.int32, device="cuda"), None]
+    outs[missing] = None
+    with pytest.raises(binding.RapidError) as e:
+        gu.rapid().rapid_accept(z, zd, t, 1.0, torch.zeros(1, 2, device="cuda"), outs=tuple(outs))
+    assert e.value.status == binding.RAPID_EINVAL
+
+
 # ---------------------------------------------------------------- full benchmark sizes
 def test_llama_vocab_full_size():
     """Configs 2/3/5: one sequence, gamma = 8, V = 128256, eta = 1 (and 5's eta sweep)."""
