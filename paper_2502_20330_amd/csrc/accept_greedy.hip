@@ -13,13 +13,15 @@
 //   greedy_decide        one workgroup per sequence: rows combined, gaps compared in fp64 (the
 //                        difference of two fp32 numbers is exact there), prefix length, token; bound by
 //                        the latency of its chain of loads
+#include <algorithm>
+
 #include "logit_rows.h"
 #include "rapid_internal.h"
 
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kDecide = 1024;                          // threads of greedy_decide: a wave per row, 16 rows at a time
+constexpr int kDecideWaves = 16;                       // waves of greedy_decide at most
 constexpr int kSlice = kThreads * 16;
 
 struct GreedyWs {
@@ -77,7 +79,8 @@ __global__ void __launch_bounds__(kThreads) greedy_slice_argmax(AcceptLaunch a, 
     float m = -INFINITY;
     int idx = 0x7fffffff;
 #pragma unroll
-    for (int v = 0; v < NV; ++v)
+    for (int v = 0; v < NV; ++v) {
+        if (!full && i0 + v * kThreads * 4 >= a.V) break;     // short rows: nothing left for this thread (whole waves leave)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int i = i0 + v * kThreads * 4 + j;
@@ -85,6 +88,7 @@ __global__ void __launch_bounds__(kThreads) greedy_slice_argmax(AcceptLaunch a, 
             const bool first = x[v][j] == m && idx == 0x7fffffff && i < a.V;
             if (x[v][j] > m || first) { m = x[v][j]; idx = i; }
         }
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) take_better(m, idx, __shfl_xor(m, o), __shfl_xor(idx, o));
     if ((threadIdx.x & 63) == 0) { shm[threadIdx.x >> 6] = m; shi[threadIdx.x >> 6] = idx; }
@@ -113,7 +117,7 @@ __device__ __forceinline__ void row_argmax(const GreedyWs& ws, int64_t row, floa
 // wave of position k leaves the arg-max of target row k in LDS, where the decision finds that of row n (the first kKept rows:
 // gmax has no small bound; beyond them row n is combined once more).
 constexpr int kKept = 1024;
-__global__ void __launch_bounds__(kDecide) greedy_decide(AcceptLaunch a, GreedyWs ws)
+__global__ void __launch_bounds__(kDecideWaves * 64) greedy_decide(AcceptLaunch a, GreedyWs ws)
 {
     __shared__ int target_arg[kKept];
     __shared__ int first_fail;
@@ -122,7 +126,7 @@ __global__ void __launch_bounds__(kDecide) greedy_decide(AcceptLaunch a, GreedyW
     if (tid == 0) first_fail = 0x7fffffff;
     __syncthreads();
     const int g = seq_gamma(a, b);
-    for (int k = wave; k <= a.gmax; k += kDecide / 64) {
+    for (int k = wave; k <= a.gmax; k += blockDim.x / 64) {
         if (k > g) break;
         const bool pair = k < g;
         const int64_t at = (int64_t)b * a.gmax + k;
@@ -160,7 +164,7 @@ __global__ void __launch_bounds__(kDecide) greedy_decide(AcceptLaunch a, GreedyW
         if (tid == 0) target_arg[0] = it;
         __syncthreads();
     }
-    for (int k = tid; k <= a.gmax; k += kDecide) {
+    for (int k = tid; k <= a.gmax; k += blockDim.x) {
         int tok = -1;
         if (k < n) tok = a.tokens[(int64_t)b * a.gmax + k];
         else if (k == n) {                                    // target row n: rejection or bonus position
@@ -183,6 +187,10 @@ hipError_t launch_accept_greedy(const AcceptLaunch& a, hipStream_t stream)
 {
     GreedyWs ws = gcarve(a.workspace, a.B, a.gmax, a.V);
     hipLaunchKernelGGL(greedy_slice_argmax, dim3(ws.W, 2 * a.gmax + 1, a.B), dim3(kThreads), 0, stream, a, ws);
-    hipLaunchKernelGGL(greedy_decide, dim3(a.B), dim3(kDecide), 0, stream, a, ws);
+    // A wave per position while every sequence has a compute unit to itself (the decision is then one chain of loads), four
+    // beyond, where the chip is full: 4096 sequences of one draft (vocabulary 100) took 53 us a call with 16 waves, 28 with four,
+    // and 21 since the row pass also leaves out what lies past a short row.
+    const int waves = std::min(a.gmax + 1, a.B <= a.n_cu ? kDecideWaves : 4);
+    hipLaunchKernelGGL(greedy_decide, dim3(a.B), dim3(waves * 64), 0, stream, a, ws);
     return hipGetLastError();
 }

@@ -55,5 +55,6 @@ __device__ __forceinline__ void shift_runs(floatx4 (&r)[N], int i, int step, int
 {
     if (full || V < 4) return;
 #pragma unroll
-    for (int v = 0; v < N; ++v) r[v] = shift_tail(r[v], i + v * step, V);
+    for (int v = 0; v < N; ++v)
+        if (i + v * step < V) r[v] = shift_tail(r[v], i + v * step, V);      // (past the end: load_runs left -inf)
 }

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import gpu_util as gu
+import oracle
 from paper_2502_20330_amd import binding
 from paper_2502_20330_amd import workloads as wl
 
@@ -276,3 +277,22 @@ def test_the_maximum_of_an_empty_chunk_does_not_count(eta, excess):
         res = gu.compare_accept(tuple(t.cpu().numpy() for t in got), ref, acc.gammas, cfg.gamma_max)
         assert res["n_mismatch"] == 0 and res["token_mismatch"] == 0 and res["exempt_sequences"] == 0, res
         assert res["max_ratio_rel_err"] <= 1e-4, res
+
+
+@pytest.mark.parametrize("B,g,V", [(256, 0, 300), (256, 3, 300), (257, 0, 300), (257, 3, 300), (300, 11, 900), (2100, 2, 65), (40, 17, 900)])
+def test_greedy_decision_of_any_number_of_waves(B, g, V):
+    """The decision's waves follow the drafted positions (at most 16) and the batch (four from 257 sequences on)."""
+    rng = np.random.default_rng(B + g)
+    zt = rng.standard_normal((B, g + 1, V)).astype(np.float32)
+    zd = (zt[:, :g] + 0.2 * rng.standard_normal((B, g, V))).astype(np.float32)
+    tok = np.argmax(zd, -1).astype(np.int32)
+    u = rng.random((B, g + 1), dtype=np.float32)
+    gam = rng.integers(0, g + 1, B).astype(np.int32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    n, toks, ratio = gu.rapid().rapid_accept(dev(zt), dev(zd), dev(tok), 1.0, dev(u), gammas=dev(gam), temperature=0.0)
+    torch.cuda.synchronize()
+    ref = oracle.accept_greedy(zt, zd, tok, u, gammas=gam)
+    np.testing.assert_array_equal(n.cpu().numpy(), ref.n_accepted)
+    np.testing.assert_array_equal(toks.cpu().numpy(), ref.out_tokens)
+    live = np.arange(g)[None, :] < gam[:, None]
+    np.testing.assert_array_equal(ratio.cpu().numpy().astype(np.float64)[live], ref.ratio[live])
