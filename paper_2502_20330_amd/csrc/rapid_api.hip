@@ -145,16 +145,22 @@ void plan_layout(const rapid_ctx* ctx, AttnLaunch& a)
 }
 
 // Groups of the balanced plan (verify_attn.hip), 0 = the fixed grid of splits.  Taken by ragged batches whose split the
-// caller leaves to the library: the partials (one slot per head, group and sequence boundary) have to fit the workspace that
-// the split size answers for, a head needs a handful of groups for the shares to be worth cutting, and at most 256 sequences:
-// every workgroup, of the merge too, scans all lengths (64 at a time; 24 to 256 sequences of 1K..16K tokens gain 8 to 17 %,
-// 256 of up to 1500 tokens 303 -> 269 us, but thousands would spend more on the scans than the shares save).
+// caller leaves to the library, where the partials (one slot per head, group and sequence boundary) fit the workspace that
+// the split size answers for and the shares are long enough to be worth cutting:
+//  * at least 16 groups a head (8 of 32 heads: 0.98 of the fixed grid's time on average, 0.82 to 1.20);
+//  * two quanta a group and one a sequence, twice that for heads of 64 (half the bytes): every piece costs a pipeline start
+//    and an epilogue that one workgroup goes through in turn, where the short splits of the fixed grid run side by side.  On 1050 batches of 2 to 256 sequences (200 to 120K tokens, 1 to 8 heads) the ones above the line take 0.81
+//    of the fixed grid's time (15 of 585 more than 1.02, 1.12 at worst), the ones below 0.97 with 1.5 at worst;
+//  * at most 256 sequences: every workgroup, of the merge too, scans all lengths, 64 at a time (on average 0.78 of the fixed
+//    grid's time at 300 sequences, 0.93 at 512, 1.15 at 700, 1.35 at 1024, up to 1.1 at the first and 1.8 at the last).
 int plan_groups(const rapid_ctx* ctx, const rapid_attn_shape* s, int nsplit)
 {
     if (s->chunk_tokens > 0 || !ragged_batch(s) || s->batch > 256) return 0;
     const int n_cu = ctx ? ctx->n_cu : 256;
     const int groups = n_cu / s->n_kv_heads & ~1;
-    if (groups < 8 || groups + s->batch - 1 > (int64_t)s->batch * nsplit) return 0;
+    if (groups < 16 || groups + s->batch - 1 > (int64_t)s->batch * nsplit) return 0;
+    const int64_t quanta = (s->ctx_sum_hint + 64 * (int64_t)s->batch) / 128;           // half a quantum a sequence is a rest
+    if (quanta < (s->head_dim == 64 ? 2 : 1) * (2 * (int64_t)groups + s->batch)) return 0;
     if ((int64_t)s->batch * (s->max_ctx / 128 + 8) >= (int64_t)1 << 30) return 0;      // positions are 32-bit
     return groups;
 }
