@@ -66,8 +66,9 @@ int rapid_last_hip_error(const rapid_ctx* ctx);
  *       computes the missing piece itself (same arithmetic, same result).  Default 100; 0 = never
  *       wait (every exchange takes the recomputation path; for tests).  0 <= value <= 10^7.
  *   RAPID_OPT_ACCEPT_SLICE    Vocabulary entries per workgroup of rapid_accept's row pass:
- *       0 = chosen from the batch size (default), or 4096, 8192, 16384.  Results of the accept
- *       tests may differ in the last bits of accept_ratio between slice sizes (fp32 sums).
+ *       0 = chosen from the batch size and eta (default), or 4096, 8192, 10240 (8192 where eta > 20),
+ *       16384.  Results of the accept tests may differ in the last bits of accept_ratio between slice
+ *       sizes (fp32 sums).
  *   RAPID_OPT_PROBE_SKEW      rapid_hbm_read_probe only: of every two consecutive workgroups the
  *       first reads (32 + value)/32 and the second (32 - value)/32 of the mean share, as
  *       rapid_verify_attn splits the tokens of a pair of KV splits unevenly when its grid is one

@@ -1176,7 +1176,8 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)
     const bool plain = a.eta <= kPlainEta;
     for (int cand : {plain ? 10240 : 16384, 8192})            // (the logarithmic form needs more registers)
         if (2 * rows * slices(cand) >= (cand == 10240 ? 3 : 4) * (int64_t)a.n_cu) { slice = cand; break; }
-    if (a.force_slice) slice = a.force_slice;
+    // (the option also reaches 16384 in the plain form, for measurements: the rule above never takes it)
+    if (a.force_slice) slice = a.force_slice == 10240 && !plain ? 8192 : a.force_slice;
     auto rows_kernel = slice == 16384 ? (plain ? accept_rows<512, 8, 4, true> : accept_rows<512, 8, 4, false>)
                      : slice == 10240 ? accept_rows<256, 10, 4, true>
                      : slice == 8192 ? (plain ? accept_rows<512, 4, 4, true> : accept_rows<512, 4, 4, false>)

@@ -233,7 +233,7 @@ int rapid_set_option(rapid_ctx* ctx, int option, int64_t value)
             ctx->accept_wait_ticks = value * 100;         // the wall clock of the device ticks at 100 MHz
             return RAPID_OK;
         case RAPID_OPT_ACCEPT_SLICE:
-            if (value != 0 && value != 4096 && value != 8192 && value != 16384) return RAPID_EINVAL;
+            if (value != 0 && value != 4096 && value != 8192 && value != 10240 && value != 16384) return RAPID_EINVAL;
             ctx->accept_slice = (int)value;
             return RAPID_OK;
         case RAPID_OPT_PROBE_SKEW:

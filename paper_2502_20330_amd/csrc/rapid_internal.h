@@ -65,7 +65,7 @@ struct AcceptLaunch {
     int32_t nch_t, nch_d;
     int64_t wait_ticks;   // bound of an exchange wait in wall-clock ticks (100 MHz); 0 = never wait
     int32_t n_cu;         // compute units of the device (sizes the slices)
-    int32_t force_slice;  // 4096 / 8192 / 16384 entries per slice; 0 = automatic
+    int32_t force_slice;  // 4096 / 8192 / 10240 / 16384 entries per slice; 0 = automatic
 };
 hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream);
 size_t accept_workspace_bytes(int B, int gmax, int V);

@@ -126,7 +126,7 @@ def test_repeat_calls_are_identical():
     assert all(torch.equal(x, y) for x, y in zip(a, b))
 
 
-@pytest.mark.parametrize("slice_entries", [4096, 8192, 16384])
+@pytest.mark.parametrize("slice_entries", [4096, 8192, 10240, 16384])
 def test_every_slice_size_and_the_give_up_path(slice_entries):
     """The row pass at each of its slice sizes against the oracle, and again with the bound of the
     inter-workgroup waits forced to zero from the host: every exchange then takes the path in which a

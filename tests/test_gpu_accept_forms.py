@@ -41,7 +41,7 @@ def _chunk_stats(z, chunk, T):
     return torch.from_numpy(np.stack([m, e.sum(-1)], -1).astype(np.float32)).cuda()
 
 
-@pytest.mark.parametrize("slice_entries", [4096, 16384, 0])          # 0: the library's choice at 24 sequences, 10240 or 16384
+@pytest.mark.parametrize("slice_entries", [4096, 8192, 10240, 16384, 0])    # 0: the library's choice at 24 sequences, 10240 or 16384
 @pytest.mark.parametrize("eta,T,mask", [(20.0, 0.1, "none"), (20.5, 0.1, "none"), (20.0, 1.0, "inf"), (20.5, 1.0, "inf"),
                                         (1.0, 0.1, "lowest"), (50.0, 0.7, "lowest"), (0.0, 0.05, "inf")])
 def test_both_forms_match_the_oracle_and_each_other(slice_entries, eta, T, mask):
@@ -55,6 +55,7 @@ def test_both_forms_match_the_oracle_and_each_other(slice_entries, eta, T, mask)
             r.set_option(binding.OPT_ACCEPT_WAIT_US, wait)
             gpu, ref = gu.run_accept_case(acc, eta=eta, temperature=T)
             runs.append(gpu)
+            assert wait > 0 or r.accept_status()[1] > 0           # the exchanges were recomputed
         r.set_option(binding.OPT_ACCEPT_WAIT_US, 100)
         dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
         for side in ((True, True), (True, False), (False, True)):
@@ -171,7 +172,7 @@ def test_shift_of_any_size(eta):
 
 
 @pytest.mark.parametrize("eta", [0.0, 1.0, 20.0, 25.0])
-@pytest.mark.parametrize("slice_entries", [4096, 8192, 16384])
+@pytest.mark.parametrize("slice_entries", [4096, 8192, 10240, 16384])
 def test_a_nan_logit_costs_its_slice_only(slice_entries, eta):
     """One NaN in a target row, a draft row or both: sums leave out the slice that holds it, so the ratio stays finite and the
     accept test can still reject (a NaN ratio would accept every draft).  Expected ratios in float64 with that slice taken
@@ -185,14 +186,15 @@ def test_a_nan_logit_costs_its_slice_only(slice_entries, eta):
     zt[[0, 2], 1, at] = np.nan
     zd[[1, 2], 1, at] = np.nan
     want = np.empty((3, g))
-    lo = at // slice_entries * slice_entries
+    size = 8192 if slice_entries == 10240 and eta > 20 else slice_entries
+    lo = at // size * size
     for b in range(3):
         for k in range(g):
             t, d = zt[b, k].astype(np.float64), zd[b, k].astype(np.float64)
             with np.errstate(invalid="ignore"):
                 et, ed = np.exp(t - np.nanmax(t)), np.exp(d - np.nanmax(d))
             out = np.zeros(V, dtype=bool)
-            out[lo:lo + slice_entries] = True
+            out[lo:lo + size] = True
             p = et / (et[~out] if np.isnan(t).any() else et).sum()
             q = ed / (ed[~out] if np.isnan(d).any() else ed).sum()
             f = p * np.exp(eta * (q - p))
@@ -216,7 +218,7 @@ def test_a_nan_logit_costs_its_slice_only(slice_entries, eta):
         r.set_option(binding.OPT_ACCEPT_SLICE, 0)
 
 
-@pytest.mark.parametrize("slice_entries", [4096, 8192, 16384])
+@pytest.mark.parametrize("slice_entries", [4096, 8192, 10240, 16384])
 @pytest.mark.parametrize("supplied", [False, True])
 def test_slices_are_combined_in_float64(slice_entries, supplied):
     """Every slice of a target row holds one value, a different distance below the maximum, and eta = 0: sums inside a slice
