@@ -53,13 +53,17 @@ def parse_args():
     return ap.parse_args()
 
 
-TRAFFIC_SOURCES = {"verify_attn": "verify_attn.hip", "rapid_accept": "accept.hip", "rapid_lm_head": "lm_head.hip"}
+TRAFFIC_SOURCES = {"verify_attn": ["verify_attn.hip"], "rapid_accept": ["accept.hip", "exp64.h", "logit_rows.h"],
+                   "rapid_lm_head": ["lm_head.hip"]}
 
 
 def source_sha256(kernel_key: str) -> str:
-    """Hash of the kernel source a traffic figure belongs to."""
-    path = os.path.join(ROOT, "paper_2502_20330_amd", "csrc", TRAFFIC_SOURCES[kernel_key])
-    return hashlib.sha256(open(path, "rb").read()).hexdigest()[:16]
+    """Hash of the kernel source a traffic figure belongs to, the headers that hold parts of it included."""
+    h = hashlib.sha256()
+    for name in TRAFFIC_SOURCES[kernel_key]:
+        with open(os.path.join(ROOT, "paper_2502_20330_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def profile_traffic(kernel_key: str):

@@ -113,14 +113,16 @@ typedef struct rapid_attn_shape {
                               /* clamped to [0, n_pages) before use; with 0 only negative entries are  */
                               /* clamped and larger ones are the caller's responsibility                */
     int64_t ctx_sum_hint;     /* sum of ctx_lens[b] if the host knows it (a scheduler usually  */
-                              /* does), else 0: only used to size the KV splits of ragged      */
-                              /* batches; results never depend on it                           */
+                              /* does), else 0: only used to divide ragged batches among the   */
+                              /* workgroups.  Any value is safe; the division decides in which */
+                              /* order sums are formed, so results agree to rounding (also     */
+                              /* with other lengths beside a sequence's own)                   */
 } rapid_attn_shape;
 
 /* Tokens per KV split the library plans with for `shape` (multiple of 128), and
  * through it the number of splits per (sequence, kv head): ceil(max_ctx / chunk); both size the workspace.
- * (Ragged batches with ctx_sum_hint set and chunk_tokens 0 are divided on the device instead, into equal shares
- * of their tokens, within the same workspace.) */
+ * (Ragged batches with ctx_sum_hint set and chunk_tokens 0 that are large enough are divided on the device instead,
+ * into equal shares of their tokens, within the same workspace.) */
 int rapid_verify_attn_chunk(const rapid_ctx* ctx, const rapid_attn_shape* shape);
 
 /* Bytes of device workspace rapid_verify_attn needs for `shape` (0 on a bad shape). */
@@ -225,8 +227,9 @@ size_t rapid_accept_workspace_bytes(const rapid_ctx* ctx, int batch, int gamma_m
  *                 included), and a call recognises what its own workgroups exchanged through the
  *                 workspace by tags derived from that counter.  Two calls that share a workspace
  *                 must not overlap in time.
- * vocab <= 2^22.  Logit rows whose address is not 16-byte aligned (vocab not a multiple of 4)
- * are read with scalar loads: same results, lower bandwidth.
+ * vocab <= 2^22.  Logit rows may start at any multiple of 4 bytes (vocab not a multiple of 4).
+ * Logits that are NaN: the slice of the row that holds one is left out of the row's sums (which
+ * entries share a slice is the library's choice).
  */
 #define RAPID_ACCEPT_STATUS_BAD_IDS 0
 #define RAPID_ACCEPT_STATUS_GIVEUPS 1

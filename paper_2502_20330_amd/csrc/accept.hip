@@ -41,8 +41,9 @@
 // termination, and results do not depend on timing.
 //
 // Numerics: per-slice sums in fp32, combined in fp32 for the elementwise pass of accept_rows
-// and in fp64 for every decision; the accept ratio therefore carries ~1e-7 relative error
-// (decisions within 1e-5 of the uniform are near-ties by the definition of the benchmark).
+// and in fp64 for every decision; the accept ratio therefore carries a relative error of 2e-7 to
+// 4e-7 (rms, temperatures of 1 to 0.1; decisions within 1e-5 of the uniform are near-ties by the
+// definition of the benchmark).
 // The draw is fp64 throughout and differs from a sequential fp64 evaluation by summation
 // order only.  Statistics are kept relative to the raw row maximum so that dividing by T
 // costs no absolute precision.
@@ -610,7 +611,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
             gather(own_t, own_d);
             STAMP_AT(id, 3);
             if (ext_t || ext_d) {
-                // The caller's statistics are hundreds of pairs per row in memory: all eight waves fetch them at
+                // The caller's statistics are hundreds of pairs per row in memory: all waves fetch them at
                 // once (one round trip) and two block reductions combine them (a side without supplied statistics
                 // brings its W gathered pairs the same way); every workgroup of the row pair gets the same bits.
                 float2 vt[2], vd[2];                          // pairs tid and tid + NT; beyond: the loops below

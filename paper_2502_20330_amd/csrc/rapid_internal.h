@@ -24,8 +24,9 @@ struct AttnLaunch {
     const int32_t* page_table;
     uint16_t* out;
     float* lse_out;
-    float* part_o;      // [B, Hkv, nsplit, RB*16, D] fp32, relative to part_m
-    float* part_ml;     // [B, Hkv, nsplit, RB*16, 2] (running max in log2 units, sum)
+    float* part_o;      // [B, Hkv, nsplit, RB*16, D] fp32, relative to the maximum in part_ml; balanced shares:
+                        // [Hkv, nslots, RB*16, D], slot g + b for group g's piece of sequence b
+    float* part_ml;     // the same slots, [.., RB*16, 2] (running max in log2 units, sum)
     int32_t B, Qmax, Hq, Hkv, G, D, gamma;
     int32_t max_ctx;    // host bound of ctx_lens
     int32_t chunk, nsplit, RB;   // RB: 16-row blocks of the partials (wide: two teams of (RB + 1) / 2 and RB / 2 blocks)

@@ -9,7 +9,8 @@
 //  * The R = Q*G query rows that share one KV head (G query heads x Q positions)
 //    are packed into the N side of bf16 MFMA tiles, so every K/V byte is read
 //    from HBM once and used by all R rows.
-//  * One workgroup = one (sequence, kv head, KV split).  Its four waves run
+//  * One workgroup = one (sequence, kv head, KV split), or, for ragged batches, one share of
+//    a kv head's tokens over all sequences, piece by piece.  Its four waves run
 //    independent pipelines, each over its own contiguous quarter of the split in
 //    32-token tiles.  K and V tiles travel
 //    HBM -> LDS directly (global_load_lds_dwordx4, 1 KiB per instruction, no
@@ -310,9 +311,10 @@ __device__ __forceinline__ int split_end(const AttnLaunch& a, int s, int h)
 // ---- balanced shares of a ragged batch.  The fixed grid of splits above gives every sequence the same split
 // size, so with unequal lengths some workgroups stream a full split and others a rest, and the last round
 // leaves compute units idle: eight sequences of 16K..131K tokens on 16-token pages took 462 us (5.5 TB/s) that way and
-// take 396 us (6.45 TB/s) with the shares below; sixteen of 1K..8K 67 -> 63 us, four of 10K..60K with 77 rows 81 -> 74 us.  Here the grid is one workgroup per compute unit ("group" g of kv head h) and the tokens of the
-// whole batch are laid end to end, in quanta of 128 tokens (whole tiles for all waves), and cut into equal
-// shares: group g works on the piece of every sequence that falls into its share.  Every piece beyond a
+// take 396 us (6.45 TB/s) with the shares below; sixteen of 1K..8K 67 -> 63 us, four of 10K..60K with 77 rows 81 -> 74 us.
+// Here the grid is one workgroup per compute unit ("group" g of kv head h), and the tokens of the whole batch are laid end
+// to end in quanta of 128 (whole tiles for all waves) and cut into equal shares: group g works on the piece of every
+// sequence that falls into its share.  The host takes this route for shares that are long enough.  Every piece beyond a
 // group's first costs a pipeline start and an epilogue, so each sequence counts kPieceQuanta more than its tokens
 // (1, 2, 4, 6 instead of 3: 0 to 2 % slower on small batches, the same on large ones).
 // The lengths are device data: every workgroup derives the shares from ctx_lens (B values, one wave scan).
@@ -995,7 +997,7 @@ __global__ void __launch_bounds__(D) verify_attn_merge(AttnLaunch a)
         }
     }
     for (int s0 = 0; s0 < ns; s0 += SB) {
-        // The loads of a block do not wait for the sequence length: every split slot of the
+        // Fixed grid: the loads of a block do not wait for the sequence length: every split slot of the
         // workspace is addressable, and the slots of splits that hold no token (stale or
         // never written) are discarded after the fact.  The length is one more dependent
         // memory round trip that this way overlaps with the loads.
