@@ -23,10 +23,18 @@
 //  * W travels HBM -> LDS directly (global_load_lds_dwordx4, 1 KiB per instruction) in tiles of
 //    16 rows x SK (8 KiB / 4 KiB) through a 32 KiB ring per wave, three / seven tiles ahead of the
 //    math; the wave counts its own outstanding loads, so the main loop has no workgroup barrier.
-//  * The matching slab of h (NR tiles of 16 rows; rows past the last real one repeat it) comes
+//  * A 256-wide slab is two runs of 256 bytes of a row, 2 KiB apart inside each 4 KiB (Slab below).  All waves of
+//    the chip run through the hidden dimension nearly in step, so with contiguous slabs they ask for the same 512 of every 4 KiB
+//    at a time, and where the row pitch is a multiple of 4 KiB that is half of the memory channels (bit 11 of the
+//    address is one of the bits that select them; the upper bits make up for it in some placements of W and not in
+//    others).  One row of 2048 x 128256: 105 us contiguous, 77 us in halves (128-byte quarters: 85); 9 rows of
+//    6144 x 64000 138 -> 115; of 4096 x 128256 152, 167 or 188 us by placement -> 154 in all of them; of
+//    8192 x 80000 194 -> 197, the cost where the upper bits did well.  The order of the sum is the same for every logit.
+//  * Up to three row blocks of h: the matching slab of h (NR tiles of 16 rows; rows past the last real one repeat it) comes
 //    through the same ring at the head of every slab (from cache: every wave of every workgroup
 //    reads the same h) and is then held in registers as the B operand of
-//    v_mfma_f32_16x16x32_bf16 for the W tiles that follow.
+//    v_mfma_f32_16x16x32_bf16 for the W tiles that follow.  From four row blocks on that would be a third of all
+//    tiles, all out of one or two channels of the L2: there the workgroup shares a slab of h (lm_head_shared).
 //  * A 16-byte-chunk XOR swizzle applied by the load addressing makes the operand reads
 //    (ds_read_b128, 16 rows of 512 / 256 B) bank-conflict free without padding.
 //  * Epilogue: fp32 logits from the accumulators (16-byte stores where the row stride allows);
@@ -56,6 +64,17 @@ struct Tile {
 };
 constexpr float kLog2e = 1.4426950408889634f;
 
+// Where slab s of a row lies.  256-wide slabs: eight to a group of 4 KiB of the row (the last group may be shorter), each a
+// run of 256 bytes of the group's first half and the one at the same place of its second half, `half` bytes on.  128-wide slabs (hidden an
+// odd multiple of 128: the row pitch itself spreads the rows): one contiguous run.
+struct Slab { int64_t byte; uint32_t half; };
+template <int SK>
+__device__ __forceinline__ Slab slab_at(int s, int nslab)
+{
+    if (SK == 128) return Slab{(int64_t)s * 256, 0u};
+    return Slab{(int64_t)(s >> 3) * 4096 + (s & 7) * 256, (uint32_t)min(nslab - (s & ~7), 8) * 256u};
+}
+
 __device__ __forceinline__ void dma16(const char* base, uint32_t byte_off, uint32_t lds_addr)
 {
     asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 nt"
@@ -81,6 +100,83 @@ __device__ __forceinline__ void lds_reads_done() { asm volatile("s_waitcnt lgkmc
 constexpr int kNBW = kNB / kWaves;                      // vocabulary blocks per wave at most
 constexpr int lds_bytes() { return kWaves * kRing + kWaves * 96 * 2 * 4; }   // rings + (max, sum) of 96 rows per wave
 
+// First vocabulary row of a block as loaded: a block that reaches past the vocabulary reads the last 16 rows instead (the
+// epilogue drops the rows that belong to the block before).
+__device__ __forceinline__ int loaded_row0(const LmHeadLaunch& a, int nominal) { return min(nominal, a.vocab - 16); }
+
+// acc[jj][rb]: lane (ln, lg) holds, for row rb*16 + ln of h, the four vocabulary
+// entries loaded_row0 + lg*4 .. +3 of block jj.  Logits go out from the registers; the chunk statistics
+// are formed per wave (own maximum) and combined over the four waves by the first threads; red: [kWaves][NR * 16][2].
+template <int NR>
+__device__ __forceinline__ void epilogue(const LmHeadLaunch& a, const floatx4 (&acc)[kNBW][NR], int nbw, int v0, float* red)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ln = lane & 15, lg = lane >> 4;
+    const float c = a.inv_T * kLog2e;
+    const bool vec_ok = (a.ldz & 3) == 0 && (reinterpret_cast<uintptr_t>(a.logits) & 15) == 0;
+#pragma unroll
+    for (int rb = 0; rb < NR; ++rb) {
+        const int hrow = rb * 16 + ln;
+        const bool row_ok = hrow < a.n_rows;
+        float m = -INFINITY;
+#pragma unroll
+        for (int jj = 0; jj < kNBW; ++jj) {
+            const int nominal = v0 + (jj * kWaves + wave) * 16;
+            if (jj < nbw && nominal < a.vocab && row_ok) {
+                const int vi = loaded_row0(a, nominal) + lg * 4;
+                float* dst = a.logits + (int64_t)hrow * a.ldz + vi;
+                if (vec_ok && vi >= nominal && (vi & 3) == 0) {
+                    *reinterpret_cast<floatx4*>(dst) = acc[jj][rb];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) m = fmaxf(m, acc[jj][rb][i]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (vi + i >= nominal) { dst[i] = acc[jj][rb][i]; m = fmaxf(m, acc[jj][rb][i]); }
+                }
+            }
+        }
+        if (!a.stats) continue;                                // uniform
+        m = fmaxf(m, __shfl_xor(m, 16));
+        m = fmaxf(m, __shfl_xor(m, 32));
+        float sum = 0.f;
+        if (m > -INFINITY) {
+#pragma unroll
+            for (int jj = 0; jj < kNBW; ++jj) {
+                const int nominal = v0 + (jj * kWaves + wave) * 16;
+                if (jj < nbw && nominal < a.vocab && row_ok) {
+                    const int vi = loaded_row0(a, nominal) + lg * 4;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (vi + i >= nominal) sum += __builtin_amdgcn_exp2f((acc[jj][rb][i] - m) * c);
+                }
+            }
+        }
+        sum += __shfl_xor(sum, 16);
+        sum += __shfl_xor(sum, 32);
+        if (lg == 0) {
+            red[((wave * NR * 16) + hrow) * 2 + 0] = m;
+            red[((wave * NR * 16) + hrow) * 2 + 1] = sum;
+        }
+    }
+    if (!a.stats) return;
+    __syncthreads();
+    if (tid < a.n_rows) {
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, red[((w * NR * 16) + tid) * 2]);
+        float S = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const float mw = red[((w * NR * 16) + tid) * 2], sw = red[((w * NR * 16) + tid) * 2 + 1];
+            if (sw > 0.f) S += sw * __builtin_amdgcn_exp2f((mw - M) * c);
+        }
+        a.stats[((int64_t)tid * gridDim.x + blockIdx.x) * 2 + 0] = M;
+        a.stats[((int64_t)tid * gridDim.x + blockIdx.x) * 2 + 1] = S;
+    }
+}
+
 template <int SK, int NR>
 __global__ void __launch_bounds__(kWaves * 64) lm_head_stream(LmHeadLaunch a)
 {
@@ -97,35 +193,34 @@ __global__ void __launch_bounds__(kWaves * 64) lm_head_stream(LmHeadLaunch a)
     char* ring = smem + wave * kRing;
     const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + wave * kRing;
 
-    // Per-lane byte offsets of the loads of a tile, relative to the tile's first row and first k:
+    // Per-lane byte offsets of the loads of a tile, relative to the tile's first row and the slab:
     // instruction e moves RPI consecutive rows; lane i writes LDS bytes [16 i, 16 i + 16) of that
-    // 1 KiB and fetches the chunk the swizzle assigns there.
-    uint32_t woff[T::NLD], coff[T::NLD];
+    // 1 KiB and fetches the chunk the swizzle assigns there (chunks 16..31: the slab's second run).
+    uint32_t coff[T::NLD];
     int rrow[T::NLD];
+    const uint32_t second = (lane % T::CPR) / 16;
 #pragma unroll
     for (int e = 0; e < T::NLD; ++e) {
         rrow[e] = T::RPI * e + lane / T::CPR;
-        coff[e] = (uint32_t)((lane % T::CPR) ^ (rrow[e] & 15)) * 16u;
-        woff[e] = (uint32_t)rrow[e] * row_bytes + coff[e];
+        coff[e] = (uint32_t)((lane % 16) ^ (rrow[e] & 15)) * 16u;
     }
-    // first vocabulary row of the wave's block jj as loaded: a block that reaches past the vocabulary
-    // reads the last 16 rows instead (the epilogue drops the rows that belong to the block before)
-    auto block_row0 = [&](int jj) { return min(v0 + (jj * kWaves + wave) * 16, a.vocab - 16); };
+    auto block_row0 = [&](int jj) { return loaded_row0(a, v0 + (jj * kWaves + wave) * 16); };
 
     // tile j of slab s: j = 0..NR-1 the row blocks of the h slab, j = NR.. the wave's W blocks
     auto issue = [&](int s, int j, int slot) {
-        const int64_t kbyte = (int64_t)s * SK * 2;
+        const Slab at = slab_at<SK>(s, nslab);
+        const uint32_t off = second * at.half;
         const uint32_t dst = ring_lds + slot * T::BYTES;
         if (j < NR) {
-            const char* base = reinterpret_cast<const char*>(a.h) + kbyte;
+            const char* base = reinterpret_cast<const char*>(a.h) + at.byte;
 #pragma unroll
             for (int e = 0; e < T::NLD; ++e)
-                dma16_keep(base, (uint32_t)min(j * 16 + rrow[e], a.n_rows - 1) * row_bytes + coff[e], dst + e * 1024);
+                dma16_keep(base, (uint32_t)min(j * 16 + rrow[e], a.n_rows - 1) * row_bytes + coff[e] + off, dst + e * 1024);
             return;
         }
-        const char* base = reinterpret_cast<const char*>(a.w) + (int64_t)block_row0(j - NR) * row_bytes + kbyte;
+        const char* base = reinterpret_cast<const char*>(a.w) + (int64_t)block_row0(j - NR) * row_bytes + at.byte;
 #pragma unroll
-        for (int e = 0; e < T::NLD; ++e) dma16(base, woff[e], dst + e * 1024);
+        for (int e = 0; e < T::NLD; ++e) dma16(base, (uint32_t)rrow[e] * row_bytes + coff[e] + off, dst + e * 1024);
     };
 
     floatx4 acc[kNBW][NR];
@@ -179,87 +274,155 @@ __global__ void __launch_bounds__(kWaves * 64) lm_head_stream(LmHeadLaunch a)
         wait_loads<0>();
     }
 
-    // ---- epilogue.  acc[jj][rb]: lane (ln, lg) holds, for row rb*16 + ln of h, the four vocabulary
-    // entries block_row0(jj) + lg*4 .. +3.  Logits go out from the registers; the chunk statistics
-    // are formed per wave (own maximum) and combined over the four waves by the first threads.
-    const float c = a.inv_T * kLog2e;
-    float* red = reinterpret_cast<float*>(smem + kWaves * kRing);          // [kWaves][NR*16][2]
-    const bool vec_ok = (a.ldz & 3) == 0 && (reinterpret_cast<uintptr_t>(a.logits) & 15) == 0;
+    epilogue<NR>(a, acc, nbw, v0, reinterpret_cast<float*>(smem + kWaves * kRing));
+}
+
+// ---------------------------------------------------------------- many rows: one copy of h per workgroup
+// From four row blocks on.  The four waves load a slab of h together (256-wide, NR tiles) and all read it into their registers; two
+// barriers a slab, eight tiles of W apart, and the loads of the next slab of h go out right behind them.  What the
+// LDS has left is the rings of W, in units of half a tile (one of the slab's two runs: 16 rows x 256 bytes), five or six units
+// ahead of the math.  Against h through every wave's own ring: 72 rows of 4096 x 128256 179 -> 171 us, 96 rows 190 -> 175, 72
+// rows of 2048 x 128256 100 -> 95; 60 rows 171 -> 168; 40 rows 162 -> 164, so three row blocks stay there.  Two or four
+// passes over the hidden dimension, so that the logits of the first leave under the loads of the second: 184 and 224 us.
+template <int NR>
+struct Shared {
+    static constexpr int HBYTES = NR * 16 * 512;                              // a slab of h
+    static constexpr int RED = kWaves * NR * 16 * 2 * 4;
+    static constexpr int UNIT = 16 * 256;                                     // half a tile of W
+    static constexpr int ULD = UNIT / 1024;                                   // loads per unit
+    static constexpr int HLD = NR * 8 / kWaves;                               // loads of a wave per slab of h
+    static constexpr int SLOTS = (160 * 1024 - HBYTES - RED) / kWaves / UNIT;
+    static constexpr int AHEAD = SLOTS - 1;
+    static constexpr int LDS = HBYTES + RED + kWaves * SLOTS * UNIT;
+};
+
+template <int NR>
+__global__ void __launch_bounds__(kWaves * 64) lm_head_shared(LmHeadLaunch a)
+{
+    using S = Shared<NR>;
+    constexpr int KH = 4;                                // k-steps of a unit
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ln = lane & 15, lg = lane >> 4;
+    const int nb = a.nb;                                 // 16-row vocabulary blocks per workgroup (<= 32)
+    const int nbw = (nb + kWaves - 1 - wave) / kWaves;   // blocks of this wave: wave, wave + 4, ...
+    const int v0 = blockIdx.x * nb * 16;
+    const uint32_t row_bytes = (uint32_t)a.hidden * 2u;
+    const int nslab = a.hidden / 256;
+    char* hbuf = smem;
+    char* ring = smem + S::HBYTES + wave * (S::SLOTS * S::UNIT);
+    const uint32_t h_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    const uint32_t ring_lds = h_lds + S::HBYTES + wave * (S::SLOTS * S::UNIT);
+
+    // Loads of a unit: instruction e moves rows 4 e .. 4 e + 3; the swizzle as above, within 16 chunks.
+    uint32_t woff[S::ULD];
 #pragma unroll
-    for (int rb = 0; rb < NR; ++rb) {
-        const int hrow = rb * 16 + ln;
-        const bool row_ok = hrow < a.n_rows;
-        float m = -INFINITY;
+    for (int e = 0; e < S::ULD; ++e) {
+        const int row = 4 * e + lane / 16;
+        woff[e] = (uint32_t)row * row_bytes + (uint32_t)((lane & 15) ^ (row & 15)) * 16u;
+    }
+    // This wave's share of slab s of h: 1 KiB (two rows) of every 4.
+    auto issue_h = [&](int s) {
+        const Slab at = slab_at<256>(s, nslab);
+        const char* base = reinterpret_cast<const char*>(a.h) + at.byte;
 #pragma unroll
-        for (int jj = 0; jj < kNBW; ++jj) {
-            const int nominal = v0 + (jj * kWaves + wave) * 16;
-            if (jj < nbw && nominal < a.vocab && row_ok) {
-                const int vi = block_row0(jj) + lg * 4;
-                float* dst = a.logits + (int64_t)hrow * a.ldz + vi;
-                if (vec_ok && vi >= nominal && (vi & 3) == 0) {
-                    *reinterpret_cast<floatx4*>(dst) = acc[jj][rb];
+        for (int i = 0; i < S::HLD; ++i) {
+            const int e = i * kWaves + wave, row = 2 * e + lane / 32;
+            const uint32_t c = (uint32_t)((lane & 15) ^ (row & 15)) * 16u + (uint32_t)((lane & 31) / 16) * at.half;
+            dma16_keep(base, (uint32_t)min(row, a.n_rows - 1) * row_bytes + c, h_lds + e * 1024);
+        }
+    };
+    // The next unit to request: half pq of slab ps of block pj; past the end any valid one keeps the count uniform.
+    int ps = 0, pj = 0, pq = 0, pslot = 0;
+    auto request_next = [&]() {
+        const Slab at = slab_at<256>(min(ps, nslab - 1), nslab);
+        const char* base = reinterpret_cast<const char*>(a.w) +
+                           (int64_t)loaded_row0(a, v0 + (pj * kWaves + wave) * 16) * row_bytes + at.byte + (pq ? at.half : 0u);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) m = fmaxf(m, acc[jj][rb][i]);
-                } else {
+        for (int e = 0; e < S::ULD; ++e) dma16(base, woff[e], ring_lds + pslot * S::UNIT + e * 1024);
+        if (++pslot == S::SLOTS) pslot = 0;
+        pq ^= 1;
+        if (pq == 0 && ++pj >= nbw) { pj = 0; ++ps; }
+    };
+
+    floatx4 acc[kNBW][NR];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (vi + i >= nominal) { dst[i] = acc[jj][rb][i]; m = fmaxf(m, acc[jj][rb][i]); }
+    for (int j = 0; j < kNBW; ++j)
+#pragma unroll
+        for (int rb = 0; rb < NR; ++rb) acc[j][rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    // (a wave without blocks, in ranges of fewer than four, only loads its share of h and meets the barriers)
+    issue_h(0);
+    if (nbw > 0)
+#pragma unroll
+        for (int j = 0; j < S::AHEAD; ++j) request_next();
+    int slot = 0;
+    for (int s = 0; s < nslab; ++s) {
+        // The own share of h has landed: AHEAD units at least were requested after it, unless the wave has too few blocks.
+        if (s == 0 ? nbw > 0 : 2 * nbw >= S::AHEAD) wait_loads<S::AHEAD * S::ULD>();
+        else wait_loads<0>();
+        __syncthreads();                                 // everybody's has
+        bf16x8 hreg[NR][2 * KH];
+#pragma unroll
+        for (int rb = 0; rb < NR; ++rb)
+#pragma unroll
+            for (int ks = 0; ks < 2 * KH; ++ks)
+                hreg[rb][ks] = *reinterpret_cast<const bf16x8*>(hbuf + rb * 8192 + ln * 512 + (((ks * 4 + lg) ^ ln) * 16));
+        lds_reads_done();
+        __syncthreads();                                 // everybody has read it
+        issue_h(min(s + 1, nslab - 1));                  // (the last one again: the count stays uniform)
+#pragma unroll
+        for (int j = 0; j < kNBW; ++j)
+            if (j < nbw) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    // the slab's first AHEAD units were requested before the loads of h just issued, so those are behind them too
+                    if (2 * j + q < S::AHEAD) wait_loads<(S::AHEAD - 1) * S::ULD + S::HLD>();
+                    else wait_loads<(S::AHEAD - 1) * S::ULD>();
+                    request_next();
+                    const char* unit = ring + slot * S::UNIT;
+                    if (++slot == S::SLOTS) slot = 0;
+#pragma unroll
+                    for (int ks = 0; ks < KH; ++ks) {
+                        const bf16x8 wa = *reinterpret_cast<const bf16x8*>(unit + ln * 256 + (((ks * 4 + lg) ^ ln) * 16));
+#pragma unroll
+                        for (int rb = 0; rb < NR; ++rb)
+                            acc[j][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, hreg[rb][q * KH + ks], acc[j][rb], 0, 0, 0);
+                    }
+                    lds_reads_done();
                 }
             }
-        }
-        if (!a.stats) continue;                                // uniform
-        m = fmaxf(m, __shfl_xor(m, 16));
-        m = fmaxf(m, __shfl_xor(m, 32));
-        float sum = 0.f;
-        if (m > -INFINITY) {
-#pragma unroll
-            for (int jj = 0; jj < kNBW; ++jj) {
-                const int nominal = v0 + (jj * kWaves + wave) * 16;
-                if (jj < nbw && nominal < a.vocab && row_ok) {
-                    const int vi = block_row0(jj) + lg * 4;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (vi + i >= nominal) sum += __builtin_amdgcn_exp2f((acc[jj][rb][i] - m) * c);
-                }
-            }
-        }
-        sum += __shfl_xor(sum, 16);
-        sum += __shfl_xor(sum, 32);
-        if (lg == 0) {
-            red[((wave * NR * 16) + hrow) * 2 + 0] = m;
-            red[((wave * NR * 16) + hrow) * 2 + 1] = sum;
-        }
     }
-    if (!a.stats) return;
-    __syncthreads();
-    if (tid < a.n_rows) {
-        float M = -INFINITY;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, red[((w * NR * 16) + tid) * 2]);
-        float S = 0.f;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            const float mw = red[((w * NR * 16) + tid) * 2], sw = red[((w * NR * 16) + tid) * 2 + 1];
-            if (sw > 0.f) S += sw * __builtin_amdgcn_exp2f((mw - M) * c);
-        }
-        a.stats[((int64_t)tid * gridDim.x + blockIdx.x) * 2 + 0] = M;
-        a.stats[((int64_t)tid * gridDim.x + blockIdx.x) * 2 + 1] = S;
-    }
+    wait_loads<0>();
+    epilogue<NR>(a, acc, nbw, v0, reinterpret_cast<float*>(smem + S::HBYTES + kWaves * S::SLOTS * S::UNIT));
 }
 
 }  // namespace
 
 namespace {
+// The build for a slab width and a number of row blocks.
+template <int SK, int NR>
+struct Build {
+    static constexpr bool kShared = SK == 256 && NR >= 4;
+    static constexpr int kLds = kShared ? Shared<NR>::LDS : lds_bytes();
+    static auto kernel()
+    {
+        if constexpr (kShared) return lm_head_shared<NR>;
+        else return lm_head_stream<SK, NR>;
+    }
+};
 template <int SK, int NR>
 hipError_t configure_one()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(lm_head_stream<SK, NR>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes());
+    using B = Build<SK, NR>;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(B::kernel()), hipFuncAttributeMaxDynamicSharedMemorySize, B::kLds);
 }
 template <int SK, int NR>
 void launch_one(const LmHeadLaunch& a, int nwg, hipStream_t stream)
 {
-    hipLaunchKernelGGL((lm_head_stream<SK, NR>), dim3(nwg), dim3(kWaves * 64), lds_bytes(), stream, a);
+    using B = Build<SK, NR>;
+    hipLaunchKernelGGL(B::kernel(), dim3(nwg), dim3(kWaves * 64), B::kLds, stream, a);
 }
 }  // namespace
 
@@ -280,8 +443,7 @@ hipError_t configure_lm_head()
     return configure_one<256, 6>();
 }
 
-// Row blocks of 16 rows of h; the 256-wide slab when the hidden size allows (at six row blocks its h
-// operands and the accumulators take 384 of the 512 registers), else the 128-wide one.
+// Row blocks of 16 rows of h; the 256-wide slab when the hidden size allows, else the 128-wide one.
 hipError_t launch_lm_head(const LmHeadLaunch& a, hipStream_t stream)
 {
     const int nwg = (a.vocab + a.nb * 16 - 1) / (a.nb * 16);

@@ -92,3 +92,27 @@ def test_head_and_accept_against_float64_logits(hidden, vocab, eta):
     # a worst case of all logits off by D at once: a drawn token whose own weight is below it (a quarter to a third of the draws
     # from such a vocabulary) cannot be told from its neighbour; the others, the majority, are compared
     assert ties < B // 2
+
+
+@pytest.mark.parametrize("hidden", [256, 1792, 2048, 2304, 4096, 128, 2176])
+@pytest.mark.parametrize("vocab", [16, 1601, 12317])
+def test_every_row_count_gives_the_same_logits(hidden, vocab):
+    """The builds for one to six row blocks, edges of the blocks on both sides, groups of slabs that end early (hidden not a
+    multiple of 2048), ranges of one to four and of twelve vocabulary blocks: against float64, and a row's logits do not
+    depend on how many rows are in the call."""
+    h, w = wl.gen_lm_head_inputs(96, hidden, vocab, salt=hidden + vocab)
+    hd, wd = gu.bf16_to_dev(h), gu.bf16_to_dev(w)
+    ref = hd.double().cpu() @ wd.double().cpu().t()
+    r = gu.rapid()
+    whole, _ = r.rapid_lm_head(hd, wd)
+    # products of bf16 are exact in float32, `hidden` additions of them round by 2^-24 of the running sum each
+    assert torch.all((whole.double().cpu() - ref).abs() <= 5e-5 + 1e-5 * ref.abs())
+    for rows in (1, 15, 16, 17, 33, 48, 49, 64, 65, 80, 81):
+        logits, stats = r.rapid_lm_head(hd[:rows].contiguous(), wd)
+        assert torch.equal(logits, whole[:rows]), rows
+        chunk = r.lm_head_chunk(vocab, rows)
+        pad = torch.nn.functional.pad(logits, (0, stats.shape[1] * chunk - vocab), value=-np.inf)
+        z = pad.view(rows, stats.shape[1], chunk)
+        assert torch.equal(stats[..., 0], z.amax(-1)), rows
+        torch.testing.assert_close(stats[..., 1].double(), torch.exp(z.double() - z.double().amax(-1, True)).sum(-1),
+                                   rtol=2e-5, atol=0)
