@@ -891,14 +891,19 @@ __device__ __forceinline__ void draw_accumulate(int phase, double et, double ed,
     }
 }
 
-// NT threads of NE entries.  OCC = waves per SIMD the kernel is compiled for; at 4 (two workgroups of 512 threads per
-// compute unit, 128 registers) and with 20 entries (256 registers) the entries are taken one at a time: several at once spill.
+// Orders the scheduler: `later` is not touched before `done` is there.
+template <class A, class B>
+__device__ __forceinline__ void after(A& done, B& later) { asm volatile("" : "+v"(done), "+v"(later)); }
+
+// NT threads of NE entries.  OCC = waves per SIMD the kernel is compiled for; at 4 (128 registers) the entries are taken one
+// at a time, each tied to the one before it: left alone, or with a compiler barrier between them, the scheduler holds the temporaries
+// of many (16 entries of six registers in 128, 20 in 156; with a barrier 20 took 224 and 24 spilled).
 template <int NT, int NE, int OCC>
 __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws, int W2)
 {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     constexpr int NW = NT / 64;
-    constexpr bool kOneByOne = OCC > 2 || NE > 8;         // few registers: one entry's temporaries at a time
+    constexpr bool kOneByOne = OCC > 2;                   // few registers: one entry's temporaries at a time
     LdsB& lds = *reinterpret_cast<LdsB*>(smem_raw);
     constexpr int kSlice = NT * NE;
     const int w = blockIdx.x, b = blockIdx.y;
@@ -920,6 +925,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
     // own slice: e_t, e_d of the thread's entries, kept in registers for all phases; wgt holds
     // f = e_t exp(eta (q - p)) after phase 2 and the draw weight after phase 3
     double et[NE], ed[NE], wgt[NE];
+    auto next = [](int i) { return i + 1 < NE ? i + 1 : i; };
     const int first = w * kSlice + tid * NE;
     float t_in[NE], d_in[NE];
     load_row<NE>(t_in, zt, d_in, zd, first, V, (int64_t)(w + 1) * kSlice <= V);
@@ -928,7 +934,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
 #pragma unroll
     for (int i = 0; i < NE; ++i) {
         et[i] = exp_tab(((double)t_in[i] - Mt) * invT, lds.tab);
-        if (kOneByOne) asm volatile("" ::: "memory");
+        if (kOneByOne) after(et[i], t_in[next(i)]);
     }
 #pragma unroll
     for (int i = 0; i < NE; ++i) ed[i] = 0.0;
@@ -936,7 +942,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
             ed[i] = exp_tab(((double)d_in[i] - Md) * invT, lds.tab);
-            if (kOneByOne) asm volatile("" ::: "memory");
+            if (kOneByOne) after(ed[i], d_in[next(i)]);
         }
     STAMP(9);
     DrawNorm nm{1.0, 0.0, 0.0, 0.0, uniform((double)a.eta)};
@@ -1017,7 +1023,10 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
                 wgt[i] = draw_f(et[i], ed[i], nm, lds.tab);
                 a0 += wgt[i];
                 a1 = fmax(a1, wgt[i]);
-                if (kOneByOne) asm volatile("" ::: "memory");
+                if (kOneByOne) {
+                    after(a0, et[next(i)]);
+                    after(a1, ed[next(i)]);
+                }
             }
             exchange(Phase<2>(), a0, a1);
         }
@@ -1033,7 +1042,10 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
                 wgt[i] = draw_weight(et[i], ed[i], wgt[i], nm, p);
                 a0 += wgt[i];
                 a1 += p;
-                if (kOneByOne) asm volatile("" ::: "memory");
+                if (kOneByOne) {
+                    after(a0, et[next(i)]);
+                    after(a1, ed[next(i)]);
+                }
             }
             exchange(Phase<3>(), a0, a1);
         }
@@ -1144,9 +1156,10 @@ size_t accept_workspace_bytes(int B, int gmax, int V)
 // The build of accept_draw_row for a call.  Small batches: the fewest entries per thread that leave every workgroup a
 // compute unit of its own and keep the exchange among at most 64 workgroups (one sequence: vocabulary 32001 22.1 us
 // with 2, 23.0 with 4, 26.7 with 8; 128256 23.7 with 2 on 126 workgroups, 23.0 with 4, 25.0 with 8).  Eight entries while
-// the grid is one round of two workgroups per compute unit; beyond that 20 entries on 256 threads, which hold a quarter more
-// entries at a time and so need fewer rounds of the three exchanges (64 sequences of 128256: 135 us against 140; 32 of
-// 152064: 95 against 105; 32 of 128256 the same).
+// the grid is one round of two workgroups per compute unit; beyond that 256 threads, four workgroups per compute unit: twelve entries while
+// that is one round (20 sequences of 152064: 35.9 us, with 16 entries 38.9), else 16.  What counts there is how many waves stand by
+// while others wait in the three exchanges, and how many rounds of them there are (64 sequences of 128256, the whole pass: 16 entries 124 us,
+// 12 130, 8 in six waves per SIMD 147, 20 in three 127, 24 in two 133; 20 in two, the build before, 138; 32 sequences 70.5 against 78.6).
 struct DrawShape {
     void (*kernel)(AcceptLaunch, Ws, int);
     int threads, wgs;
@@ -1159,7 +1172,9 @@ static DrawShape draw_shape(const AcceptLaunch& a)
     if (w4 <= 64 && (int64_t)w4 * a.B <= a.n_cu) return {accept_draw_row<512, 4, 2>, 512, w4};
     if ((int64_t)w8 * a.B <= a.n_cu) return {accept_draw_row<512, 8, 2>, 512, w8};
     if ((int64_t)w8 * a.B <= 2 * (int64_t)a.n_cu) return {accept_draw_row<512, 8, 4>, 512, w8};
-    return {accept_draw_row<256, 20, 2>, 256, wgs(256, 20)};
+    const int w12 = wgs(256, 12);
+    if ((int64_t)w12 * a.B <= 4 * (int64_t)a.n_cu) return {accept_draw_row<256, 12, 4>, 256, w12};
+    return {accept_draw_row<256, 16, 4>, 256, wgs(256, 16)};
 }
 
 hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)

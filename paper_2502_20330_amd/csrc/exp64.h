@@ -44,7 +44,7 @@ __device__ __forceinline__ double exp_c(double x)
 // stand for the next term (Chebyshev economisation; Taylor's own would leave 4e-17).
 // About two thirds of exp_c's time and as exact (at most 1.2e-16 relative error, exp_c 1.4e-16): the table also
 // holds what rounding took from each power, without which it would be 2.3e-16 (a table of its own: pairs of doubles in one
-// 128-bit read spilled registers in the build of 20 entries).  Rounding to a multiple of ln2/64 by adding 1.5 2^52
+// 128-bit read spilled registers).  Rounding to a multiple of ln2/64 by adding 1.5 2^52
 // leaves the integer in the low word, which holds it up to 2^31 only: arguments are clamped above too, where the result
 // is +inf already (a shift eta (q - p) may be of any size; without the clamp 2.4e7 gave 0).
 struct Exp2 { double v[64]; float rest[64]; };      // 2^(j/64) = v (1 + rest)

@@ -131,6 +131,13 @@ def test_every_build_of_the_draw_and_its_give_up_path(batch, V):
     assert st["n_mismatch"] == 0 and st["token_mismatch"] == 0 and st["exempt_sequences"] == 0, st
 
 
+@pytest.mark.parametrize("batch,V", [(61, 50257), (61, 49152), (1025, 1030)])
+def test_draws_beyond_one_round_of_workgroups(batch, V):
+    """The build of 16 entries (17 slices of 12 entries a sequence no longer fit four workgroups to a compute unit): slices that end
+    inside a thread's entries and with the row, and one slice per sequence; the give-up path included."""
+    test_every_build_of_the_draw_and_its_give_up_path(batch, V)
+
+
 @pytest.mark.parametrize("g", [1023, 1024, 1100, 20000])
 def test_greedy_with_thousands_of_drafted_positions(g):
     """More positions than the decision keeps arg-maxima for in LDS: all accepted, and rejected at the last one."""
