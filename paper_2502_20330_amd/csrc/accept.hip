@@ -303,12 +303,16 @@ __device__ __forceinline__ void poll_into(Addr addr, int lo, int hi, u64* dst, i
 
 // The same by the whole workgroup, one word per thread and round, for exchanges of hundreds of words;
 // miss[wave] = words of that wave still unpublished.  The caller synchronises before it reads dst and miss.
+// The first look comes half a microsecond (20 x 64 cycles) after the own publication, when the others' are usually there: a
+// look in vain costs its round trip and holds up the stores that it waits for (one sequence, the whole pass: no delay 22.9 us, 8 x 64 cycles
+// 21.5, 16 20.4, 20 20.1, 28 20.5, 40 21.3; 64 sequences 124.3, 121.0, 120.0, 118.4, 117.5, 118.4; two looks in flight instead: 24 and 145).
 template <int NT>
 __device__ __forceinline__ void poll_all(const u64* words, int n, u64* dst, int* miss, int64_t wait_ticks, const Tags& tg)
 {
     const int64_t t0 = (int64_t)wall_clock64();
     const uint32_t want = tag_of(threadIdx.x, tg);        // NT is even: every word of a thread has its parity
     int m = 0;
+    if (n > 4) __builtin_amdgcn_s_sleep(20);              // (one slice: the own one)
     for (int i0 = 0; i0 < n; i0 += NT) {
         const int i = i0 + threadIdx.x;
         u64 v = 0;
