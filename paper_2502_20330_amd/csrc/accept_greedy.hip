@@ -55,6 +55,28 @@ __device__ __forceinline__ void take_better(float& m, int& i, float m2, int i2)
     if (m2 > m || (m2 == m && i2 < i)) { m = m2; i = i2; }
 }
 
+// The best pair of a wave, in every lane: the maximum (never a NaN: maxima start at -inf and NaN entries do not pass), then the lowest
+// index that has it; lane permutes on the way to the vector unit, no LDS.  Lanes without a source keep their own value.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp_or_own(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, ROW_MASK, 0xf, false); }
+template <class Op>
+__device__ __forceinline__ int wave_fold(int v, Op op)
+{
+    v = op(v, dpp_or_own<0x111, 0xf>(v));                     // row_shr 1, 2, 4, 8 inside rows of 16 lanes
+    v = op(v, dpp_or_own<0x112, 0xf>(v));
+    v = op(v, dpp_or_own<0x114, 0xf>(v));
+    v = op(v, dpp_or_own<0x118, 0xf>(v));
+    v = op(v, dpp_or_own<0x142, 0xa>(v));                     // lane 15 of a row into the next: rows 1 and 3
+    v = op(v, dpp_or_own<0x143, 0xc>(v));                     // lane 31 into the upper half
+    return __builtin_amdgcn_readlane(v, 63);
+}
+__device__ __forceinline__ void wave_best(float& m, int& idx)
+{
+    const float best = __int_as_float(wave_fold(__float_as_int(m), [](int x, int y) { return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(y))); }));
+    idx = wave_fold(m == best ? idx : 0x7fffffff, [](int x, int y) { return min(x, y); });
+    m = best;
+}
+
 // Row y of sequence b: y <= gmax the target rows, then the draft rows.  Four 128-bit loads per thread, all in flight
 // at once (eight, in half as many workgroups: 101 us instead of 97 at 64 sequences of 128256 entries and 8 drafts,
 // 558 MB); a thread's entries come in index order, so equal maxima keep the lowest index by themselves.
@@ -89,8 +111,7 @@ __global__ void __launch_bounds__(kThreads) greedy_slice_argmax(AcceptLaunch a, 
             if (x[v][j] > m || first) { m = x[v][j]; idx = i; }
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) take_better(m, idx, __shfl_xor(m, o), __shfl_xor(idx, o));
+    wave_best(m, idx);
     if ((threadIdx.x & 63) == 0) { shm[threadIdx.x >> 6] = m; shi[threadIdx.x >> 6] = idx; }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -101,16 +122,20 @@ __global__ void __launch_bounds__(kThreads) greedy_slice_argmax(AcceptLaunch a, 
     }
 }
 
-// One wave combines the slices of row y of sequence b; the result is valid in every lane.
-__device__ __forceinline__ void row_argmax(const GreedyWs& ws, int64_t row, float& m, int& idx)
+// One wave combines the slices of row y of sequence b; the result is valid in every lane.  first: the row's first 64 slices, one per lane,
+// fetched before (so that the loads of several rows are in flight together).
+struct Best { float m; int i; };
+__device__ __forceinline__ Best fetch_slice(const GreedyWs& ws, int64_t row, int s)
 {
-    const int lane = threadIdx.x & 63;
+    return s < ws.W ? Best{ws.smax[row * ws.W + s], ws.sidx[row * ws.W + s]} : Best{-INFINITY, 0x7fffffff};
+}
+__device__ __forceinline__ void row_argmax(const GreedyWs& ws, int64_t row, Best first, float& m, int& idx)
+{
     m = -INFINITY;
     idx = 0x7fffffff;
-    const int64_t base = row * ws.W;
-    for (int s = lane; s < ws.W; s += 64) take_better(m, idx, ws.smax[base + s], ws.sidx[base + s]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) take_better(m, idx, __shfl_xor(m, o), __shfl_xor(idx, o));
+    take_better(m, idx, first.m, first.i);
+    for (int s = (threadIdx.x & 63) + 64; s < ws.W; s += 64) take_better(m, idx, ws.smax[row * ws.W + s], ws.sidx[row * ws.W + s]);
+    wave_best(m, idx);
 }
 
 // One wave per position: the drafted token, its two logits and the slices of both rows are fetched side by side, and the
@@ -127,18 +152,23 @@ __global__ void __launch_bounds__(kDecideWaves * 64) greedy_decide(AcceptLaunch 
     __syncthreads();
     const int g = seq_gamma(a, b);
     for (int k = wave; k <= a.gmax; k += blockDim.x / 64) {
+        // what does not depend on the sequence's own count of drafts is requested before that has arrived (rows past it hold whatever
+        // an earlier call left, and are not used)
+        const int64_t at = (int64_t)b * a.gmax + k;
+        const Best first_t = fetch_slice(ws, (int64_t)b * nrows + k, lane);
+        const Best first_d = k < a.gmax ? fetch_slice(ws, (int64_t)b * nrows + a.gmax + 1 + k, lane) : Best{-INFINITY, 0x7fffffff};
+        const int drafted = k < a.gmax ? a.tokens[at] : 0;
         if (k > g) break;
         const bool pair = k < g;
-        const int64_t at = (int64_t)b * a.gmax + k;
-        const int x = pair ? a.tokens[at] : 0;
+        const int x = pair ? drafted : 0;
         const bool in_range = pair && x >= 0 && x < a.V;
         const float zx_t = in_range ? a.zt[((int64_t)b * (a.gmax + 1) + k) * a.V + x] : 0.f;
         const float zx_d = in_range ? a.zd[at * a.V + x] : 0.f;
         const double u = (double)a.uniforms[(int64_t)b * (a.gmax + 1) + k];
         float mt, md = 0.f;
         int it, id;
-        row_argmax(ws, (int64_t)b * nrows + k, mt, it);
-        if (pair) row_argmax(ws, (int64_t)b * nrows + a.gmax + 1 + k, md, id);
+        row_argmax(ws, (int64_t)b * nrows + k, first_t, mt, it);
+        if (pair) row_argmax(ws, (int64_t)b * nrows + a.gmax + 1 + k, first_d, md, id);
         if (lane != 0) continue;
         if (k < kKept) target_arg[k] = it;
         if (!pair) continue;
@@ -160,7 +190,7 @@ __global__ void __launch_bounds__(kDecideWaves * 64) greedy_decide(AcceptLaunch 
     if (n >= kKept) {                                         // uniform
         float m;
         int it;
-        if (wave == 0) row_argmax(ws, (int64_t)b * nrows + n, m, it);
+        if (wave == 0) row_argmax(ws, (int64_t)b * nrows + n, fetch_slice(ws, (int64_t)b * nrows + n, lane), m, it);
         if (tid == 0) target_arg[0] = it;
         __syncthreads();
     }
