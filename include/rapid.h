@@ -294,6 +294,20 @@ int rapid_accept_prestats(rapid_ctx* ctx, int batch, int gamma_max, int vocab,
                           void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * rapid_accept_prestats that writes all of accept_ratio, 0 for the rows k >= gamma_b, which the other two
+ * entry points leave as they are: a caller with a buffer of its own need not clear it by another launch.
+ */
+int rapid_accept_filled(rapid_ctx* ctx, int batch, int gamma_max, int vocab,
+                        const float* target_logits, const float* draft_logits,
+                        const int32_t* draft_tokens, const int32_t* gammas,
+                        float eta, float temperature, float tail_alpha,
+                        const float* uniforms,
+                        const float* target_stats, int target_chunks,
+                        const float* draft_stats, int draft_chunks,
+                        int32_t* n_accepted, int32_t* out_tokens, float* accept_ratio,
+                        void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * Cache bookkeeping around one validation round (implied by Alg. 1: the target scores
  * [C; x_<j] for every drafted position j; its index i advances to j+1 with every accepted
  * draft and by one more after the residual draw).

@@ -22,7 +22,7 @@ OPT_ACCEPT_WAIT_US, OPT_ACCEPT_SLICE, OPT_PROBE_SKEW = 1, 2, 3
 EXPORTS = ["rapid_create", "rapid_destroy", "rapid_strerror", "rapid_last_hip_error", "rapid_set_option",
            "rapid_verify_attn_chunk", "rapid_verify_attn_workspace_bytes", "rapid_verify_attn",
            "rapid_verify_attn_static",
-           "rapid_accept_workspace_bytes", "rapid_accept", "rapid_accept_prestats",
+           "rapid_accept_workspace_bytes", "rapid_accept", "rapid_accept_prestats", "rapid_accept_filled",
            "rapid_lm_head_chunk", "rapid_lm_head_stat_chunks", "rapid_lm_head", "rapid_kv_append", "rapid_kv_commit",
            "rapid_kv_commit_pages",
            "rapid_retrieve", "rapid_hbm_read_probe"]
@@ -90,6 +90,8 @@ def load_library() -> ctypes.CDLL:
                                           f32p, ctypes.c_int, f32p, ctypes.c_int, i32p, i32p, f32p,
                                           vp, ctypes.c_size_t, vp]
     lib.rapid_accept_prestats.restype = ctypes.c_int
+    lib.rapid_accept_filled.argtypes = lib.rapid_accept_prestats.argtypes
+    lib.rapid_accept_filled.restype = ctypes.c_int
     lib.rapid_lm_head_chunk.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int]
     lib.rapid_lm_head_chunk.restype = ctypes.c_int
     lib.rapid_lm_head_stat_chunks.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int]
@@ -259,7 +261,8 @@ class Rapid:
         """target_logits fp32 [B,g+1,V], draft_logits fp32 [B,g,V], draft_tokens int32 [B,g],
         uniforms fp32 [B,g+1].  Returns (n_accepted int32 [B], out_tokens int32 [B,g+1], ratio fp32 [B,g] or None).
         target_stats / draft_stats: optional fp32 [rows, chunks, 2] row statistics (see rapid_lm_head); with
-        either one the call goes to rapid_accept_prestats."""
+        either one the call goes to rapid_accept_prestats.  Ratios past a sequence's drafts are 0, in a buffer passed in
+        `outs` untouched."""
         B, g1, V = target_logits.shape
         g = g1 - 1
         assert target_logits.dtype == torch.float32 and target_logits.is_contiguous()
@@ -269,14 +272,13 @@ class Rapid:
         if outs is None:
             n_acc = torch.empty(B, dtype=torch.int32, device=self.device)
             toks = torch.empty(B, g + 1, dtype=torch.int32, device=self.device)
-            ratio = None
-            if want_ratio:
-                # without per-sequence counts every element is written
-                make = torch.empty if gammas is None else torch.zeros
-                ratio = make((B, g), dtype=torch.float32, device=self.device)
+            ratio = torch.empty((B, g), dtype=torch.float32, device=self.device) if want_ratio else None
         else:
             n_acc, toks, ratio = outs
-        prestats = target_stats is not None or draft_stats is not None
+        # a ratio buffer made here is written in full (a fill of its own was a sixth of a small call's time); the caller's keeps what
+        # it holds past a sequence's drafts
+        fill = outs is None and want_ratio and gammas is not None
+        prestats = fill or target_stats is not None or draft_stats is not None
         args = (self._ctx, B, g, V, target_logits.data_ptr(), draft_logits.data_ptr(), draft_tokens.data_ptr(), _dptr(gammas),
                 float(eta), float(temperature), float(tail_alpha), uniforms.data_ptr())
         results = (_dptr(n_acc), _dptr(toks), _dptr(ratio))
@@ -286,7 +288,7 @@ class Rapid:
                                       and st.shape[0] == rows and st.shape[2] == 2)
             args += (_dptr(target_stats), 0 if target_stats is None else target_stats.shape[1],
                      _dptr(draft_stats), 0 if draft_stats is None else draft_stats.shape[1])
-        call = self.lib.rapid_accept_prestats if prestats else self.lib.rapid_accept
+        call = self.lib.rapid_accept_filled if fill else self.lib.rapid_accept_prestats if prestats else self.lib.rapid_accept
         ws, stream = self._ws_accept, _stream_ptr(self.device)
         rc = call(*args, *results, _dptr(ws), 0 if ws is None else ws.numel(), stream)
         if rc == RAPID_EWORKSPACE:                             # the last check of the call: nothing has been launched

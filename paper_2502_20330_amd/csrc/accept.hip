@@ -1093,6 +1093,8 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
         // What the draw does not wait for: accepted drafts, then -1 (the draw fills slot n), and the counters.
         for (int k = tid; k <= a.gmax; k += NT)
             if (k != n) a.out_tokens[(int64_t)b * (a.gmax + 1) + k] = k < n ? a.tokens[(int64_t)b * a.gmax + k] : -1;
+        if (a.fill_ratio)
+            for (int k = g + tid; k < a.gmax; k += NT) a.ratio[(int64_t)b * a.gmax + k] = 0.f;
         if (tid == 0) {
             a.n_accepted[b] = n;
             if (bad) atomicAdd(ws.status + 0, bad);

@@ -203,6 +203,8 @@ __global__ void __launch_bounds__(kDecideWaves * 64) greedy_decide(AcceptLaunch 
         }
         a.out_tokens[(int64_t)b * (a.gmax + 1) + k] = tok;
     }
+    if (a.fill_ratio)
+        for (int k = g + tid; k < a.gmax; k += blockDim.x) a.ratio[(int64_t)b * a.gmax + k] = 0.f;
     if (tid == 0) a.n_accepted[b] = n;
 }
 

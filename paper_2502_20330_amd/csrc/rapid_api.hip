@@ -347,7 +347,7 @@ size_t rapid_accept_workspace_bytes(const rapid_ctx*, int batch, int gamma_max, 
     return general > greedy ? general : greedy;
 }
 
-int rapid_accept_prestats(rapid_ctx* ctx, int batch, int gamma_max, int vocab,
+static int accept_call(rapid_ctx* ctx, bool fill_ratio, int batch, int gamma_max, int vocab,
                           const float* target_logits, const float* draft_logits,
                           const int32_t* draft_tokens, const int32_t* gammas,
                           float eta, float temperature, float tail_alpha,
@@ -395,6 +395,7 @@ int rapid_accept_prestats(rapid_ctx* ctx, int batch, int gamma_max, int vocab,
     a.nch_d = draft_chunks;
     a.wait_ticks = ctx->accept_wait_ticks;
     a.n_cu = ctx->n_cu;
+    a.fill_ratio = fill_ratio && accept_ratio;
     a.force_slice = ctx->accept_slice;
     DeviceScope dev(ctx->device);
     if (dev.err != hipSuccess) return hip_fail(ctx, dev.err);
@@ -402,6 +403,36 @@ int rapid_accept_prestats(rapid_ctx* ctx, int batch, int gamma_max, int vocab,
                           : launch_accept(a, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(ctx, e);
     return RAPID_OK;
+}
+
+int rapid_accept_prestats(rapid_ctx* ctx, int batch, int gamma_max, int vocab,
+                          const float* target_logits, const float* draft_logits,
+                          const int32_t* draft_tokens, const int32_t* gammas,
+                          float eta, float temperature, float tail_alpha,
+                          const float* uniforms,
+                          const float* target_stats, int target_chunks,
+                          const float* draft_stats, int draft_chunks,
+                          int32_t* n_accepted, int32_t* out_tokens, float* accept_ratio,
+                          void* workspace, size_t workspace_bytes, void* stream)
+{
+    return accept_call(ctx, false, batch, gamma_max, vocab, target_logits, draft_logits, draft_tokens, gammas, eta, temperature,
+                       tail_alpha, uniforms, target_stats, target_chunks, draft_stats, draft_chunks, n_accepted, out_tokens,
+                       accept_ratio, workspace, workspace_bytes, stream);
+}
+
+int rapid_accept_filled(rapid_ctx* ctx, int batch, int gamma_max, int vocab,
+                          const float* target_logits, const float* draft_logits,
+                          const int32_t* draft_tokens, const int32_t* gammas,
+                          float eta, float temperature, float tail_alpha,
+                          const float* uniforms,
+                          const float* target_stats, int target_chunks,
+                          const float* draft_stats, int draft_chunks,
+                          int32_t* n_accepted, int32_t* out_tokens, float* accept_ratio,
+                          void* workspace, size_t workspace_bytes, void* stream)
+{
+    return accept_call(ctx, true, batch, gamma_max, vocab, target_logits, draft_logits, draft_tokens, gammas, eta, temperature,
+                       tail_alpha, uniforms, target_stats, target_chunks, draft_stats, draft_chunks, n_accepted, out_tokens,
+                       accept_ratio, workspace, workspace_bytes, stream);
 }
 
 int rapid_accept(rapid_ctx* ctx, int batch, int gamma_max, int vocab,

@@ -305,3 +305,27 @@ def test_greedy_decision_of_any_number_of_waves(B, g, V):
     np.testing.assert_array_equal(toks.cpu().numpy(), ref.out_tokens)
     live = np.arange(g)[None, :] < gam[:, None]
     np.testing.assert_array_equal(ratio.cpu().numpy().astype(np.float64)[live], ref.ratio[live])
+
+
+@pytest.mark.parametrize("T", [1.0, 0.0])
+def test_ratios_past_a_sequences_drafts(T):
+    """The buffer that the binding makes is written in full, 0 past a sequence's own drafts, whatever the memory held; a
+    buffer of the caller's keeps what it holds there."""
+    cfg = wl.scaled(wl.CONFIGS["llama8b_32k"], batch=6, vocab=5003, gamma_choices=(0, 1, 3), draft_noise_std=2.0, name="ratios")
+    acc = wl.gen_accept_inputs(cfg, salt=7)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    gam = np.asarray(acc.gammas, dtype=np.int32)
+    args = [dev(x) for x in (acc.target_logits, acc.draft_logits, acc.draft_tokens)] + [1.0, dev(acc.uniforms)]
+    r = gu.rapid()
+    B, g = acc.draft_tokens.shape
+    mine = torch.full((B, g), 7.0, device="cuda")
+    outs = (torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, g + 1), dtype=torch.int32, device="cuda"), mine)
+    r.rapid_accept(*args, gammas=dev(gam), temperature=T, outs=outs)
+    for _ in range(3):
+        torch.full((B, g), float("nan"), device="cuda")        # what the next allocation of this size may hold
+        n, toks, ratio = r.rapid_accept(*args, gammas=dev(gam), temperature=T)
+        past = torch.arange(g, device="cuda")[None] >= dev(gam)[:, None]
+        assert past.any() and not past.all()
+        assert torch.equal(ratio[past], torch.zeros_like(ratio[past])) and torch.equal(mine[past], torch.full_like(mine[past], 7.0))
+        assert torch.equal(ratio[~past].view(torch.int32), mine[~past].view(torch.int32))
+        assert torch.equal(n, outs[0]) and torch.equal(toks, outs[1])
