@@ -93,7 +93,7 @@ __device__ __forceinline__ double dpp_move(double id, double v)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 template <class T, class Op>
-__device__ __forceinline__ T wave_scan(T v, Op op)
+__device__ __forceinline__ T half_wave_scan(T v, Op op)         // lanes 0..31 and 32..63 by themselves
 {
     const T id = Op::id();
     v = op(v, dpp_move<0x111, 0xf>(id, v));      // row_shr:1
@@ -101,7 +101,13 @@ __device__ __forceinline__ T wave_scan(T v, Op op)
     v = op(v, dpp_move<0x114, 0xf>(id, v));      // row_shr:4
     v = op(v, dpp_move<0x118, 0xf>(id, v));      // row_shr:8
     v = op(v, dpp_move<0x142, 0xa>(id, v));      // row_bcast:15 into rows 1 and 3
-    v = op(v, dpp_move<0x143, 0xc>(id, v));      // row_bcast:31 into rows 2 and 3
+    return v;
+}
+template <class T, class Op>
+__device__ __forceinline__ T wave_scan(T v, Op op)
+{
+    v = half_wave_scan(v, op);
+    v = op(v, dpp_move<0x143, 0xc>(Op::id(), v));  // row_bcast:31 into rows 2 and 3
     return v;
 }
 __device__ __forceinline__ float lane_value(float v, int lane)
@@ -481,6 +487,18 @@ __device__ __forceinline__ void wave_combine_f32(Pair pair, int n, float c, floa
     }
     S = wave_sum(s);
 }
+// The same for both rows of a pair of at most 32 slices each, side by side in the halves of a wave (the pairs of the target row
+// in lanes 0..31, of the draft row in lanes 32..63): the chain of one on the way to the shifted row.  Same bits.
+__device__ __forceinline__ void half_waves_combine_f32(float2 v, float c, PairNorm& r)
+{
+    const bool lower = (threadIdx.x & 63) < 32;
+    const float m = half_wave_scan(v.x, OpMaxF());
+    r.Mt = lane_value(m, 31);
+    r.Md = lane_value(m, 63);
+    const float s = half_wave_scan(v.y > 0.f ? v.y * fexp2((v.x - (lower ? r.Mt : r.Md)) * c) : 0.f, OpAddF());
+    r.St = lane_value(s, 31);
+    r.Sd = lane_value(s, 63);
+}
 // The same in fp64 (decisions); `scale` multiplies the difference of maxima (1/T for raw logits,
 // ln 2 for maxima kept in log2 units).
 template <class Pair>
@@ -649,8 +667,13 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
                 if (tid == 0) lds.norm = PairNorm{mt, st, __log2f(st), md, sd, __log2f(sd)};
             } else if (tid < 64) {
                 PairNorm r;
-                wave_combine_f32(pair_t, n_t, c, r.Mt, r.St);
-                wave_combine_f32(pair_d, n_d, c, r.Md, r.Sd);
+                if (W <= 32) {
+                    half_waves_combine_f32(lane < 32 ? (lane < W ? pair_t(lane) : make_float2(-INFINITY, 0.f))
+                                                     : (lane - 32 < W ? pair_d(lane - 32) : make_float2(-INFINITY, 0.f)), c, r);
+                } else {
+                    wave_combine_f32(pair_t, n_t, c, r.Mt, r.St);
+                    wave_combine_f32(pair_d, n_d, c, r.Md, r.Sd);
+                }
                 r.l2St = __log2f(r.St);
                 r.l2Sd = __log2f(r.Sd);
                 if (tid == 0) lds.norm = r;
