@@ -23,9 +23,9 @@
 //  * W travels HBM -> LDS directly (global_load_lds_dwordx4, 1 KiB per instruction) in tiles of
 //    16 rows x SK (8 KiB / 4 KiB) through a 32 KiB ring per wave, three / seven tiles ahead of the
 //    math; the wave counts its own outstanding loads, so the main loop has no workgroup barrier.
-//  * A 256-wide slab is two runs of 256 bytes of a row, 2 KiB apart inside each 4 KiB (Slab below).  All waves of
+//  * Where rows of W are a multiple of 4 KiB, a 256-wide slab is two runs of 256 bytes of a row, 2 KiB apart (Slab below).  All waves of
 //    the chip run through the hidden dimension nearly in step, so with contiguous slabs they ask for the same 512 of every 4 KiB
-//    at a time, and where the row pitch is a multiple of 4 KiB that is half of the memory channels (bit 11 of the
+//    at a time, which is half of the memory channels (bit 11 of the
 //    address is one of the bits that select them; the upper bits make up for it in some placements of W and not in
 //    others).  One row of 2048 x 128256: 105 us contiguous, 77 us in halves (128-byte quarters: 85); 9 rows of
 //    6144 x 64000 138 -> 115; of 4096 x 128256 152, 167 or 188 us by placement -> 154 in all of them; of
@@ -64,15 +64,17 @@ struct Tile {
 };
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Where slab s of a row lies.  256-wide slabs: eight to a group of 4 KiB of the row (the last group may be shorter), each a
-// run of 256 bytes of the group's first half and the one at the same place of its second half, `half` bytes on.  128-wide slabs (hidden an
-// odd multiple of 128: the row pitch itself spreads the rows): one contiguous run.
+// Where slab s of a row lies.  128-wide slabs: one run of 256 bytes.  256-wide ones: two, the second `half` bytes behind the first: in
+// rows that are a multiple of 4 KiB, the runs of eight slabs fill either half of 4 KiB in turn; else they adjoin (a pitch that is no
+// multiple of 4 KiB spreads the rows of a tile by itself, and whole lines of 512 bytes are 1 % faster: 9 rows of 3072 x 128256
+// 118.4 us against 120.1, 5 of 2304 x 100000 69.9 against 71.1).
 struct Slab { int64_t byte; uint32_t half; };
 template <int SK>
 __device__ __forceinline__ Slab slab_at(int s, int nslab)
 {
     if (SK == 128) return Slab{(int64_t)s * 256, 0u};
-    return Slab{(int64_t)(s >> 3) * 4096 + (s & 7) * 256, (uint32_t)min(nslab - (s & ~7), 8) * 256u};
+    if (nslab & 7) return Slab{(int64_t)s * 512, 256u};
+    return Slab{(int64_t)(s >> 3) * 4096 + (s & 7) * 256, 2048u};
 }
 
 __device__ __forceinline__ void dma16(const char* base, uint32_t byte_off, uint32_t lds_addr)

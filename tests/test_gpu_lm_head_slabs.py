@@ -97,7 +97,7 @@ def test_head_and_accept_against_float64_logits(hidden, vocab, eta):
 @pytest.mark.parametrize("hidden", [256, 1792, 2048, 2304, 4096, 128, 2176])
 @pytest.mark.parametrize("vocab", [16, 1601, 12317])
 def test_every_row_count_gives_the_same_logits(hidden, vocab):
-    """The builds for one to six row blocks, edges of the blocks on both sides, groups of slabs that end early (hidden not a
+    """The builds for one to six row blocks, edges of the blocks on both sides, slabs in one piece and in two (hidden a
     multiple of 2048), ranges of one to four and of twelve vocabulary blocks: against float64, and a row's logits do not
     depend on how many rows are in the call."""
     h, w = wl.gen_lm_head_inputs(96, hidden, vocab, salt=hidden + vocab)
