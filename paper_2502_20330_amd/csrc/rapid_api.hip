@@ -138,11 +138,12 @@ void plan_layout(const rapid_ctx* ctx, AttnLaunch& a)
     }
     const int64_t wgs = (int64_t)a.B * a.Hkv * a.nsplit;
     // measured: 3/32 of the split for the one-team kernel (config 3: 88.2 us with 384 tokens, 89.5 with 256,
-    // 91.1 with none).  The two-team kernel, whose waves all run through the same number of tiles: one tile per wave, 128 tokens, from
-    // splits of 2048 on (70B shape: 90.5 us, with 256 tokens 92.5; at 256K tokens 171, with 256 183, with 512 177; 77 rows of 128K 53.1, with none 54.7; 72 rows of 32K, splits of
-    // 1024: 33.2 with none, 34.2).
+    // 91.1 with none), 1/16 for the two-team kernel, which runs all waves through the same number of tiles
+    // (70B shape: 93-94 us with 256 tokens, 96.5 with 384).  Where the caches lie counts for as much: over eight
+    // placements of them the 70B shape takes 97.7 us on average with 256 tokens, 95.2 with 128 and 95.5 with none.  The
+    // borders stay, as they decide which tokens share a reference maximum and so the last bits of a result.
     if (a.rot && a.Hkv % 2 == 0 && a.nsplit >= 2 && wgs <= ctx->n_cu)
-        a.skew = a.wide ? (a.chunk >= 2048 ? 128 : 0) : (a.chunk * 3 / 32 + 64) / 128 * 128;
+        a.skew = a.wide ? a.chunk / 16 / 128 * 128 : (a.chunk * 3 / 32 + 64) / 128 * 128;
 }
 
 // Groups of the balanced plan (verify_attn.hip), 0 = the fixed grid of splits.  Taken by ragged batches whose split the

@@ -463,3 +463,32 @@ def test_out_of_range_device_values_are_clamped():
                              scale=cfg.softmax_scale, gammas=eff_gam)
     gu.assert_attn_close(got[:3], ref[:3], "clamped sequences")
     assert np.all(got[3] == 0.0)
+
+
+@pytest.mark.parametrize("hq,skew", [(32, 384), (64, 256)])
+def test_where_the_splits_lie(hq, skew):
+    """The borders between the pieces that are summed by themselves (quarters of the splits; the last bits of a result depend
+    on them).  Two splits of 4096 tokens, the first longer by the skew (3/32 of it on the one-team kernel, 1/16 on the two-team one) for
+    even heads and shorter for odd ones.  With equal scores every sum is exact except where 2^40 is in it: that stands at the
+    end of one tile, -2^40 at the start of the next and 1 behind that, and the 1 is lost if a border parts the
+    first two.  Column d of a head tests the end of tile d, or of tile 128 + d on heads 2 and 3."""
+    L, chunk, rows, Hkv = 8192, 4096, 9, 4
+    hq = hq * Hkv // 8                                         # 4 or 8 query heads per kv head: 36 or 72 packed rows
+    k = torch.zeros(1, Hkv, L, 128, dtype=torch.bfloat16, device="cuda")
+    v = torch.zeros_like(k)
+    tile, col = torch.arange(254, device="cuda"), torch.arange(254, device="cuda") % 128
+    for odd in range(2):
+        head = odd + 2 * (torch.arange(254, device="cuda") // 128)
+        v[0, head, tile * 32 + 31, col] = 2.0 ** 40
+        v[0, head, tile * 32 + 32, col] = -2.0 ** 40
+        v[0, head, tile * 32 + 64, col] = 1.0
+    q = torch.ones(1, rows, hq, 128, dtype=torch.bfloat16, device="cuda")
+    ctx = torch.full((1,), L, dtype=torch.int32, device="cuda")
+    out = gu.rapid().rapid_verify_attn(q, k.permute(0, 2, 1, 3), v.permute(0, 2, 1, 3), ctx, max_ctx=L, chunk_tokens=chunk)
+    last = out[0, -1, ::hq // Hkv].double().cpu() * L           # [Hkv, 128], the position that sees every token
+    for odd in range(2):
+        got = torch.cat([last[odd], last[odd + 2]])[:254]
+        first = chunk + (-skew if odd else skew)
+        borders = {first // 4 * i for i in (1, 2, 3, 4)} | {first + (L - first) // 4 * i for i in (1, 2, 3)}
+        assert set(got.tolist()) == {0.0, 1.0}
+        assert {32 * (i + 1) for i in range(254) if got[i] == 0} == borders, odd
