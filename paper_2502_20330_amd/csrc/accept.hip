@@ -38,7 +38,9 @@
 // bounded (wall-clock ticks): when a word stays unpublished, the waiting workgroup computes that
 // slice's publication itself from the logits in memory -- same code, same order of operations,
 // hence the same bits -- stores it, and goes on.  No workgroup ever depends on another one for
-// termination, and results do not depend on timing.
+// termination, and results do not depend on timing.  With a bound of 0 nothing is published at all, so that
+// every workgroup computes every slice (for tests; checked where words are stored, which costs less code than where
+// they are polled).
 //
 // Numerics: per-slice sums in fp32, combined in fp32 for the elementwise pass of accept_rows
 // and in fp64 for every decision; the accept ratio therefore carries a relative error of 2e-7 to
@@ -538,6 +540,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
     const int V = a.V, rows = a.gmax + 1;
     int bank = 0;
     const float c = a.inv_T * kLog2e, eta_l2 = a.eta * kLog2e;
+    const int teller = a.wait_ticks != 0 ? 0 : -1;            // the thread that publishes
 
     // Item id -> (w, k, b); g = drafts of its sequence (a device value, read one item ahead).
     auto row_t = [&](int b, int k) { return a.zt + ((int64_t)b * rows + k) * V; };
@@ -587,7 +590,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
             // (six sequences of 128256: 27.6 -> 26.5 us, 8 30.1 -> 29.0, 24 53.9 -> 52.7; one round or none: the same; 64 116.5 -> 116.8).
             __builtin_amdgcn_s_setprio(1);
             slice_stats<NW, NV, true>(reg_t, reg_d, put_t, put_d, own_t, own_d, c, lds.red, bank, mt, st, md, sd);
-            if (tid == 0) {
+            if (tid == teller) {
                 if (own_t) publish2f(slot_t + 2 * w, mt, st, tg);
                 if (own_d) publish2f(slot_d + 2 * w, md, sd, tg);
             }
@@ -618,8 +621,10 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
                     slice_stats<NW, NV, false>(mem_slice(zt, s), mem_slice(zd, s), drop, drop, miss_t, miss_d, c,
                                            lds.red, bank, mt, st, md, sd);
                     if (tid == 0) {
-                        if (miss_t) { keep2f(got, s, mt, st); publish2f(slot_t + 2 * s, mt, st, tg); }
-                        if (miss_d) { keep2f(got + W2w, s, md, sd); publish2f(slot_d + 2 * s, md, sd, tg); }
+                        if (miss_t) keep2f(got, s, mt, st);
+                        if (miss_d) keep2f(got + W2w, s, md, sd);
+                        if (miss_t && teller == 0) publish2f(slot_t + 2 * s, mt, st, tg);
+                        if (miss_d && teller == 0) publish2f(slot_d + 2 * s, md, sd, tg);
                         count_giveup(ws.status, tg);
                     }
                     __syncthreads();
@@ -711,7 +716,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
                 };
                 shifted_stats<NW, NV, true>(d_first, reg_t, lds.red, bank, mh, shs);
             }
-            if (tid == 0) publish2f(slot_h + 2 * w, mh, shs, tg);
+            if (tid == teller) publish2f(slot_h + 2 * w, mh, shs, tg);
             STAMP_AT(id, 4);
         }
 
@@ -773,7 +778,11 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
                             };
                             shifted_stats<NW, NV, false>(d_mem, d_mem, lds.red, bank, mh, shs);
                         }
-                        if (tid == 0) { keep2f(got_h, s, mh, shs); publish2f(slot_h + 2 * s, mh, shs, tg); count_giveup(ws.status, tg); }
+                        if (tid == 0) {
+                            keep2f(got_h, s, mh, shs);
+                            if (teller == 0) publish2f(slot_h + 2 * s, mh, shs, tg);
+                            count_giveup(ws.status, tg);
+                        }
                         __syncthreads();
                     }
                 }
@@ -978,6 +987,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
     STAMP(9);
     DrawNorm nm{1.0, 0.0, 0.0, 0.0, uniform((double)a.eta)};
     u64* my_slots = ws.slot_b + (int64_t)b * ws.w2 * 12;
+    const int teller = a.wait_ticks != 0 ? 0 : -1;            // the thread that publishes
 
     // Reduction of word `word` (0 / 1) of the current phase over all slices, in a fixed order (the
     // same in every workgroup): lanes take slices lane, lane + 64, ...; then the wave reduction.
@@ -998,7 +1008,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
         if (phase == 2) block_reduce2<NW>(a0, a1, lds.red, bank, OpAddD(), OpMaxD());
         else block_reduce2<NW>(a0, a1, lds.red, bank, OpAddD(), OpAddD());
         u64* base = my_slots + (phase - 1) * 4 * W2;         // slice s: words base[4 s .. 4 s + 3]
-        if (tid == 0) { put_d(base + 4 * w, a0, tg, true); put_d(base + 4 * w + 2, a1, tg, true); }
+        if (tid == teller) { put_d(base + 4 * w, a0, tg, true); put_d(base + 4 * w + 2, a1, tg, true); }
         poll_all<NT>(base, 4 * W2, lds.slots, lds.miss, a.wait_ticks, tg);
         __syncthreads();
         int miss = 0;
@@ -1022,8 +1032,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
                 if (tid == 0) {
                     put_d(lds.slots + 4 * s, m0, tg, false);
                     put_d(lds.slots + 4 * s + 2, m1, tg, false);
-                    put_d(base + 4 * s, m0, tg, true);
-                    put_d(base + 4 * s + 2, m1, tg, true);
+                    if (teller == 0) { put_d(base + 4 * s, m0, tg, true); put_d(base + 4 * s + 2, m1, tg, true); }
                     atomicAdd(ws.status + 1, 1);
                 }
                 __syncthreads();

@@ -64,7 +64,7 @@ struct AcceptLaunch {
     const float* ext_t;
     const float* ext_d;
     int32_t nch_t, nch_d;
-    int64_t wait_ticks;   // bound of an exchange wait in wall-clock ticks (100 MHz); 0 = never wait
+    int64_t wait_ticks;   // bound of an exchange wait in wall-clock ticks (100 MHz); 0 = publish nothing, compute every slice
     int32_t n_cu;         // compute units of the device (sizes the slices)
     int32_t fill_ratio;   // 1: ratios of positions past a sequence's drafts are written as 0, else left alone
     int32_t force_slice;  // 4096 / 8192 / 10240 / 16384 entries per slice; 0 = automatic

@@ -27,6 +27,16 @@ def rapid():
     return _rapid
 
 
+def draw_giveups(r) -> int:
+    """Exchange waits that gave up in accept_draw_row alone, in the last sampled rapid_accept call of `r`.  The status word counts both
+    kernels; accept_rows' share stands in words 10 (count) and 11 (tag of its call), and counts if that is the call's tag,
+    a function of the call counter in word 8, which has moved on by one since."""
+    torch.cuda.synchronize()
+    w = r._ws_accept[:256].view(torch.int32).cpu().numpy().astype(np.int64)
+    tag = ((w[8] - 1) * 0x9E3779B1 + 0x7F4A7C15) & 0xFFFFFFFF
+    return int(w[1] - (w[10] if w[11] & 0xFFFFFFFF == tag else 0))
+
+
 def bf16_to_dev(bits: np.ndarray) -> torch.Tensor:
     return torch.from_numpy(bits.view(np.int16)).cuda().view(torch.bfloat16)
 

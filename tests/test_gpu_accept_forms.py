@@ -110,10 +110,11 @@ def test_greedy_ties_masks_and_row_ends(V):
             assert np.all(toks[b, want + 1:] == -1)
 
 
-@pytest.mark.parametrize("batch,V", [(1, 20000), (1, 100001), (6, 100001), (24, 50257), (44, 50257), (600, 1030)])
-def test_every_build_of_the_draw_and_its_give_up_path(batch, V):
-    """Vocabularies and batches that select 2, 4, 8 and 20 entries per thread (one round of workgroups and several), a row
-    end inside a thread's entries; with every exchange recomputed the results are the same bits."""
+@pytest.mark.parametrize("batch,V,slices", [(1, 20000, 20), (1, 100001, 49), (6, 100001, 25), (24, 50257, 13), (44, 50257, 17), (600, 1030, 1)])
+def test_every_build_of_the_draw_and_its_give_up_path(batch, V, slices):
+    """Vocabularies and batches that select 2, 4, 8 (one round of one and of two workgroups per compute unit) and 12 entries per
+    thread, a row end inside a thread's entries; with every exchange recomputed the results are the same bits, and it is every one:
+    each of a sequence's `slices` workgroups gives up on all slices in each of the draw's exchanges (three, one for a bonus row)."""
     cfg = wl.scaled(wl.CONFIGS["llama8b_32k"], batch=batch, vocab=V, gamma_choices=(0, 1), draft_noise_std=2.0, name="draws")
     acc = wl.gen_accept_inputs(cfg, salt=V)
     r = gu.rapid()
@@ -123,6 +124,9 @@ def test_every_build_of_the_draw_and_its_give_up_path(batch, V):
             r.set_option(binding.OPT_ACCEPT_WAIT_US, wait)
             gpu, ref = gu.run_accept_case(acc, eta=cfg.eta)
             runs.append(gpu)
+            if wait == 0:
+                bonus = int((gpu[0] == acc.gammas).sum())
+                assert gu.draw_giveups(r) == slices ** 2 * (3 * (batch - bonus) + bonus)
     finally:
         r.set_option(binding.OPT_ACCEPT_WAIT_US, 100)
     for other in runs[1:]:
@@ -131,11 +135,11 @@ def test_every_build_of_the_draw_and_its_give_up_path(batch, V):
     assert st["n_mismatch"] == 0 and st["token_mismatch"] == 0 and st["exempt_sequences"] == 0, st
 
 
-@pytest.mark.parametrize("batch,V", [(61, 50257), (61, 49152), (1025, 1030)])
-def test_draws_beyond_one_round_of_workgroups(batch, V):
-    """The build of 16 entries (17 slices of 12 entries a sequence no longer fit four workgroups to a compute unit): slices that end
+@pytest.mark.parametrize("batch,V,slices", [(61, 50257, 13), (65, 49152, 12), (1025, 1030, 1)])
+def test_draws_beyond_one_round_of_workgroups(batch, V, slices):
+    """The build of 16 entries (17 and 16 slices of 12 entries a sequence no longer fit four workgroups to a compute unit): slices that end
     inside a thread's entries and with the row, and one slice per sequence; the give-up path included."""
-    test_every_build_of_the_draw_and_its_give_up_path(batch, V)
+    test_every_build_of_the_draw_and_its_give_up_path(batch, V, slices)
 
 
 @pytest.mark.parametrize("g", [1023, 1024, 1100, 20000])
