@@ -314,13 +314,15 @@ __device__ __forceinline__ void poll_into(Addr addr, int lo, int hi, u64* dst, i
 // The first look comes half a microsecond (20 x 64 cycles) after the own publication, when the others' are usually there: a
 // look in vain costs its round trip and holds up the stores that it waits for (one sequence, the whole pass: no delay 22.9 us, 8 x 64 cycles
 // 21.5, 16 20.4, 20 20.1, 28 20.5, 40 21.3; 64 sequences 124.3, 121.0, 120.0, 118.4, 117.5, 118.4; two looks in flight instead: 24 and 145).
+// Up to four slices report sooner than that (eight sequences of 2048 entries: 17.5 us without the delay, 18.2 with it; of 4000 17.5 and 18.2; five
+// slices: 17.7 and 17.8; nine: 18.1 and 18.2; twelve 18.6 and 18.3).
 template <int NT>
 __device__ __forceinline__ void poll_all(const u64* words, int n, u64* dst, int* miss, int64_t wait_ticks, const Tags& tg)
 {
     const int64_t t0 = (int64_t)wall_clock64();
     const uint32_t want = tag_of(threadIdx.x, tg);        // NT is even: every word of a thread has its parity
     int m = 0;
-    if (n > 4) __builtin_amdgcn_s_sleep(20);              // (one slice: the own one)
+    if (n > 16) __builtin_amdgcn_s_sleep(20);
     for (int i0 = 0; i0 < n; i0 += NT) {
         const int i = i0 + threadIdx.x;
         u64 v = 0;
