@@ -938,7 +938,7 @@ __device__ __forceinline__ void draw_accumulate(int phase, double et, double ed,
 template <class A, class B>
 __device__ __forceinline__ void after(A& done, B& later) { asm volatile("" : "+v"(done), "+v"(later)); }
 
-// NT threads of NE entries.  OCC = waves per SIMD the kernel is compiled for; at 4 (128 registers) the entries are taken one
+// NT threads of NE entries.  OCC = waves per SIMD the kernel is compiled for; at 4 (128 registers) and with 20 entries the entries are taken one
 // at a time, each tied to the one before it: left alone, or with a compiler barrier between them, the scheduler holds the temporaries
 // of many (16 entries of six registers in 128, 20 in 156; with a barrier 20 took 224 and 24 spilled).
 template <int NT, int NE, int OCC>
@@ -946,7 +946,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
 {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     constexpr int NW = NT / 64;
-    constexpr bool kOneByOne = OCC > 2;                   // few registers: one entry's temporaries at a time
+    constexpr bool kOneByOne = OCC > 2 || NE > 8;         // few registers: one entry's temporaries at a time
     LdsB& lds = *reinterpret_cast<LdsB*>(smem_raw);
     constexpr int kSlice = NT * NE;
     const int w = blockIdx.x, b = blockIdx.y;
@@ -1201,10 +1201,12 @@ size_t accept_workspace_bytes(int B, int gmax, int V)
 // The build of accept_draw_row for a call.  Small batches: the fewest entries per thread that leave every workgroup a
 // compute unit of its own and keep the exchange among at most 64 workgroups (one sequence: vocabulary 32001 22.1 us
 // with 2, 23.0 with 4, 26.7 with 8; 128256 23.7 with 2 on 126 workgroups, 23.0 with 4, 25.0 with 8).  Eight entries while
-// the grid is one round of two workgroups per compute unit; beyond that 256 threads, four workgroups per compute unit: twelve entries while
-// that is one round (20 sequences of 152064: 35.9 us, with 16 entries 38.9), else 16.  What counts there is how many waves stand by
-// while others wait in the three exchanges, and how many rounds of them there are (64 sequences of 128256, the whole pass: 16 entries 124 us,
-// 12 130, 8 in six waves per SIMD 147, 20 in three 127, 24 in two 133; 20 in two, the build before, 138; 32 sequences 70.5 against 78.6).
+// the grid is one round of two workgroups per compute unit; beyond that 256 threads.  What counts there is how many waves stand by
+// while others wait in the three exchanges, and how many entries a compute unit has to take: twelve entries, up to four workgroups per
+// compute unit, while that is one round (20 sequences of 152064: 35.9 us, with 16 entries 38.9), but 20 entries in two workgroups where twelve need the
+// fourth and 20 do not need a third, 40 entries instead of 48 for the busiest compute units (48 sequences of 50257 53.9 -> 52.7 us, 32 of 75000 56.1 -> 54.7, 10 of
+// 256000 58.6 -> 55.7; where most rows are bonus rows, with a single exchange, up to 4 % slower: 16 sequences of 152064 36.0 -> 37.1); else 16 in four workgroups (64 sequences of 128256, the whole pass: 16 entries 124 us,
+// 12 130, 8 in six waves per SIMD 147, 20 in three 127, 24 in two 133; 20 in two, the only build before, 138; 32 sequences 70.5 against 78.6).
 struct DrawShape {
     void (*kernel)(AcceptLaunch, Ws, int);
     int threads, wgs;
@@ -1217,7 +1219,8 @@ static DrawShape draw_shape(const AcceptLaunch& a)
     if (w4 <= 64 && (int64_t)w4 * a.B <= a.n_cu) return {accept_draw_row<512, 4, 2>, 512, w4};
     if ((int64_t)w8 * a.B <= a.n_cu) return {accept_draw_row<512, 8, 2>, 512, w8};
     if ((int64_t)w8 * a.B <= 2 * (int64_t)a.n_cu) return {accept_draw_row<512, 8, 4>, 512, w8};
-    const int w12 = wgs(256, 12);
+    const int w12 = wgs(256, 12), w20 = wgs(256, 20);
+    if ((int64_t)w12 * a.B > 3 * (int64_t)a.n_cu && (int64_t)w20 * a.B <= 2 * (int64_t)a.n_cu) return {accept_draw_row<256, 20, 2>, 256, w20};
     if ((int64_t)w12 * a.B <= 4 * (int64_t)a.n_cu) return {accept_draw_row<256, 12, 4>, 256, w12};
     return {accept_draw_row<256, 16, 4>, 256, wgs(256, 16)};
 }
