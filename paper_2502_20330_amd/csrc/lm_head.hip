@@ -64,18 +64,17 @@ struct Tile {
 };
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Where slab s of a row lies.  128-wide slabs: one run of 256 bytes.  256-wide ones: two, the second `half` bytes behind the first: in
-// rows that are a multiple of 4 KiB, the runs of eight slabs fill either half of 4 KiB in turn; else they adjoin (a pitch that is no
-// multiple of 4 KiB spreads the rows of a tile by itself, and whole lines of 512 bytes are 1 % faster: 9 rows of 3072 x 128256
-// 118.4 us against 120.1, 5 of 2304 x 100000 69.9 against 71.1).
-struct Slab { int64_t byte; uint32_t half; };
-template <int SK>
-__device__ __forceinline__ Slab slab_at(int s, int nslab)
-{
-    if (SK == 128) return Slab{(int64_t)s * 256, 0u};
-    if (nslab & 7) return Slab{(int64_t)s * 512, 256u};
-    return Slab{(int64_t)(s >> 3) * 4096 + (s & 7) * 256, 2048u};
-}
+// Where the slabs of a row lie.  128-wide slabs: one run of 256 bytes.  256-wide ones: two, the second kHalf bytes behind the first: in
+// rows that are a multiple of 4 KiB (TWO), the runs of eight slabs fill either half of 4 KiB in turn; else they adjoin (such a
+// pitch spreads the rows of a tile by itself, and whole lines of 512 bytes are 1 % faster: 9 rows of 3072 x 128256
+// 118.4 us against 120.1, 5 of 2304 x 100000 69.9 against 71.1).  A template parameter: told apart
+// at every load it made heads of a few thousand entries 3 to 10 % slower.
+template <int SK, bool TWO>
+struct Slabs {
+    static_assert(SK == 256 || !TWO, "");
+    static constexpr uint32_t kHalf = TWO ? 2048u : 256u;
+    static __device__ __forceinline__ int64_t byte(int s) { return TWO ? (int64_t)(s >> 3) * 4096 + (s & 7) * 256 : (int64_t)s * SK * 2; }
+};
 
 __device__ __forceinline__ void dma16(const char* base, uint32_t byte_off, uint32_t lds_addr)
 {
@@ -179,10 +178,11 @@ __device__ __forceinline__ void epilogue(const LmHeadLaunch& a, const floatx4 (&
     }
 }
 
-template <int SK, int NR>
+template <int SK, int NR, bool TWO>
 __global__ void __launch_bounds__(kWaves * 64) lm_head_stream(LmHeadLaunch a)
 {
     using T = Tile<SK>;
+    using At = Slabs<SK, TWO>;
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -198,31 +198,30 @@ __global__ void __launch_bounds__(kWaves * 64) lm_head_stream(LmHeadLaunch a)
     // Per-lane byte offsets of the loads of a tile, relative to the tile's first row and the slab:
     // instruction e moves RPI consecutive rows; lane i writes LDS bytes [16 i, 16 i + 16) of that
     // 1 KiB and fetches the chunk the swizzle assigns there (chunks 16..31: the slab's second run).
-    uint32_t coff[T::NLD];
+    uint32_t woff[T::NLD], coff[T::NLD];
     int rrow[T::NLD];
-    const uint32_t second = (lane % T::CPR) / 16;
 #pragma unroll
     for (int e = 0; e < T::NLD; ++e) {
         rrow[e] = T::RPI * e + lane / T::CPR;
-        coff[e] = (uint32_t)((lane % 16) ^ (rrow[e] & 15)) * 16u;
+        coff[e] = (uint32_t)((lane % 16) ^ (rrow[e] & 15)) * 16u + (uint32_t)((lane % T::CPR) / 16) * At::kHalf;
+        woff[e] = (uint32_t)rrow[e] * row_bytes + coff[e];
     }
     auto block_row0 = [&](int jj) { return loaded_row0(a, v0 + (jj * kWaves + wave) * 16); };
 
     // tile j of slab s: j = 0..NR-1 the row blocks of the h slab, j = NR.. the wave's W blocks
     auto issue = [&](int s, int j, int slot) {
-        const Slab at = slab_at<SK>(s, nslab);
-        const uint32_t off = second * at.half;
+        const int64_t kbyte = At::byte(s);
         const uint32_t dst = ring_lds + slot * T::BYTES;
         if (j < NR) {
-            const char* base = reinterpret_cast<const char*>(a.h) + at.byte;
+            const char* base = reinterpret_cast<const char*>(a.h) + kbyte;
 #pragma unroll
             for (int e = 0; e < T::NLD; ++e)
-                dma16_keep(base, (uint32_t)min(j * 16 + rrow[e], a.n_rows - 1) * row_bytes + coff[e] + off, dst + e * 1024);
+                dma16_keep(base, (uint32_t)min(j * 16 + rrow[e], a.n_rows - 1) * row_bytes + coff[e], dst + e * 1024);
             return;
         }
-        const char* base = reinterpret_cast<const char*>(a.w) + (int64_t)block_row0(j - NR) * row_bytes + at.byte;
+        const char* base = reinterpret_cast<const char*>(a.w) + (int64_t)block_row0(j - NR) * row_bytes + kbyte;
 #pragma unroll
-        for (int e = 0; e < T::NLD; ++e) dma16(base, (uint32_t)rrow[e] * row_bytes + coff[e] + off, dst + e * 1024);
+        for (int e = 0; e < T::NLD; ++e) dma16(base, woff[e], dst + e * 1024);
     };
 
     floatx4 acc[kNBW][NR];
@@ -298,10 +297,11 @@ struct Shared {
     static constexpr int LDS = HBYTES + RED + kWaves * SLOTS * UNIT;
 };
 
-template <int NR>
+template <int NR, bool TWO>
 __global__ void __launch_bounds__(kWaves * 64) lm_head_shared(LmHeadLaunch a)
 {
     using S = Shared<NR>;
+    using At = Slabs<256, TWO>;
     constexpr int KH = 4;                                // k-steps of a unit
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -326,21 +326,19 @@ __global__ void __launch_bounds__(kWaves * 64) lm_head_shared(LmHeadLaunch a)
     }
     // This wave's share of slab s of h: 1 KiB (two rows) of every 4.
     auto issue_h = [&](int s) {
-        const Slab at = slab_at<256>(s, nslab);
-        const char* base = reinterpret_cast<const char*>(a.h) + at.byte;
+        const char* base = reinterpret_cast<const char*>(a.h) + At::byte(s);
 #pragma unroll
         for (int i = 0; i < S::HLD; ++i) {
             const int e = i * kWaves + wave, row = 2 * e + lane / 32;
-            const uint32_t c = (uint32_t)((lane & 15) ^ (row & 15)) * 16u + (uint32_t)((lane & 31) / 16) * at.half;
+            const uint32_t c = (uint32_t)((lane & 15) ^ (row & 15)) * 16u + (uint32_t)((lane & 31) / 16) * At::kHalf;
             dma16_keep(base, (uint32_t)min(row, a.n_rows - 1) * row_bytes + c, h_lds + e * 1024);
         }
     };
     // The next unit to request: half pq of slab ps of block pj; past the end any valid one keeps the count uniform.
     int ps = 0, pj = 0, pq = 0, pslot = 0;
     auto request_next = [&]() {
-        const Slab at = slab_at<256>(min(ps, nslab - 1), nslab);
         const char* base = reinterpret_cast<const char*>(a.w) +
-                           (int64_t)loaded_row0(a, v0 + (pj * kWaves + wave) * 16) * row_bytes + at.byte + (pq ? at.half : 0u);
+                           (int64_t)loaded_row0(a, v0 + (pj * kWaves + wave) * 16) * row_bytes + At::byte(min(ps, nslab - 1)) + (pq ? At::kHalf : 0u);
 #pragma unroll
         for (int e = 0; e < S::ULD; ++e) dma16(base, woff[e], ring_lds + pslot * S::UNIT + e * 1024);
         if (++pslot == S::SLOTS) pslot = 0;
@@ -403,62 +401,72 @@ __global__ void __launch_bounds__(kWaves * 64) lm_head_shared(LmHeadLaunch a)
 }  // namespace
 
 namespace {
-// The build for a slab width and a number of row blocks.
-template <int SK, int NR>
-struct Build {
-    static constexpr bool kShared = SK == 256 && NR >= 4;
-    static constexpr int kLds = kShared ? Shared<NR>::LDS : lds_bytes();
-    static auto kernel()
-    {
-        if constexpr (kShared) return lm_head_shared<NR>;
-        else return lm_head_stream<SK, NR>;
+// Calls f(kernel, bytes of LDS) for a build: 128-wide slabs, 256-wide ones in adjoining or in two runs, and these with h shared.
+enum Kind { kNarrow, kAdjoining, kTwoRuns, kSharedAdjoining, kSharedTwoRuns };
+template <int NR, class F>
+hipError_t for_build(Kind kind, F f)
+{
+    if constexpr (NR >= 4) {
+        if (kind == kSharedAdjoining) return f(lm_head_shared<NR, false>, Shared<NR>::LDS);
+        if (kind == kSharedTwoRuns) return f(lm_head_shared<NR, true>, Shared<NR>::LDS);
+    } else {
+        if (kind == kTwoRuns) return f(lm_head_stream<256, NR, true>, lds_bytes());
     }
-};
-template <int SK, int NR>
-hipError_t configure_one()
-{
-    using B = Build<SK, NR>;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(B::kernel()), hipFuncAttributeMaxDynamicSharedMemorySize, B::kLds);
+    if (kind == kNarrow || NR >= 4) return f(lm_head_stream<128, NR, false>, lds_bytes());
+    return f(lm_head_stream<256, (NR < 4 ? NR : 1), false>, lds_bytes());
 }
-template <int SK, int NR>
-void launch_one(const LmHeadLaunch& a, int nwg, hipStream_t stream)
+// The 256-wide slab when the hidden size allows, else the 128-wide one; from four row blocks on the workgroup shares h.
+Kind kind_of(const LmHeadLaunch& a, int nr)
 {
-    using B = Build<SK, NR>;
-    hipLaunchKernelGGL(B::kernel(), dim3(nwg), dim3(kWaves * 64), B::kLds, stream, a);
+    if (a.hidden % 256 != 0) return kNarrow;
+    const bool two_runs = a.hidden % 2048 == 0;
+    if (nr >= 4) return two_runs ? kSharedTwoRuns : kSharedAdjoining;
+    return two_runs ? kTwoRuns : kAdjoining;
+}
+template <int NR>
+hipError_t configure_rows()
+{
+    for (Kind kind : {kNarrow, kAdjoining, kTwoRuns, kSharedAdjoining, kSharedTwoRuns}) {
+        const hipError_t e = for_build<NR>(kind, [](auto kernel, int lds) {
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        });
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+template <int NR>
+hipError_t launch_rows(const LmHeadLaunch& a, hipStream_t stream)
+{
+    const int nwg = (a.vocab + a.nb * 16 - 1) / (a.nb * 16);
+    return for_build<NR>(kind_of(a, NR), [&](auto kernel, int lds) {
+        hipLaunchKernelGGL(kernel, dim3(nwg), dim3(kWaves * 64), lds, stream, a);
+        return hipGetLastError();
+    });
 }
 }  // namespace
 
 hipError_t configure_lm_head()
 {
     hipError_t e;
-    if ((e = configure_one<256, 1>()) != hipSuccess) return e;
-    if ((e = configure_one<128, 1>()) != hipSuccess) return e;
-    if ((e = configure_one<256, 2>()) != hipSuccess) return e;
-    if ((e = configure_one<128, 2>()) != hipSuccess) return e;
-    if ((e = configure_one<128, 3>()) != hipSuccess) return e;
-    if ((e = configure_one<128, 4>()) != hipSuccess) return e;
-    if ((e = configure_one<128, 5>()) != hipSuccess) return e;
-    if ((e = configure_one<128, 6>()) != hipSuccess) return e;
-    if ((e = configure_one<256, 3>()) != hipSuccess) return e;
-    if ((e = configure_one<256, 4>()) != hipSuccess) return e;
-    if ((e = configure_one<256, 5>()) != hipSuccess) return e;
-    return configure_one<256, 6>();
+    if ((e = configure_rows<1>()) != hipSuccess) return e;
+    if ((e = configure_rows<2>()) != hipSuccess) return e;
+    if ((e = configure_rows<3>()) != hipSuccess) return e;
+    if ((e = configure_rows<4>()) != hipSuccess) return e;
+    if ((e = configure_rows<5>()) != hipSuccess) return e;
+    return configure_rows<6>();
 }
 
-// Row blocks of 16 rows of h; the 256-wide slab when the hidden size allows, else the 128-wide one.
 hipError_t launch_lm_head(const LmHeadLaunch& a, hipStream_t stream)
 {
-    const int nwg = (a.vocab + a.nb * 16 - 1) / (a.nb * 16);
-    const int nr = (a.n_rows + 15) / 16;
-    if (a.hidden % 128 != 0 || nr < 1 || nr > 6 || a.nb < 1 || a.nb > kNB) return hipErrorInvalidValue;
-    const bool wide_slab = a.hidden % 256 == 0;
+    const int nr = (a.n_rows + 15) / 16;                 // row blocks of 16 rows of h
+    if (a.hidden % 128 != 0 || a.nb < 1 || a.nb > kNB) return hipErrorInvalidValue;
     switch (nr) {
-        case 1: wide_slab ? launch_one<256, 1>(a, nwg, stream) : launch_one<128, 1>(a, nwg, stream); break;
-        case 2: wide_slab ? launch_one<256, 2>(a, nwg, stream) : launch_one<128, 2>(a, nwg, stream); break;
-        case 3: wide_slab ? launch_one<256, 3>(a, nwg, stream) : launch_one<128, 3>(a, nwg, stream); break;
-        case 4: wide_slab ? launch_one<256, 4>(a, nwg, stream) : launch_one<128, 4>(a, nwg, stream); break;
-        case 5: wide_slab ? launch_one<256, 5>(a, nwg, stream) : launch_one<128, 5>(a, nwg, stream); break;
-        default: wide_slab ? launch_one<256, 6>(a, nwg, stream) : launch_one<128, 6>(a, nwg, stream); break;
+        case 1: return launch_rows<1>(a, stream);
+        case 2: return launch_rows<2>(a, stream);
+        case 3: return launch_rows<3>(a, stream);
+        case 4: return launch_rows<4>(a, stream);
+        case 5: return launch_rows<5>(a, stream);
+        case 6: return launch_rows<6>(a, stream);
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
