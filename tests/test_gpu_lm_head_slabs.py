@@ -116,3 +116,16 @@ def test_every_row_count_gives_the_same_logits(hidden, vocab):
         assert torch.equal(stats[..., 0], z.amax(-1)), rows
         torch.testing.assert_close(stats[..., 1].double(), torch.exp(z.double() - z.double().amax(-1, True)).sum(-1),
                                    rtol=2e-5, atol=0)
+
+
+@pytest.mark.parametrize("hidden", [1280, 2048, 4096, 6144, 8192, 12288, 16384, 18432, 24576, 32768])
+def test_pitches_at_which_a_slab_is_two_runs(hidden):
+    """The order of the sum over the hidden dimension: slabs of 256, or, where rows of W are a multiple of 4 KiB but no
+    power of two from 16 KiB on, of 128 and the 128 that lie 2 KiB further on.  With 2^30 first, -2^30 at 1024 and 1 at 128, the 1 is lost
+    unless the other two meet before it is added."""
+    w = torch.zeros(1601, hidden, dtype=torch.bfloat16, device="cuda")
+    w[:, 0], w[:, 1024], w[:, 128] = 2.0 ** 30, -2.0 ** 30, 1.0
+    two_runs = 2 * hidden % 4096 == 0 and 2 * hidden not in (1 << 14, 1 << 15, 1 << 16)
+    for rows in (1, 17, 48, 49, 96):
+        logits, _ = gu.rapid().rapid_lm_head(torch.ones(rows, hidden, dtype=torch.bfloat16, device="cuda"), w)
+        assert torch.all(logits == float(two_runs)), rows
