@@ -97,9 +97,9 @@ def test_head_and_accept_against_float64_logits(hidden, vocab, eta):
 @pytest.mark.parametrize("hidden", [256, 1792, 2048, 2304, 4096, 128, 2176])
 @pytest.mark.parametrize("vocab", [16, 1601, 12317])
 def test_every_row_count_gives_the_same_logits(hidden, vocab):
-    """The builds for one to six row blocks, edges of the blocks on both sides, slabs in one piece and in two (hidden a
-    multiple of 2048), ranges of one to four and of twelve vocabulary blocks: against float64, and a row's logits do not
-    depend on how many rows are in the call."""
+    """The builds for one to six row blocks, edges of the blocks on both sides, slabs in one piece and in two (2048, 4096),
+    ranges of one and of four vocabulary blocks, that is at most one for a wave: against float64, and a row's logits do
+    not depend on how many rows are in the call."""
     h, w = wl.gen_lm_head_inputs(96, hidden, vocab, salt=hidden + vocab)
     hd, wd = gu.bf16_to_dev(h), gu.bf16_to_dev(w)
     ref = hd.double().cpu() @ wd.double().cpu().t()
@@ -129,3 +129,27 @@ def test_pitches_at_which_a_slab_is_two_runs(hidden):
     for rows in (1, 17, 48, 49, 96):
         logits, _ = gu.rapid().rapid_lm_head(torch.ones(rows, hidden, dtype=torch.bfloat16, device="cuda"), w)
         assert torch.all(logits == float(two_runs)), rows
+
+
+@pytest.mark.parametrize("hidden", [256, 1792, 2048, 8192])
+@pytest.mark.parametrize("vocab,blocks", [(33001, 9), (57001, 14), (68001, 17), (131072, 32)])
+def test_waves_with_many_vocabulary_blocks(hidden, vocab, blocks):
+    """The steady state of the builds for four to six row blocks: two to eight vocabulary blocks a wave, unevenly among the
+    waves or evenly, so that loads of a slab of h are waited for by count or drained, and units of W requested before or after
+    them; at 8192 also the line between the two kernels (4 NR blocks).  Against float64, and the same bits as in a
+    call of fewer rows."""
+    r = gu.rapid()
+    assert r.lm_head_chunk(vocab, 96) == 16 * blocks
+    g = torch.Generator(device="cuda").manual_seed(hidden + vocab)
+    h = torch.randn(96, hidden, device="cuda", generator=g).bfloat16()
+    w = (torch.randn(vocab, hidden, device="cuda", generator=g, dtype=torch.bfloat16) * (4 / hidden ** 0.5))
+    few = [r.rapid_lm_head(h[i:i + 16].contiguous(), w)[0] for i in range(0, 96, 16)]
+    whole = torch.cat(few)
+    for at in range(0, vocab, 16384):
+        ref = h.double() @ w[at:at + 16384].double().t().contiguous()
+        assert torch.all((whole[:, at:at + 16384].double() - ref).abs() <= 5e-5 + 1e-5 * ref.abs())
+    for rows in (48, 49, 64, 65, 80, 81, 96):
+        logits, stats = r.rapid_lm_head(h[:rows].contiguous(), w)
+        assert torch.equal(logits, whole[:rows]), rows
+        z = torch.nn.functional.pad(logits, (0, stats.shape[1] * 16 * blocks - vocab), value=-np.inf).view(rows, -1, 16 * blocks)
+        assert torch.equal(stats[..., 0], z.amax(-1)), rows
