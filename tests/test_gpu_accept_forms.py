@@ -314,23 +314,31 @@ def test_greedy_decision_of_any_number_of_waves(B, g, V):
 
 @pytest.mark.parametrize("T", [1.0, 0.0])
 def test_ratios_past_a_sequences_drafts(T):
-    """The buffer that the binding makes is written in full, 0 past a sequence's own drafts, whatever the memory held; a
-    buffer of the caller's keeps what it holds there."""
+    """rapid_accept_filled writes all of a ratio buffer, 0 past a sequence's own drafts, whatever it held (here NaN); the binding calls it
+    for a buffer that it makes.  A buffer of the caller's keeps what it holds there."""
     cfg = wl.scaled(wl.CONFIGS["llama8b_32k"], batch=6, vocab=5003, gamma_choices=(0, 1, 3), draft_noise_std=2.0, name="ratios")
     acc = wl.gen_accept_inputs(cfg, salt=7)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
-    gam = np.asarray(acc.gammas, dtype=np.int32)
-    args = [dev(x) for x in (acc.target_logits, acc.draft_logits, acc.draft_tokens)] + [1.0, dev(acc.uniforms)]
+    gam = dev(np.asarray(acc.gammas, dtype=np.int32))
+    zt, zd, tok, u = (dev(x) for x in (acc.target_logits, acc.draft_logits, acc.draft_tokens, acc.uniforms))
     r = gu.rapid()
     B, g = acc.draft_tokens.shape
-    mine = torch.full((B, g), 7.0, device="cuda")
-    outs = (torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, g + 1), dtype=torch.int32, device="cuda"), mine)
-    r.rapid_accept(*args, gammas=dev(gam), temperature=T, outs=outs)
-    for _ in range(3):
-        torch.full((B, g), float("nan"), device="cuda")        # what the next allocation of this size may hold
-        n, toks, ratio = r.rapid_accept(*args, gammas=dev(gam), temperature=T)
-        past = torch.arange(g, device="cuda")[None] >= dev(gam)[:, None]
-        assert past.any() and not past.all()
-        assert torch.equal(ratio[past], torch.zeros_like(ratio[past])) and torch.equal(mine[past], torch.full_like(mine[past], 7.0))
-        assert torch.equal(ratio[~past].view(torch.int32), mine[~past].view(torch.int32))
-        assert torch.equal(n, outs[0]) and torch.equal(toks, outs[1])
+    past = torch.arange(g, device="cuda")[None] >= gam[:, None]
+    assert past.any() and not past.all()
+
+    def buffers(fill):
+        return (torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty((B, g + 1), dtype=torch.int32, device="cuda"),
+                torch.full((B, g), fill, device="cuda"))
+    n, toks, mine = buffers(7.0)
+    r.rapid_accept(zt, zd, tok, 1.0, u, gammas=gam, temperature=T, outs=(n, toks, mine))
+    assert torch.equal(mine[past], torch.full_like(mine[past], 7.0))
+    filled = buffers(float("nan"))
+    ws = torch.zeros(r.lib.rapid_accept_workspace_bytes(r._ctx, B, g, zt.shape[2]), dtype=torch.uint8, device="cuda")
+    rc = r.lib.rapid_accept_filled(r._ctx, B, g, zt.shape[2], zt.data_ptr(), zd.data_ptr(), tok.data_ptr(), gam.data_ptr(), 1.0, T, 0.1,
+                                   u.data_ptr(), None, 0, None, 0, *(t.data_ptr() for t in filled), ws.data_ptr(), ws.numel(),
+                                   torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    for out in (filled, r.rapid_accept(zt, zd, tok, 1.0, u, gammas=gam, temperature=T)):
+        assert torch.equal(out[0], n) and torch.equal(out[1], toks)
+        assert torch.equal(out[2][~past].view(torch.int32), mine[~past].view(torch.int32))
+        assert torch.equal(out[2][past].view(torch.int32), torch.zeros_like(out[2][past]).view(torch.int32))
