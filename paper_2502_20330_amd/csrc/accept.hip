@@ -940,7 +940,9 @@ __device__ __forceinline__ void after(A& done, B& later) { asm volatile("" : "+v
 
 // NT threads of NE entries.  OCC = waves per SIMD the kernel is compiled for; at 4 (128 registers) and with 20 entries the entries are taken one
 // at a time, each tied to the one before it: left alone, or with a compiler barrier between them, the scheduler holds the temporaries
-// of many (16 entries of six registers in 128, 20 in 156; with a barrier 20 took 224 and 24 spilled).
+// of many.  As compiled: 12 entries take 111 registers, 20 take 159 (with a barrier 224, and 24 entries spilled), 16 take 128 and
+// spill eight (36 bytes of scratch a thread, written and read back once between the phases: 4 of the 75 MB that the kernel moves for 64 sequences of
+// 128256); it is the fastest of the builds measured there all the same (draw_shape).
 template <int NT, int NE, int OCC>
 __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws, int W2)
 {

@@ -123,7 +123,8 @@ int plan_chunk(const rapid_ctx* ctx, const rapid_attn_shape* s)
 //  * skew: with a single wave of workgroups (one per compute unit) the dies on odd
 //    dispatch slots finish 10..15 % later than the even ones.  Moving about a tenth of a
 //    split from each odd-slot workgroup to its even-slot pair partner evens that out
-//    (2..3 % on the whole call).  With several workgroups per compute unit the
+//    (2..3 % on the whole call).  It also moves which addresses the waves read at a time, so
+//    that its gain depends on where the caches lie.  With several workgroups per compute unit the
 //    dispatcher balances by itself and the skew only hurts.
 // The skew is a multiple of 128 tokens so both partners keep whole tiles per wave.
 void plan_layout(const rapid_ctx* ctx, AttnLaunch& a)
