@@ -940,9 +940,11 @@ __device__ __forceinline__ void after(A& done, B& later) { asm volatile("" : "+v
 
 // NT threads of NE entries.  OCC = waves per SIMD the kernel is compiled for; at 4 (128 registers) and with 20 entries the entries are taken one
 // at a time, each tied to the one before it: left alone, or with a compiler barrier between them, the scheduler holds the temporaries
-// of many.  As compiled: 12 entries take 111 registers, 20 take 159 (with a barrier 224, and 24 entries spilled), 16 take 128 and
-// spill eight (36 bytes of scratch a thread, written and read back once between the phases: 4 of the 75 MB that the kernel moves for 64 sequences of
-// 128256); it is the fastest of the builds measured there all the same (draw_shape).
+// of many.  As compiled: 12 entries take 111 registers, 20 take 159 (with a barrier 224, and 24 entries spilled), 16 take 127 with six
+// weights a thread in LDS.  With these in registers too it spilled eight, which cost no time in a call (64 sequences of 128256: 137.5 us, 138.0 spilled)
+// but scratch memory: the first launch of a process took 1150 us instead of 985, and was once held up for so long between workgroups that
+// their waits ran out and 10752 slices were computed again.
+constexpr int draw_in_lds(int ne) { return ne == 16 ? 6 : 0; }      // weights of a thread in LDS, the last ones
 template <int NT, int NE, int OCC>
 __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws, int W2)
 {
@@ -950,7 +952,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
     constexpr int NW = NT / 64;
     constexpr bool kOneByOne = OCC > 2 || NE > 8;         // few registers: one entry's temporaries at a time
     LdsB& lds = *reinterpret_cast<LdsB*>(smem_raw);
-    constexpr int kSlice = NT * NE;
+    constexpr int kSlice = NT * NE, kInRegs = NE - draw_in_lds(NE);
     const int w = blockIdx.x, b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     STAMP(8);
@@ -968,8 +970,12 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
     const double Mt = uniform(rec[0]), Md = uniform(rec[1]), invT = a.inv_T_exact;
 
     // own slice: e_t, e_d of the thread's entries, kept in registers for all phases; wgt holds
-    // f = e_t exp(eta (q - p)) after phase 2 and the draw weight after phase 3
+    // f = e_t exp(eta (q - p)) after phase 2 and the draw weight after phase 3, from kInRegs on put into LDS in between (read by no
+    // other thread)
     double et[NE], ed[NE], wgt[NE];
+    double* in_lds = reinterpret_cast<double*>(lds.slots + 4 * W2) + tid;
+    auto put = [&](int i) { if constexpr (kInRegs < NE) if (i >= kInRegs) in_lds[(i - kInRegs) * NT] = wgt[i]; };
+    auto fetch = [&](int i) { if constexpr (kInRegs < NE) if (i >= kInRegs) wgt[i] = in_lds[(i - kInRegs) * NT]; };
     auto next = [](int i) { return i + 1 < NE ? i + 1 : i; };
     const int first = w * kSlice + tid * NE;
     float t_in[NE], d_in[NE];
@@ -1068,6 +1074,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
                 wgt[i] = draw_f(et[i], ed[i], nm, lds.tab);
                 a0 += wgt[i];
                 a1 = fmax(a1, wgt[i]);
+                put(i);
                 if (kOneByOne) {
                     after(a0, et[next(i)]);
                     after(a1, ed[next(i)]);
@@ -1084,9 +1091,11 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
 #pragma unroll
             for (int i = 0; i < NE; ++i) {
                 double p;
+                fetch(i);
                 wgt[i] = draw_weight(et[i], ed[i], wgt[i], nm, p);
                 a0 += wgt[i];
                 a1 += p;
+                put(i);
                 if (kOneByOne) {
                     after(a0, et[next(i)]);
                     after(a1, ed[next(i)]);
@@ -1157,6 +1166,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_draw_row(AcceptLaunch a, Ws ws
     double seg = 0.0;
 #pragma unroll
     for (int i = 0; i < NE; ++i) {
+        fetch(i);                                             // (a bonus row has put nothing there, and does not use it)
         if (bonus) wgt[i] = et[i];
         else if (word == 1) wgt[i] = et[i] * nm.iSt;           // (else: the residual weight from phase 3)
         seg += wgt[i];
@@ -1211,7 +1221,7 @@ size_t accept_workspace_bytes(int B, int gmax, int V)
 // 12 130, 8 in six waves per SIMD 147, 20 in three 127, 24 in two 133; 20 in two, the only build before, 138; 32 sequences 70.5 against 78.6).
 struct DrawShape {
     void (*kernel)(AcceptLaunch, Ws, int);
-    int threads, wgs;
+    int threads, wgs, in_lds;
 };
 static DrawShape draw_shape(const AcceptLaunch& a)
 {
@@ -1224,7 +1234,7 @@ static DrawShape draw_shape(const AcceptLaunch& a)
     const int w12 = wgs(256, 12), w20 = wgs(256, 20);
     if ((int64_t)w12 * a.B > 3 * (int64_t)a.n_cu && (int64_t)w20 * a.B <= 2 * (int64_t)a.n_cu) return {accept_draw_row<256, 20, 2>, 256, w20};
     if ((int64_t)w12 * a.B <= 4 * (int64_t)a.n_cu) return {accept_draw_row<256, 12, 4>, 256, w12};
-    return {accept_draw_row<256, 16, 4>, 256, wgs(256, 16)};
+    return {accept_draw_row<256, 16, 4>, 256, wgs(256, 16), draw_in_lds(16)};
 }
 
 hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)
@@ -1253,7 +1263,7 @@ hipError_t launch_accept(const AcceptLaunch& a, hipStream_t stream)
     const size_t lds_a = sizeof(LdsA) + (size_t)6 * W * sizeof(u64);
     hipLaunchKernelGGL(rows_kernel, dim3((unsigned)n_items), dim3(slice == 10240 ? 256 : 512), lds_a, stream, a, ws, W, (int)n_items);
     const DrawShape draw = draw_shape(a);
-    const size_t lds_b = sizeof(LdsB) + (size_t)4 * draw.wgs * sizeof(u64);
+    const size_t lds_b = sizeof(LdsB) + (size_t)4 * draw.wgs * sizeof(u64) + (size_t)draw.in_lds * draw.threads * sizeof(double);
     hipLaunchKernelGGL(draw.kernel, dim3(draw.wgs, a.B), dim3(draw.threads), lds_b, stream, a, ws, draw.wgs);
     return hipGetLastError();
 }
