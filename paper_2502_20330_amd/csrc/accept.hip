@@ -590,8 +590,9 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
             auto put_d = [&](int v, floatx4 e) { if (PLAIN) y[v] = e; };
             // Other workgroups wait for these statistics, nobody for what the compute unit's other workgroups are at: they come first
             // (six sequences of 128256: 29.4 -> 28.1 us, 8 32.7 -> 31.4; of 50257 24: 39.1 -> 38.0).  Up to two rounds of four workgroups
-            // per compute unit: further rounds lose by it (64 sequences of 32000 50.0 -> 51.2, 32 of 80000 56.5 -> 57.6, 32 of 128256 74.5 -> 75.2).
-            if (n_items <= 8 * a.n_cu) __builtin_amdgcn_s_setprio(1);
+            // per compute unit: further rounds lose by it (64 sequences of 32000 50.0 -> 51.2, 32 of 80000 56.5 -> 57.6, 32 of 128256 74.5 -> 75.2),
+            // and so does the logarithmic form where a row is one slice (200 sequences of 5003: 45.4 -> 47.2 us; plain 32.8 -> 31.9).
+            if ((PLAIN || W > 1) && n_items <= 8 * a.n_cu) __builtin_amdgcn_s_setprio(1);
             slice_stats<NW, NV, true>(reg_t, reg_d, put_t, put_d, own_t, own_d, c, lds.red, bank, mt, st, md, sd);
             if (tid == teller) {
                 if (own_t) publish2f(slot_t + 2 * w, mt, st, tg);
