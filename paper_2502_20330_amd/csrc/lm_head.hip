@@ -28,7 +28,7 @@
 //    of every 4 KiB at a time, which is half of the memory channels (bit 11 of the address is one of the bits that select them; the upper
 //    bits make up for it in some placements of W and not in others, and at pitches of 16 and 32 KiB by themselves).  Means over placements of W, contiguous ->
 //    two runs: 9 rows of 2048 x 128256 98 -> 82 us, 6144 x 64000 148 -> 122, 10240 x 32000 127 -> 99, 14336 x 50000 233 -> 227, 24576 x 16000 136 -> 122; 12288 x
-//    50000 195 -> 194; 32768 x 16000 166 -> 163; 4096 x 128256 160 -> 161, 164 -> 163 and 184 -> 164 on three days (154 to 194 by placement -> 155 to 170), one row 166 -> 162, 72
+//    50000 195 -> 194; 32768 x 16000 166 -> 163; 4096 x 128256 160 -> 161, 164 -> 163 and 184 -> 164 in three runs (154 to 194 by placement -> 155 to 170), one row 166 -> 162, 72
 //    rows 200 -> 180, 9 of 4096 x 152064 200 -> 195, but of 4096 x 12000 18.2 -> 18.8; 8192 x 80000 201 -> 203, 8192 x 32000 88 -> 93, 16384 x 16000 87 -> 102,
 //    16384 x 32000 160 -> 177, and a first pass right after a kernel that wrote W 219 -> 246 and 181 -> 219 at these two pitches (4096 x 128256: 196 -> 204 with
 //    9 rows, 243 -> 223 with 72).  The order of the sum is the same for every logit.
