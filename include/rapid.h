@@ -73,12 +73,16 @@ int rapid_last_hip_error(const rapid_ctx* ctx);
  *       first reads (32 + value)/32 and the second (32 - value)/32 of the mean share, as
  *       rapid_verify_attn splits the tokens of a pair of KV splits unevenly when its grid is one
  *       workgroup per compute unit.  0 <= value <= 16; default 0 (equal shares).
+ *   RAPID_OPT_ATTN_WAIT_US    rapid_verify_attn_exchange: a workgroup looks at most this many microseconds
+ *       for the partial results of the others and then leaves its part of the merge to the last of them
+ *       (same results).  Default 100; 0 = one look (for tests).  0 <= value <= 10^7.
  * Returns RAPID_EINVAL for an unknown option or a value out of range.
  */
 typedef enum rapid_option {
     RAPID_OPT_ACCEPT_WAIT_US = 1,
     RAPID_OPT_ACCEPT_SLICE = 2,
-    RAPID_OPT_PROBE_SKEW = 3
+    RAPID_OPT_PROBE_SKEW = 3,
+    RAPID_OPT_ATTN_WAIT_US = 4
 } rapid_option;
 int rapid_set_option(rapid_ctx* ctx, int option, int64_t value);
 
@@ -157,6 +161,25 @@ int rapid_verify_attn(rapid_ctx* ctx, const rapid_attn_shape* shape,
                       const int32_t* page_table,
                       void* out, float* lse_out,
                       void* workspace, size_t workspace_bytes, void* stream);
+
+/*
+ * rapid_verify_attn, in one launch where the shape has few query rows per kv head and its grid is at most one workgroup per
+ * compute unit: the workgroups then exchange their partial results and merge them themselves, with the same bits as the merge
+ * launch.  Same operation, same argument rules; two more arguments:
+ *   exchange   device memory of rapid_verify_attn_exchange_bytes() or more, 256-byte aligned, or NULL (the call is then
+ *              rapid_verify_attn).  It is state: all of it is zero before the first call that uses it, and
+ *              between calls only this function writes to it.  Calls of any shapes may follow one another on it (also eager calls and
+ *              replays of captured graphs in turn), but two of them must not overlap in time.
+ *   workspace  as for rapid_verify_attn; only looked at where the call takes two launches
+ *              (rapid_verify_attn_exchange_bytes() == 0, or exchange == NULL).
+ * RAPID_EWORKSPACE if the one that the shape needs is missing, misaligned or too small; it is the last check.
+ */
+size_t rapid_verify_attn_exchange_bytes(const rapid_ctx* ctx, const rapid_attn_shape* shape);   /* 0: bad shape, or two launches */
+int rapid_verify_attn_exchange(rapid_ctx* ctx, const rapid_attn_shape* shape,
+                               const void* q, const void* k_cache, const void* v_cache,
+                               const int32_t* ctx_lens, const int32_t* gammas, const int32_t* page_table,
+                               void* out, float* lse_out, void* exchange, size_t exchange_bytes,
+                               void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * rapid_verify_attn for callers that cannot allocate device memory at all: code under HIP graph

@@ -18,10 +18,10 @@ LIB_PATH = os.path.join(_PKG, "librapid.so")
 RAPID_OK = 0
 RAPID_EINVAL, RAPID_EALIGN, RAPID_EUNSUPPORTED, RAPID_EWORKSPACE, RAPID_EHIP, RAPID_ETOOLARGE = -1, -2, -3, -4, -5, -6
 STATIC_SCRATCH_BYTES = 32 << 20
-OPT_ACCEPT_WAIT_US, OPT_ACCEPT_SLICE, OPT_PROBE_SKEW = 1, 2, 3
+OPT_ACCEPT_WAIT_US, OPT_ACCEPT_SLICE, OPT_PROBE_SKEW, OPT_ATTN_WAIT_US = 1, 2, 3, 4
 EXPORTS = ["rapid_create", "rapid_destroy", "rapid_strerror", "rapid_last_hip_error", "rapid_set_option",
            "rapid_verify_attn_chunk", "rapid_verify_attn_workspace_bytes", "rapid_verify_attn",
-           "rapid_verify_attn_static",
+           "rapid_verify_attn_exchange_bytes", "rapid_verify_attn_exchange", "rapid_verify_attn_static",
            "rapid_accept_workspace_bytes", "rapid_accept", "rapid_accept_prestats", "rapid_accept_filled",
            "rapid_lm_head_chunk", "rapid_lm_head_stat_chunks", "rapid_lm_head", "rapid_kv_append", "rapid_kv_commit",
            "rapid_kv_commit_pages",
@@ -76,6 +76,11 @@ def load_library() -> ctypes.CDLL:
     lib.rapid_verify_attn.argtypes = [ctypes.c_void_p, ctypes.POINTER(AttnShape), vp, vp, vp, i32p, i32p, i32p,
                                       vp, f32p, vp, ctypes.c_size_t, vp]
     lib.rapid_verify_attn.restype = ctypes.c_int
+    lib.rapid_verify_attn_exchange_bytes.argtypes = [ctypes.c_void_p, ctypes.POINTER(AttnShape)]
+    lib.rapid_verify_attn_exchange_bytes.restype = ctypes.c_size_t
+    lib.rapid_verify_attn_exchange.argtypes = [ctypes.c_void_p, ctypes.POINTER(AttnShape), vp, vp, vp, i32p, i32p, i32p,
+                                               vp, f32p, vp, ctypes.c_size_t, vp, ctypes.c_size_t, vp]
+    lib.rapid_verify_attn_exchange.restype = ctypes.c_int
     lib.rapid_verify_attn_static.argtypes = [ctypes.c_void_p, ctypes.POINTER(AttnShape), vp, vp, vp, i32p, i32p, i32p,
                                              vp, f32p, vp]
     lib.rapid_verify_attn_static.restype = ctypes.c_int
@@ -150,6 +155,7 @@ class Rapid:
         torch.cuda.set_device(self.device)
         _check(self.lib, self.lib.rapid_create(ctypes.byref(self._ctx), device))
         self._ws: Optional[torch.Tensor] = None
+        self._ws_exchange: Optional[torch.Tensor] = None
         self._ws_accept: Optional[torch.Tensor] = None
         self._sink: Optional[torch.Tensor] = None
 
@@ -178,6 +184,13 @@ class Rapid:
         if self._ws is None or self._ws.numel() < nbytes:
             self._ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=self.device)
         return self._ws
+
+    def _exchange_workspace(self, nbytes: int) -> torch.Tensor:
+        # its own buffer, zero at first: the attention call keeps the number of the call in it.  At once large enough for every
+        # shape (256 workgroups of 16 rows of 128)
+        if self._ws_exchange is None or self._ws_exchange.numel() < nbytes:
+            self._ws_exchange = torch.zeros(max(nbytes, 5 << 20), dtype=torch.uint8, device=self.device)
+        return self._ws_exchange
 
     def _accept_workspace(self, nbytes: int) -> torch.Tensor:
         # its own buffer: the accept pass keeps a call counter in it from one call to the next
@@ -229,11 +242,18 @@ class Rapid:
             out = torch.empty_like(q)
         args = (self._ctx, shape, q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), ctx_lens.data_ptr(), _dptr(gammas),
                 _dptr(page_table), out.data_ptr(), _dptr(lse_out))
-        ws, stream = self._ws, _stream_ptr(self.device)
-        rc = self.lib.rapid_verify_attn(*args, _dptr(ws), 0 if ws is None else ws.numel(), stream)
+        call, stream = self.lib.rapid_verify_attn_exchange, _stream_ptr(self.device)
+        xch, ws = self._ws_exchange, self._ws
+        if xch is None and not torch.cuda.is_current_stream_capturing():   # (a fill that is only recorded does not clear it)
+            xch = self._exchange_workspace(0)
+        rc = call(*args, _dptr(xch), 0 if xch is None else xch.numel(), _dptr(ws), 0 if ws is None else ws.numel(), stream)
         if rc == RAPID_EWORKSPACE:                             # the last check of the call: nothing has been launched
-            ws = self._workspace(self.lib.rapid_verify_attn_workspace_bytes(self._ctx, shape))
-            rc = self.lib.rapid_verify_attn(*args, ws.data_ptr(), ws.numel(), stream)
+            need = 0 if xch is None else self.lib.rapid_verify_attn_exchange_bytes(self._ctx, shape)
+            if need:
+                xch = self._exchange_workspace(need)
+            else:
+                ws = self._workspace(self.lib.rapid_verify_attn_workspace_bytes(self._ctx, shape))
+            rc = call(*args, _dptr(xch), 0 if xch is None else xch.numel(), _dptr(ws), 0 if ws is None else ws.numel(), stream)
         if rc:
             _check(self.lib, rc, self._ctx)
         return out

@@ -137,13 +137,13 @@ void plan_layout(const rapid_ctx* ctx, AttnLaunch& a)
         if (a.rot && a.Hkv % 2 == 0) a.skew = 2;
         return;
     }
-    const int64_t wgs = (int64_t)a.B * a.Hkv * a.nsplit;
+    const int64_t wgs = (int64_t)a.B * a.Hkv * a.nsplit, n_cu = ctx ? ctx->n_cu : 256;
     // measured: 3/32 of the split for the one-team kernel (config 3: 88.2 us with 384 tokens, 89.5 with 256,
     // 91.1 with none), 1/16 for the two-team kernel, which runs all waves through the same number of tiles
     // (70B shape: 93-94 us with 256 tokens, 96.5 with 384).  Where the caches lie counts for as much: over eight
     // placements of them the 70B shape takes 97.7 us on average with 256 tokens, 95.2 with 128 and 95.5 with none.  The
     // borders stay, as they decide which tokens share a reference maximum and so the last bits of a result.
-    if (a.rot && a.Hkv % 2 == 0 && a.nsplit >= 2 && wgs <= ctx->n_cu)
+    if (a.rot && a.Hkv % 2 == 0 && a.nsplit >= 2 && wgs <= n_cu)
         a.skew = a.wide ? a.chunk / 16 / 128 * 128 : (a.chunk * 3 / 32 + 64) / 128 * 128;
 }
 
@@ -166,6 +166,50 @@ int plan_groups(const rapid_ctx* ctx, const rapid_attn_shape* s, int nsplit)
     if (quanta < (s->head_dim == 64 ? 2 : 1) * (2 * (int64_t)groups + s->batch)) return 0;
     if ((int64_t)s->batch * (s->max_ctx / 128 + 8) >= (int64_t)1 << 30) return 0;      // positions are 32-bit
     return groups;
+}
+
+// What the kernels need to know of a shape, apart from pointers.
+void plan_attn(const rapid_ctx* ctx, const rapid_attn_shape* shape, AttnLaunch& a)
+{
+    a.B = shape->batch;
+    a.Qmax = shape->q_max;
+    a.Hq = shape->n_q_heads;
+    a.Hkv = shape->n_kv_heads;
+    a.G = a.Hq / a.Hkv;
+    a.D = shape->head_dim;
+    a.gamma = shape->gamma;
+    a.max_ctx = shape->max_ctx;
+    a.chunk = plan_chunk(ctx, shape);
+    a.nsplit = (shape->max_ctx + a.chunk - 1) / a.chunk;
+    a.RB = attn_row_blocks(shape, &a.wide);
+    a.groups = plan_groups(ctx, shape, a.nsplit);
+    a.nslots = a.groups + a.B - 1;
+    a.bstride = shape->kv_batch_stride;
+    a.tstride = shape->kv_token_stride;
+    a.hstride = shape->kv_head_stride;
+    a.pstride = shape->kv_page_stride;
+    a.max_pages = shape->max_pages;
+    a.page_shift = -1;
+    a.page_mask = 0;
+    if (shape->page_size) {
+        int sh = 0;
+        while ((1 << sh) < shape->page_size) ++sh;
+        a.page_shift = sh;
+        a.page_mask = shape->page_size - 1;
+    }
+    a.page_hi = page_hi_of(shape);
+    a.scale_log2e = shape->softmax_scale * 1.4426950408889634f;
+    plan_layout(ctx, a);
+}
+
+// Bytes of exchange memory with which the call is one launch, 0 where it is two: few rows (attn_in_one_launch), a fixed grid of
+// at most one workgroup per compute unit (they wait for one another), and no more splits than one wave forms weights for.
+size_t plan_exchange(const rapid_ctx* ctx, const AttnLaunch& a)
+{
+    const int64_t wgs = (int64_t)a.B * a.Hkv * a.nsplit;
+    if (a.groups || !attn_in_one_launch(a.RB, a.D) || a.nsplit > kMaxShares) return 0;
+    if (wgs > (ctx ? ctx->n_cu : 256) || wgs > kAttnTeams) return 0;
+    return attn_exchange_bytes(a.B, a.Hkv, a.nsplit, a.RB, a.D);
 }
 
 }  // namespace
@@ -202,6 +246,7 @@ int rapid_create(rapid_ctx** out, int device)
     c->static_scratch = scratch_ptr;
     c->accept_wait_ticks = 100 * 100;                 // 100 us
     c->accept_slice = 0;
+    c->attn_wait_ticks = 100 * 100;
     c->probe_skew = 0;
     c->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     c->last_hip_error = 0;
@@ -239,6 +284,10 @@ int rapid_set_option(rapid_ctx* ctx, int option, int64_t value)
             if (value != 0 && value != 4096 && value != 8192 && value != 10240 && value != 16384) return RAPID_EINVAL;
             ctx->accept_slice = (int)value;
             return RAPID_OK;
+        case RAPID_OPT_ATTN_WAIT_US:
+            if (value < 0 || value > 10 * 1000 * 1000) return RAPID_EINVAL;
+            ctx->attn_wait_ticks = value * 100;
+            return RAPID_OK;
         case RAPID_OPT_PROBE_SKEW:
             if (value < 0 || value > 16) return RAPID_EINVAL;
             ctx->probe_skew = (int)value;
@@ -263,11 +312,11 @@ size_t rapid_verify_attn_workspace_bytes(const rapid_ctx* ctx, const rapid_attn_
     return attn_workspace_bytes(shape->batch, shape->n_kv_heads, nsplit, RB, shape->head_dim);
 }
 
-int rapid_verify_attn(rapid_ctx* ctx, const rapid_attn_shape* shape,
-                      const void* q, const void* k_cache, const void* v_cache,
-                      const int32_t* ctx_lens, const int32_t* gammas, const int32_t* page_table,
-                      void* out, float* lse_out,
-                      void* workspace, size_t workspace_bytes, void* stream)
+static int attn_call(rapid_ctx* ctx, const rapid_attn_shape* shape,
+                     const void* q, const void* k_cache, const void* v_cache,
+                     const int32_t* ctx_lens, const int32_t* gammas, const int32_t* page_table,
+                     void* out, float* lse_out,
+                     void* exchange, size_t exchange_bytes, void* workspace, size_t workspace_bytes, void* stream)
 {
     if (!ctx) return RAPID_EINVAL;
     int rc = check_attn_shape(shape);
@@ -275,8 +324,6 @@ int rapid_verify_attn(rapid_ctx* ctx, const rapid_attn_shape* shape,
     if (!q || !k_cache || !v_cache || !ctx_lens || !out) return RAPID_EINVAL;
     if (shape->page_size != 0 && !page_table) return RAPID_EINVAL;
     if (!aligned(q, 16) || !aligned(k_cache, 16) || !aligned(v_cache, 16) || !aligned(out, 16)) return RAPID_EALIGN;
-    const size_t need = rapid_verify_attn_workspace_bytes(ctx, shape);
-    if (!workspace || !aligned(workspace, 256) || workspace_bytes < need) return RAPID_EWORKSPACE;
 
     AttnLaunch a{};
     a.q = static_cast<const uint16_t*>(q);
@@ -287,45 +334,59 @@ int rapid_verify_attn(rapid_ctx* ctx, const rapid_attn_shape* shape,
     a.page_table = shape->page_size ? page_table : nullptr;
     a.out = static_cast<uint16_t*>(out);
     a.lse_out = lse_out;
-    a.B = shape->batch;
-    a.Qmax = shape->q_max;
-    a.Hq = shape->n_q_heads;
-    a.Hkv = shape->n_kv_heads;
-    a.G = a.Hq / a.Hkv;
-    a.D = shape->head_dim;
-    a.gamma = shape->gamma;
-    a.max_ctx = shape->max_ctx;
-    a.chunk = plan_chunk(ctx, shape);
-    a.nsplit = (shape->max_ctx + a.chunk - 1) / a.chunk;
-    a.RB = attn_row_blocks(shape, &a.wide);
-    a.groups = plan_groups(ctx, shape, a.nsplit);
-    a.nslots = a.groups + a.B - 1;
-    a.bstride = shape->kv_batch_stride;
-    a.tstride = shape->kv_token_stride;
-    a.hstride = shape->kv_head_stride;
-    a.pstride = shape->kv_page_stride;
-    a.max_pages = shape->max_pages;
-    a.page_shift = -1;
-    a.page_mask = 0;
-    if (shape->page_size) {
-        int sh = 0;
-        while ((1 << sh) < shape->page_size) ++sh;
-        a.page_shift = sh;
-        a.page_mask = shape->page_size - 1;
+    plan_attn(ctx, shape, a);
+    const size_t need_x = exchange ? plan_exchange(ctx, a) : 0;
+    if (need_x) {
+        if (!aligned(exchange, 256) || exchange_bytes < need_x) return RAPID_EWORKSPACE;
+        a.xhead = static_cast<AttnExchangeHead*>(exchange);
+        a.xwords = static_cast<char*>(exchange) + kAttnExchangeHeadBytes;
+        a.xbytes = (uint32_t)(need_x - kAttnExchangeHeadBytes);
+        a.xml_offset = a.xbytes / (a.D + 2) * a.D;
+        a.xwait_ticks = ctx->attn_wait_ticks;
+    } else if (!workspace || !aligned(workspace, 256) ||
+               workspace_bytes < attn_workspace_bytes(a.B, a.Hkv, a.nsplit, a.RB, a.D)) {
+        return RAPID_EWORKSPACE;
     }
-    a.page_hi = page_hi_of(shape);
-    a.scale_log2e = shape->softmax_scale * 1.4426950408889634f;
-    plan_layout(ctx, a);
     const size_t rows = (size_t)a.B * a.Hkv * a.nsplit * a.RB * 16;
     const size_t o_bytes = (rows * a.D * sizeof(float) + 255) / 256 * 256;
-    a.part_o = static_cast<float*>(workspace);
-    a.part_ml = reinterpret_cast<float*>(static_cast<char*>(workspace) + o_bytes);
+    if (!need_x) {
+        a.part_o = static_cast<float*>(workspace);
+        a.part_ml = reinterpret_cast<float*>(static_cast<char*>(workspace) + o_bytes);
+    }
 
     DeviceScope dev(ctx->device);
     if (dev.err != hipSuccess) return hip_fail(ctx, dev.err);
     hipError_t e = launch_verify_attn(a, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(ctx, e);
     return RAPID_OK;
+}
+
+size_t rapid_verify_attn_exchange_bytes(const rapid_ctx* ctx, const rapid_attn_shape* shape)
+{
+    if (check_attn_shape(shape) != RAPID_OK) return 0;
+    AttnLaunch a{};
+    plan_attn(ctx, shape, a);
+    return plan_exchange(ctx, a);
+}
+
+int rapid_verify_attn(rapid_ctx* ctx, const rapid_attn_shape* shape,
+                      const void* q, const void* k_cache, const void* v_cache,
+                      const int32_t* ctx_lens, const int32_t* gammas, const int32_t* page_table,
+                      void* out, float* lse_out,
+                      void* workspace, size_t workspace_bytes, void* stream)
+{
+    return attn_call(ctx, shape, q, k_cache, v_cache, ctx_lens, gammas, page_table, out, lse_out, nullptr, 0,
+                     workspace, workspace_bytes, stream);
+}
+
+int rapid_verify_attn_exchange(rapid_ctx* ctx, const rapid_attn_shape* shape,
+                               const void* q, const void* k_cache, const void* v_cache,
+                               const int32_t* ctx_lens, const int32_t* gammas, const int32_t* page_table,
+                               void* out, float* lse_out, void* exchange, size_t exchange_bytes,
+                               void* workspace, size_t workspace_bytes, void* stream)
+{
+    return attn_call(ctx, shape, q, k_cache, v_cache, ctx_lens, gammas, page_table, out, lse_out, exchange, exchange_bytes,
+                     workspace, workspace_bytes, stream);
 }
 
 int rapid_verify_attn_static(rapid_ctx* ctx, const rapid_attn_shape* shape,

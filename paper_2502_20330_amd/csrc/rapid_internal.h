@@ -10,11 +10,13 @@ struct rapid_ctx {
     int last_hip_error;
     void* static_scratch;   // device address of this GPU's copy of the library's static scratch array
     int64_t accept_wait_ticks;   // bound of every inter-workgroup wait of the accept pass, 10 ns ticks
+    int64_t attn_wait_ticks;     // the same of the attention call's exchange
     int accept_slice;            // entries per workgroup of the accept row pass (0 = automatic)
     int probe_skew;              // streaming probe: 32nds of the mean share moved from odd to even workgroups
 };
 
 // ---- verify attention (verify_attn.hip)
+struct AttnExchangeHead;
 struct AttnLaunch {
     const uint16_t* q;
     const uint16_t* k;
@@ -40,7 +42,28 @@ struct AttnLaunch {
     int32_t page_shift, page_mask, max_pages;     // page_shift < 0: contiguous
     int32_t page_hi;    // largest page id the kernels will use (ids are clamped to [0, page_hi])
     float scale_log2e;
+    // one launch: the workgroups exchange their partials and merge them themselves (null: a second kernel merges)
+    AttnExchangeHead* xhead;
+    void* xwords;            // tagged words: partials [B, Hkv, nsplit, RB*16, D], behind them (max, sum) of the rows
+    uint32_t xbytes;         // of the words
+    uint32_t xml_offset;     // bytes from xwords to the (max, sum) words
+    int64_t xwait_ticks;     // bound of a wait in wall-clock ticks (100 MHz)
 };
+constexpr int kAttnTeams = 256;  // largest grid that merges by itself: every workgroup then has one of the usual 256 compute units
+// Row counts (in blocks of 16) for which the workgroups merge their partials themselves, up to 16 rows of 128 or 32 of 64.  In graphs
+// of calls, two launches against one: 4 rows of 128, 512 tokens 8.75 and 8.37 us, 8K 12.2 and 11.7, 32K 27.6 and 27.1, 128K 87.9
+// and 87.5; 20 rows of 64, 2K tokens 7.65 and 7.43; sixteen sequences of 2K with 10 rows of 64 16.9 and 16.5.  Beyond, the words (twice the
+// partials) take longer to go through memory and back than a second launch: 20 rows of 128, 8K tokens 14.3 and 14.7, 36 rows 17.0
+// and 18.3, 72 rows 20.2 and 23.0; 40 rows of 64, 2K tokens 8.6 and 9.2.  Calls that the host cannot enqueue as fast as they run gain a launch.
+constexpr bool attn_in_one_launch(int row_blocks, int D) { return row_blocks * D <= 128; }
+constexpr int kMaxShares = 32;   // workgroups of a (sequence, kv head) that merge rows
+// Head of the exchange memory of the attention call (attn_exchange.h).
+struct AttnExchangeHead {
+    uint32_t calls[kAttnTeams];                  // calls so far, a copy per (sequence, kv head)
+    uint32_t marks[kAttnTeams][kMaxShares];      // number of the last call that left this share to others
+};
+constexpr size_t kAttnExchangeHeadBytes = (sizeof(AttnExchangeHead) + 255) / 256 * 256;
+size_t attn_exchange_bytes(int B, int Hkv, int nsplit, int RB, int D);
 hipError_t launch_verify_attn(const AttnLaunch& a, hipStream_t stream);
 hipError_t configure_verify_attn();   // per device, before the first launch
 size_t attn_workspace_bytes(int B, int Hkv, int nsplit, int RB, int D);

@@ -29,12 +29,12 @@
 //    ds_read_b64_tr_b16 delivers the transposed MFMA operand straight from LDS.
 //  * Waves combine (m, l, O) through LDS in a fixed order; the workgroup writes
 //    one fp32 partial.  A second small kernel merges the splits with the
-//    log-sum-exp rule and rounds to bf16.
+//    log-sum-exp rule and rounds to bf16; with few rows the workgroups do that
+//    themselves (attn_exchange.h).
+#include "attn_exchange.h"
 #include "rapid_internal.h"
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
@@ -448,8 +448,9 @@ __device__ __forceinline__ int live_splits(const AttnLaunch& a, int L, int h)
 
 // One workgroup's work on tokens [c0, c1) of one (sequence, kv head): the partial goes to the packed rows
 // from `pbase` on.
-template <int D, int RB, bool PAGED>
-__device__ __forceinline__ void split_piece(const AttnLaunch& a, char* smem, int b, int hkv, int L, int c0, int c1, int64_t pbase)
+template <int D, int RB, bool PAGED, bool XCH>
+__device__ __forceinline__ void split_piece(const AttnLaunch& a, char* smem, int b, int hkv, int L, int c0, int c1, int64_t pbase,
+                                            uint32_t calls)
 {
     using G = Geo<D>;
     constexpr int RP = RB * 16;
@@ -604,6 +605,27 @@ __device__ __forceinline__ void split_piece(const AttnLaunch& a, char* smem, int
         for (int db = 0; db < G::DB; ++db)
             *reinterpret_cast<floatx4*>(obuf + (wave * RP + row) * OROW + db * 16 + lg * 4) = st.acc[db][rb] * f_own;
     }
+    if constexpr (XCH) if (a.xhead) {
+        const Exchange x = make_exchange(a, calls);
+        if (wave == 0 && lg == 0) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                const int row = rb * 16 + ln;
+                if (row < R) publish_pair(x, a.xml_offset / 8 + (uint32_t)(pbase + row) * 2, m_all[rb], l_all[rb]);
+            }
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int f = tid; f < R * (D / 2); f += kWaves * 64) {
+            const float* y = obuf + (f / (D / 2)) * OROW + f % (D / 2) * 2;
+            float2 part[kWaves];
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) part[w] = *reinterpret_cast<const float2*>(y + w * RP * OROW);
+            publish_pair(x, (uint32_t)(pbase * D) + f * 2, (part[0].x + part[2].x) + (part[1].x + part[3].x),
+                         (part[0].y + part[2].y) + (part[1].y + part[3].y));
+        }
+        return;
+    }
     __syncthreads();
     floatx4* po = reinterpret_cast<floatx4*>(a.part_o + pbase * D);
     for (int f = tid; f < R * (D / 4); f += kWaves * 64) {
@@ -641,17 +663,24 @@ __global__ void __launch_bounds__(kWaves * 64) verify_attn_split(AttnLaunch a)
     const int hkv = a.rot ? (int)((blockIdx.x + split) % a.Hkv) : (int)blockIdx.x;
     if (BALANCED) {
         for_each_piece(a, split, hkv, threadIdx.x & 63, [&](int pb, int L, int c0, int c1) {
-            split_piece<D, RB, PAGED>(a, smem, pb, hkv, L, c0, c1, ((int64_t)hkv * a.nslots + split + pb) * (RB * 16));
+            split_piece<D, RB, PAGED, false>(a, smem, pb, hkv, L, c0, c1, ((int64_t)hkv * a.nslots + split + pb) * (RB * 16), 0);
             wait_loads<0>();                             // the partial's stores are out of the load account
             __syncthreads();                             // the exchange buffers become rings again
         });
         return;
     }
-    const int L = seq_len(a, b);
+    int L = seq_len(a, b);
+    constexpr bool one_launch = !BALANCED && attn_in_one_launch(RB, D);
+    uint32_t calls = 0;
+    if constexpr (one_launch) calls = exchange_call(a, b * a.Hkv + hkv, L);
     const int c0 = split_begin(a, split, hkv);
-    if (c0 >= L) return;                                 // this split holds no token of sequence b
-    split_piece<D, RB, PAGED>(a, smem, b, hkv, L, c0, min(split_end(a, split, hkv), L),
-                              (((int64_t)b * a.Hkv + hkv) * a.nsplit + split) * (RB * 16));
+    if (c0 < L)                                          // else this split holds no token of sequence b
+        split_piece<D, RB, PAGED, one_launch>(a, smem, b, hkv, L, c0, min(split_end(a, split, hkv), L),
+                                              (((int64_t)b * a.Hkv + hkv) * a.nsplit + split) * (RB * 16), calls);
+    if constexpr (one_launch)
+        if (a.xhead)
+            exchange_finish<D, RB * 16, kWaves>(a, calls, smem, b * a.Hkv + hkv, split, live_splits(a, L, hkv),
+                                                seq_queries(a, b) * a.G);
 }
 
 // ---------------------------------------------------------------- wide row counts: two row teams
@@ -943,30 +972,6 @@ __global__ void __launch_bounds__(2 * kWaves * 64) verify_attn_split_wide(AttnLa
                                          (((int64_t)b * a.Hkv + hkv) * a.nsplit + split) * RP);
 }
 
-// Reductions over 32 values, one per lane of the wave's lower and again of its upper half; result in every lane.
-template <int ROR>
-__device__ __forceinline__ float row_ror(float v)      // rotation inside rows of 16 lanes, without LDS
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + ROR, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float lane_of(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
-__device__ __forceinline__ float max32(float v)
-{
-    v = fmaxf(v, row_ror<8>(v));
-    v = fmaxf(v, row_ror<4>(v));
-    v = fmaxf(v, row_ror<2>(v));
-    v = fmaxf(v, row_ror<1>(v));
-    return fmaxf(lane_of(v, 0), lane_of(v, 16));
-}
-__device__ __forceinline__ float sum32(float v)
-{
-    v += row_ror<8>(v);
-    v += row_ror<4>(v);
-    v += row_ror<2>(v);
-    v += row_ror<1>(v);
-    return lane_of(v, 0) + lane_of(v, 16);
-}
-
 // Merge the splits of one query row: out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
 // One workgroup of D threads per (sequence, kv head, packed row), splits taken 32 at a
 // time.  The kernel is latency bound, so every thread issues the loads of its column
@@ -977,7 +982,7 @@ __device__ __forceinline__ float sum32(float v)
 template <int D, bool BALANCED>
 __global__ void __launch_bounds__(D) verify_attn_merge(AttnLaunch a)
 {
-    constexpr int SB = 32;                             // splits per block
+    constexpr int SB = kMergeBlock;
     const int row = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
     const int d = threadIdx.x;
     const int Q = seq_queries(a, b);
@@ -991,7 +996,8 @@ __global__ void __launch_bounds__(D) verify_attn_merge(AttnLaunch a)
         return;
     }
     int64_t pbase = ((int64_t)b * a.Hkv + hkv) * a.nsplit * RP;
-    float M = -INFINITY, den = 0.f, num = 0.f;
+    RowMerge r;
+    float num = 0.f;
     int ns = a.nsplit;                                 // refined below, once the length has arrived
     if (BALANCED) {
         // the groups whose shares hold a token of this sequence
@@ -1041,12 +1047,8 @@ __global__ void __launch_bounds__(D) verify_attn_merge(AttnLaunch a)
 #pragma unroll
         for (int j = 0; j < SB; ++j) o[j] = j < nb ? o[j] : 0.f;
         if (sl >= nb) { ms = -INFINITY; ls = 0.f; }
-        const float Mn = fmaxf(M, max32(ms));
-        const float Mu = (Mn == -INFINITY) ? 0.f : Mn;
-        const float resc = fast_exp2(M - Mu);
-        M = Mn;
-        const float w = fast_exp2(ms - Mu);            // lanes >= nb: 0
-        den = den * resc + sum32(w * ls);
+        float resc;
+        const float w = r.block(ms, ls, &resc);        // lanes >= nb: 0
         float acc0 = 0.f, acc1 = 0.f;
 #pragma unroll
         for (int j = 0; j < SB; j += 2) {
@@ -1055,11 +1057,11 @@ __global__ void __launch_bounds__(D) verify_attn_merge(AttnLaunch a)
         }
         num = num * resc + (acc0 + acc1);
     }
-    float o = den > 0.f ? num / den : 0.f;
+    float o = r.den > 0.f ? num / r.den : 0.f;
     __bf16 ob = (__bf16)o;
     *dst = __builtin_bit_cast(uint16_t, ob);
     if (a.lse_out && d == 0)
-        a.lse_out[((int64_t)b * a.Hq + h) * a.Qmax + qi] = (M + log2f(den)) * 0.6931471805599453f;
+        a.lse_out[((int64_t)b * a.Hq + h) * a.Qmax + qi] = (r.M + log2f(r.den)) * 0.6931471805599453f;
 }
 
 // Grid: (kv head, split, sequence), or one workgroup per (kv head, group) with balanced shares.
@@ -1130,7 +1132,7 @@ hipError_t dispatch_rb(const AttnLaunch& a, hipStream_t stream)
         case 5: e = launch_split_wide<D, 3, 2, PAGED, BALANCED>(a, stream); break;     // two teams from five row blocks on
         case 6: e = launch_split_wide<D, 3, 3, PAGED, BALANCED>(a, stream); break;
     }
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || a.xhead) return e;
     auto merge = verify_attn_merge<D, BALANCED>;
     hipLaunchKernelGGL(merge, dim3(a.Qmax * a.G, a.Hkv, a.B), dim3(D), 0, stream, a);
     return hipGetLastError();
@@ -1155,6 +1157,11 @@ size_t attn_workspace_bytes(int B, int Hkv, int nsplit, int RB, int D)
     size_t rows = (size_t)B * Hkv * nsplit * RB * 16;
     size_t o = rows * D * sizeof(float), ml = rows * 2 * sizeof(float);
     return ((o + 255) / 256) * 256 + ((ml + 255) / 256) * 256;
+}
+
+size_t attn_exchange_bytes(int B, int Hkv, int nsplit, int RB, int D)
+{
+    return kAttnExchangeHeadBytes + (size_t)B * Hkv * nsplit * RB * 16 * (D + 2) * 8;
 }
 
 hipError_t launch_verify_attn(const AttnLaunch& a, hipStream_t stream)

@@ -1,0 +1,175 @@
+"""The attention call in one launch (workgroups exchange their partials and merge them) against the same call in two: the
+same partials are folded in the same order, so every output has the same bits."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2502_20330_amd import binding
+from paper_2502_20330_amd.binding import OPT_ATTN_WAIT_US, Rapid
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(B, Q, Hq, Hkv, d, lens, gammas, page=0, layout="head", seed=0, max_ctx=None):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    max_ctx = max_ctx or max(max(lens), Q)
+    q = torch.randn(B, Q, Hq, d, device="cuda", generator=g).bfloat16()
+    table = None
+    if page:
+        per = -(-max_ctx // page)
+        table = torch.randperm(B * per, device="cuda", generator=g).to(torch.int32).view(B, per)
+        shape = (B * per, page, Hkv, d)
+    else:
+        shape = (B, max_ctx, Hkv, d)
+    if layout == "head":
+        k, v = (torch.randn(shape[0], shape[2], shape[1], d, device="cuda", generator=g).bfloat16().permute(0, 2, 1, 3) for _ in "kv")
+    else:
+        k, v = (torch.randn(shape, device="cuda", generator=g).bfloat16() for _ in "kv")
+    return dict(q=q, k=k, v=v, lens=torch.tensor(lens, dtype=torch.int32, device="cuda"),
+                gammas=None if gammas is None else torch.tensor(gammas, dtype=torch.int32, device="cuda"), table=table, max_ctx=max_ctx)
+
+
+def _two(r, c, chunk=0):
+    s = r.attn_shape(c["q"], c["k"], c["max_ctx"], page_table=c["table"], chunk_tokens=chunk)
+    out = torch.full_like(c["q"], float("nan"))
+    lse = torch.full((s.batch, s.n_q_heads, s.q_max), float("nan"), device="cuda")
+    ws = torch.empty(r.lib.rapid_verify_attn_workspace_bytes(r._ctx, ctypes.byref(s)), dtype=torch.uint8, device="cuda")
+    p = lambda t: None if t is None else t.data_ptr()
+    rc = r.lib.rapid_verify_attn(r._ctx, ctypes.byref(s), p(c["q"]), p(c["k"]), p(c["v"]), p(c["lens"]), p(c["gammas"]), p(c["table"]),
+                                 p(out), p(lse), p(ws), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    assert r.lib.rapid_verify_attn_exchange_bytes(r._ctx, ctypes.byref(s)) > 0, "this shape is meant to run in one launch"
+    return out, lse
+
+
+def _one(r, c, chunk=0):
+    out = torch.full_like(c["q"], float("nan"))
+    lse = torch.full((c["q"].shape[0], c["q"].shape[2], c["q"].shape[1]), float("nan"), device="cuda")
+    r.rapid_verify_attn(c["q"], c["k"], c["v"], c["lens"], gammas=c["gammas"], page_table=c["table"], max_ctx=c["max_ctx"], out=out,
+                        lse_out=lse, chunk_tokens=chunk)
+    return out, lse
+
+
+def _same(x, y):
+    for a, b in zip(x, y):
+        assert torch.equal(a.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32),
+                           b.view(torch.int16 if b.dtype == torch.bfloat16 else torch.int32))
+
+
+# B, Q, Hq, Hkv, d, lens, gammas, page, layout: one split and several, up to the 32 that run in one launch; shares of less than a
+# row and of several rows, more shares than elements to share; splits and whole sequences without tokens; one and two row blocks
+SHAPES = [
+    (1, 1, 4, 4, 64, [1], None, 0, "head"),
+    (1, 1, 1, 1, 64, [8192], None, 0, "head"),
+    (1, 5, 4, 1, 64, [2048], None, 0, "token"),
+    (1, 4, 8, 1, 64, [200], None, 0, "head"),
+    (1, 2, 8, 1, 128, [300], None, 0, "head"),
+    (1, 1, 32, 8, 128, [8192], None, 0, "head"),
+    (1, 4, 32, 8, 128, [32768], None, 0, "head"),
+    (1, 3, 32, 8, 128, [9000], [1], 16, "head"),
+    (1, 2, 28, 4, 128, [8161], None, 0, "token"),
+    (1, 5, 3, 1, 128, [7300], None, 0, "token"),
+    (1, 4, 8, 1, 64, [8192], [2], 64, "head"),
+    (2, 2, 64, 8, 128, [4000, 700], [1, 0], 0, "head"),
+    (3, 4, 16, 4, 64, [5000, 0, 4], [3, 3, 3], 16, "head"),
+    (8, 8, 16, 8, 64, [1024] * 8, None, 0, "head"),
+    (16, 3, 8, 4, 64, [513] * 16, [0, 1, 2, 2] * 4, 0, "token"),
+    (64, 3, 8, 4, 64, [33] * 64, [0, 1, 2, 2] * 16, 0, "token"),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_one_launch_has_the_bits_of_two(shape):
+    r = Rapid(0)
+    c = _case(*shape)
+    want = _two(r, c)
+    for wait in (100, 100, 0, 1, 3, 100):              # 0: nearly all rows are left to the last workgroup of their head
+        r.set_option(OPT_ATTN_WAIT_US, wait)
+        _same(_one(r, c), want)
+
+
+def test_calls_of_many_shapes_and_replays_share_one_exchange():
+    r = Rapid(0)
+    cases = [_case(*s, seed=i) for i, s in enumerate(SHAPES)]
+    want = [_two(r, c) for c in cases]
+    for c in cases:
+        _one(r, c)                                     # the exchange has its size from here on
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        got = [_one(r, c) for c in cases[:6]]
+    order = torch.Generator().manual_seed(1)
+    for _ in range(6):
+        for o, l in got:
+            o.fill_(float("nan")), l.fill_(float("nan"))
+        graph.replay()
+        for i in torch.randint(len(cases), (8,), generator=order).tolist():
+            _same(_one(r, cases[i]), want[i])
+        torch.cuda.synchronize()
+        for g, w in zip(got, want):
+            _same(g, w)
+
+
+def test_every_copy_of_the_calls_number_moves_by_one():
+    r = Rapid(0)
+    cases = [_case(*s) for s in SHAPES]
+    for c in cases:
+        _one(r, c)
+    n = int(r._ws_exchange[:4].view(torch.int32))
+    for i, c in enumerate(cases * 2):
+        r.set_option(OPT_ATTN_WAIT_US, 100 if i % 3 else 0)
+        _one(r, c)
+        n += 1
+        assert r._ws_exchange[:1024].view(torch.int32).unique().tolist() == [n]
+
+
+def test_missing_or_small_exchange_is_refused_and_none_takes_two_launches():
+    r = Rapid(0)
+    c = _case(*SHAPES[2])
+    s = r.attn_shape(c["q"], c["k"], c["max_ctx"])
+    need = r.lib.rapid_verify_attn_exchange_bytes(r._ctx, ctypes.byref(s))
+    out = torch.empty_like(c["q"])
+    x = torch.zeros(need + 256, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(r.lib.rapid_verify_attn_workspace_bytes(r._ctx, ctypes.byref(s)), dtype=torch.uint8, device="cuda")
+
+    def call(xp, xn, wp, wn):
+        return r.lib.rapid_verify_attn_exchange(r._ctx, ctypes.byref(s), c["q"].data_ptr(), c["k"].data_ptr(), c["v"].data_ptr(),
+                                                c["lens"].data_ptr(), None, None, out.data_ptr(), None, xp, xn, wp, wn,
+                                                torch.cuda.current_stream().cuda_stream)
+    assert call(x.data_ptr(), need - 1, ws.data_ptr(), ws.numel()) == binding.RAPID_EWORKSPACE
+    assert call(x.data_ptr() + 16, need, ws.data_ptr(), ws.numel()) == binding.RAPID_EWORKSPACE
+    assert call(None, 0, None, 0) == binding.RAPID_EWORKSPACE
+    assert call(x.data_ptr(), need, None, 0) == 0
+    one = out.clone()
+    assert call(None, 0, ws.data_ptr(), ws.numel()) == 0
+    _same((one,), (out,))
+
+
+@pytest.mark.parametrize("shape", [(1, 5, 4, 1, 128, [2048], None), (1, 9, 4, 1, 64, [2048], None), (1, 1, 4, 1, 64, [65536], None),
+                                   (33, 1, 8, 8, 64, [64] * 33, None)])
+def test_shapes_that_stay_at_two_launches(shape):
+    """More rows, more than 32 splits, more workgroups than compute units: no exchange memory is asked for, and none is needed."""
+    r = Rapid(0)
+    c = _case(*shape)
+    s = r.attn_shape(c["q"], c["k"], c["max_ctx"])
+    assert r.lib.rapid_verify_attn_exchange_bytes(r._ctx, ctypes.byref(s)) == 0
+    got = _one(r, c)
+    assert r._ws is not None and bool(got[0].float().isfinite().all())
+
+
+def test_first_call_of_an_object_inside_a_capture():
+    """Nothing can be cleared there, so the call takes two launches; the next eager one makes the exchange memory."""
+    r = Rapid(0)
+    c = _case(*SHAPES[5])
+    want = _two(r, c)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        got = _one(r, c)
+    assert r._ws_exchange is None
+    for _ in range(3):
+        _same(_one(r, c), want)
+        graph.replay()
+        _same(got, want)
