@@ -52,7 +52,7 @@ constexpr int kExchangeRows = 98;      // rows that a share may touch
 // What bounds it: round trips past the dies' L2s (0.7 us each: the own words' arrival, one or two looks) and code that every
 // workgroup meets for the first time, about 3 us from the last tile to the end at 4 rows where a store, a second launch and its
 // gap took 3.6.  So everything that is missing is asked for at once, one element of the output a thread, and partials keep
-// the order of the merge kernel.  Measured (a graph of 16 layers of 8K tokens with the head and the draw): 290 -> 279 us; 2K
+// the order of the merge kernel.  Measured (a graph of 16 layers of 8K tokens with the head and the draw): 290 -> 277 us; 2K
 // tokens, 4 heads of 64, enqueued one by one 9.9 -> 7.7.  Not kept: a counter of arrivals per team (256 atomic additions on a few
 // lines: 345 us); a wave per row asking for 32 splits (304); asking for words only where (maximum, sum) had come (282 to 292).
 struct Exchange {
@@ -107,7 +107,7 @@ template <int NWAVES>
 struct MergeLds {
     float weight[kExchangeRows][kMergeBlock];          // of the share's rows, for each split
     float den[kExchangeRows], top[kExchangeRows];      // sum and maximum of a row
-    uint32_t flags[NWAVES][2];                         // not all words there; marks of the team
+    uint32_t missing[NWAVES], seen[NWAVES];            // not all words there; marks of the team, by wave
     float vals[];                                      // [split][element of the share]
 };
 
@@ -145,18 +145,17 @@ __device__ __forceinline__ bool merge_share(const AttnLaunch& a, const Exchange&
             if (p >= step) { p -= step; ++s; }
         }
     }
-    // Every look asks for all that is missing at once: the words, (maximum, sum) of the wave's first row, the marks of the team, one per
-    // lane.  The first one comes when this wave's own words have arrived in memory.
-    const uint32_t* marks_at = &x.head->marks[team][lane & (kMaxShares - 1)];
-    uint32_t mark = 0;
+    // Every look asks for all that is missing at once: the words, (maximum, sum) of the wave's first row, the marks of the team, one
+    // per lane.  Marks count once this wave's own words have arrived, which is after the first look; they are needed in the end.
     int row = row0 + wave;
     const int sl = min(lane & (kMergeBlock - 1), n - 1);
     const uint32_t ml_at = a.xml_offset + (base + sl * RP + min(row, max(row1 - 1, 0))) * 16;
+    const uint32_t* marks_at = &x.head->marks[team][lane & (kMaxShares - 1)];
+    uint32_t mark = 0;
     u32x4 ml = {0, 0, 0, 0};
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    for (;;) {
+    for (bool early = true;; early = false) {
         ml = __builtin_amdgcn_raw_buffer_load_b128(x.words, ml_at, 0, kDeviceScope);
-        if (first) mark = __hip_atomic_load(marks_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mark = __hip_atomic_load(marks_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         u32x4 v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -172,9 +171,12 @@ __device__ __forceinline__ bool merge_share(const AttnLaunch& a, const Exchange&
                     open = true;
                 }
             }
-        if (!__any(open)) break;
-        if (ticks < 0 || (int64_t)wall_clock64() - t0 >= ticks) {
-            missing = true;
+        missing = __any(open);
+        if (!missing || ticks < 0 || (int64_t)wall_clock64() - t0 >= ticks) {
+            if (early) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                mark = __hip_atomic_load(marks_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
             break;
         }
         asm volatile("" ::: "memory");
@@ -200,59 +202,56 @@ __device__ __forceinline__ bool merge_share(const AttnLaunch& a, const Exchange&
             if (live && !__all(ml.y == x.tag && ml.w == x.tag)) missing = true;
         }
     }
-    if (lane == 0) lds.flags[wave][0] = 0;
-    if (missing) lds.flags[wave][0] = 1;
-    const uint32_t seen = (uint32_t)__ballot(first && mark == x.tag);
-    if (lane == 0) lds.flags[wave][1] = seen;
+    if (lane == 0) lds.missing[wave] = missing;
     __syncthreads();
-    uint32_t any = 0, left = 0;
+    uint32_t any = 0;
 #pragma unroll
-    for (int w = 0; w < NWAVES; ++w) {
-        any |= lds.flags[w][0];
-        left |= lds.flags[w][1];
-    }
-    if (first) *marks = left;
-    if (any) return false;
+    for (int w = 0; w < NWAVES; ++w) any |= lds.missing[w];
     const int b = team / a.Hkv, hkv = team - b * a.Hkv;
-    for (int e = e0 + tid; e < e1; e += NT) {
+    for (int e = any ? e1 : e0 + tid; e < e1; e += NT) {
         const int row = e / D, d = e % D;
         const int qi = row / a.G, h = hkv * a.G + row % a.G;
-        float num = 0.f, lse = 0.f;
+        float num = 0.f;
         if (row < R) {
             const float* w = lds.weight[row - row0];
             const float* val = lds.vals + (e - e0);
-            float acc0 = 0.f, acc1 = 0.f;
+            float acc[2] = {0.f, 0.f};
             int s = 0;
-            for (; s + 8 <= live; s += 8) {
-                const floatx4 w0 = *reinterpret_cast<const floatx4*>(w + s), w1 = *reinterpret_cast<const floatx4*>(w + s + 4);
-                float y[8];
+            for (; s + 16 <= live; s += 16) {
+                floatx4 w4[4];
+                float y[16];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) y[i] = val[(s + i) * E];
+                for (int i = 0; i < 4; ++i) w4[i] = *reinterpret_cast<const floatx4*>(w + s + i * 4);
 #pragma unroll
-                for (int i = 0; i < 4; i += 2) {
-                    acc0 = fmaf(w0[i], y[i], acc0);
-                    acc1 = fmaf(w0[i + 1], y[i + 1], acc1);
-                }
+                for (int i = 0; i < 16; ++i) y[i] = val[(s + i) * E];
 #pragma unroll
-                for (int i = 0; i < 4; i += 2) {
-                    acc0 = fmaf(w1[i], y[i + 4], acc0);
-                    acc1 = fmaf(w1[i + 1], y[i + 5], acc1);
-                }
+                for (int i = 0; i < 16; ++i) acc[i & 1] = fmaf(w4[i / 4][i % 4], y[i], acc[i & 1]);
             }
-            for (; s < live; ++s) {
-                const float y = val[s * E];
-                if (s & 1) acc1 = fmaf(w[s], y, acc1);
-                else acc0 = fmaf(w[s], y, acc0);
+            for (; s < live; s += 2) {
+                acc[0] = fmaf(w[s], val[s * E], acc[0]);
+                if (s + 1 < live) acc[1] = fmaf(w[s + 1], val[(s + 1) * E], acc[1]);
             }
             const float den = lds.den[row - row0];
-            num = den > 0.f ? (acc0 + acc1) / den : 0.f;
-            lse = (lds.top[row - row0] + log2f(den)) * 0.6931471805599453f;
+            num = den > 0.f ? (acc[0] + acc[1]) / den : 0.f;
         }
         const __bf16 ob = (__bf16)num;
         a.out[(((int64_t)b * a.Qmax + qi) * a.Hq + h) * D + d] = __builtin_bit_cast(uint16_t, ob);
-        if (a.lse_out && d == 0) a.lse_out[((int64_t)b * a.Hq + h) * a.Qmax + qi] = lse;
+        if (a.lse_out && d == 0) {
+            float lse = 0.f;
+            if (row < R) lse = (lds.top[row - row0] + log2f(lds.den[row - row0])) * 0.6931471805599453f;
+            a.lse_out[((int64_t)b * a.Hq + h) * a.Qmax + qi] = lse;
+        }
     }
-    return true;
+    if (first) {
+        const uint32_t seen = (uint32_t)__ballot(mark == x.tag);
+        if (lane == 0) lds.seen[wave] = seen;
+        __syncthreads();
+        uint32_t left = 0;
+#pragma unroll
+        for (int w = 0; w < NWAVES; ++w) left |= lds.seen[w];
+        *marks = left;
+    }
+    return !any;
 }
 
 // What a workgroup does after it has published (`split` of n that hold tokens; split 0 answers for a sequence without any).
