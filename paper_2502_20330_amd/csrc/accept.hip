@@ -555,6 +555,7 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
         const bool pair = k < g;
         const float* zt = row_t(b, k);
         const float* zd = pair ? row_d(b, k) : nullptr;
+        if (!pair && a.ext_t) return;                         // of a bonus row only the maximum is needed, and that is given
         const bool full = (int64_t)(w + 1) * kSlice <= V;
         const int i = w * kSlice + tid * 4;
         load_runs(x, zt, i, NT * 4, V, full);
@@ -812,7 +813,10 @@ __global__ void __launch_bounds__(NT, OCC) accept_rows(AcceptLaunch a, Ws ws, in
                         wave_combine_f64(pair_h, W, kLn2, Mh, Sh);
                     }
                 } else {
-                    wave_combine_f64(pair_t, n_t, a.inv_T_exact, Mt, St);
+                    float m = -INFINITY;                     // the draw forms the sum itself
+                    for (int i = lane; i < n_t; i += 64) m = fmaxf(m, max_of(pair_t(i)));
+                    Mt = (double)wave_max(m);
+                    St = 1.0;
                 }
                 if (tid == 0) {
                     double* rec = ws.rows + ((int64_t)b * rows + k) * 4;
