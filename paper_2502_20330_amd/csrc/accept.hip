@@ -71,7 +71,7 @@ namespace {
 
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
-constexpr int kDrawSlice = kThreads * 2;            // smallest slice of accept_draw_row (2 entries per thread)
+constexpr int kDrawSlice = 256 * 4;                 // smallest slice of accept_draw_row
 constexpr int kMinSlice = kThreads * 4 * 2;         // smallest slice of accept_rows (NV = 2)
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -158,23 +158,16 @@ __device__ __forceinline__ void block_reduce2(T& a, T& b, T* sh, int& bank, OpA 
 template <int NE>
 __device__ __forceinline__ void load_row(float (&t)[NE], const float* rt, float (&d)[NE], const float* rd, int i, int V, bool full)
 {
-    if constexpr (NE >= 4) {
-        floatx4 x[NE / 4], y[NE / 4];
-        load_runs(x, rt, i, 4, V, full);
-        if (rd) load_runs(y, rd, i, 4, V, full);
-        shift_runs(x, i, 4, V, full);
-        if (rd) shift_runs(y, i, 4, V, full);
+    static_assert(NE % 4 == 0);
+    floatx4 x[NE / 4], y[NE / 4];
+    load_runs(x, rt, i, 4, V, full);
+    if (rd) load_runs(y, rd, i, 4, V, full);
+    shift_runs(x, i, 4, V, full);
+    if (rd) shift_runs(y, i, 4, V, full);
 #pragma unroll
-        for (int j = 0; j < NE; ++j) {
-            t[j] = x[j / 4][j % 4];
-            d[j] = rd ? y[j / 4][j % 4] : -INFINITY;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < NE; ++j) {
-            t[j] = i + j < V ? rt[i + j] : -INFINITY;
-            d[j] = rd && i + j < V ? rd[i + j] : -INFINITY;
-        }
+    for (int j = 0; j < NE; ++j) {
+        t[j] = x[j / 4][j % 4];
+        d[j] = rd ? y[j / 4][j % 4] : -INFINITY;
     }
 }
 
@@ -1215,10 +1208,13 @@ size_t accept_workspace_bytes(int B, int gmax, int V)
     return carve(nullptr, B, gmax, V).bytes;
 }
 
-// The build of accept_draw_row for a call.  Small batches: the fewest entries per thread that leave every workgroup a
-// compute unit of its own and keep the exchange among at most 64 workgroups (one sequence: vocabulary 32001 22.1 us
-// with 2, 23.0 with 4, 26.7 with 8; 128256 23.7 with 2 on 126 workgroups, 23.0 with 4, 25.0 with 8).  Eight entries while
-// the grid is one round of two workgroups per compute unit; beyond that 256 threads.  What counts there is how many waves stand by
+// The build of accept_draw_row for a call.  Small batches: 256 threads of 4 entries while that is at most 64 workgroups a sequence and three a
+// compute unit, 8 entries while one workgroup has a compute unit of its own.  Four waves meet faster than eight, and the
+// entries spread over as many compute units again: against 512 threads of half as many entries, the whole pass, vocabulary 4096 17.0 -> 16.3 us (1 to
+// 24 sequences), 32000 16.9 -> 16.0 (1), 20.0 -> 19.2 (8), 27.9 -> 26.4 (24), 50257 17.0 -> 16.2 (1), 21.7 -> 21.1 (8), 26.0 -> 25.3 (12), 28.7 -> 28.6 (16); with 8
+// 80000 18.7 -> 18.3 (1), 128256 18.3 -> 18.1 (1), 25.2 -> 24.9 (4); beyond 64 workgroups the exchange outweighs it (80000 with 4 entries 19.2, 152064 with 8 30.0
+// against 28.7 at 6 sequences).  Then 512 threads of eight entries while the grid is one round of two workgroups per compute unit;
+// beyond that 256 threads.  What counts there is how many waves stand by
 // while others wait in the three exchanges, and how many entries a compute unit has to take: twelve entries, up to four workgroups per
 // compute unit, while that is one round (20 sequences of 152064: 35.9 us, with 16 entries 38.9), but 20 entries in two workgroups where twelve need the
 // fourth and 20 do not need a third, 40 entries instead of 48 for the busiest compute units (48 sequences of 50257 53.9 -> 52.7 us, 32 of 75000 56.1 -> 54.7, 10 of
@@ -1231,9 +1227,9 @@ struct DrawShape {
 static DrawShape draw_shape(const AcceptLaunch& a)
 {
     const auto wgs = [&](int threads, int ne) { return (a.V + threads * ne - 1) / (threads * ne); };
-    const int w2 = wgs(512, 2), w4 = wgs(512, 4), w8 = wgs(512, 8);
-    if (w2 <= 64 && (int64_t)w2 * a.B <= a.n_cu) return {accept_draw_row<512, 2, 2>, 512, w2};
-    if (w4 <= 64 && (int64_t)w4 * a.B <= a.n_cu) return {accept_draw_row<512, 4, 2>, 512, w4};
+    const int w4 = wgs(256, 4), s8 = wgs(256, 8), w8 = wgs(512, 8);
+    if (w4 <= 64 && (int64_t)w4 * a.B <= 3 * (int64_t)a.n_cu) return {accept_draw_row<256, 4, 4>, 256, w4};
+    if (s8 <= 64 && (int64_t)s8 * a.B <= a.n_cu) return {accept_draw_row<256, 8, 2>, 256, s8};
     if ((int64_t)w8 * a.B <= a.n_cu) return {accept_draw_row<512, 8, 2>, 512, w8};
     if ((int64_t)w8 * a.B <= 2 * (int64_t)a.n_cu) return {accept_draw_row<512, 8, 4>, 512, w8};
     const int w12 = wgs(256, 12), w20 = wgs(256, 20);
