@@ -20,9 +20,10 @@
 
 namespace {
 
-constexpr int kThreads = 256;
 constexpr int kDecideWaves = 16;                       // waves of greedy_decide at most
-constexpr int kSlice = kThreads * 16;
+constexpr int kPerThread = 16;                         // entries of a thread of the row pass
+// Threads of its workgroups: 512, but 256 where these hold the whole row (4096 rows of 100: 16 us against 24, 1024 of 1000 12.7 against 13.5).
+__host__ __device__ inline int row_threads(int V) { return V <= 256 * kPerThread ? 256 : 512; }
 
 struct GreedyWs {
     int32_t* status;      // same place and meaning as in the general accept pass
@@ -35,7 +36,8 @@ __host__ __device__ inline size_t galign(size_t x) { return (x + 255) / 256 * 25
 __host__ __device__ inline GreedyWs gcarve(void* base, int B, int gmax, int V)
 {
     GreedyWs w;
-    w.W = (V + kSlice - 1) / kSlice;
+    const int slice = row_threads(V) * kPerThread;
+    w.W = (V + slice - 1) / slice;
     char* p = static_cast<char*>(base);
     w.status = reinterpret_cast<int32_t*>(p); p += 256;
     const size_t n = (size_t)B * (2 * gmax + 1) * w.W;
@@ -77,13 +79,14 @@ __device__ __forceinline__ void wave_best(float& m, int& idx)
     m = best;
 }
 
-// Row y of sequence b: y <= gmax the target rows, then the draft rows.  Four 128-bit loads per thread, all in flight
-// at once (eight, in half as many workgroups: 101 us instead of 97 at 64 sequences of 128256 entries and 8 drafts,
-// 558 MB); a thread's entries come in index order, so equal maxima keep the lowest index by themselves.
-__global__ void __launch_bounds__(kThreads) greedy_slice_argmax(AcceptLaunch a, GreedyWs ws)
+// Row y of sequence b: y <= gmax the target rows, then the draft rows.  Bound by the read: four 128-bit loads per thread, all in flight
+// at once, with the streaming hint (64 sequences of 128256 entries and 8 drafts, 558 MB, both launches: 97.0 us without it, 88.5 with it, 86.6 = 6.4 TB/s with
+// 512 threads instead of 256; eight loads 88.0 on 256; 16 sequences of 6 drafts 23.2, 22.2, 21.9, 22.7; 64 of 32000 18.2, 17.1, 16.9, 17.6); a thread's entries come in index order, so equal maxima keep the lowest index by themselves.
+template <int NT>
+__global__ void __launch_bounds__(NT) greedy_slice_argmax(AcceptLaunch a, GreedyWs ws)
 {
-    __shared__ float shm[kThreads / 64];
-    __shared__ int shi[kThreads / 64];
+    __shared__ float shm[NT / 64];
+    __shared__ int shi[NT / 64];
     const int w = blockIdx.x, y = blockIdx.y, b = blockIdx.z;
     // only the two status words: the words behind them are the general pass's call counters, which persist
     if (w == 0 && y == 0 && b == 0 && threadIdx.x < 2) ws.status[threadIdx.x] = 0;
@@ -92,20 +95,20 @@ __global__ void __launch_bounds__(kThreads) greedy_slice_argmax(AcceptLaunch a, 
     const int k = is_t ? y : y - (a.gmax + 1);
     if (is_t ? (k > g) : (k >= g)) return;
     const float* row = is_t ? a.zt + ((int64_t)b * (a.gmax + 1) + k) * a.V : a.zd + ((int64_t)b * a.gmax + k) * a.V;
-    constexpr int NV = kSlice / (4 * kThreads);
+    constexpr int NV = kPerThread / 4, kSlice = NT * kPerThread;
     const int i0 = w * kSlice + threadIdx.x * 4;
     const bool full = (int64_t)(w + 1) * kSlice <= a.V;
     floatx4 x[NV];
-    load_runs(x, row, i0, kThreads * 4, a.V, full);
-    shift_runs(x, i0, kThreads * 4, a.V, full);
+    load_runs<NV, true>(x, row, i0, NT * 4, a.V, full);
+    shift_runs(x, i0, NT * 4, a.V, full);
     float m = -INFINITY;
     int idx = 0x7fffffff;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        if (!full && i0 + v * kThreads * 4 >= a.V) break;     // short rows: nothing left for this thread (whole waves leave)
+        if (!full && i0 + v * NT * 4 >= a.V) break;     // short rows: nothing left for this thread (whole waves leave)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int i = i0 + v * kThreads * 4 + j;
+            const int i = i0 + v * NT * 4 + j;
             // (-inf is a maximum like any other as long as it is an entry of the row)
             const bool first = x[v][j] == m && idx == 0x7fffffff && i < a.V;
             if (x[v][j] > m || first) { m = x[v][j]; idx = i; }
@@ -115,7 +118,7 @@ __global__ void __launch_bounds__(kThreads) greedy_slice_argmax(AcceptLaunch a, 
     if ((threadIdx.x & 63) == 0) { shm[threadIdx.x >> 6] = m; shi[threadIdx.x >> 6] = idx; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int s = 1; s < kThreads / 64; ++s) take_better(m, idx, shm[s], shi[s]);
+        for (int s = 1; s < NT / 64; ++s) take_better(m, idx, shm[s], shi[s]);
         const int64_t slot = ((int64_t)b * (2 * a.gmax + 1) + y) * ws.W + w;
         ws.smax[slot] = m;
         ws.sidx[slot] = idx;
@@ -218,7 +221,9 @@ size_t accept_greedy_workspace_bytes(int B, int gmax, int V)
 hipError_t launch_accept_greedy(const AcceptLaunch& a, hipStream_t stream)
 {
     GreedyWs ws = gcarve(a.workspace, a.B, a.gmax, a.V);
-    hipLaunchKernelGGL(greedy_slice_argmax, dim3(ws.W, 2 * a.gmax + 1, a.B), dim3(kThreads), 0, stream, a, ws);
+    const int threads = row_threads(a.V);
+    hipLaunchKernelGGL(threads == 256 ? greedy_slice_argmax<256> : greedy_slice_argmax<512>, dim3(ws.W, 2 * a.gmax + 1, a.B),
+                       dim3(threads), 0, stream, a, ws);
     // A wave per position while every sequence has a compute unit to itself (the decision is then one chain of loads), four
     // beyond, where the chip is full: 4096 sequences of one draft (vocabulary 100) took 53 us a call with 16 waves, 28 with four,
     // and 21 since the row pass also leaves out what lies past a short row.

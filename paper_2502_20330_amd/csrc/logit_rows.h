@@ -33,12 +33,16 @@ __device__ __forceinline__ floatx4 load4(const float* row, int i, int V)
     return r;
 }
 // N runs of four, `step` entries apart, the first at index i; `full`: the row holds all of them for every thread.
-template <int N>
+// ONCE: nobody reads the row again (streaming hint; rows that the draw reads again lose by it, 64 sequences 115 -> 119 us).
+template <int N, bool ONCE = false>
 __device__ __forceinline__ void load_runs(floatx4 (&r)[N], const float* row, int i, int step, int V, bool full)
 {
     if (full) {
 #pragma unroll
-        for (int v = 0; v < N; ++v) r[v] = load4_full(row + v * step + (unsigned)i);      // uniform base + 32-bit offset
+        for (int v = 0; v < N; ++v) {
+            const float* p = row + v * step + (unsigned)i;                                 // uniform base + 32-bit offset
+            r[v] = ONCE ? __builtin_nontemporal_load(reinterpret_cast<const floatx4_any*>(p)) : load4_full(p);
+        }
     } else if (V >= 4) {
 #pragma unroll
         for (int v = 0; v < N; ++v) {

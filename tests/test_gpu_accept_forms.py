@@ -342,3 +342,9 @@ def test_ratios_past_a_sequences_drafts(T):
         assert torch.equal(out[0], n) and torch.equal(out[1], toks)
         assert torch.equal(out[2][~past].view(torch.int32), mine[~past].view(torch.int32))
         assert torch.equal(out[2][past].view(torch.int32), torch.zeros_like(out[2][past]).view(torch.int32))
+
+
+@pytest.mark.parametrize("V", [4096, 8192, 12289])
+def test_greedy_rows_at_the_borders_of_slices(V):
+    """One workgroup of 256 threads a row up to 4096 entries, slices of 8192 on 512 threads beyond."""
+    test_greedy_ties_masks_and_row_ends(V)
