@@ -8,6 +8,11 @@
 // handle for hipGetSymbolAddress; the device address is looked up once per context
 // (rapid_create, with the context's device current) and kept in rapid_ctx::static_scratch.
 static __device__ __align__(256) unsigned char scratch[RAPID_STATIC_SCRATCH_BYTES];
+// And its exchange memory (zero when the library is loaded), enough for every shape that takes one launch.
+constexpr size_t kStaticExchangeBytes = 9u << 19;
+static_assert(kStaticExchangeBytes >= kAttnExchangeHeadBytes + (size_t)kAttnTeams * 32 * (64 + 2) * 8 &&
+              kStaticExchangeBytes >= kAttnExchangeHeadBytes + (size_t)kAttnTeams * 16 * (128 + 2) * 8);
+static __device__ __align__(256) unsigned char exchange_memory[kStaticExchangeBytes];
 
 namespace {
 
@@ -215,11 +220,22 @@ void plan_attn(const rapid_ctx* ctx, const rapid_attn_shape* shape, AttnLaunch& 
 
 // Bytes of exchange memory with which the call is one launch, 0 where it is two: few rows (attn_in_one_launch), a fixed grid of
 // at most one workgroup per compute unit (they wait for one another), and no more splits than one wave forms weights for.
-size_t plan_exchange(const rapid_ctx* ctx, const AttnLaunch& a)
+// Where the library chooses the split and half of the compute units would do, such a call takes splits of 128 tokens, one tile a wave, instead
+// of the 256 below which a second launch has too much to merge (us a call in a graph, 256 and 128 tokens: 2K tokens, one head of 64, 5 rows
+// 7.7 and 7.1; 4K 7.8 and 7.3; 8 heads of 128, 4 rows, 512 tokens 8.5 and 7.9, 2K 9.0 and 8.2; 4 heads, 4K 8.9 and 8.5; on all compute units 8 heads,
+// 4K 9.2 and 9.5, 16 rows 9.9 and 11.1).
+size_t plan_exchange(const rapid_ctx* ctx, const rapid_attn_shape* shape, AttnLaunch& a)
 {
+    const int64_t n_cu = ctx ? ctx->n_cu : 256;
+    if (a.groups || !attn_in_one_launch(a.RB, a.D)) return 0;
+    const int fine = (a.max_ctx + 127) / 128;
+    if (shape->chunk_tokens == 0 && a.chunk > 128 && fine <= kMaxShares && 2 * (int64_t)a.B * a.Hkv * fine <= n_cu) {
+        a.chunk = 128;
+        a.nsplit = fine;
+        plan_layout(ctx, a, false);
+    }
     const int64_t wgs = (int64_t)a.B * a.Hkv * a.nsplit;
-    if (a.groups || !attn_in_one_launch(a.RB, a.D) || a.nsplit > kMaxShares) return 0;
-    if (wgs > (ctx ? ctx->n_cu : 256) || wgs > kAttnTeams) return 0;
+    if (a.nsplit > kMaxShares || wgs > n_cu || wgs > kAttnTeams) return 0;
     return attn_exchange_bytes(a.B, a.Hkv, a.nsplit, a.RB, a.D);
 }
 
@@ -248,13 +264,16 @@ int rapid_create(rapid_ctx** out, int device)
     if (ec == hipSuccess) ec = configure_lm_head();
     if (ec == hipSuccess) ec = configure_hbm_read_probe();
     void* scratch_ptr = nullptr;                      // this device's copy of `scratch`
+    void* exchange_ptr = nullptr;
     if (ec == hipSuccess) ec = hipGetSymbolAddress(&scratch_ptr, HIP_SYMBOL(scratch));
+    if (ec == hipSuccess) ec = hipGetSymbolAddress(&exchange_ptr, HIP_SYMBOL(exchange_memory));
     (void)hipSetDevice(prev);
-    if (ec != hipSuccess || !scratch_ptr) return RAPID_EHIP;
+    if (ec != hipSuccess || !scratch_ptr || !exchange_ptr) return RAPID_EHIP;
     rapid_ctx* c = new (std::nothrow) rapid_ctx;
     if (!c) return RAPID_EINVAL;
     c->device = device;
     c->static_scratch = scratch_ptr;
+    c->static_exchange = exchange_ptr;
     c->accept_wait_ticks = 100 * 100;                 // 100 us
     c->accept_slice = 0;
     c->attn_wait_ticks = 100 * 100;
@@ -346,7 +365,7 @@ static int attn_call(rapid_ctx* ctx, const rapid_attn_shape* shape,
     a.out = static_cast<uint16_t*>(out);
     a.lse_out = lse_out;
     plan_attn(ctx, shape, a);
-    const size_t need_x = exchange ? plan_exchange(ctx, a) : 0;
+    const size_t need_x = exchange ? plan_exchange(ctx, shape, a) : 0;
     if (need_x) {
         if (!aligned(exchange, 256) || exchange_bytes < need_x) return RAPID_EWORKSPACE;
         a.xhead = static_cast<AttnExchangeHead*>(exchange);
@@ -377,7 +396,7 @@ size_t rapid_verify_attn_exchange_bytes(const rapid_ctx* ctx, const rapid_attn_s
     if (check_attn_shape(shape) != RAPID_OK) return 0;
     AttnLaunch a{};
     plan_attn(ctx, shape, a);
-    return plan_exchange(ctx, a);
+    return plan_exchange(ctx, shape, a);
 }
 
 int rapid_verify_attn(rapid_ctx* ctx, const rapid_attn_shape* shape,
@@ -409,9 +428,9 @@ int rapid_verify_attn_static(rapid_ctx* ctx, const rapid_attn_shape* shape,
     const int rc = check_attn_shape(shape);
     if (rc != RAPID_OK) return rc;
     if (rapid_verify_attn_workspace_bytes(ctx, shape) > (size_t)RAPID_STATIC_SCRATCH_BYTES) return RAPID_ETOOLARGE;
-    // same kernels, same argument checks; the split partials go to this device's static array
-    return rapid_verify_attn(ctx, shape, q, k_cache, v_cache, ctx_lens, gammas, page_table, out, lse_out,
-                             ctx->static_scratch, (size_t)RAPID_STATIC_SCRATCH_BYTES, stream);
+    // same kernels, same argument checks; partials go to this device's static arrays
+    return attn_call(ctx, shape, q, k_cache, v_cache, ctx_lens, gammas, page_table, out, lse_out, ctx->static_exchange,
+                     kStaticExchangeBytes, ctx->static_scratch, (size_t)RAPID_STATIC_SCRATCH_BYTES, stream);
 }
 
 size_t rapid_accept_workspace_bytes(const rapid_ctx*, int batch, int gamma_max, int vocab)
