@@ -53,7 +53,7 @@ def parse_args():
     return ap.parse_args()
 
 
-TRAFFIC_SOURCES = {"verify_attn": ["verify_attn.hip"], "rapid_accept": ["accept.hip", "exp64.h", "logit_rows.h"],
+TRAFFIC_SOURCES = {"verify_attn": ["verify_attn.hip", "attn_exchange.h"], "rapid_accept": ["accept.hip", "exp64.h", "logit_rows.h"],
                    "rapid_lm_head": ["lm_head.hip"]}
 
 
@@ -137,12 +137,13 @@ def also_workload(r, cfg, n_layers, head_major, steps=5, warmup=2):
                          ctx_sum_hint=tokens)
     ws = torch.empty(max(lib.rapid_verify_attn_workspace_bytes(r._ctx, ctypes.byref(shape)), 256),
                      dtype=torch.uint8, device=dev)
+    xch = torch.zeros(max(lib.rapid_verify_attn_exchange_bytes(r._ctx, ctypes.byref(shape)), 256), dtype=torch.uint8, device=dev)
     # a workspace of its own: the accept pass keeps a call counter in it from one call to the next
     ws_a = torch.empty(max(lib.rapid_accept_workspace_bytes(r._ctx, B, gmax, V), 256), dtype=torch.uint8, device=dev)
     stream = ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
     P = lambda t: ctypes.c_void_p(t.data_ptr()) if t is not None else None
     attn_args = [(r._ctx, ctypes.byref(shape), P(qs[l]), P(ks[l]), P(vs[l]), P(ctx_lens), P(gammas), P(page_table),
-                  P(out), None, P(ws), ws.numel(), stream) for l in range(nbuf)]
+                  P(out), None, P(xch), xch.numel(), P(ws), ws.numel(), stream) for l in range(nbuf)]
     acc_args = (r._ctx, B, gmax, V, P(zt), P(zd), P(draft_tokens), P(gammas), float(cfg.eta), float(cfg.temperature),
                 float(cfg.tail_alpha), P(uniforms), P(n_acc), P(out_tok), None, P(ws_a), ws_a.numel(), stream)
 
@@ -158,7 +159,7 @@ def also_workload(r, cfg, n_layers, head_major, steps=5, warmup=2):
         first = (it * n_layers) % nbuf
         e[0].record()
         for a in attn_args[first:first + n_layers]:
-            check(lib.rapid_verify_attn(*a))
+            check(lib.rapid_verify_attn_exchange(*a))
         e[1].record()
         check(lib.rapid_accept(*acc_args))
         e[2].record()
@@ -347,11 +348,12 @@ def main():
     ws_attn = lib.rapid_verify_attn_workspace_bytes(r._ctx, ctypes.byref(shape))
     ws_acc = lib.rapid_accept_workspace_bytes(r._ctx, B, gmax, V)
     ws = torch.empty(max(ws_attn, 256), dtype=torch.uint8, device=dev)
+    xch = torch.zeros(max(lib.rapid_verify_attn_exchange_bytes(r._ctx, ctypes.byref(shape)), 256), dtype=torch.uint8, device=dev)
     ws_a = torch.empty(max(ws_acc, 256), dtype=torch.uint8, device=dev)      # the accept pass's own (it keeps state)
     stream = ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
     P = lambda t: ctypes.c_void_p(t.data_ptr()) if t is not None else None
     attn_args = [(r._ctx, ctypes.byref(shape), P(qs[l]), P(ks[l]), P(vs[l]), P(ctx_lens), P(gammas), P(page_table),
-                  P(outs[l & 1]), None, P(ws), ws.numel(), stream) for l in range(nbuf)]
+                  P(outs[l & 1]), None, P(xch), xch.numel(), P(ws), ws.numel(), stream) for l in range(nbuf)]
     acc_args = (r._ctx, B, gmax, V, P(zt), P(zd), P(draft_tokens), P(gammas), float(cfg.eta),
                 float(cfg.temperature), float(cfg.tail_alpha), P(uniforms), P(n_acc), P(out_tok), P(ratio),
                 P(ws_a), ws_a.numel(), stream)
@@ -373,7 +375,7 @@ def main():
         if ev:
             ev[0].record()
         for a in attn_args[first:first + layers]:
-            check(lib.rapid_verify_attn(*a))
+            check(lib.rapid_verify_attn_exchange(*a))
         if ev:
             ev[1].record()
         if head:
@@ -530,7 +532,7 @@ def main():
                 vs.append(kv_randn(g))
                 qs.append(torch.randn((B, Q, Hq, d), dtype=torch.bfloat16, device=dev, generator=g))
             attn_args = [(r._ctx, ctypes.byref(shape), P(qs[l]), P(ks[l]), P(vs[l]), P(ctx_lens), P(gammas), P(page_table),
-                          P(outs[l & 1]), None, P(ws), ws.numel(), stream) for l in range(nl)]
+                          P(outs[l & 1]), None, P(xch), xch.numel(), P(ws), ws.numel(), stream) for l in range(nl)]
         host = [(to_bits(qs[l]), to_bits(ks[l]), to_bits(vs[l])) for l in range(nl)]
         acc_host = (zt.cpu().numpy(), zd.cpu().numpy(), draft_tokens.cpu().numpy(), uniforms.cpu().numpy())
         worst = 0.0
@@ -541,7 +543,7 @@ def main():
                                 tail_alpha=cfg.tail_alpha, gammas=seqs.gammas)
         cpu_s = time.perf_counter() - t0
         for l in range(nl):             # parity of the timed launch configuration, for the record
-            check(lib.rapid_verify_attn(*attn_args[l]))
+            check(lib.rapid_verify_attn_exchange(*attn_args[l]))
             torch.cuda.synchronize()
             got = wl.bf16_bits_to_f32(to_bits(outs[l & 1])).astype(np.float64)
             worst = max(worst, float(np.max(np.abs(got - refs[l]) - 1e-2 * np.abs(refs[l]))))
