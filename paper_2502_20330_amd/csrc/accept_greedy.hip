@@ -20,10 +20,9 @@
 
 namespace {
 
+constexpr int kThreads = 256;
 constexpr int kDecideWaves = 16;                       // waves of greedy_decide at most
-constexpr int kPerThread = 16;                         // entries of a thread of the row pass
-// Threads of its workgroups: 512, but 256 where these hold the whole row (4096 rows of 100: 16 us against 24, 1024 of 1000 12.7 against 13.5).
-__host__ __device__ inline int row_threads(int V) { return V <= 256 * kPerThread ? 256 : 512; }
+constexpr int kSlice = kThreads * 16;
 
 struct GreedyWs {
     int32_t* status;      // same place and meaning as in the general accept pass
@@ -36,8 +35,7 @@ __host__ __device__ inline size_t galign(size_t x) { return (x + 255) / 256 * 25
 __host__ __device__ inline GreedyWs gcarve(void* base, int B, int gmax, int V)
 {
     GreedyWs w;
-    const int slice = row_threads(V) * kPerThread;
-    w.W = (V + slice - 1) / slice;
+    w.W = (V + kSlice - 1) / kSlice;
     char* p = static_cast<char*>(base);
     w.status = reinterpret_cast<int32_t*>(p); p += 256;
     const size_t n = (size_t)B * (2 * gmax + 1) * w.W;
@@ -80,13 +78,13 @@ __device__ __forceinline__ void wave_best(float& m, int& idx)
 }
 
 // Row y of sequence b: y <= gmax the target rows, then the draft rows.  Bound by the read: four 128-bit loads per thread, all in flight
-// at once, with the streaming hint (64 sequences of 128256 entries and 8 drafts, 558 MB, both launches: 97.0 us without it, 88.5 with it, 86.6 = 6.4 TB/s with
-// 512 threads instead of 256; eight loads 88.0 on 256; 16 sequences of 6 drafts 23.2, 22.2, 21.9, 22.7; 64 of 32000 18.2, 17.1, 16.9, 17.6); a thread's entries come in index order, so equal maxima keep the lowest index by themselves.
-template <int NT>
-__global__ void __launch_bounds__(NT) greedy_slice_argmax(AcceptLaunch a, GreedyWs ws)
+// at once, with the streaming hint (64 sequences of 128256 entries and 8 drafts, 558 MB, both launches: 97.0 us without it, 88.5 = 6.3 TB/s with it; 16
+// sequences of 4 to 8 drafts 21.0 and 20.4).  512 threads take 86.6 and 21.4, and 24 instead of 16 for 4096 rows of 100; eight loads 88.0 and 22.7 against 22.2 at
+// 16 sequences of 6 drafts.  A thread's entries come in index order, so equal maxima keep the lowest index by themselves.
+__global__ void __launch_bounds__(kThreads) greedy_slice_argmax(AcceptLaunch a, GreedyWs ws)
 {
-    __shared__ float shm[NT / 64];
-    __shared__ int shi[NT / 64];
+    __shared__ float shm[kThreads / 64];
+    __shared__ int shi[kThreads / 64];
     const int w = blockIdx.x, y = blockIdx.y, b = blockIdx.z;
     // only the two status words: the words behind them are the general pass's call counters, which persist
     if (w == 0 && y == 0 && b == 0 && threadIdx.x < 2) ws.status[threadIdx.x] = 0;
@@ -95,20 +93,20 @@ __global__ void __launch_bounds__(NT) greedy_slice_argmax(AcceptLaunch a, Greedy
     const int k = is_t ? y : y - (a.gmax + 1);
     if (is_t ? (k > g) : (k >= g)) return;
     const float* row = is_t ? a.zt + ((int64_t)b * (a.gmax + 1) + k) * a.V : a.zd + ((int64_t)b * a.gmax + k) * a.V;
-    constexpr int NV = kPerThread / 4, kSlice = NT * kPerThread;
+    constexpr int NV = kSlice / (4 * kThreads);
     const int i0 = w * kSlice + threadIdx.x * 4;
     const bool full = (int64_t)(w + 1) * kSlice <= a.V;
     floatx4 x[NV];
-    load_runs<NV, true>(x, row, i0, NT * 4, a.V, full);
-    shift_runs(x, i0, NT * 4, a.V, full);
+    load_runs<NV, true>(x, row, i0, kThreads * 4, a.V, full);
+    shift_runs(x, i0, kThreads * 4, a.V, full);
     float m = -INFINITY;
     int idx = 0x7fffffff;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        if (!full && i0 + v * NT * 4 >= a.V) break;     // short rows: nothing left for this thread (whole waves leave)
+        if (!full && i0 + v * kThreads * 4 >= a.V) break;     // short rows: nothing left for this thread (whole waves leave)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int i = i0 + v * NT * 4 + j;
+            const int i = i0 + v * kThreads * 4 + j;
             // (-inf is a maximum like any other as long as it is an entry of the row)
             const bool first = x[v][j] == m && idx == 0x7fffffff && i < a.V;
             if (x[v][j] > m || first) { m = x[v][j]; idx = i; }
@@ -118,7 +116,7 @@ __global__ void __launch_bounds__(NT) greedy_slice_argmax(AcceptLaunch a, Greedy
     if ((threadIdx.x & 63) == 0) { shm[threadIdx.x >> 6] = m; shi[threadIdx.x >> 6] = idx; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int s = 1; s < NT / 64; ++s) take_better(m, idx, shm[s], shi[s]);
+        for (int s = 1; s < kThreads / 64; ++s) take_better(m, idx, shm[s], shi[s]);
         const int64_t slot = ((int64_t)b * (2 * a.gmax + 1) + y) * ws.W + w;
         ws.smax[slot] = m;
         ws.sidx[slot] = idx;
@@ -221,9 +219,7 @@ size_t accept_greedy_workspace_bytes(int B, int gmax, int V)
 hipError_t launch_accept_greedy(const AcceptLaunch& a, hipStream_t stream)
 {
     GreedyWs ws = gcarve(a.workspace, a.B, a.gmax, a.V);
-    const int threads = row_threads(a.V);
-    hipLaunchKernelGGL(threads == 256 ? greedy_slice_argmax<256> : greedy_slice_argmax<512>, dim3(ws.W, 2 * a.gmax + 1, a.B),
-                       dim3(threads), 0, stream, a, ws);
+    hipLaunchKernelGGL(greedy_slice_argmax, dim3(ws.W, 2 * a.gmax + 1, a.B), dim3(kThreads), 0, stream, a, ws);
     // A wave per position while every sequence has a compute unit to itself (the decision is then one chain of loads), four
     // beyond, where the chip is full: 4096 sequences of one draft (vocabulary 100) took 53 us a call with 16 waves, 28 with four,
     // and 21 since the row pass also leaves out what lies past a short row.

@@ -346,5 +346,5 @@ def test_ratios_past_a_sequences_drafts(T):
 
 @pytest.mark.parametrize("V", [4096, 8192, 12289])
 def test_greedy_rows_at_the_borders_of_slices(V):
-    """One workgroup of 256 threads a row up to 4096 entries, slices of 8192 on 512 threads beyond."""
+    """One slice, two, and four with one entry in the last."""
     test_greedy_ties_masks_and_row_ends(V)
