@@ -190,3 +190,22 @@ def test_first_call_of_an_object_inside_a_capture():
         _same(_one(r, c), want)
         graph.replay()
         _same(got, want)
+
+
+def test_two_objects_on_two_streams():
+    """Each has exchange memory of its own; their workgroups share the compute units, so that one may wait for another that has
+    none yet: the bounded waits and left-over shares are what ends that."""
+    cases = [_case(*SHAPES[5]), _case(*SHAPES[6], seed=1)]
+    objects = [Rapid(0), Rapid(0)]
+    want = [_one(r, c) for r, c in zip(objects, cases)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    got = [[], []]
+    for _ in range(40):
+        for i in range(2):
+            with torch.cuda.stream(streams[i]):
+                got[i].append(_one(objects[i], cases[i]))
+    torch.cuda.synchronize()
+    for i in range(2):
+        for g in got[i]:
+            _same(g, want[i])
