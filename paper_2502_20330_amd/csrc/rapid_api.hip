@@ -126,13 +126,13 @@ int plan_chunk(const rapid_ctx* ctx, const rapid_attn_shape* s)
 //    batches; when heads interleave inside a token row it costs 2.5 %, because the
 //    workgroups that share those rows no longer run side by side.
 //  * skew: with a single wave of workgroups (one per compute unit) the dies on odd
-//    dispatch slots finish 10..15 % later than the even ones.  Moving a part of a
+//    dispatch slots finish 10..15 % later than the even ones.  Moving about a tenth of a
 //    split from each odd-slot workgroup to its even-slot pair partner evens that out
-//    (2..5 % on the whole call).  It also moves which addresses the waves read at a time, so
+//    (2..3 % on the whole call).  It also moves which addresses the waves read at a time, so
 //    that its gain depends on where the caches lie.  With several workgroups per compute unit the
 //    dispatcher balances by itself and the skew only hurts.
 // The skew is a multiple of 128 tokens so both partners keep whole tiles per wave.
-void plan_layout(const rapid_ctx* ctx, AttnLaunch& a, bool chunk_chosen)
+void plan_layout(const rapid_ctx* ctx, AttnLaunch& a)
 {
     a.rot = a.hstride > a.tstride && a.Hkv > 1;
     a.skew = 0;
@@ -143,24 +143,15 @@ void plan_layout(const rapid_ctx* ctx, AttnLaunch& a, bool chunk_chosen)
         return;
     }
     const int64_t wgs = (int64_t)a.B * a.Hkv * a.nsplit, n_cu = ctx ? ctx->n_cu : 256;
-    if (!(a.rot && a.Hkv % 2 == 0 && a.nsplit >= 2 && wgs <= n_cu)) return;
-    // A caller who chose the split size finds the borders where they have always been, 3/32 of the split (1/16 in the two-team
-    // kernel) apart: they decide which tokens share a reference maximum, and so the last bits of a result.
-    if (chunk_chosen) {
+    // measured: 3/32 of the split for the one-team kernel (36 rows, 128K tokens: 88.2 us with 384 tokens, 89.5 with 256,
+    // 91.1 with none), 1/16 for the two-team kernel, which runs all waves through the same number of tiles
+    // (70B shape: 93-94 us with 256 tokens, 96.5 with 384).  Where the caches lie counts for as much: over eight
+    // placements of them the 70B shape takes 97.7 us on average with 256 tokens, 95.2 with 128 and 95.5 with none; 128 tokens for every
+    // split were worth 2 % at 36 rows of 64K tokens (49.9 -> 48.8) and 6 % at 256K (176 -> 166).  The
+    // borders stay all the same, whoever chose the split: they decide which tokens share a reference maximum and so the last bits of
+    // a result.
+    if (a.rot && a.Hkv % 2 == 0 && a.nsplit >= 2 && wgs <= n_cu)
         a.skew = a.wide ? a.chunk / 16 / 128 * 128 : (a.chunk * 3 / 32 + 64) / 128 * 128;
-        return;
-    }
-    // Else 128 tokens, one tile a wave, nearly everywhere: what a larger skew evens out between the dies it loses in the order in
-    // which the channels are read (three placements of the caches each, us, none / 128 / 256 / 384 tokens; 8 kv heads):
-    //   two teams, 72 rows:  32K 32.6 / 32.1 / 33.3 / 34.2, 64K 53.6 / 51.2 / 52.5 / 52.5, 128K 93.8 / 89.6 / 92.2 / 90.0, 256K 128 165.5, 512 171.1;
-    //              77 rows, 4 heads: 32K 24.9 / 24.2 / 25.6, 64K 33.7 / 33.4 / 34.4, 128K 54.3 / 52.2 / 53.4
-    //   one team, 36 rows:   32K 30.2 / 29.7 / 30.9, 64K 50.7 / 48.8 / 49.9 / 50.2, 96K 69.6 / 67.8 / 68.3 / 68.8, 112K 79.4 / 77.6 / 77.8 / 78.4
-    // The one-team kernel takes 384 from splits of 3840 tokens on (124K - / 87.0 / 84.0 / 85.6, 128K 89.4 / 86.9 / 87.6 / 86.3, 144K - / 96.7 / 96.9 / 96.5,
-    // 192K - / 125.9 / 125.6 / 124.7; 256K 164.2 with 128, 165.9 with 384, 176.2 with the 3/32 it had), and none below 768
-    // rows of 256 bytes (17K of 128: 20.6 / 21.2, 32K of 64: 15.4 / 16.2, 44K 18.6 / 19.0, 48K 20.7 / 19.9); the two-team kernel none
-    // below 512.
-    if (a.wide) a.skew = a.chunk >= 512 ? 128 : 0;
-    else a.skew = a.chunk * a.D < 768 * 128 ? 0 : a.chunk < 3840 ? 128 : 384;
 }
 
 // Groups of the balanced plan (verify_attn.hip), 0 = the fixed grid of splits.  Taken by ragged batches whose split the
@@ -215,7 +206,7 @@ void plan_attn(const rapid_ctx* ctx, const rapid_attn_shape* shape, AttnLaunch& 
     }
     a.page_hi = page_hi_of(shape);
     a.scale_log2e = shape->softmax_scale * 1.4426950408889634f;
-    plan_layout(ctx, a, shape->chunk_tokens > 0);
+    plan_layout(ctx, a);
 }
 
 // Bytes of exchange memory with which the call is one launch, 0 where it is two: few rows (attn_in_one_launch), a fixed grid of
@@ -232,7 +223,7 @@ size_t plan_exchange(const rapid_ctx* ctx, const rapid_attn_shape* shape, AttnLa
     if (shape->chunk_tokens == 0 && a.chunk > 128 && fine <= kMaxShares && 2 * (int64_t)a.B * a.Hkv * fine <= n_cu) {
         a.chunk = 128;
         a.nsplit = fine;
-        plan_layout(ctx, a, false);
+        plan_layout(ctx, a);
     }
     const int64_t wgs = (int64_t)a.B * a.Hkv * a.nsplit;
     if (a.nsplit > kMaxShares || wgs > n_cu || wgs > kAttnTeams) return 0;

@@ -492,3 +492,18 @@ def test_where_the_splits_lie(hq, skew):
         borders = {first // 4 * i for i in (1, 2, 3, 4)} | {first + (L - first) // 4 * i for i in (1, 2, 3)}
         assert set(got.tolist()) == {0.0, 1.0}
         assert {32 * (i + 1) for i in range(254) if got[i] == 0} == borders, odd
+
+
+@pytest.mark.parametrize("rows,hq,hkv,d,L", [(9, 32, 8, 128, 32768), (9, 32, 8, 128, 65536), (9, 32, 8, 128, 131072),
+                                             (9, 64, 8, 128, 65536), (9, 64, 8, 128, 131072), (4, 16, 8, 64, 65536)])
+def test_the_planned_split_passed_back_is_the_same_plan(rows, hq, hkv, d, L):
+    """rapid_verify_attn_chunk names the split that a call without one runs with; a caller who passes it gets the same borders
+    and so the same bits."""
+    g = torch.Generator(device="cuda").manual_seed(L + hq)
+    q = torch.randn(1, rows, hq, d, device="cuda", generator=g).bfloat16()
+    k, v = (torch.randn(1, hkv, L, d, device="cuda", generator=g).bfloat16().permute(0, 2, 1, 3) for _ in "kv")
+    ctx = torch.full((1,), L, dtype=torch.int32, device="cuda")
+    r = gu.rapid()
+    chunk = r.verify_attn_chunk(r.attn_shape(q, k, L))
+    got = [r.rapid_verify_attn(q, k, v, ctx, max_ctx=L, chunk_tokens=c) for c in (0, chunk)]
+    assert torch.equal(*(t.view(torch.int16) for t in got))
