@@ -126,8 +126,7 @@ typedef struct rapid_attn_shape {
 /* Tokens per KV split the library plans with for `shape` (multiple of 128), and
  * through it the number of splits per (sequence, kv head): ceil(max_ctx / chunk); both size the workspace.
  * (Ragged batches with ctx_sum_hint set and chunk_tokens 0 that are large enough are divided on the device instead,
- * into equal shares of their tokens, within the same workspace; rapid_verify_attn_exchange may take smaller splits where it
- * needs one launch.) */
+ * into equal shares of their tokens, within the same workspace.) */
 int rapid_verify_attn_chunk(const rapid_ctx* ctx, const rapid_attn_shape* shape);
 
 /* Bytes of device workspace rapid_verify_attn needs for `shape` (0 on a bad shape). */
@@ -165,8 +164,8 @@ int rapid_verify_attn(rapid_ctx* ctx, const rapid_attn_shape* shape,
 
 /*
  * rapid_verify_attn, in one launch where the shape has few query rows per kv head and its grid is at most one workgroup per
- * compute unit: the workgroups then exchange their partial results and merge them themselves, with the same bits as the merge
- * launch.  Same operation, same argument rules; two more arguments:
+ * compute unit: the workgroups then exchange their partial results and merge them themselves.  Same operation, same splits, same bits,
+ * same argument rules; two more arguments:
  *   exchange   device memory of rapid_verify_attn_exchange_bytes() or more, 256-byte aligned, or NULL (the call is then
  *              rapid_verify_attn).  It is state: all of it is zero before the first call that uses it, and
  *              between calls only this function writes to it.  Calls of any shapes may follow one another on it (also eager calls and

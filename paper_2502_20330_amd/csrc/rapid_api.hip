@@ -211,20 +211,12 @@ void plan_attn(const rapid_ctx* ctx, const rapid_attn_shape* shape, AttnLaunch& 
 
 // Bytes of exchange memory with which the call is one launch, 0 where it is two: few rows (attn_in_one_launch), a fixed grid of
 // at most one workgroup per compute unit (they wait for one another), and no more splits than one wave forms weights for.
-// Where the library chooses the split and half of the compute units would do, such a call takes splits of 128 tokens, one tile a wave, instead
-// of the 256 below which a second launch has too much to merge (us a call in a graph, 256 and 128 tokens: 2K tokens, one head of 64, 5 rows
-// 7.7 and 7.1; 4K 7.8 and 7.3; 8 heads of 128, 4 rows, 512 tokens 8.5 and 7.9, 2K 9.0 and 8.2; 4 heads, 4K 8.9 and 8.5; on all compute units 8 heads,
-// 4K 9.2 and 9.5, 16 rows 9.9 and 11.1).
-size_t plan_exchange(const rapid_ctx* ctx, const rapid_attn_shape* shape, AttnLaunch& a)
+// The splits are those of two launches, so that the results are the same bits either way.  (128 tokens instead of 256 where half of the compute
+// units hold them would be worth 0.3 to 0.8 us: 2K tokens, one head of 64, 5 rows 7.7 and 7.1, 8 heads of 128, 4 rows 9.0 and 8.2.)
+size_t plan_exchange(const rapid_ctx* ctx, const AttnLaunch& a)
 {
     const int64_t n_cu = ctx ? ctx->n_cu : 256;
     if (a.groups || !attn_in_one_launch(a.RB, a.D)) return 0;
-    const int fine = (a.max_ctx + 127) / 128;
-    if (shape->chunk_tokens == 0 && a.chunk > 128 && fine <= kMaxShares && 2 * (int64_t)a.B * a.Hkv * fine <= n_cu) {
-        a.chunk = 128;
-        a.nsplit = fine;
-        plan_layout(ctx, a);
-    }
     const int64_t wgs = (int64_t)a.B * a.Hkv * a.nsplit;
     if (a.nsplit > kMaxShares || wgs > n_cu || wgs > kAttnTeams) return 0;
     return attn_exchange_bytes(a.B, a.Hkv, a.nsplit, a.RB, a.D);
@@ -356,7 +348,7 @@ static int attn_call(rapid_ctx* ctx, const rapid_attn_shape* shape,
     a.out = static_cast<uint16_t*>(out);
     a.lse_out = lse_out;
     plan_attn(ctx, shape, a);
-    const size_t need_x = exchange ? plan_exchange(ctx, shape, a) : 0;
+    const size_t need_x = exchange ? plan_exchange(ctx, a) : 0;
     if (need_x) {
         if (!aligned(exchange, 256) || exchange_bytes < need_x) return RAPID_EWORKSPACE;
         a.xhead = static_cast<AttnExchangeHead*>(exchange);
@@ -387,7 +379,7 @@ size_t rapid_verify_attn_exchange_bytes(const rapid_ctx* ctx, const rapid_attn_s
     if (check_attn_shape(shape) != RAPID_OK) return 0;
     AttnLaunch a{};
     plan_attn(ctx, shape, a);
-    return plan_exchange(ctx, shape, a);
+    return plan_exchange(ctx, a);
 }
 
 int rapid_verify_attn(rapid_ctx* ctx, const rapid_attn_shape* shape,

@@ -149,6 +149,28 @@ def test_split_planning_invariants_on_random_shapes():
     assert seen_ok > 100 and seen_bad > 30
 
 
+def test_one_launch_runs_with_the_planned_splits():
+    """The exchange memory holds the partials of the splits that rapid_verify_attn_chunk names, for every shape that takes one launch: the
+    same plan as with two, whether the caller passes the split or not."""
+    lib = binding.load_library()
+    ones = 0
+    for batch, q_max, (hq, hkv, d) in [(b, q, h) for b in (1, 2, 4, 16) for q in (1, 3, 4, 5, 8)
+                                       for h in ((4, 1, 64), (8, 1, 64), (32, 8, 128), (28, 4, 128), (16, 8, 64))]:
+        for max_ctx in (q_max, 128, 200, 300, 512, 2048, 4000, 8192, 32768, 131072):
+            s = _shape(batch, q_max, hq, hkv, d, max_ctx, token_major=False)
+            got = lib.rapid_verify_attn_exchange_bytes(None, ctypes.byref(s))
+            chunk = lib.rapid_verify_attn_chunk(None, ctypes.byref(s))
+            nsplit = -(-max_ctx // chunk)
+            rows = -(-q_max * (hq // hkv) // 16) * 16
+            if got:
+                ones += 1
+                words = batch * hkv * nsplit * rows * (d + 2) * 8
+                assert 1024 + 4 * 256 * 32 <= got - words <= 72 * 1024, (batch, q_max, hq, hkv, d, max_ctx)
+            s.chunk_tokens = chunk
+            assert lib.rapid_verify_attn_exchange_bytes(None, ctypes.byref(s)) == got
+    assert ones > 200
+
+
 def test_product_path_has_no_cpu_fallback():
     """Without a GPU the binding refuses to construct instead of computing elsewhere."""
     import torch

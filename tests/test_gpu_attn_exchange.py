@@ -50,13 +50,6 @@ def _one(r, c, chunk=0):
     return out, lse
 
 
-def _chunk(c):
-    """The split with which a call in one launch that leaves it to the library runs, for the two-launch entry: 128 tokens where half
-    of 256 compute units (and 32 splits) hold them, else the library's own."""
-    B, Hkv, fine = c["q"].shape[0], c["k"].shape[2], -(-c["max_ctx"] // 128)
-    return 128 if fine <= 32 and B * Hkv * fine <= 128 else 0
-
-
 def _same(x, y):
     for a, b in zip(x, y):
         assert torch.equal(a.view(torch.int16 if a.dtype == torch.bfloat16 else torch.int32),
@@ -100,7 +93,7 @@ def test_one_launch_has_the_bits_of_two(shape):
     r = Rapid(0)
     c = _case(*shape)
     for chunk in (0, 384):
-        want = _two(r, c, chunk or _chunk(c))
+        want = _two(r, c, chunk)
         for wait in (100, 100, 0, 1, 3, 100):          # 0: nearly all shares are left to the last workgroup of their head
             r.set_option(OPT_ATTN_WAIT_US, wait)
             _same(_one(r, c, chunk), want)
@@ -109,7 +102,7 @@ def test_one_launch_has_the_bits_of_two(shape):
 def test_calls_of_many_shapes_and_replays_share_one_exchange():
     r = Rapid(0)
     cases = [_case(*s, seed=i) for i, s in enumerate(SHAPES)]
-    want = [_two(r, c, _chunk(c)) for c in cases]
+    want = [_two(r, c) for c in cases]
     for c in cases:
         _one(r, c)                                     # the exchange has its size from here on
     side = torch.cuda.Stream()
@@ -159,7 +152,7 @@ def test_missing_or_small_exchange_is_refused_and_none_takes_two_launches():
     assert call(x.data_ptr() + 16, need, ws.data_ptr(), ws.numel()) == binding.RAPID_EWORKSPACE
     assert call(None, 0, None, 0) == binding.RAPID_EWORKSPACE
     assert call(x.data_ptr(), need, None, 0) == 0
-    _same((out,), (_two(r, c, _chunk(c))[0],))
+    _same((out,), (_two(r, c)[0],))
     assert call(None, 0, ws.data_ptr(), ws.numel()) == 0
     _same((out,), (_two(r, c)[0],))
 
@@ -176,11 +169,13 @@ def test_shapes_that_stay_at_two_launches(shape):
     assert r._ws is not None and bool(got[0].float().isfinite().all())
 
 
-def test_first_call_of_an_object_inside_a_capture():
-    """Nothing can be cleared there, so the call takes two launches; the next eager one makes the exchange memory."""
+@pytest.mark.parametrize("shape", [SHAPES[2], SHAPES[5], SHAPES[6]])
+def test_first_call_of_an_object_inside_a_capture(shape):
+    """Nothing can be cleared there, so the call takes two launches; the next eager one makes the exchange memory and takes one.  The
+    splits are the same."""
     r = Rapid(0)
-    c = _case(*SHAPES[5])
-    want = _two(r, c)                                  # (8K tokens of 8 heads: the same split either way)
+    c = _case(*shape)
+    want = _two(r, c)
     graph = torch.cuda.CUDAGraph()
     torch.cuda.synchronize()
     with torch.cuda.graph(graph):
