@@ -163,8 +163,8 @@ int rapid_verify_attn(rapid_ctx* ctx, const rapid_attn_shape* shape,
                       void* workspace, size_t workspace_bytes, void* stream);
 
 /*
- * rapid_verify_attn, in one launch where the shape has few query rows per kv head and its grid is at most one workgroup per
- * compute unit: the workgroups then exchange their partial results and merge them themselves.  Same operation, same splits, same bits,
+ * rapid_verify_attn, in one launch where the shape has few query rows per kv head and its grid is at most a quarter of the
+ * workgroups that the chip holds: the workgroups then exchange their partial results and merge them themselves.  Same operation, same splits, same bits,
  * same argument rules; two more arguments:
  *   exchange   device memory of rapid_verify_attn_exchange_bytes() or more, 256-byte aligned, or NULL (the call is then
  *              rapid_verify_attn).  It is state: all of it is zero before the first call that uses it, and

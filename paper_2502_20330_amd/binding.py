@@ -187,9 +187,9 @@ class Rapid:
 
     def _exchange_workspace(self, nbytes: int) -> torch.Tensor:
         # its own buffer, zero at first: the attention call keeps the number of the call in it.  At once large enough for every
-        # shape (256 workgroups of 16 rows of 128)
+        # shape (128 workgroups of 32 rows of 64)
         if self._ws_exchange is None or self._ws_exchange.numel() < nbytes:
-            self._ws_exchange = torch.zeros(max(nbytes, 5 << 20), dtype=torch.uint8, device=self.device)
+            self._ws_exchange = torch.zeros(max(nbytes, 3 << 20), dtype=torch.uint8, device=self.device)
         return self._ws_exchange
 
     def _accept_workspace(self, nbytes: int) -> torch.Tensor:

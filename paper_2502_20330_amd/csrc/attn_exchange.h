@@ -52,9 +52,9 @@ constexpr int kExchangeRows = 98;      // rows that a share may touch
 // What bounds it: round trips past the dies' L2s (0.7 us each: the own words' arrival, one or two looks) and code that every
 // workgroup meets for the first time, about 3 us from the last tile to the end at 4 rows where a store, a second launch and its
 // gap took 3.6.  So everything that is missing is asked for at once, one element of the output a thread, and partials keep
-// the order of the merge kernel.  Measured (a graph of 16 layers of 8K tokens with the head and the draw): 290 -> 277 us; 2K
-// tokens, 4 heads of 64, enqueued one by one 9.9 -> 7.7.  Not kept: a counter of arrivals per team (256 atomic additions on a few
-// lines: 345 us); a wave per row asking for 32 splits (304); asking for words only where (maximum, sum) had come (282 to 292).
+// the order of the merge kernel.  Measured: 2K tokens, 4 heads of 64, 5 rows, enqueued one by one 9.9 -> 7.7 us, in a graph 8.2 -> 7.9.  Not kept (a graph
+// of 16 calls on 8K tokens with the head and the draw, 290 us with two launches, 277 like this): a counter of arrivals per team (256 atomic additions on a few
+// lines: 345); a wave per row asking for 32 splits (304); asking for words only where (maximum, sum) had come (282 to 292).
 struct Exchange {
     AttnExchangeHead* head;
     __amdgpu_buffer_rsrc_t words;

@@ -50,10 +50,9 @@ struct AttnLaunch {
     uint32_t xml_offset;     // bytes from xwords to the (max, sum) words
     int64_t xwait_ticks;     // bound of a wait in wall-clock ticks (100 MHz)
 };
-constexpr int kAttnTeams = 256;  // largest grid that merges by itself: every workgroup then has one of the usual 256 compute units
+constexpr int kAttnTeams = 256;  // largest grid that merges by itself
 // Row counts (in blocks of 16) for which the workgroups merge their partials themselves, up to 16 rows of 128 or 32 of 64.  In graphs
-// of calls, two launches against one: 4 rows of 128, 512 tokens 8.75 and 8.37 us, 8K 12.2 and 11.7, 32K 27.6 and 27.1, 128K 87.9
-// and 87.5; 20 rows of 64, 2K tokens 7.65 and 7.43; sixteen sequences of 2K with 10 rows of 64 16.9 and 16.5.  Beyond, the words (twice the
+// of calls, two launches against one: 4 rows of 128, 512 tokens 8.75 and 8.37 us; 20 rows of 64, 2K tokens 7.65 and 7.43.  Beyond, the words (twice the
 // partials) take longer to go through memory and back than a second launch: 20 rows of 128, 8K tokens 14.3 and 14.7, 36 rows 17.0
 // and 18.3, 72 rows 20.2 and 23.0; 40 rows of 64, 2K tokens 8.6 and 9.2.  Calls that the host cannot enqueue as fast as they run gain a launch.
 constexpr bool attn_in_one_launch(int row_blocks, int D) { return row_blocks * D <= 128; }

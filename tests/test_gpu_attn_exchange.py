@@ -1,6 +1,7 @@
 """The attention call in one launch (workgroups exchange their partials and merge them) against the same call in two: the
 same partials are folded in the same order, so every output has the same bits."""
 import ctypes
+import time
 
 import pytest
 import torch
@@ -57,24 +58,25 @@ def _same(x, y):
 
 
 # B, Q, Hq, Hkv, d, lens, gammas, page, layout: one split and several, up to the 32 that run in one launch; shares of less than a
-# row and of several rows, more shares than elements to share; splits and whole sequences without tokens; one and two row blocks
+# row and of several rows, more shares than elements to share; splits and whole sequences without tokens; one and two row blocks; grids
+# of up to 64 workgroups with heads of 128, 128 with heads of 64
 SHAPES = [
     (1, 1, 4, 4, 64, [1], None, 0, "head"),
     (1, 1, 1, 1, 64, [8192], None, 0, "head"),
     (1, 5, 4, 1, 64, [2048], None, 0, "token"),
     (1, 4, 8, 1, 64, [200], None, 0, "head"),
     (1, 2, 8, 1, 128, [300], None, 0, "head"),
-    (1, 1, 32, 8, 128, [8192], None, 0, "head"),
-    (1, 4, 32, 8, 128, [32768], None, 0, "head"),
-    (1, 3, 32, 8, 128, [9000], [1], 16, "head"),
-    (1, 2, 28, 4, 128, [8161], None, 0, "token"),
+    (1, 1, 32, 8, 128, [2048], None, 0, "head"),
+    (1, 4, 8, 2, 128, [8192], None, 0, "head"),
+    (1, 3, 32, 8, 128, [1900], [1], 16, "head"),
+    (1, 2, 28, 4, 128, [4065], None, 0, "token"),
     (1, 5, 3, 1, 128, [7300], None, 0, "token"),
     (1, 4, 8, 1, 64, [8192], [2], 64, "head"),
-    (2, 2, 64, 8, 128, [4000, 700], [1, 0], 0, "head"),
-    (3, 4, 16, 4, 64, [5000, 0, 4], [3, 3, 3], 16, "head"),
-    (8, 8, 16, 8, 64, [1024] * 8, None, 0, "head"),
-    (16, 3, 8, 4, 64, [513] * 16, [0, 1, 2, 2] * 4, 0, "token"),
-    (64, 3, 8, 4, 64, [33] * 64, [0, 1, 2, 2] * 16, 0, "token"),
+    (2, 2, 32, 4, 128, [2000, 700], [1, 0], 0, "head"),
+    (3, 4, 16, 4, 64, [2500, 0, 4], [3, 3, 3], 16, "head"),
+    (8, 8, 8, 4, 64, [1024] * 8, None, 0, "head"),
+    (8, 3, 8, 4, 64, [513] * 8, [0, 1, 2, 2] * 2, 0, "token"),
+    (32, 3, 8, 4, 64, [33] * 32, [0, 1, 2, 2] * 8, 0, "token"),
 ]
 
 
@@ -158,9 +160,10 @@ def test_missing_or_small_exchange_is_refused_and_none_takes_two_launches():
 
 
 @pytest.mark.parametrize("shape", [(1, 5, 4, 1, 128, [2048], None), (1, 9, 4, 1, 64, [2048], None), (1, 1, 4, 1, 64, [65536], None),
-                                   (33, 1, 8, 8, 64, [64] * 33, None)])
+                                   (1, 1, 32, 8, 128, [2049], None), (1, 1, 32, 8, 128, [8192], None), (33, 1, 8, 4, 64, [64] * 33, None)])
 def test_shapes_that_stay_at_two_launches(shape):
-    """More rows, more than 32 splits, more workgroups than compute units: no exchange memory is asked for, and none is needed."""
+    """More rows, more than 32 splits, more than a quarter of the workgroups that the chip holds: no exchange memory is asked for, and none is
+    needed."""
     r = Rapid(0)
     c = _case(*shape)
     s = r.attn_shape(c["q"], c["k"], c["max_ctx"])
@@ -185,6 +188,37 @@ def test_first_call_of_an_object_inside_a_capture(shape):
         _same(_one(r, c), want)
         graph.replay()
         _same(got, want)
+
+
+@pytest.mark.parametrize("shape", [(1, 4, 32, 8, 128, [2048], None), (1, 4, 32, 8, 128, [8192], None), (4, 2, 16, 8, 64, [1024] * 4, None),
+                                   (1, 4, 16, 8, 64, [8192], None)])
+def test_chains_on_four_streams_do_not_wait_for_one_another(shape):
+    """Four objects, a recorded chain of calls each, replayed side by side, with a bound of the waits that is far longer than all of them
+    take: no workgroup may keep another one's partner off the chip."""
+    objects, graphs, outs, want = [Rapid(0) for _ in range(4)], [], [], []
+    cases = [_case(*shape, seed=i) for i in range(4)]  # (kept: the graphs read them)
+    for r, c in zip(objects, cases):
+        want.append(_one(r, c))
+        r.set_option(OPT_ATTN_WAIT_US, 30000)
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            outs.append([_one(r, c) for _ in range(8)])
+        graphs.append(graph)
+        graph.replay()
+    streams = [torch.cuda.Stream() for _ in objects]
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    for _ in range(3):
+        for s, graph in zip(streams, graphs):
+            with torch.cuda.stream(s):
+                graph.replay()
+    torch.cuda.synchronize()
+    took = time.perf_counter() - t0
+    for got, w in zip(outs, want):
+        for g in got:
+            _same(g, w)
+    assert took < 0.03, took
 
 
 def test_two_objects_on_two_streams():
