@@ -78,9 +78,10 @@ __device__ __forceinline__ void wave_best(float& m, int& idx)
 }
 
 // Row y of sequence b: y <= gmax the target rows, then the draft rows.  Bound by the read: four 128-bit loads per thread, all in flight
-// at once, with the streaming hint (64 sequences of 128256 entries and 8 drafts, 558 MB, both launches: 97.0 us without it, 88.5 = 6.3 TB/s with it; 16
-// sequences of 4 to 8 drafts 21.0 and 20.4).  512 threads take 86.6 and 21.4, and 24 instead of 16 for 4096 rows of 100; eight loads 88.0 and 22.7 against 22.2 at
-// 16 sequences of 6 drafts.  A thread's entries come in index order, so equal maxima keep the lowest index by themselves.
+// at once, STREAM: with the streaming hint (see launch_accept_greedy; 64 sequences of 128256 entries and 8 drafts, 558 MB, both launches: 97.0 us
+// without it, 88.5 = 6.3 TB/s with it; 16 sequences of 4 to 8 drafts 21.0 and 20.4).  512 threads take 86.6 and 21.4, and 24 instead of 16 for 4096 rows of 100; eight loads
+// 88.0 and 22.7 against 22.2 at 16 sequences of 6 drafts.  A thread's entries come in index order, so equal maxima keep the lowest index by themselves.
+template <bool STREAM>
 __global__ void __launch_bounds__(kThreads) greedy_slice_argmax(AcceptLaunch a, GreedyWs ws)
 {
     __shared__ float shm[kThreads / 64];
@@ -97,7 +98,7 @@ __global__ void __launch_bounds__(kThreads) greedy_slice_argmax(AcceptLaunch a, 
     const int i0 = w * kSlice + threadIdx.x * 4;
     const bool full = (int64_t)(w + 1) * kSlice <= a.V;
     floatx4 x[NV];
-    load_runs<NV, true>(x, row, i0, kThreads * 4, a.V, full);
+    load_runs<NV, STREAM>(x, row, i0, kThreads * 4, a.V, full);
     shift_runs(x, i0, kThreads * 4, a.V, full);
     float m = -INFINITY;
     int idx = 0x7fffffff;
@@ -219,7 +220,13 @@ size_t accept_greedy_workspace_bytes(int B, int gmax, int V)
 hipError_t launch_accept_greedy(const AcceptLaunch& a, hipStream_t stream)
 {
     GreedyWs ws = gcarve(a.workspace, a.B, a.gmax, a.V);
-    hipLaunchKernelGGL(greedy_slice_argmax, dim3(ws.W, 2 * a.gmax + 1, a.B), dim3(kThreads), 0, stream, a, ws);
+    // The streaming hint from 80 MiB of logits on.  Logits that are still in the caches, as when the head has just written them, are
+    // read faster without it in smaller calls, others with it in all (calls in a graph, us without and with it; one set of logits again and again, sets past the
+    // caches): 35 MB 9.1 and 9.7, 11.6 and 10.8; 46 MB of rows of 8192 10.2 and 11.3, 13.3 and 12.1; 74 MB of 32000 14.4 and 14.8, 16.8 and 15.7; 87 MB
+    // 15.8 and 15.5, 18.1 and 17.0; 174 MB 25.1 and 25.0, 28.3 and 26.2; 349 MB 42.6 and 42.9, 49.4 and 45.1; 558 MB 74.8 and 66.2, 73.3 and 65.6.
+    const bool streams = (int64_t)a.B * (2 * a.gmax + 1) * a.V * 4 >= 80 << 20;
+    hipLaunchKernelGGL(streams ? greedy_slice_argmax<true> : greedy_slice_argmax<false>, dim3(ws.W, 2 * a.gmax + 1, a.B), dim3(kThreads), 0,
+                       stream, a, ws);
     // A wave per position while every sequence has a compute unit to itself (the decision is then one chain of loads), four
     // beyond, where the chip is full: 4096 sequences of one draft (vocabulary 100) took 53 us a call with 16 waves, 28 with four,
     // and 21 since the row pass also leaves out what lies past a short row.

@@ -348,3 +348,25 @@ def test_ratios_past_a_sequences_drafts(T):
 def test_greedy_rows_at_the_borders_of_slices(V):
     """One slice, two, and four with one entry in the last."""
     test_greedy_ties_masks_and_row_ends(V)
+
+
+@pytest.mark.parametrize("V", [41120, 41123])
+def test_greedy_batches_past_the_caches(V):
+    """A call on more than 80 MiB of logits, whose rows are read with the streaming hint, against the same sequences in calls below
+    the line; rows with ties, masks and a NaN, rows that are not 16-byte aligned."""
+    B, g = 172, 1
+    assert B * (2 * g + 1) * V * 4 > 80 << 20 > 86 * (2 * g + 1) * V * 4
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    t = torch.randn(B, g + 1, V, device="cuda", generator=gen)
+    t[::3] = t[::3].mul_(2).round_()
+    t[5, :, 1000:] = -torch.inf
+    t[7, 0, V - 1] = torch.nan
+    d = torch.where(torch.rand(B, g, V, device="cuda", generator=gen) < 0.5, t[:, :g], t[:, :g] - 1).contiguous()
+    tok = d.nan_to_num(-9).argmax(-1).to(torch.int32)
+    u = torch.rand(B, g + 1, device="cuda", generator=gen)
+    whole = gu.rapid().rapid_accept(t, d, tok, 0.5, u, temperature=0.0)
+    for lo in (0, 86):
+        part = gu.rapid().rapid_accept(*(x[lo:lo + 86] for x in (t, d, tok)), 0.5, u[lo:lo + 86], temperature=0.0)
+        for a, b in zip(whole, part):
+            assert torch.equal(a[lo:lo + 86].view(torch.int32), b.view(torch.int32))
+    assert 0 < int(whole[0].sum()) < B
