@@ -182,19 +182,20 @@ int rapid_verify_attn_exchange(rapid_ctx* ctx, const rapid_attn_shape* shape,
                                void* workspace, size_t workspace_bytes, void* stream);
 
 /*
- * rapid_verify_attn_exchange for callers that cannot allocate device memory at all: code under HIP graph
+ * rapid_verify_attn for callers that cannot allocate device memory at all: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same operation, same kernels,
- * same argument rules and results as rapid_verify_attn_exchange, but the split partials go to static
- * device arrays inside the library (RAPID_STATIC_SCRATCH_BYTES and 4.5 MiB of exchange memory per GPU, held
- * from the moment the library is loaded until the process ends) instead of memory of the caller's; the call
+ * same argument rules and results as rapid_verify_attn, but the split partials go to a static
+ * device array inside the library (RAPID_STATIC_SCRATCH_BYTES per GPU, held from the moment the
+ * library is loaded until the process ends) instead of a caller-supplied workspace; the call
  * allocates and frees nothing.
  *   - A shape whose rapid_verify_attn_workspace_bytes() exceeds RAPID_STATIC_SCRATCH_BYTES is
  *     refused with RAPID_ETOOLARGE (all other errors as for rapid_verify_attn).  The limit covers
  *     every configuration this library is benchmarked on (the largest, eight ragged 128K-token
  *     sequences, needs 21 MB).
- *   - All calls on one GPU share that GPU's arrays: two calls that overlap in time on the same GPU
+ *   - All calls on one GPU share that GPU's array: two calls that overlap in time on the same GPU
  *     (different streams, or different contexts on that GPU) race.  Calls on one stream are safe.
- *   - The arrays keep whatever the previous call left, and the call clears nothing.
+ *   - The array keeps whatever the previous call left; nothing in it has to start at zero (slots of
+ *     splits that hold no token are never read), so the call clears nothing.  (No exchange memory: that would be state that a race spoils for good, and nobody could clear.)
  */
 #define RAPID_STATIC_SCRATCH_BYTES (32u << 20)
 int rapid_verify_attn_static(rapid_ctx* ctx, const rapid_attn_shape* shape,

@@ -8,11 +8,6 @@
 // handle for hipGetSymbolAddress; the device address is looked up once per context
 // (rapid_create, with the context's device current) and kept in rapid_ctx::static_scratch.
 static __device__ __align__(256) unsigned char scratch[RAPID_STATIC_SCRATCH_BYTES];
-// And its exchange memory (zero when the library is loaded), enough for every shape that takes one launch.
-constexpr size_t kStaticExchangeBytes = 9u << 19;
-static_assert(kStaticExchangeBytes >= kAttnExchangeHeadBytes + (size_t)kAttnTeams * 32 * (64 + 2) * 8 &&
-              kStaticExchangeBytes >= kAttnExchangeHeadBytes + (size_t)kAttnTeams * 16 * (128 + 2) * 8);
-static __device__ __align__(256) unsigned char exchange_memory[kStaticExchangeBytes];
 
 namespace {
 
@@ -255,16 +250,13 @@ int rapid_create(rapid_ctx** out, int device)
     if (ec == hipSuccess) ec = configure_lm_head();
     if (ec == hipSuccess) ec = configure_hbm_read_probe();
     void* scratch_ptr = nullptr;                      // this device's copy of `scratch`
-    void* exchange_ptr = nullptr;
     if (ec == hipSuccess) ec = hipGetSymbolAddress(&scratch_ptr, HIP_SYMBOL(scratch));
-    if (ec == hipSuccess) ec = hipGetSymbolAddress(&exchange_ptr, HIP_SYMBOL(exchange_memory));
     (void)hipSetDevice(prev);
-    if (ec != hipSuccess || !scratch_ptr || !exchange_ptr) return RAPID_EHIP;
+    if (ec != hipSuccess || !scratch_ptr) return RAPID_EHIP;
     rapid_ctx* c = new (std::nothrow) rapid_ctx;
     if (!c) return RAPID_EINVAL;
     c->device = device;
     c->static_scratch = scratch_ptr;
-    c->static_exchange = exchange_ptr;
     c->accept_wait_ticks = 100 * 100;                 // 100 us
     c->accept_slice = 0;
     c->attn_wait_ticks = 100 * 100;
@@ -419,9 +411,9 @@ int rapid_verify_attn_static(rapid_ctx* ctx, const rapid_attn_shape* shape,
     const int rc = check_attn_shape(shape);
     if (rc != RAPID_OK) return rc;
     if (rapid_verify_attn_workspace_bytes(ctx, shape) > (size_t)RAPID_STATIC_SCRATCH_BYTES) return RAPID_ETOOLARGE;
-    // same kernels, same argument checks; partials go to this device's static arrays
-    return attn_call(ctx, shape, q, k_cache, v_cache, ctx_lens, gammas, page_table, out, lse_out, ctx->static_exchange,
-                     kStaticExchangeBytes, ctx->static_scratch, (size_t)RAPID_STATIC_SCRATCH_BYTES, stream);
+    // same kernels, same argument checks; the split partials go to this device's static array
+    return rapid_verify_attn(ctx, shape, q, k_cache, v_cache, ctx_lens, gammas, page_table, out, lse_out,
+                             ctx->static_scratch, (size_t)RAPID_STATIC_SCRATCH_BYTES, stream);
 }
 
 size_t rapid_accept_workspace_bytes(const rapid_ctx*, int batch, int gamma_max, int vocab)

@@ -9,7 +9,6 @@ struct rapid_ctx {
     int n_cu;
     int last_hip_error;
     void* static_scratch;   // device address of this GPU's copy of the library's static scratch array
-    void* static_exchange;  // and of its exchange memory
     int64_t accept_wait_ticks;   // bound of every inter-workgroup wait of the accept pass, 10 ns ticks
     int64_t attn_wait_ticks;     // the same of the attention call's exchange
     int accept_slice;            // entries per workgroup of the accept row pass (0 = automatic)

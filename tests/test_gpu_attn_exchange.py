@@ -172,6 +172,30 @@ def test_shapes_that_stay_at_two_launches(shape):
     assert r._ws is not None and bool(got[0].float().isfinite().all())
 
 
+def _launches(r, call):
+    """Kernels that a call enqueues: nodes of its recorded graph."""
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        call()
+    n = ctypes.c_size_t(0)
+    assert r.lib.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+def test_launches_of_the_entries():
+    """One launch with exchange memory, two without; the static entry has none, as nobody could clear it after a race."""
+    r = Rapid(0)
+    c = _case(*SHAPES[5])
+    out = torch.empty_like(c["q"])
+    call = dict(max_ctx=c["max_ctx"], out=out)
+    eager = lambda: r.rapid_verify_attn(c["q"], c["k"], c["v"], c["lens"], **call)
+    assert _launches(r, eager) == 2                    # an object's first call, inside a capture: no exchange memory yet
+    eager()
+    assert _launches(r, eager) == 1
+    assert _launches(r, lambda: r.rapid_verify_attn_static(c["q"], c["k"], c["v"], c["lens"], **call)) == 2
+
+
 @pytest.mark.parametrize("shape", [SHAPES[2], SHAPES[5], SHAPES[6]])
 def test_first_call_of_an_object_inside_a_capture(shape):
     """Nothing can be cleared there, so the call takes two launches; the next eager one makes the exchange memory and takes one.  The
