@@ -73,7 +73,7 @@ int rapid_last_hip_error(const rapid_ctx* ctx);
  *       first reads (32 + value)/32 and the second (32 - value)/32 of the mean share, as
  *       rapid_verify_attn splits the tokens of a pair of KV splits unevenly when its grid is one
  *       workgroup per compute unit.  0 <= value <= 16; default 0 (equal shares).
- *   RAPID_OPT_ATTN_WAIT_US    rapid_verify_attn_exchange: a workgroup looks at most this many microseconds
+ *   RAPID_OPT_ATTN_WAIT_US    rapid_verify_attn_exchange, where it is one launch: a workgroup looks at most this many microseconds
  *       for the partial results of the others and then leaves its part of the merge to the last of them
  *       (same results).  Default 100; 0 = one look (for tests).  0 <= value <= 10^7.
  * Returns RAPID_EINVAL for an unknown option or a value out of range.
@@ -169,7 +169,9 @@ int rapid_verify_attn(rapid_ctx* ctx, const rapid_attn_shape* shape,
  *   exchange   device memory of rapid_verify_attn_exchange_bytes() or more, 256-byte aligned, or NULL (the call is then
  *              rapid_verify_attn).  It is state: all of it is zero before the first call that uses it, and
  *              between calls only this function writes to it.  Calls of any shapes may follow one another on it (also eager calls and
- *              replays of captured graphs in turn), but two of them must not overlap in time.
+ *              replays of captured graphs in turn), but two of them must not overlap in time.  Two that do can spoil, besides their own
+ *              results, those of any later call on this memory: fill all of it with zeros before the next one, after both
+ *              have ended (hipMemsetAsync on the calls' stream, or a fill kernel where the fill is captured).
  *   workspace  as for rapid_verify_attn; only looked at where the call takes two launches
  *              (rapid_verify_attn_exchange_bytes() == 0, or exchange == NULL).
  * RAPID_EWORKSPACE if the one that the shape needs is missing, misaligned or too small; it is the last check.
@@ -195,7 +197,8 @@ int rapid_verify_attn_exchange(rapid_ctx* ctx, const rapid_attn_shape* shape,
  *   - All calls on one GPU share that GPU's array: two calls that overlap in time on the same GPU
  *     (different streams, or different contexts on that GPU) race.  Calls on one stream are safe.
  *   - The array keeps whatever the previous call left; nothing in it has to start at zero (slots of
- *     splits that hold no token are never read), so the call clears nothing.  (No exchange memory: that would be state that a race spoils for good, and nobody could clear.)
+ *     splits that hold no token are never read), so the call clears nothing.  (It has no exchange memory, which a race
+ *     would spoil for later calls too, and which nobody could clear here.)
  */
 #define RAPID_STATIC_SCRATCH_BYTES (32u << 20)
 int rapid_verify_attn_static(rapid_ctx* ctx, const rapid_attn_shape* shape,

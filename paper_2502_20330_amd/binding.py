@@ -192,6 +192,13 @@ class Rapid:
             self._ws_exchange = torch.zeros(max(nbytes, 3 << 20), dtype=torch.uint8, device=self.device)
         return self._ws_exchange
 
+    def clear_exchange(self):
+        """Attention calls of this object that overlapped in time (on two streams, or a graph's replay beside an eager call) can spoil
+        later ones too, until the memory that they exchange their partial results through is cleared: by this method, on the current
+        stream, after they have ended."""
+        if self._ws_exchange is not None:
+            self._ws_exchange.zero_()
+
     def _accept_workspace(self, nbytes: int) -> torch.Tensor:
         # its own buffer: the accept pass keeps a call counter in it from one call to the next
         if self._ws_accept is None or self._ws_accept.numel() < nbytes:

@@ -39,9 +39,11 @@ constexpr int kExchangeRows = 98;      // rows that a share may touch
 // Every workgroup of a team, the splits of a (sequence, kv head) that hold tokens, publishes its partial and then merges its share of the
 // team's output, every share as many elements.  What it publishes are 64-bit words, 32 bits of payload under a tag that no
 // earlier call on the same memory used; whoever needs a word looks until it carries the tag, so no fence, flag or counter
-// stands between a store and its reader.  The memory holds nothing but such words and starts as zeros.  The tag is the number of the call.
+// stands between a store and its reader.  The memory holds nothing but such words and starts as zeros.  The tag is the number of the call, and never 0,
+// the tag of a word that nobody has written.  (32 bits: a word that exactly 2^32 - 1 calls have left alone would pass for new.)
 // Every possible team has a copy of it, moved by a plain store once the first share of a team has been merged: all
-// workgroups of the team have read it then.  Replays of a captured graph move it too.
+// workgroups of the team have read it then.  Replays of a captured graph move it too.  Two calls that overlap in time on one memory can leave unequal
+// copies, and then a team may later meet words of another one under its own tag: the memory has to be cleared (rapid.h).
 //
 // No workgroup depends on another one for its end.  It looks for a bounded time; then it marks its share as left over and looks
 // once more.  Every wave, after its own words have arrived in memory, looks at the marks, and its workgroup merges what is left
@@ -76,7 +78,7 @@ __device__ __forceinline__ Exchange make_exchange(const AttnLaunch& a, uint32_t 
     Exchange x;
     x.head = a.xhead;
     x.words = __builtin_amdgcn_make_buffer_rsrc(a.xwords, 0, a.xbytes, 0x00027000);
-    x.tag = calls + 1;
+    x.tag = calls + 1 ? calls + 1 : 1;
     return x;
 }
 // Two values side by side; `at` in words.

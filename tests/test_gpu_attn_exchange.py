@@ -137,6 +137,46 @@ def test_every_copy_of_the_calls_number_moves_by_one():
         assert r._ws_exchange[:1024].view(torch.int32).unique().tolist() == [n]
 
 
+# 4 kv heads in 8 splits, and as many words of one head in 32: the words of the second shape's later splits are those of other heads of the first
+ACROSS = [(1, 1, 4, 4, 64, [2048], None, 0, "head"), (1, 1, 1, 1, 64, [8192], None, 0, "head")]
+
+
+def _set_calls(r, values):
+    r._ws_exchange[:1024].view(torch.int32).copy_(torch.as_tensor(values, dtype=torch.int64).to(torch.int32))
+
+
+def test_the_number_of_the_call_skips_0():
+    """0 is the tag of words that nobody has written: a call under it would take them for its partners'.  The third call after the
+    copies were set is the one that would have it, the first on most of its part of the memory; its last split holds 8 tokens and looks for
+    the words of the others long before they are there."""
+    for seed in range(3):
+        r = Rapid(0)
+        short, long = _case(1, 1, 1, 1, 64, [64], None, seed=seed), _case(1, 1, 4, 1, 64, [8200], None, seed=seed)
+        want = {False: _two(r, short, 4096), True: _two(r, long, 4096)}
+        _one(r, short, 4096)
+        _set_calls(r, [0xfffffffd - (1 << 32)] * 256)
+        for now in (False, False, True, False, True):
+            _same(_one(r, long if now else short, 4096), want[now])
+        assert r._ws_exchange[:1024].view(torch.int32).unique().tolist() == [3]
+
+
+def test_clearing_mends_what_overlapping_calls_leave():
+    """Unequal copies of the number, and words of other heads under the tags that the next calls have."""
+    r = Rapid(0)
+    cases = [_case(*s, seed=i) for i, s in enumerate(ACROSS)]
+    want = [_two(r, c) for c in cases]
+    for trial in range(8):
+        _one(r, cases[0])
+        n = int(r._ws_exchange[:4].view(torch.int32))
+        _set_calls(r, [n + (t + trial) % 5 for t in range(256)])
+        _one(r, cases[0])
+        r.clear_exchange()
+        for _ in range(3):
+            for c, w in zip(cases[::-1], want[::-1]):
+                _same(_one(r, c), w)
+        assert r._ws_exchange[:1024].view(torch.int32).unique().tolist() == [6]
+
+
 def test_missing_or_small_exchange_is_refused_and_none_takes_two_launches():
     r = Rapid(0)
     c = _case(*SHAPES[2])
