@@ -33,7 +33,6 @@ __device__ __forceinline__ float sum32(float v)
 }
 
 constexpr int kMergeBlock = 32;        // splits whose weights are formed together, one per lane
-constexpr int kExchangeRows = 98;      // rows that a share may touch
 
 // ---- one launch for the whole call.
 // Every workgroup of a team, the splits of a (sequence, kv head) that hold tokens, publishes its partial and then merges its share of the
@@ -105,10 +104,10 @@ struct RowMerge {
 };
 
 // What lies in LDS while a workgroup merges.
-template <int NWAVES>
+template <int ROWS, int NWAVES>
 struct MergeLds {
-    float weight[kExchangeRows][kMergeBlock];          // of the share's rows, for each split
-    float den[kExchangeRows], top[kExchangeRows];      // sum and maximum of a row
+    float weight[ROWS][kMergeBlock];                   // of the share's rows, for each split
+    float den[ROWS], top[ROWS];                        // sum and maximum of a row
     uint32_t missing[NWAVES], seen[NWAVES];            // not all words there; marks of the team, by wave
     float vals[];                                      // [split][element of the share]
 };
@@ -120,7 +119,7 @@ __device__ __forceinline__ bool merge_share(const AttnLaunch& a, const Exchange&
                                             int share, int64_t ticks, bool first, uint32_t* marks)
 {
     constexpr int NT = NWAVES * 64;
-    MergeLds<NWAVES>& lds = *reinterpret_cast<MergeLds<NWAVES>*>(smem);
+    MergeLds<ROWS, NWAVES>& lds = *reinterpret_cast<MergeLds<ROWS, NWAVES>*>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int RP = a.RB * 16, total = a.Qmax * a.G * D, n = max(live, 1);

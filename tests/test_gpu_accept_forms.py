@@ -110,11 +110,11 @@ def test_greedy_ties_masks_and_row_ends(V):
             assert np.all(toks[b, want + 1:] == -1)
 
 
-@pytest.mark.parametrize("batch,V,slices", [(1, 20000, 20), (1, 100001, 49), (6, 100001, 25), (24, 50257, 13), (44, 50257, 17), (48, 50257, 10),
+@pytest.mark.parametrize("batch,V,slices", [(1, 20000, 20), (1, 100001, 49), (6, 100001, 25), (15, 50257, 50), (24, 50257, 13), (44, 50257, 17), (48, 50257, 10),
                                             (600, 1030, 1)])
 def test_every_build_of_the_draw_and_its_give_up_path(batch, V, slices):
-    """Vocabularies and batches that select 2, 4, 8 (one round of one and of two workgroups per compute unit), 12 (up to three) and 20 entries per
-    thread, a row end inside a thread's entries; with every exchange recomputed the results are the same bits, and it is every one:
+    """Vocabularies and batches that select 256 threads of 4 (one and up to three workgroups per compute unit) and 8 entries, 512 of 8 (one round of one
+    and of two workgroups per compute unit), 256 of 12 (up to three) and 20, a row end inside a thread's entries; with every exchange recomputed the results are the same bits, and it is every one:
     each of a sequence's `slices` workgroups gives up on all slices in each of the draw's exchanges (three, one for a bonus row)."""
     cfg = wl.scaled(wl.CONFIGS["llama8b_32k"], batch=batch, vocab=V, gamma_choices=(0, 1), draft_noise_std=2.0, name="draws")
     acc = wl.gen_accept_inputs(cfg, salt=V)

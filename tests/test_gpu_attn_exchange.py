@@ -96,7 +96,7 @@ def test_one_launch_has_the_bits_of_two(shape):
     c = _case(*shape)
     for chunk in (0, 384):
         want = _two(r, c, chunk)
-        for wait in (100, 100, 0, 1, 3, 100):          # 0: nearly all shares are left to the last workgroup of their head
+        for wait in (100, 100, 0, 1, 3, 100):          # (short bounds: shares that are not there yet are left to the last workgroup of their head)
             r.set_option(OPT_ATTN_WAIT_US, wait)
             _same(_one(r, c, chunk), want)
 
@@ -285,20 +285,44 @@ def test_chains_on_four_streams_do_not_wait_for_one_another(shape):
     assert took < 0.03, took
 
 
+@pytest.mark.parametrize("d,hq", [(64, 4), (128, 8), (64, 32)])
+def test_shares_are_left_to_the_last_workgroup(d, hq):
+    """Splits of 4096, 4096 and 8 tokens: with one look the workgroup of the last one leaves its share, marked with the call's number, and
+    others merge it.  With a bound of 100 ms it waits, and no share is marked."""
+    r = Rapid(0)
+    c = _case(1, 1, hq, 1, d, [8200], None)
+    want = _two(r, c, 4096)
+    for wait in (0, 100000, 1, 100000, 0):
+        r.set_option(OPT_ATTN_WAIT_US, wait)
+        _same(_one(r, c, 4096), want)
+        words = r._ws_exchange[:1024 + 128].view(torch.int32).tolist()
+        tag, marks = words[0], words[256:259]
+        assert marks[2] == tag if wait < 100000 else tag not in marks, (wait, tag, marks)
+
+
 def test_two_objects_on_two_streams():
-    """Each has exchange memory of its own; their workgroups share the compute units, so that one may wait for another that has
-    none yet: the bounded waits and left-over shares are what ends that."""
+    """Each has exchange memory of its own.  Recorded chains of calls, replayed side by side so that their kernels run back to back, and
+    one with workgroups that leave their shares to others."""
     cases = [_case(*SHAPES[5]), _case(*SHAPES[6], seed=1)]
     objects = [Rapid(0), Rapid(0)]
     want = [_one(r, c) for r, c in zip(objects, cases)]
-    torch.cuda.synchronize()
-    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
-    got = [[], []]
-    for _ in range(40):
-        for i in range(2):
-            with torch.cuda.stream(streams[i]):
-                got[i].append(_one(objects[i], cases[i]))
-    torch.cuda.synchronize()
-    for i in range(2):
-        for g in got[i]:
-            _same(g, want[i])
+    for wait in (100, 0):
+        objects[1].set_option(OPT_ATTN_WAIT_US, wait)
+        graphs, got = [torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()], []
+        for graph, r, c in zip(graphs, objects, cases):
+            torch.cuda.synchronize()
+            with torch.cuda.graph(graph):
+                got.append([_one(r, c) for _ in range(20)])
+        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+        torch.cuda.synchronize()
+        for _ in range(4):
+            for o, l in got[0] + got[1]:
+                o.fill_(float("nan")), l.fill_(float("nan"))
+            torch.cuda.synchronize()
+            for s, graph in zip(streams, graphs):
+                with torch.cuda.stream(s):
+                    graph.replay()
+            torch.cuda.synchronize()
+            for i in range(2):
+                for g in got[i]:
+                    _same(g, want[i])
