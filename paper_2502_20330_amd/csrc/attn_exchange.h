@@ -35,7 +35,7 @@ __device__ __forceinline__ float sum32(float v)
 constexpr int kMergeBlock = 32;        // splits whose weights are formed together, one per lane
 
 // ---- one launch for the whole call.
-// Every workgroup of a team, the splits of a (sequence, kv head) that hold tokens, publishes its partial and then merges its share of the
+// Every workgroup of a team, the splits of a (sequence, kv head), publishes its partial, or that it holds no tokens, and then merges its share of the
 // team's output, every share as many elements.  What it publishes are 64-bit words, 32 bits of payload under a tag that no
 // earlier call on the same memory used; whoever needs a word looks until it carries the tag, so no fence, flag or counter
 // stands between a store and its reader.  The memory holds nothing but such words and starts as zeros.  The tag is the number of the call, and never 0,
@@ -114,6 +114,7 @@ struct MergeLds {
 
 // One try at a share (`share` of n) of a team whose partials start at row slot `base`: every wave looks until `ticks` have passed, or
 // once (ticks < 0).  False: words are missing.
+// The shares are those of all splits, so that a thread has one element whatever the length of the sequence is (plan_exchange).
 template <int D, int ROWS, int NWAVES>
 __device__ __forceinline__ bool merge_share(const AttnLaunch& a, const Exchange& x, char* smem, int team, uint32_t base, int live, int R,
                                             int share, int64_t ticks, bool first, uint32_t* marks)
@@ -122,7 +123,7 @@ __device__ __forceinline__ bool merge_share(const AttnLaunch& a, const Exchange&
     MergeLds<ROWS, NWAVES>& lds = *reinterpret_cast<MergeLds<ROWS, NWAVES>*>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int RP = a.RB * 16, total = a.Qmax * a.G * D, n = max(live, 1);
+    const int RP = a.RB * 16, total = a.Qmax * a.G * D, n = a.nsplit;
     const int E = ((total + n - 1) / n + 15) & ~15;    // elements of a share; whole 32-byte pieces of the output
     const int e0 = share * E, e1 = min(e0 + E, total), er = min(e1, R * D);      // from er on: rows that this sequence does not have
     const int row0 = e0 / D, row1 = (er + D - 1) / D;
@@ -161,7 +162,7 @@ __device__ __forceinline__ bool merge_share(const AttnLaunch& a, const Exchange&
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (at[u] >= 0) v[u] = __builtin_amdgcn_raw_buffer_load_b128(x.words, off[u], 0, kDeviceScope);
-        bool open = pairs > 0 && (ml.y != x.tag || ml.w != x.tag);
+        bool open = row0 < row1 && (ml.y != x.tag || ml.w != x.tag);
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (at[u] >= 0) {
@@ -200,7 +201,7 @@ __device__ __forceinline__ bool merge_share(const AttnLaunch& a, const Exchange&
         }
         if (row + NWAVES < row1) {                     // (all have published)
             ml = __builtin_amdgcn_raw_buffer_load_b128(x.words, a.xml_offset + (base + sl * RP + row + NWAVES) * 16, 0, kDeviceScope);
-            if (live && !__all(ml.y == x.tag && ml.w == x.tag)) missing = true;
+            if (!__all(ml.y == x.tag && ml.w == x.tag)) missing = true;
         }
     }
     if (lane == 0) lds.missing[wave] = missing;
@@ -255,14 +256,14 @@ __device__ __forceinline__ bool merge_share(const AttnLaunch& a, const Exchange&
     return !any;
 }
 
-// What a workgroup does after it has published (`split` of n that hold tokens; split 0 answers for a sequence without any).
+// What a workgroup does after it has published its partial (`live` splits hold tokens; the others say so here).
 template <int D, int ROWS, int NWAVES>
 __device__ __forceinline__ void exchange_finish(const AttnLaunch& a, uint32_t calls, char* smem, int team, int split, int live, int R)
 {
-    const int n = max(live, 1);
-    if (split >= n) return;                            // no tokens, no words
     const Exchange x = make_exchange(a, calls);
     const uint32_t base = (uint32_t)team * a.nsplit * (a.RB * 16);
+    if (split >= live && (int)threadIdx.x < R)
+        publish_pair(x, a.xml_offset / 8 + (base + split * (a.RB * 16) + threadIdx.x) * 2, -INFINITY, 0.f);
     uint32_t left = 0;
     int64_t ticks = a.xwait_ticks;
     int share = split;

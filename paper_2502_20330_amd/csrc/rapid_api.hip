@@ -205,7 +205,8 @@ void plan_attn(const rapid_ctx* ctx, const rapid_attn_shape* shape, AttnLaunch& 
 }
 
 // Bytes of exchange memory with which the call is one launch, 0 where it is two: few rows (attn_in_one_launch), no more splits than
-// one wave forms weights for, and a fixed grid of which four fit on the chip at a time.  The workgroups wait for one another and hold their compute units
+// one wave forms weights for, at most one output element a thread in the shares that the workgroups of a head merge, and a fixed grid of which four
+// fit on the chip at a time.  The workgroups wait for one another and hold their compute units
 // meanwhile, so that calls on several streams must not keep each other's last workgroups off the chip until a wait ends; a
 // process has four hardware queues.  A workgroup takes a compute unit with heads of 128, half of one with heads of 64.
 // us a call in chains of 16 on 1 / 2 / 3 / 4 streams, two launches against one, heads of 128 (splits of 256 tokens):
@@ -214,6 +215,9 @@ void plan_attn(const rapid_ctx* ctx, const rapid_attn_shape* shape, AttnLaunch& 
 //   8 heads, 8K, 256 workgroups        12.4 / 18.6 / 23.8 / 29.9  against  11.8 / 21.2 / 49 / 381, 32K with 4 rows 28.4 / 47 / 68 / 88 against 26.8 / 50 / 140 / 498
 // heads of 64, 4 rows: 4K, 128 workgroups  8.1 / 10.6 / 13.1 / 14.7 against 7.5 / 9.7 / 10.9 / 12.3; 8K, 256  9.3 / 12.6 / 15.9 / 18.9 against 8.7 / 11.8 / 16.5 / 39.
 // (Leaving a share to others as soon as a workgroup of the team has not started: 8K 58 and 32K 166 on four streams, and 0.1 to 0.2 us more everywhere.)
+// Elements of a share: with more than the 256 threads have at a time, and rows whose (maximum, sum) a wave fetches one after another, a
+// second launch merges faster (us a call in a graph, two launches against one: 16 rows of 64, 1000 tokens in 4 splits, 256 elements 7.2 and 6.9; 20 rows, 320, 7.9 and 8.6; 28 rows in one
+// split, 1792, 7.9 and 12.1; 16 rows of 128 in 8 splits, 256, 9.3 and 9.1; in 4, 512, 9.0 and 9.3; in one 8.6 and 11.7).
 // The splits are those of two launches, so that the results are the same bits either way.  (128 tokens instead of 256 where half of the compute
 // units hold them would be worth 0.3 to 0.8 us: 2K tokens, one head of 64, 5 rows 7.7 and 7.1, 8 heads of 128, 4 rows 9.0 and 8.2.)
 size_t plan_exchange(const rapid_ctx* ctx, const AttnLaunch& a)
@@ -221,6 +225,7 @@ size_t plan_exchange(const rapid_ctx* ctx, const AttnLaunch& a)
     const int64_t n_cu = ctx ? ctx->n_cu : 256;
     if (a.groups || !attn_in_one_launch(a.RB, a.D)) return 0;
     const int64_t wgs = (int64_t)a.B * a.Hkv * a.nsplit;
+    if (a.Qmax * a.G * a.D > 256 * a.nsplit) return 0;
     if (a.nsplit > kMaxShares || 4 * wgs > n_cu * (a.D == 64 ? 2 : 1) || wgs > kAttnTeams) return 0;
     return attn_exchange_bytes(a.B, a.Hkv, a.nsplit, a.RB, a.D);
 }

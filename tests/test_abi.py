@@ -165,10 +165,11 @@ def test_one_launch_runs_with_the_planned_splits():
             if got:
                 ones += 1
                 words = batch * hkv * nsplit * rows * (d + 2) * 8
+                assert q_max * (hq // hkv) * d <= 256 * nsplit
                 assert 1024 + 4 * 256 * 32 <= got - words <= 72 * 1024, (batch, q_max, hq, hkv, d, max_ctx)
             s.chunk_tokens = chunk
             assert lib.rapid_verify_attn_exchange_bytes(None, ctypes.byref(s)) == got
-    assert ones > 200
+    assert ones > 100
 
 
 def test_product_path_has_no_cpu_fallback():

@@ -58,14 +58,14 @@ def _same(x, y):
 
 
 # B, Q, Hq, Hkv, d, lens, gammas, page, layout: one split and several, up to the 32 that run in one launch; shares of less than a
-# row and of several rows, more shares than elements to share; splits and whole sequences without tokens; one and two row blocks; grids
-# of up to 64 workgroups with heads of 128, 128 with heads of 64
+# row and of several rows, up to the 256 elements that they may have, more shares than elements to share; splits and whole sequences without tokens, nearly
+# all of a sequence's splits among them; one and two row blocks; grids of up to 64 workgroups with heads of 128, 128 with heads of 64
 SHAPES = [
     (1, 1, 4, 4, 64, [1], None, 0, "head"),
     (1, 1, 1, 1, 64, [8192], None, 0, "head"),
     (1, 5, 4, 1, 64, [2048], None, 0, "token"),
-    (1, 4, 8, 1, 64, [200], None, 0, "head"),
-    (1, 2, 8, 1, 128, [300], None, 0, "head"),
+    (1, 4, 1, 1, 64, [200], None, 0, "head"),
+    (1, 2, 4, 1, 128, [1000], None, 0, "head"),
     (1, 1, 32, 8, 128, [2048], None, 0, "head"),
     (1, 4, 8, 2, 128, [8192], None, 0, "head"),
     (1, 3, 32, 8, 128, [1900], [1], 16, "head"),
@@ -76,7 +76,9 @@ SHAPES = [
     (3, 4, 16, 4, 64, [2500, 0, 4], [3, 3, 3], 16, "head"),
     (8, 8, 8, 4, 64, [1024] * 8, None, 0, "head"),
     (8, 3, 8, 4, 64, [513] * 8, [0, 1, 2, 2] * 2, 0, "token"),
-    (32, 3, 8, 4, 64, [33] * 32, [0, 1, 2, 2] * 8, 0, "token"),
+    (32, 2, 8, 4, 64, [33] * 32, [0, 1, 1, 1] * 8, 0, "token"),
+    (2, 4, 8, 1, 64, [8192, 100], None, 0, "head"),
+    (2, 2, 8, 1, 128, [4096, 0], [1, 0], 0, "token"),
 ]
 
 
@@ -200,9 +202,10 @@ def test_missing_or_small_exchange_is_refused_and_none_takes_two_launches():
 
 
 @pytest.mark.parametrize("shape", [(1, 5, 4, 1, 128, [2048], None), (1, 9, 4, 1, 64, [2048], None), (1, 1, 4, 1, 64, [65536], None),
-                                   (1, 1, 32, 8, 128, [2049], None), (1, 1, 32, 8, 128, [8192], None), (33, 1, 8, 4, 64, [64] * 33, None)])
+                                   (1, 1, 32, 8, 128, [2049], None), (1, 1, 32, 8, 128, [8192], None), (33, 1, 8, 4, 64, [64] * 33, None),
+                                   (1, 4, 8, 1, 64, [200], None), (1, 2, 8, 1, 128, [1700], None)])
 def test_shapes_that_stay_at_two_launches(shape):
-    """More rows, more than 32 splits, more than a quarter of the workgroups that the chip holds: no exchange memory is asked for, and none is
+    """More rows, more than 32 splits, more than a quarter of the workgroups that the chip holds, more than 256 elements a share: no exchange memory is asked for, and none is
     needed."""
     r = Rapid(0)
     c = _case(*shape)
@@ -285,19 +288,19 @@ def test_chains_on_four_streams_do_not_wait_for_one_another(shape):
     assert took < 0.03, took
 
 
-@pytest.mark.parametrize("d,hq", [(64, 4), (128, 8), (64, 32)])
-def test_shares_are_left_to_the_last_workgroup(d, hq):
-    """Splits of 4096, 4096 and 8 tokens: with one look the workgroup of the last one leaves its share, marked with the call's number, and
+@pytest.mark.parametrize("d,hq,L", [(64, 4, 8200), (128, 4, 8200), (64, 32, 7 * 4096 + 8)])
+def test_shares_are_left_to_the_last_workgroup(d, hq, L):
+    """Splits of 4096 tokens and a last one of 8: with one look the workgroup of the last one leaves its share, marked with the call's number, and
     others merge it.  With a bound of 100 ms it waits, and no share is marked."""
     r = Rapid(0)
-    c = _case(1, 1, hq, 1, d, [8200], None)
+    c = _case(1, 1, hq, 1, d, [L], None)
     want = _two(r, c, 4096)
     for wait in (0, 100000, 1, 100000, 0):
         r.set_option(OPT_ATTN_WAIT_US, wait)
         _same(_one(r, c, 4096), want)
         words = r._ws_exchange[:1024 + 128].view(torch.int32).tolist()
-        tag, marks = words[0], words[256:259]
-        assert marks[2] == tag if wait < 100000 else tag not in marks, (wait, tag, marks)
+        tag, marks = words[0], words[256:256 + -(-L // 4096)]
+        assert marks[-1] == tag if wait < 100000 else tag not in marks, (wait, tag, marks)
 
 
 def test_two_objects_on_two_streams():
