@@ -66,7 +66,7 @@ constexpr int kDeviceScope = 16;       // sc1: past the dies' own L2s
 // The number of this call, read by every workgroup beside its sequence's length.
 __device__ __forceinline__ uint32_t exchange_call(const AttnLaunch& a, int team, int& L)
 {
-    uint32_t calls = *(a.xhead ? &a.xhead->calls[team] : reinterpret_cast<const uint32_t*>(a.ctx_lens));
+    uint32_t calls = a.xhead->calls[team];
     calls = __builtin_amdgcn_readfirstlane(calls);
     L = __builtin_amdgcn_readfirstlane(L);
     asm volatile("" : "+s"(calls), "+s"(L));

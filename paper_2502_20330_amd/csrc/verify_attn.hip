@@ -605,7 +605,7 @@ __device__ __forceinline__ void split_piece(const AttnLaunch& a, char* smem, int
         for (int db = 0; db < G::DB; ++db)
             *reinterpret_cast<floatx4*>(obuf + (wave * RP + row) * OROW + db * 16 + lg * 4) = st.acc[db][rb] * f_own;
     }
-    if constexpr (XCH) if (a.xhead) {
+    if constexpr (XCH) {
         const Exchange x = make_exchange(a, calls);
         if (wave == 0 && lg == 0) {
 #pragma unroll
@@ -649,7 +649,8 @@ __device__ __forceinline__ void split_piece(const AttnLaunch& a, char* smem, int
 
 // Partials of a fixed grid: [b][kv head][split]; of balanced shares: [kv head][g + b], which no two pieces
 // share (from one piece of a head to the next, g or b grows).
-template <int D, int RB, bool PAGED, bool BALANCED>
+// ONE: the workgroups merge the partials themselves (a build of its own: the number of the call and the code behind it cost the other one 0.1 us).
+template <int D, int RB, bool PAGED, bool BALANCED, bool ONE>
 __global__ void __launch_bounds__(kWaves * 64) verify_attn_split(AttnLaunch a)
 {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -670,17 +671,14 @@ __global__ void __launch_bounds__(kWaves * 64) verify_attn_split(AttnLaunch a)
         return;
     }
     int L = seq_len(a, b);
-    constexpr bool one_launch = !BALANCED && attn_in_one_launch(RB, D);
     uint32_t calls = 0;
-    if constexpr (one_launch) calls = exchange_call(a, b * a.Hkv + hkv, L);
+    if constexpr (ONE) calls = exchange_call(a, b * a.Hkv + hkv, L);
     const int c0 = split_begin(a, split, hkv);
     if (c0 < L)                                          // else this split holds no token of sequence b
-        split_piece<D, RB, PAGED, one_launch>(a, smem, b, hkv, L, c0, min(split_end(a, split, hkv), L),
-                                              (((int64_t)b * a.Hkv + hkv) * a.nsplit + split) * (RB * 16), calls);
-    if constexpr (one_launch)
-        if (a.xhead)
-            exchange_finish<D, RB * 16, kWaves>(a, calls, smem, b * a.Hkv + hkv, split, live_splits(a, L, hkv),
-                                                seq_queries(a, b) * a.G);
+        split_piece<D, RB, PAGED, ONE>(a, smem, b, hkv, L, c0, min(split_end(a, split, hkv), L),
+                                       (((int64_t)b * a.Hkv + hkv) * a.nsplit + split) * (RB * 16), calls);
+    if constexpr (ONE)
+        exchange_finish<D, RB * 16, kWaves>(a, calls, smem, b * a.Hkv + hkv, split, live_splits(a, L, hkv), seq_queries(a, b) * a.G);
 }
 
 // ---------------------------------------------------------------- wide row counts: two row teams
@@ -1071,7 +1069,8 @@ template <int D, int RB, bool PAGED, bool BALANCED>
 hipError_t launch_split(const AttnLaunch& a, hipStream_t stream)
 {
     constexpr int lds = attn_lds_bytes<D, RB>();
-    auto fn = verify_attn_split<D, RB, PAGED, BALANCED>;
+    auto fn = verify_attn_split<D, RB, PAGED, BALANCED, false>;
+    if constexpr (!BALANCED && attn_in_one_launch(RB, D)) if (a.xhead) fn = verify_attn_split<D, RB, PAGED, false, true>;
     hipLaunchKernelGGL(fn, split_grid(a), dim3(kWaves * 64), lds, stream, a);
     return hipGetLastError();
 }
@@ -1096,7 +1095,12 @@ hipError_t configure_split_wide()
 template <int D, int RB, bool PAGED, bool BALANCED>
 hipError_t configure_split()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(verify_attn_split<D, RB, PAGED, BALANCED>),
+    if constexpr (!BALANCED && attn_in_one_launch(RB, D)) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(verify_attn_split<D, RB, PAGED, false, true>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, attn_lds_bytes<D, RB>());
+        if (e != hipSuccess) return e;
+    }
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(verify_attn_split<D, RB, PAGED, BALANCED, false>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, attn_lds_bytes<D, RB>());
 }
 template <int D, bool PAGED, bool BALANCED>
