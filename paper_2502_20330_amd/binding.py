@@ -156,6 +156,7 @@ class Rapid:
         _check(self.lib, self.lib.rapid_create(ctypes.byref(self._ctx), device))
         self._ws: Optional[torch.Tensor] = None
         self._ws_exchange: Optional[torch.Tensor] = None
+        self._ws_args = (None, 0, None, 0)             # address and size of the exchange memory and of the workspace, as a call takes them
         self._ws_accept: Optional[torch.Tensor] = None
         self._sink: Optional[torch.Tensor] = None
 
@@ -183,6 +184,7 @@ class Rapid:
     def _workspace(self, nbytes: int) -> torch.Tensor:
         if self._ws is None or self._ws.numel() < nbytes:
             self._ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=self.device)
+            self._ws_args = (*self._ws_args[:2], self._ws.data_ptr(), self._ws.numel())
         return self._ws
 
     def _exchange_workspace(self, nbytes: int) -> torch.Tensor:
@@ -190,6 +192,7 @@ class Rapid:
         # shape (128 workgroups of 32 rows of 64)
         if self._ws_exchange is None or self._ws_exchange.numel() < nbytes:
             self._ws_exchange = torch.zeros(max(nbytes, 3 << 20), dtype=torch.uint8, device=self.device)
+            self._ws_args = (self._ws_exchange.data_ptr(), self._ws_exchange.numel(), *self._ws_args[2:])
         return self._ws_exchange
 
     def clear_exchange(self):
@@ -250,17 +253,16 @@ class Rapid:
         args = (self._ctx, shape, q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), ctx_lens.data_ptr(), _dptr(gammas),
                 _dptr(page_table), out.data_ptr(), _dptr(lse_out))
         call, stream = self.lib.rapid_verify_attn_exchange, _stream_ptr(self.device)
-        xch, ws = self._ws_exchange, self._ws
-        if xch is None and not torch.cuda.is_current_stream_capturing():   # (a fill that is only recorded does not clear it)
-            xch = self._exchange_workspace(0)
-        rc = call(*args, _dptr(xch), 0 if xch is None else xch.numel(), _dptr(ws), 0 if ws is None else ws.numel(), stream)
+        if self._ws_exchange is None and not torch.cuda.is_current_stream_capturing():   # (a fill that is only recorded does not clear it)
+            self._exchange_workspace(0)
+        rc = call(*args, *self._ws_args, stream)
         if rc == RAPID_EWORKSPACE:                             # the last check of the call: nothing has been launched
-            need = 0 if xch is None else self.lib.rapid_verify_attn_exchange_bytes(self._ctx, shape)
+            need = 0 if self._ws_exchange is None else self.lib.rapid_verify_attn_exchange_bytes(self._ctx, shape)
             if need:
-                xch = self._exchange_workspace(need)
+                self._exchange_workspace(need)
             else:
-                ws = self._workspace(self.lib.rapid_verify_attn_workspace_bytes(self._ctx, shape))
-            rc = call(*args, _dptr(xch), 0 if xch is None else xch.numel(), _dptr(ws), 0 if ws is None else ws.numel(), stream)
+                self._workspace(self.lib.rapid_verify_attn_workspace_bytes(self._ctx, shape))
+            rc = call(*args, *self._ws_args, stream)
         if rc:
             _check(self.lib, rc, self._ctx)
         return out
