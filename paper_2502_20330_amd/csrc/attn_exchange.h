@@ -53,7 +53,7 @@ constexpr int kMergeBlock = 32;        // splits whose weights are formed togeth
 // What bounds it: round trips past the dies' L2s (0.7 us each: the own words' arrival, one or two looks) and code that every
 // workgroup meets for the first time, about 3 us from the last tile to the end at 4 rows where a store, a second launch and its
 // gap took 3.6.  So everything that is missing is asked for at once, one element of the output a thread, and partials keep
-// the order of the merge kernel.  Measured: 2K tokens, 4 heads of 64, 5 rows, enqueued one by one 9.9 -> 7.7 us, in a graph 8.2 -> 7.9.  Not kept (a graph
+// the order of the merge kernel.  Measured: 2K tokens, 4/1 heads of 64, 5 positions, enqueued one by one 9.9 -> 7.9 us, in a graph 8.2 -> 8.0; 4 rows 7.1 -> 6.8.  Not kept (a graph
 // of 16 calls on 8K tokens with the head and the draw, 290 us with two launches, 277 like this): a counter of arrivals per team (256 atomic additions on a few
 // lines: 345); a wave per row asking for 32 splits (304); asking for words only where (maximum, sum) had come (282 to 292).
 struct Exchange {
@@ -262,12 +262,14 @@ __device__ __forceinline__ void exchange_finish(const AttnLaunch& a, uint32_t ca
 {
     const Exchange x = make_exchange(a, calls);
     const uint32_t base = (uint32_t)team * a.nsplit * (a.RB * 16);
-    if (split >= live && (int)threadIdx.x < R)
-        publish_pair(x, a.xml_offset / 8 + (base + split * (a.RB * 16) + threadIdx.x) * 2, -INFINITY, 0.f);
     uint32_t left = 0;
     int64_t ticks = a.xwait_ticks;
     int share = split;
-    __syncthreads();                                   // what this workgroup published has been read out of LDS
+    // What this workgroup published has been read out of LDS; and one without tokens publishes only now that all of its waves have read
+    // the number of the call, which moves once all have published.
+    __syncthreads();
+    if (split >= live && (int)threadIdx.x < R)
+        publish_pair(x, a.xml_offset / 8 + (base + split * (a.RB * 16) + threadIdx.x) * 2, -INFINITY, 0.f);
     for (;;) {
         const bool done = merge_share<D, ROWS, NWAVES>(a, x, smem, team, base, live, R, share, ticks, ticks >= 0, &left);
         if (!done && ticks >= 0) {

@@ -51,7 +51,7 @@ struct AttnLaunch {
 };
 constexpr int kAttnTeams = 256;  // largest grid that merges by itself
 // Row counts (in blocks of 16) for which the workgroups merge their partials themselves, up to 16 rows of 128 or 32 of 64.  In graphs
-// of calls, two launches against one: 4 rows of 128, 512 tokens 8.75 and 8.37 us; 20 rows of 64, 2K tokens 7.65 and 7.43.  Beyond, the words (twice the
+// of calls, two launches against one: 4 rows of 128, 500 tokens 8.30 and 7.90 us, 16 rows, 4000 tokens 9.73 and 9.28; 32 rows of 64, 4000 tokens 8.50 and 8.20.  Beyond, the words (twice the
 // partials) take longer to go through memory and back than a second launch: 20 rows of 128, 8K tokens 14.3 and 14.7, 36 rows 17.0
 // and 18.3, 72 rows 20.2 and 23.0; 40 rows of 64, 2K tokens 8.6 and 9.2.  Calls that the host cannot enqueue as fast as they run gain a launch.
 constexpr bool attn_in_one_launch(int row_blocks, int D) { return row_blocks * D <= 128; }

@@ -179,6 +179,26 @@ def test_clearing_mends_what_overlapping_calls_leave():
         assert r._ws_exchange[:1024].view(torch.int32).unique().tolist() == [6]
 
 
+@pytest.mark.parametrize("d,hkv", [(64, 8), (128, 4)])
+def test_sequences_without_tokens_many_times(d, hkv):
+    """Workgroups without tokens publish at once, so that their team's number moves as early as it ever does: it still moves by one a call,
+    and every share is merged."""
+    r = Rapid(0)
+    c = _case(4, 2, hkv, hkv, d, [0, 3, 0, 0], None, max_ctx=1024)
+    want = _two(r, c)
+    _one(r, c)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        got = [_one(r, c) for _ in range(32)]
+    for _ in range(20):
+        graph.replay()
+        torch.cuda.synchronize()
+        for g in got:
+            _same(g, want)
+    assert r._ws_exchange[:1024].view(torch.int32).unique().tolist() == [1 + 32 * 20]
+
+
 def test_missing_or_small_exchange_is_refused_and_none_takes_two_launches():
     r = Rapid(0)
     c = _case(*SHAPES[2])
