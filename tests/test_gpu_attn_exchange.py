@@ -286,7 +286,7 @@ def test_chains_on_four_streams_do_not_wait_for_one_another(shape):
     cases = [_case(*shape, seed=i) for i in range(4)]  # (kept: the graphs read them)
     for r, c in zip(objects, cases):
         want.append(_one(r, c))
-        r.set_option(OPT_ATTN_WAIT_US, 30000)
+        r.set_option(OPT_ATTN_WAIT_US, 100000)
         graph = torch.cuda.CUDAGraph()
         torch.cuda.synchronize()
         with torch.cuda.graph(graph):
@@ -305,7 +305,7 @@ def test_chains_on_four_streams_do_not_wait_for_one_another(shape):
     for got, w in zip(outs, want):
         for g in got:
             _same(g, w)
-    assert took < 0.03, took
+    assert took < 0.1, took
 
 
 @pytest.mark.parametrize("d,hq,L", [(64, 4, 8200), (128, 4, 8200), (64, 32, 7 * 4096 + 8)])
